@@ -335,13 +335,14 @@ void kernel_columns(const ffk_system* sys, const int64_t* cols, int64_t k, doubl
 void kernel_diag(const ffk_system* sys, double* d, hipStream_t st);
 double max_diag(ffk_system* sys, hipStream_t st);
 
-// dense.hip : FP64 GEMM (C = alpha A B^T + beta C on strided views) and factorizations
-struct View64 {
-  const double* p;
-  int64_t s0, s1;   // element (i, j) at p[i * s0 + j * s1]
-};
-void gemm64(int M, int N, int K, double alpha, View64 A, View64 B, double beta, double* C,
-            int64_t scm, int64_t scn, bool lower_only, hipStream_t st);
+// dense.hip : FP64 GEMM and factorizations on column-major matrices.
+// C = alpha A B^T + beta C: A (M x K) and C unit stride along m; B n-contiguous
+// (element (n, k) at B[n + k ldb]) or k-contiguous (B[n ldb + k]).  A and B
+// 16-byte aligned, lda and ldb even, lda (and ldb of an n-contiguous B) at
+// least M (N) rounded up to even; beta = 0 does not read C.  lower_only skips
+// tiles above the diagonal.  C = A in place is safe for N <= 64.
+void gemm64(int M, int N, int K, double alpha, const double* A, int64_t lda, const double* B, int64_t ldb,
+            bool b_kcontig, double beta, double* C, int64_t ldc, bool lower_only, hipStream_t st);
 // The same product with FP32 operands, FP64 arithmetic and output.
 struct View32 {
   const float* p;
@@ -349,10 +350,11 @@ struct View32 {
 };
 void gemm64_in32(int M, int N, int K, double alpha, View32 A, View32 B, double beta, double* C, int64_t scm,
                  int64_t scn, hipStream_t st);
-// Lower Cholesky in place of the n x n column-major matrix A (lda). Returns the
-// index of the first failing pivot or -1.
+// Lower Cholesky in place of the n x n column-major matrix A (16-byte aligned,
+// lda even, >= n). Returns the index of the first failing pivot or -1.
 int64_t potrf_lower(double* A, int64_t n, int64_t lda, hipStream_t st);
-// In-place inverse of the lower-triangular n x n column-major matrix A.
+// In-place inverse of the lower-triangular n x n column-major matrix A (16-byte
+// aligned, lda even, >= n; for odd n it clears the padding row n).
 void trtri_lower(double* A, int64_t n, int64_t lda, hipStream_t st);
 
 // reduce.hip -- deterministic two-stage reductions; `part` holds >= kRedParts doubles.

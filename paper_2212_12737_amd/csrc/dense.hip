@@ -1,52 +1,48 @@
-// FP64 dense linear algebra on FP64 MFMA: strided GEMM, blocked Cholesky and
-// triangular inversion (column-major, lower).  Used for the k x k Woodbury
+// FP64 dense linear algebra on FP64 MFMA: column-major GEMM, blocked Cholesky
+// and triangular inversion (column-major, lower).  Used for the k x k Woodbury
 // core of the preconditioner (Eq. 4), the panel updates of the incomplete
 // Cholesky and the dense factorization behind the exact leverage scores.
-#include "gemm.hpp"
+#include "chol64.hpp"
+#include "gemm64.hpp"
 
 namespace ffk {
 
-template <int BN, bool AKC, bool BKC>
-static void gemm64_t(int M, int N, int K, double alpha, View64 A, View64 B, double beta, double* C, int64_t scm,
-                     int64_t scn, bool lower_only, bool a_lower, hipStream_t st) {
-  ScalarArgs<double> g{};
-  g.M = M;
-  g.N = N;
-  g.nseg = 1;
-  g.seg[0] = SegS<double>{A.p, A.s0, A.s1, B.p, B.s0, B.s1, K};
-  g.lower_only = lower_only;
-  g.a_lower = a_lower;
-  EpiAxpby<double> e{C, scm, scn, M, N, alpha, beta};
-  dim3 grid(cdiv(N, BN), cdiv(M, 128));
-  gemm_scalar_kernel<double, 128, BN, 16, AKC, BKC, EpiAxpby<double>><<<grid, 256, 0, st>>>(g, e);
+// Tiles of the column-major GEMM.
+typedef Tile64<128, 128, 2, 2, 1, 4> T64L;   // the large tile
+typedef Tile64<64, 64, 2, 2, 1, 4> T64S;     // grids that leave CUs idle with it
+typedef Tile64<128, 64, 4, 1, 1, 4> T64N;    // N <= 64; in place (C = A) is safe: one tile spans the columns
+typedef Tile64<64, 256, 1, 4, 1, 3> T64W;    // in place for N <= 256 (C = A)
+typedef Tile64<256, 64, 4, 1, 1, 3> T64H;    // in place for M = K <= 256 (C = B)
+
+template <class TL, bool BKC>
+static void launch64(const Gemm64Args& g, EpiCol64 e, int ntn, int ntm, int batch, hipStream_t st) {
+  require(reinterpret_cast<uintptr_t>(g.A) % 16 == 0 && reinterpret_cast<uintptr_t>(g.B) % 16 == 0 &&
+              g.lda % 2 == 0 && g.ldb % 2 == 0 && g.sA % 2 == 0 && g.sB % 2 == 0,
+          "gemm64: operands need 16-byte alignment and even leading dimensions");
+  e.vec = reinterpret_cast<uintptr_t>(e.C) % 16 == 0 && e.ldc % 2 == 0 && e.sC % 2 == 0;
+  k_gemm64<TL, BKC><<<dim3(ntn, ntm, batch), TL::NT, 0, st>>>(g, e);
   LAUNCHCHK();
 }
 
-static void gemm64_dispatch(int M, int N, int K, double alpha, View64 A, View64 B, double beta, double* C,
-                            int64_t scm, int64_t scn, bool lower_only, bool a_lower, hipStream_t st) {
-  if (M <= 0 || N <= 0) return;
-  const bool akc = (A.s1 == 1), bkc = (B.s1 == 1);
-  require(akc || A.s0 == 1, "gemm64: A needs a unit stride");
-  require(bkc || B.s0 == 1, "gemm64: B needs a unit stride");
-  const bool narrow = N <= 64;
-#define GEMM64_CASE(BNv, a, b) gemm64_t<BNv, a, b>(M, N, K, alpha, A, B, beta, C, scm, scn, lower_only, a_lower, st)
-  if (narrow) {
-    if (akc && bkc) GEMM64_CASE(64, true, true);
-    else if (akc) GEMM64_CASE(64, true, false);
-    else if (bkc) GEMM64_CASE(64, false, true);
-    else GEMM64_CASE(64, false, false);
-  } else {
-    if (akc && bkc) GEMM64_CASE(128, true, true);
-    else if (akc) GEMM64_CASE(128, true, false);
-    else if (bkc) GEMM64_CASE(128, false, true);
-    else GEMM64_CASE(128, false, false);
-  }
-#undef GEMM64_CASE
+template <class TL>
+static void launch64(const Gemm64Args& g, const EpiCol64& e, bool b_kcontig, hipStream_t st, int batch = 1) {
+  const int ntn = cdiv(g.N, TL::BN), ntm = cdiv(g.M, TL::BM);
+  if (b_kcontig) launch64<TL, true>(g, e, ntn, ntm, batch, st);
+  else launch64<TL, false>(g, e, ntn, ntm, batch, st);
 }
 
-void gemm64(int M, int N, int K, double alpha, View64 A, View64 B, double beta, double* C, int64_t scm, int64_t scn,
-            bool lower_only, hipStream_t st) {
-  gemm64_dispatch(M, N, K, alpha, A, B, beta, C, scm, scn, lower_only, false, st);
+void gemm64(int M, int N, int K, double alpha, const double* A, int64_t lda, const double* B, int64_t ldb,
+            bool b_kcontig, double beta, double* C, int64_t ldc, bool lower_only, hipStream_t st) {
+  if (M <= 0 || N <= 0) return;
+  Gemm64Args g{};
+  g.A = A; g.B = B; g.lda = lda; g.ldb = ldb;
+  g.M = M; g.N = N; g.K = K;
+  g.lower_only = lower_only;
+  const EpiCol64 e{C, ldc, 0, alpha, beta, 0};
+  const int64_t large = (int64_t)cdiv(M, 128) * cdiv(N, 128) / (lower_only ? 2 : 1);
+  if (N <= 64) launch64<T64N>(g, e, b_kcontig, st);
+  else if (large < 256) launch64<T64S>(g, e, b_kcontig, st);
+  else launch64<T64L>(g, e, b_kcontig, st);
 }
 
 template <bool AKC, bool BKC>
@@ -75,205 +71,90 @@ void gemm64_in32(int M, int N, int K, double alpha, View32 A, View32 B, double b
   else gemm64_in32_t<false, false>(M, N, K, alpha, A, B, beta, C, scm, scn, st);
 }
 
-void gemm64_alower(int M, int N, int K, double alpha, View64 A, View64 B, double beta, double* C, int64_t scm,
-                   int64_t scn, hipStream_t st) {
-  gemm64_dispatch(M, N, K, alpha, A, B, beta, C, scm, scn, false, true, st);
-}
-
 // ------------------------------------- Cholesky and triangular inversion ----
-constexpr int NB = 64;
+constexpr int NB = 64, NB2 = 256;
 
-// Unblocked Cholesky of one jb x jb diagonal block (column-major, lda) in LDS.
-__global__ __launch_bounds__(256) void k_potf2(double* A, int jb, int64_t lda, int64_t j0, int64_t* info) {
-  __shared__ double L[NB][NB + 1];
-  __shared__ int bad;
-  const int tid = threadIdx.x;
-  if (tid == 0) bad = 0;
-  for (int e = tid; e < jb * jb; e += 256) {
-    const int r = e % jb, c = e / jb;
-    L[r][c] = A[r + c * lda];
-  }
-  __syncthreads();
-  for (int c = 0; c < jb; ++c) {   // right-looking, column by column
-    if (tid == 0) {
-      const double d = L[c][c];
-      if (!(d > 0.0) || !isfinite(d)) {
-        if (!bad) {
-          bad = 1;
-          atomicMin(reinterpret_cast<unsigned long long*>(info), (unsigned long long)(j0 + c));
-        }
-        L[c][c] = 1.0;
-      } else {
-        L[c][c] = sqrt(d);
-      }
-    }
-    __syncthreads();
-    const double piv = L[c][c];
-    for (int r = c + 1 + tid; r < jb; r += 256) L[r][c] /= piv;
-    __syncthreads();
-    const int w = jb - c - 1;
-    for (int e = tid; e < w * w; e += 256) {
-      const int r = c + 1 + e % w, q = c + 1 + e / w;
-      if (q <= r) L[r][q] -= L[r][c] * L[q][c];
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < jb * jb; e += 256) {
-    const int r = e % jb, c = e / jb;
-    A[r + c * lda] = r >= c ? L[r][c] : 0.0;   // clean lower-triangular block
-  }
-}
-
-// Inverse of the jb x jb lower-triangular block at A (lda) into X (NB x NB row-major, zero padded).
-__global__ __launch_bounds__(64) void k_tri_inverse(const double* A, int jb, int64_t lda, double* X) {
-  __shared__ double L[NB][NB + 1];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < NB * NB; e += 64) {
+// Cholesky of the jb x jb diagonal block at A (in place, zero above its
+// diagonal) and its inverse Linv (NB x NB row-major, unit rows past jb); the
+// first failing column (offset by j0) goes to info.
+__global__ __launch_bounds__(256) void k_potf2(double* A, int jb, int64_t lda, int64_t j0, int64_t* info,
+                                               double* Linv) {
+  __shared__ Chol64 s;
+  for (int e = threadIdx.x; e < NB * NB; e += 256) {
     const int r = e % NB, c = e / NB;
-    L[r][c] = (r < jb && c < jb) ? A[r + c * lda] : (r == c ? 1.0 : 0.0);
+    s.T[r][c] = r < jb && c <= r ? A[r + c * lda] : (r == c ? 1.0 : 0.0);
   }
   __syncthreads();
-  const int c = tid;
-  double x[NB];
-#pragma unroll
-  for (int r = 0; r < NB; ++r) x[r] = 0.0;
-  // column c of the inverse, computed in registers with static indices
-#pragma unroll
-  for (int r = 0; r < NB; ++r) {
-    if (r == c) x[r] = 1.0 / L[r][r];
-    if (r > c) {
-      double sacc = 0.0;
-#pragma unroll
-      for (int q = 0; q < r; ++q) sacc += L[r][q] * x[q];
-      x[r] = -sacc / L[r][r];
-    }
+  chol64<false>(s, 0.0);
+  if (threadIdx.x == 0) {
+    int bad = -1;
+    for (int c = NB - 1; c >= 0; --c)
+      if (s.bad[c]) bad = c;
+    if (bad >= 0) atomicMin(reinterpret_cast<unsigned long long*>(info), (unsigned long long)(j0 + bad));
   }
-#pragma unroll
-  for (int r = 0; r < NB; ++r) X[r * NB + c] = x[r];
+  tri64_inverse(s);
+  __syncthreads();
+  for (int e = threadIdx.x; e < NB * NB; e += 256) {
+    const int r = e % NB, c = e / NB;
+    if (r < jb && c < jb) A[r + c * lda] = r >= c ? s.T[r][c] : 0.0;
+    Linv[e] = s.X[e / NB][e % NB];
+  }
 }
 
-// In-place inverse of a jb x jb lower-triangular diagonal block.
-__global__ __launch_bounds__(64) void k_trtri_small(double* A, int jb, int64_t lda) {
-  __shared__ double L[NB][NB + 1];
-  __shared__ double X[NB][NB + 1];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < jb * jb; e += 64) {
-    const int r = e % jb, c = e / jb;
-    L[r][c] = A[r + c * lda];
+// In-place inverse of every 64 x 64 lower-triangular diagonal block of the
+// n x n matrix A, one block each; zero above their diagonals.
+__global__ __launch_bounds__(256) void k_tri64(double* A, int64_t n, int64_t lda) {
+  __shared__ Chol64 s;
+  const int64_t j0 = (int64_t)blockIdx.x * NB;
+  const int jb = (int)min((int64_t)NB, n - j0);
+  double* D = A + j0 + j0 * lda;
+  for (int e = threadIdx.x; e < NB * NB; e += 256) {
+    const int r = e % NB, c = e / NB;
+    s.T[r][c] = r < jb && c <= r ? D[r + c * lda] : (r == c ? 1.0 : 0.0);
   }
   __syncthreads();
-  const int c = tid;   // one column of the inverse per thread
-  if (c < jb) {
-    X[c][c] = 1.0 / L[c][c];
-    for (int r = c + 1; r < jb; ++r) {
-      double s = 0.0;
-      for (int q = c; q < r; ++q) s += L[r][q] * X[q][c];
-      X[r][c] = -s / L[r][r];
-    }
-  }
+  tri64_diag(s);
   __syncthreads();
-  for (int e = tid; e < jb * jb; e += 64) {
-    const int r = e % jb, cc = e / jb;
-    A[r + cc * lda] = r >= cc ? X[r][cc] : 0.0;
+  tri64_inverse(s);
+  __syncthreads();
+  for (int e = threadIdx.x; e < jb * NB; e += 256) {
+    const int r = e % NB, c = e / NB;
+    if (r < jb) D[r + c * lda] = s.X[r][c];
   }
 }
 
-// In-place inverse of the lower-triangular A (n x n, lda) in 64-wide blocks,
-// last block first, with T ((n - 64) x 64) as scratch; entries above the
-// diagonal of each 64-wide diagonal block become zero, those further above
-// are not touched.
-static void trtri_nb(double* A, int64_t n, int64_t lda, hipStream_t st, double* T) {
-  const int64_t nblk = (n + NB - 1) / NB;
-  for (int64_t b = nblk - 1; b >= 0; --b) {
-    const int64_t j0 = b * NB;
-    const int jb = (int)std::min<int64_t>(NB, n - j0);
-    const int64_t rest = n - j0 - jb;
-    if (rest > 0) {
-      // T = X22 * A21 (X22 = already inverted trailing block, lower-triangular)
-      const double* X22 = A + (j0 + jb) + (j0 + jb) * lda;
-      double* A21 = A + (j0 + jb) + j0 * lda;
-      gemm64_alower((int)rest, jb, (int)rest, 1.0, View64{X22, 1, lda}, View64{A21, lda, 1}, 0.0, T, 1, rest, st);
-      k_trtri_small<<<1, 64, 0, st>>>(A + j0 + j0 * lda, jb, lda);
-      LAUNCHCHK();
-      // A21 = -T * X11
-      const double* X11 = A + j0 + j0 * lda;
-      gemm64((int)rest, jb, jb, -1.0, View64{T, 1, rest}, View64{X11, lda, 1}, 0.0, A21, 1, lda, false, st);
-    } else {
-      k_trtri_small<<<1, 64, 0, st>>>(A + j0 + j0 * lda, jb, lda);
-      LAUNCHCHK();
-    }
-  }
+// Zero the entries above the diagonal of every 256 x 256 diagonal block of A
+// and, for odd n, its padding row n, which a product with a k-contiguous
+// operand of odd depth reads.
+__global__ void k_zero_upper_blocks(double* A, int64_t n, int64_t lda) {
+  const int64_t c = blockIdx.x, j0 = c / NB2 * NB2;
+  for (int64_t r = j0 + threadIdx.x; r < c; r += blockDim.x) A[r + c * lda] = 0.0;
+  if ((n & 1) && threadIdx.x == 0) A[n + c * lda] = 0.0;
 }
 
-// Zero the entries above the diagonal of the n x n block A (lda).
-__global__ void k_zero_upper(double* A, int64_t lda, int n) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (int64_t)n * n) return;
-  const int r = (int)(e % n), c = (int)(e / n);
-  if (r < c) A[r + c * lda] = 0.0;
-}
-
-// Right-looking Cholesky in 64-wide panels on the block A (n x n, lda); the
-// first failing column (offset by j_off) goes to info.
-static void potrf_nb(double* A, int64_t n, int64_t lda, int64_t j_off, int64_t* info, double* Xinv,
-                     hipStream_t st) {
-  for (int64_t j0 = 0; j0 < n; j0 += NB) {
-    const int jb = (int)std::min<int64_t>(NB, n - j0);
-    k_potf2<<<1, 256, 0, st>>>(A + j0 + j0 * lda, jb, lda, j_off + j0, info);
-    LAUNCHCHK();
-    const int64_t rest = n - j0 - jb;
-    if (rest > 0) {
-      // panel <- panel L_jj^-T  (in place: one 128-row tile covers all jb columns)
-      k_tri_inverse<<<1, 64, 0, st>>>(A + j0 + j0 * lda, jb, lda, Xinv);
-      LAUNCHCHK();
-      double* P = A + (j0 + jb) + j0 * lda;
-      gemm64((int)rest, jb, jb, 1.0, View64{P, 1, lda}, View64{Xinv, NB, 1}, 0.0, P, 1, lda, false, st);
-      double* C = A + (j0 + jb) + (j0 + jb) * lda;
-      gemm64((int)rest, (int)rest, jb, -1.0, View64{P, 1, lda}, View64{P, 1, lda}, 1.0, C, 1, lda, true, st);
-    }
-  }
-}
-
-// dst (n x n, ldd) = the lower triangle of src (lda), zero above the diagonal
-__global__ void k_copy_lower(const double* __restrict__ src, int64_t lda, int n, double* __restrict__ dst,
-                             int64_t ldd) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (int64_t)n * n) return;
-  const int r = (int)(e % n), c = (int)(e / n);
-  dst[r + c * ldd] = r >= c ? src[r + c * lda] : 0.0;
-}
-
-// Two levels of blocking.  With 64-wide panels every trailing update reads
-// and writes the whole trailing matrix for a K = 64 product, about 2 TB for
-// n = 31500, so the factorization ran at the speed of HBM.  Here 256-wide
-// panels are factored by the 64-wide code (diagonal block), their rows
-// below are solved against the inverted diagonal block, and the trailing
-// matrix takes one K = 256 update per panel: a quarter of the traffic, for
-// products that the matrix cores, not HBM, bound.
+// Lower Cholesky in 256-wide panels of four 64-wide columns each.  A 64-wide
+// column is one small kernel (diagonal block and its inverse), one product
+// that solves the rows below it and one that updates the rest of the panel;
+// the trailing matrix takes one K = 256 product per panel.  (K = 64 updates of
+// the whole trailing matrix ran at the speed of HBM: about 2 TB at n = 31500.)
 int64_t potrf_lower(double* A, int64_t n, int64_t lda, hipStream_t st) {
-  constexpr int NB2 = 256;
-  DBuf info(8), Xinv(NB * NB * 8), L1((size_t)NB2 * NB2 * 8), T(std::max<int64_t>(n - NB2, 1) * NB2 * 8),
-      Ts((size_t)(NB2 - NB) * NB * 8);
+  DBuf info(8), Xinv(NB * NB * 8);
   const unsigned long long none = ~0ull;
   HIPCHK(hipMemcpyAsync(info.get(), &none, 8, hipMemcpyHostToDevice, st));
   for (int64_t J0 = 0; J0 < n; J0 += NB2) {
-    const int jb = (int)std::min<int64_t>(NB2, n - J0);
-    double* D = A + J0 + J0 * lda;
-    potrf_nb(D, jb, lda, J0, info.as<int64_t>(), Xinv.as<double>(), st);
-    const int64_t rest = n - J0 - jb;
-    if (rest > 0) {
-      // L1 = L_JJ^-1 (lower, zero above), T = A_21 L1^T, then A_22 -= T T^T and A_21 = T
-      k_copy_lower<<<cdiv((int64_t)jb * jb, 256), 256, 0, st>>>(D, lda, jb, L1.as<double>(), jb);
+    const int64_t J1 = std::min<int64_t>(J0 + NB2, n);
+    for (int64_t j0 = J0; j0 < J1; j0 += NB) {
+      const int jb = (int)std::min<int64_t>(NB, J1 - j0);
+      k_potf2<<<1, 256, 0, st>>>(A + j0 + j0 * lda, jb, lda, j0, info.as<int64_t>(), Xinv.as<double>());
       LAUNCHCHK();
-      trtri_nb(L1.as<double>(), jb, jb, st, Ts.as<double>());
-      double* A21 = A + (J0 + jb) + J0 * lda;
-      gemm64((int)rest, jb, jb, 1.0, View64{A21, 1, lda}, View64{L1.as<double>(), 1, jb}, 0.0, T.as<double>(), 1,
-             rest, false, st);
-      double* C = A + (J0 + jb) + (J0 + jb) * lda;
-      gemm64((int)rest, (int)rest, jb, -1.0, View64{T.as<double>(), 1, rest}, View64{T.as<double>(), 1, rest}, 1.0,
-             C, 1, lda, true, st);
-      HIPCHK(hipMemcpy2DAsync(A21, lda * 8, T.get(), rest * 8, rest * 8, jb, hipMemcpyDeviceToDevice, st));
+      const int64_t j1 = j0 + jb;
+      double* P = A + j1 + j0 * lda;   // panel <- panel L_jj^-T
+      gemm64((int)(n - j1), jb, jb, 1.0, P, lda, Xinv.as<double>(), NB, true, 0.0, P, lda, false, st);
+      gemm64((int)(n - j1), (int)(J1 - j1), jb, -1.0, P, lda, P, lda, false, 1.0, A + j1 + j1 * lda, lda, true, st);
     }
+    const double* P = A + J1 + J0 * lda;
+    gemm64((int)(n - J1), (int)(n - J1), (int)(J1 - J0), -1.0, P, lda, P, lda, false, 1.0, A + J1 + J1 * lda, lda,
+           true, st);
   }
   unsigned long long h = 0;
   HIPCHK(hipMemcpyAsync(&h, info.get(), 8, hipMemcpyDeviceToHost, st));
@@ -281,36 +162,60 @@ int64_t potrf_lower(double* A, int64_t n, int64_t lda, hipStream_t st) {
   return h == none ? -1 : (int64_t)h;
 }
 
-// In-place inverse of the lower-triangular A (n x n, lda).  Two levels, as
-// potrf_lower: 256-wide blocks, last first.  For each, T = X22 A21 with the
-// already inverted trailing block (K = rest, N = 256: a quarter of the reads
-// of X22 that 64-wide blocks needed), the diagonal block inverted by the
-// 64-wide code, then A21 = -T X11.
+// In-place inverse of the lower-triangular A (n x n, lda).  The 256-wide
+// diagonal blocks are inverted first, all at once: 64-wide blocks by one
+// kernel, then pairs of them twice, [X11 0; -X22 L21 X11 X22], as batched
+// products.  Then, with C = L below the diagonal blocks, from the first block
+// column on: C_ij <- C_ij X_jj (in place), C_i,<j -= C_ij C_j,<j (one K = 256
+// product over the whole trailing part), and at the end X_k,<k = -X_kk C_k,<k.
+// Every large product has many tiles of equal depth.  (Block columns from the
+// last on, T = X22 A21, gave at most n / 64 tiles, of depths up to n.)
 void trtri_lower(double* A, int64_t n, int64_t lda, hipStream_t st) {
-  constexpr int NB2 = 256;
-  const int64_t nblk = (n + NB2 - 1) / NB2;
-  DBuf T(std::max<int64_t>(n - NB2, 1) * NB2 * sizeof(double)), Ts((NB2 - NB) * NB * sizeof(double));
-  for (int64_t b = nblk - 1; b >= 0; --b) {
-    const int64_t j0 = b * NB2;
-    const int jb = (int)std::min<int64_t>(NB2, n - j0);
-    const int64_t rest = n - j0 - jb;
-    double* D = A + j0 + j0 * lda;
-    if (rest > 0) {
-      const double* X22 = A + (j0 + jb) + (j0 + jb) * lda;
-      double* A21 = A + (j0 + jb) + j0 * lda;
-      gemm64_alower((int)rest, jb, (int)rest, 1.0, View64{X22, 1, lda}, View64{A21, lda, 1}, 0.0, T.as<double>(), 1,
-                    rest, st);
-      trtri_nb(D, jb, lda, st, Ts.as<double>());
-      // X11 enters the product below as a full block: nothing above its diagonal
-      k_zero_upper<<<cdiv((int64_t)jb * jb, 256), 256, 0, st>>>(D, lda, jb);
-      LAUNCHCHK();
-      gemm64((int)rest, jb, jb, -1.0, View64{T.as<double>(), 1, rest}, View64{D, lda, 1}, 0.0, A21, 1, lda, false,
-             st);
-    } else {
-      trtri_nb(D, jb, lda, st, Ts.as<double>());
-    }
+  if (n <= 0) return;
+  const int64_t nblk = cdiv(n, NB2);
+  k_tri64<<<cdiv(n, NB), 256, 0, st>>>(A, n, lda);
+  LAUNCHCHK();
+  k_zero_upper_blocks<<<(unsigned)n, 64, 0, st>>>(A, n, lda);
+  LAUNCHCHK();
+  const size_t tb = (size_t)nblk * (NB2 / 2) * (NB2 / 2) * 8;   // products of the pairs: larger at the second level
+  DBuf T(tb);
+  HIPCHK(hipMemsetAsync(T.get(), 0, tb, st));
+  for (int h = NB; h < NB2; h *= 2) {
+    const int pairs = cdiv(n, 2 * h);
+    const int64_t step = 2 * h * (1 + lda);   // from one pair to the next
+    Gemm64Args g{};
+    g.M = h; g.N = h; g.K = h;
+    g.row_step = 2 * h;
+    g.row_end = n - h;   // rows left for the second block of a pair
+    g.A = A + h; g.lda = lda; g.sA = step;   // L21 X11 -> T
+    g.B = A; g.ldb = lda; g.sB = step;
+    launch64<T64S>(g, EpiCol64{T.as<double>(), h, (int64_t)h * h, 1.0, 0.0, 0}, true, st, pairs);
+    g.A = A + h + h * lda;                   // -X22 T -> X21
+    g.B = T.as<double>(); g.ldb = h; g.sB = (int64_t)h * h;
+    g.ktrim = 1;
+    launch64<T64S>(g, EpiCol64{A + h, lda, step, -1.0, 0.0, 0}, true, st, pairs);
   }
-  HIPCHK(hipStreamSynchronize(st));   // T and Ts are released on return
+  for (int64_t j0 = 0; j0 + NB2 < n; j0 += NB2) {
+    const int64_t j1 = j0 + NB2;
+    double* P = A + j1 + j0 * lda;
+    Gemm64Args g{};
+    g.M = (int)(n - j1); g.N = NB2; g.K = NB2;
+    g.A = P; g.lda = lda;
+    g.B = A + j0 + j0 * lda; g.ldb = lda;
+    launch64<T64W>(g, EpiCol64{P, lda, 0, 1.0, 0.0, 0}, true, st);
+    gemm64((int)(n - j1), (int)j0, NB2, -1.0, P, lda, A + j0, lda, true, 1.0, A + j1, lda, false, st);
+  }
+  if (nblk > 1) {   // rows of block k >= 1, all its columns left of the diagonal block, in place
+    Gemm64Args g{};
+    g.M = NB2; g.N = (int)((nblk - 1) * NB2); g.K = NB2;
+    g.A = A; g.lda = lda; g.sA = NB2 * (1 + lda);
+    g.B = A; g.ldb = lda; g.sB = NB2;
+    g.row_step = NB2; g.row_end = n;
+    g.ktrim = 1;
+    g.ncol_step = NB2;
+    launch64<T64H>(g, EpiCol64{A, lda, NB2, -1.0, 0.0, 0}, true, st, (int)nblk);
+  }
+  HIPCHK(hipStreamSynchronize(st));   // T is released on return
 }
 
 }  // namespace ffk

@@ -4,12 +4,13 @@
 // L is built as the incomplete Cholesky factor with pivots forced to the
 // selected column order: for identical columns this equals the Nystroem
 // factor K_nk K_kk^-1 K_nk^T (section 3).  The columns are processed in panels
-// of 64: (1) evaluate the raw kernel columns, (2) subtract the contribution of
-// all earlier panels with one FP64 MFMA GEMM, (3) factor the 64 x 64 pivot
-// block (dropping columns whose remaining diagonal is <= 1e-12 max diag K) and
-// invert it, (4) multiply the panel by that inverse (an in-place MFMA GEMM),
-// (5) zero the rows of earlier pivots and set the exact pivot values, as
-// Algorithm 1 leaves them.
+// of 64, four to a group: (1) evaluate the group's raw kernel columns, (2)
+// subtract the contribution of all earlier groups with one FP64 MFMA GEMM,
+// then per panel (3) subtract that of the group's earlier panels, (4) factor
+// the 64 x 64 pivot block (dropping columns whose remaining diagonal is <=
+// 1e-12 max diag K) and invert it, (5) multiply the panel by that inverse (an
+// in-place MFMA GEMM), (6) zero the rows of earlier pivots and set the exact
+// pivot values, as Algorithm 1 leaves them.
 // The core C = lambda I + L^T L is formed from the stored L (FP64, FP32 or BF16)
 // in FP64 and factored, C = F F^T, and the triangular inverse F^-1 is kept:
 // z = lambda^-1 (r - L F^-T F^-1 L^T r), two passes over L and two over the
@@ -18,11 +19,12 @@
 // then needs half again as many iterations.)
 // L and F^-1 are column-major with leading dimensions padded to 64 elements
 // (zero padding), so the GEMVs of the apply use aligned 16-byte loads.
-#include "gemm.hpp"
+#include "chol64.hpp"
 
 namespace ffk {
 
-constexpr int PB = 64;   // panel width
+constexpr int PB = 64;      // panel width
+constexpr int GB = 4 * PB;   // group width
 
 inline int64_t pad64(int64_t a) { return (a + 63) / 64 * 64; }
 
@@ -45,67 +47,26 @@ __global__ void k_gather_rows32(const float* L, int64_t ld, const int64_t* idx, 
 }
 
 // Factor the nb x nb pivot block T[c][c'] = panel[idx[c], c'] with drops and
-// invert it.  Outputs: Lb (PB x PB row-major, lower; dropped columns zero),
-// Linv (PB x PB row-major) = inverse of Lb with a unit diagonal put at dropped
-// positions, drop flags.
+// invert it.  Outputs: diag (PB) of the factor, Linv (PB x PB row-major) = its
+// inverse with a unit diagonal put at dropped positions, kept flags.  One
+// block on one CU: 218 us with three barriers a column, 42 us on 16 x 16
+// blocks (chol64.hpp).
 __global__ __launch_bounds__(256) void k_panel_chol(const double* Lp, int64_t ld, const int64_t* idx, int nb,
-                                                    double thr, double* Lb, double* Linv, unsigned char* dropped) {
-  __shared__ double T[PB][PB + 1];
-  __shared__ double X[PB][PB + 1];
-  __shared__ unsigned char dr[PB];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < PB * PB; e += 256) {
+                                                    double thr, double* diag, double* Linv, unsigned char* kept) {
+  __shared__ Chol64 s;
+  for (int e = threadIdx.x; e < PB * PB; e += 256) {
     const int r = e % PB, c = e / PB;
-    T[r][c] = (r < nb && c < nb) ? Lp[idx[r] + (int64_t)c * ld] : (r == c ? 1.0 : 0.0);
+    s.T[r][c] = (r < nb && c <= r) ? Lp[idx[r] + (int64_t)c * ld] : (r == c ? 1.0 : 0.0);
   }
   __syncthreads();
-  for (int c = 0; c < nb; ++c) {
-    if (tid == 0) {
-      const double d = T[c][c];
-      if (!(d > thr)) {
-        dr[c] = 1;
-        T[c][c] = 0.0;
-      } else {
-        dr[c] = 0;
-        T[c][c] = sqrt(d);
-      }
-    }
-    __syncthreads();
-    const bool drop = dr[c];
-    const double piv = T[c][c];
-    for (int r = c + 1 + tid; r < nb; r += 256) T[r][c] = drop ? 0.0 : T[r][c] / piv;
-    __syncthreads();
-    if (!drop) {
-      const int w = nb - c - 1;
-      for (int e = tid; e < w * w; e += 256) {
-        const int r = c + 1 + e % w, q = c + 1 + e / w;
-        if (q <= r) T[r][q] -= T[r][c] * T[q][c];
-      }
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < PB * PB; e += 256) {
-    const int r = e / PB, c = e % PB;
-    Lb[e] = (r < nb && c < nb && r >= c) ? T[r][c] : 0.0;
-  }
-  for (int c = tid; c < nb; c += 256) dropped[c] = dr[c];
+  chol64<true>(s, thr);
+  tri64_inverse(s);
   __syncthreads();
-  // unit diagonal at dropped (and padding) positions: their columns are zero
-  // below the diagonal, so the kept part of the solve is unaffected
-  if (tid < PB && (tid >= nb || dr[tid])) T[tid][tid] = 1.0;
-  __syncthreads();
-  if (tid < PB) {   // column tid of the inverse by forward substitution
-    const int c = tid;
-    for (int r = 0; r < c; ++r) X[r][c] = 0.0;
-    X[c][c] = 1.0 / T[c][c];
-    for (int r = c + 1; r < PB; ++r) {
-      double sacc = 0.0;
-      for (int q = c; q < r; ++q) sacc += (q < nb && r < nb) ? T[r][q] * X[q][c] : 0.0;
-      X[r][c] = -sacc / T[r][r];
-    }
+  for (int e = threadIdx.x; e < PB * PB; e += 256) Linv[e] = s.X[e / PB][e % PB];
+  if ((int)threadIdx.x < nb) {
+    diag[threadIdx.x] = s.T[threadIdx.x][threadIdx.x];
+    kept[threadIdx.x] = s.bad[threadIdx.x] ? 0 : 1;
   }
-  __syncthreads();
-  for (int e = tid; e < PB * PB; e += 256) Linv[e] = X[e / PB][e % PB];
 }
 
 // Exact zeros at earlier pivot rows and the exact pivot value on the diagonal;
@@ -113,7 +74,7 @@ __global__ __launch_bounds__(256) void k_panel_chol(const double* Lp, int64_t ld
 // (The panel's column c is at L + (m0 - col0 + c) ld: col0 = 0 when L is the
 // whole factor, col0 = m0 when L is a panel buffer of its own.)
 __global__ void k_panel_fix(double* L, int64_t n, int64_t ld, const int64_t* idx, const unsigned char* kept,
-                            int64_t m0, int nb, const double* Lb, int64_t col0) {
+                            int64_t m0, int nb, const double* diag, int64_t col0) {
   const int c = blockIdx.x;
   double* col = L + (m0 - col0 + c) * ld;
   if (!kept[m0 + c]) {
@@ -122,38 +83,38 @@ __global__ void k_panel_fix(double* L, int64_t n, int64_t ld, const int64_t* idx
   }
   for (int64_t j = threadIdx.x; j < m0 + c; j += blockDim.x)
     if (kept[j]) col[idx[j]] = 0.0;
-  if (threadIdx.x == 0) col[idx[m0 + c]] = Lb[c * PB + c];
-}
-
-__global__ void k_set_kept(const unsigned char* dropped, int nb, unsigned char* kept) {
-  const int c = threadIdx.x;
-  if (c < nb) kept[c] = dropped[c] ? 0 : 1;
+  if (threadIdx.x == 0) col[idx[m0 + c]] = diag[c];
 }
 
 int64_t icd_forced(ffk_system* s, const int64_t* idx, int64_t k, double shift, double* L, int64_t ld,
                    std::vector<char>* kept_out, hipStream_t st) {
   const int64_t n = s->n;
   const double thr = 1e-12 * (max_diag(s, st) + shift);
-  DBuf G((int64_t)PB * std::max<int64_t>(k, 1) * 8), Lb(PB * PB * 8), Linv(PB * PB * 8), dropped(PB),
-      kept(std::max<int64_t>(k, 1));
-  for (int64_t m0 = 0; m0 < k; m0 += PB) {
-    const int nb = (int)std::min<int64_t>(PB, k - m0);
-    double* Lp = L + m0 * ld;
-    kernel_columns(s, idx + m0, nb, Lp, ld, shift, st);
-    if (m0 > 0) {
-      k_gather_rows<<<cdiv((int64_t)nb * m0, 256), 256, 0, st>>>(L, ld, idx + m0, nb, m0, G.as<double>());
+  DBuf G((int64_t)GB * std::max<int64_t>(k, 1) * 8), diag(PB * 8), Linv(PB * PB * 8), kept(std::max<int64_t>(k, 1));
+  // columns [m0, m0 + nb) -= L[:, j0 .. m0) (rows idx[m0 ..) of it)^T
+  auto subtract = [&](int64_t m0, int nb, int64_t j0) {
+    const int64_t w = m0 - j0;
+    if (w == 0) return;
+    k_gather_rows<<<cdiv(nb * w, 256), 256, 0, st>>>(L + j0 * ld, ld, idx + m0, nb, w, G.as<double>());
+    LAUNCHCHK();
+    gemm64((int)n, nb, (int)w, -1.0, L + j0 * ld, ld, G.as<double>(), w, true, 1.0, L + m0 * ld, ld, false, st);
+  };
+  for (int64_t g0 = 0; g0 < k; g0 += GB) {
+    const int64_t g1 = std::min<int64_t>(g0 + GB, k);
+    kernel_columns(s, idx + g0, g1 - g0, L + g0 * ld, ld, shift, st);
+    subtract(g0, (int)(g1 - g0), 0);
+    for (int64_t m0 = g0; m0 < g1; m0 += PB) {
+      const int nb = (int)std::min<int64_t>(PB, g1 - m0);
+      double* Lp = L + m0 * ld;
+      subtract(m0, nb, g0);
+      k_panel_chol<<<1, 256, 0, st>>>(Lp, ld, idx + m0, nb, thr, diag.as<double>(), Linv.as<double>(),
+                                      kept.as<unsigned char>() + m0);
       LAUNCHCHK();
-      gemm64((int)n, nb, (int)m0, -1.0, View64{L, 1, ld}, View64{G.as<double>(), m0, 1}, 1.0, Lp, 1, ld, false, st);
+      // panel <- panel Linv^T; in place is safe: one tile covers all nb columns
+      gemm64((int)n, nb, nb, 1.0, Lp, ld, Linv.as<double>(), PB, true, 0.0, Lp, ld, false, st);
+      k_panel_fix<<<nb, 256, 0, st>>>(L, n, ld, idx, kept.as<unsigned char>(), m0, nb, diag.as<double>(), 0);
+      LAUNCHCHK();
     }
-    k_panel_chol<<<1, 256, 0, st>>>(Lp, ld, idx + m0, nb, thr, Lb.as<double>(), Linv.as<double>(),
-                                    dropped.as<unsigned char>());
-    LAUNCHCHK();
-    // panel <- panel Linv^T; in place is safe: one 128-row tile covers all nb columns
-    gemm64((int)n, nb, nb, 1.0, View64{Lp, 1, ld}, View64{Linv.as<double>(), PB, 1}, 0.0, Lp, 1, ld, false, st);
-    k_set_kept<<<1, PB, 0, st>>>(dropped.as<unsigned char>(), nb, kept.as<unsigned char>() + m0);
-    LAUNCHCHK();
-    k_panel_fix<<<nb, 256, 0, st>>>(L, n, ld, idx, kept.as<unsigned char>(), m0, nb, Lb.as<double>(), 0);
-    LAUNCHCHK();
   }
   std::vector<char> hk(std::max<int64_t>(k, 1));
   HIPCHK(hipMemcpyAsync(hk.data(), kept.get(), k, hipMemcpyDeviceToHost, st));
@@ -178,8 +139,8 @@ static int64_t icd_forced_f32(ffk_system* s, const int64_t* idx, int64_t k, floa
                               std::vector<char>* kept_out, hipStream_t st) {
   const int64_t n = s->n;
   const double thr = 1e-12 * max_diag(s, st);
-  DBuf P64(ld * PB * 8), G((int64_t)PB * std::max<int64_t>(k, 1) * 4), Lb(PB * PB * 8), Linv(PB * PB * 8),
-      dropped(PB), kept(std::max<int64_t>(k, 1));
+  DBuf P64(ld * PB * 8), G((int64_t)PB * std::max<int64_t>(k, 1) * 4), diag(PB * 8), Linv(PB * PB * 8),
+      kept(std::max<int64_t>(k, 1));
   double* Lp = P64.as<double>();
   for (int64_t m0 = 0; m0 < k; m0 += PB) {
     const int nb = (int)std::min<int64_t>(PB, k - m0);
@@ -190,13 +151,11 @@ static int64_t icd_forced_f32(ffk_system* s, const int64_t* idx, int64_t k, floa
       LAUNCHCHK();
       gemm64_in32((int)n, nb, (int)m0, -1.0, View32{L32, 1, ld}, View32{G.as<float>(), m0, 1}, 1.0, Lp, 1, ld, st);
     }
-    k_panel_chol<<<1, 256, 0, st>>>(Lp, ld, idx + m0, nb, thr, Lb.as<double>(), Linv.as<double>(),
-                                    dropped.as<unsigned char>());
+    k_panel_chol<<<1, 256, 0, st>>>(Lp, ld, idx + m0, nb, thr, diag.as<double>(), Linv.as<double>(),
+                                    kept.as<unsigned char>() + m0);
     LAUNCHCHK();
-    gemm64((int)n, nb, nb, 1.0, View64{Lp, 1, ld}, View64{Linv.as<double>(), PB, 1}, 0.0, Lp, 1, ld, false, st);
-    k_set_kept<<<1, PB, 0, st>>>(dropped.as<unsigned char>(), nb, kept.as<unsigned char>() + m0);
-    LAUNCHCHK();
-    k_panel_fix<<<nb, 256, 0, st>>>(Lp, n, ld, idx, kept.as<unsigned char>(), m0, nb, Lb.as<double>(), m0);
+    gemm64((int)n, nb, nb, 1.0, Lp, ld, Linv.as<double>(), PB, true, 0.0, Lp, ld, false, st);
+    k_panel_fix<<<nb, 256, 0, st>>>(Lp, n, ld, idx, kept.as<unsigned char>(), m0, nb, diag.as<double>(), m0);
     LAUNCHCHK();
     k_cols_to_f32<<<cdiv(ld * nb, 256), 256, 0, st>>>(Lp, ld, n, nb, L32 + m0 * ld);
     LAUNCHCHK();
@@ -969,10 +928,11 @@ void precond_export(const ffk_precond* P, double* L, hipStream_t st) {
   if (P->matrix_free) {
     // L = K[:, S] T^T, formed from the kernel's columns
     const int64_t n = P->n, k = P->k_eff;
-    DBuf C(n * k * 8);
-    kernel_columns(P->sys, P->sel.as<int64_t>(), k, C.as<double>(), n, 0.0, st);
-    gemm64((int)n, (int)k, (int)k, 1.0, View64{C.as<double>(), 1, n}, View64{P->Tinv.as<double>(), 1, P->ldf}, 0.0,
-           L, 1, n, false, st);
+    const int64_t ld = pad64(n);
+    DBuf C(ld * k * 8);
+    kernel_columns(P->sys, P->sel.as<int64_t>(), k, C.as<double>(), ld, 0.0, st);
+    gemm64((int)n, (int)k, (int)k, 1.0, C.as<double>(), ld, P->Tinv.as<double>(), P->ldf, false, 0.0, L, n, false,
+           st);
     HIPCHK(hipStreamSynchronize(st));
     return;
   }

@@ -13,12 +13,13 @@ __global__ void k_iota(int64_t* a, int64_t n) {
   if (i < n) a[i] = i;
 }
 
-// tau_c = 1 - lambda sum_{r >= c} X[r + c n]^2   (one wave per column)
-__global__ __launch_bounds__(256) void k_rls_from_inverse(const double* X, int64_t n, double lambda, double* tau) {
+// tau_c = 1 - lambda sum_{r >= c} X[r + c ld]^2   (one wave per column)
+__global__ __launch_bounds__(256) void k_rls_from_inverse(const double* X, int64_t n, int64_t ld, double lambda,
+                                                          double* tau) {
   const int lane = threadIdx.x & 63;
   const int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (c >= n) return;
-  const double* col = X + c * n;
+  const double* col = X + c * ld;
   double a = 0.0;
   for (int64_t r = c + lane; r < n; r += 64) a += col[r] * col[r];
 #pragma unroll
@@ -30,19 +31,20 @@ void exact_rls(ffk_system* s, double lambda, double* tau, hipStream_t st) {
   const int64_t n = s->n;
   size_t freeb = 0, total = 0;
   HIPCHK(hipMemGetInfo(&freeb, &total));
+  const int64_t ld = (n + 1) / 2 * 2;   // the factorization moves pairs of rows
   require((double)n * n * 8.0 < 0.9 * (double)freeb, "exact_rls: dense n x n matrix does not fit in device memory");
-  DBuf A((size_t)n * n * 8), cols(n * 8);
+  DBuf A((size_t)ld * n * 8), cols(n * 8);
   k_iota<<<cdiv(n, 256), 256, 0, st>>>(cols.as<int64_t>(), n);
   LAUNCHCHK();
   const int64_t chunk = 8192;
   for (int64_t c0 = 0; c0 < n; c0 += chunk) {
     const int64_t kc = std::min(chunk, n - c0);
-    kernel_columns(s, cols.as<int64_t>() + c0, kc, A.as<double>() + c0 * n, n, lambda, st);
+    kernel_columns(s, cols.as<int64_t>() + c0, kc, A.as<double>() + c0 * ld, ld, lambda, st);
   }
-  const int64_t bad = potrf_lower(A.as<double>(), n, n, st);
+  const int64_t bad = potrf_lower(A.as<double>(), n, ld, st);
   if (bad >= 0) fail(FFK_ERR_NOT_SPD, "exact_rls: K + lambda I is not numerically positive definite");
-  trtri_lower(A.as<double>(), n, n, st);
-  k_rls_from_inverse<<<cdiv(n, 4), 256, 0, st>>>(A.as<double>(), n, lambda, tau);
+  trtri_lower(A.as<double>(), n, ld, st);
+  k_rls_from_inverse<<<cdiv(n, 4), 256, 0, st>>>(A.as<double>(), n, ld, lambda, tau);
   LAUNCHCHK();
   HIPCHK(hipStreamSynchronize(st));
 }

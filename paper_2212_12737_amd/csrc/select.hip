@@ -292,18 +292,18 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
 }
 
 // ------------------------------------------------------------- leverage ----
-__global__ void k_leverage(const double* L0, int64_t n, int64_t s, const double* diag, double lambda,
+__global__ void k_leverage(const double* L0, int64_t n, int64_t ld, int64_t s, const double* diag, double lambda,
                            const unsigned char* pilot, double* tau) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   double a0 = 0.0, a1 = 0.0;
   int64_t j = 0;
   for (; j + 2 <= s; j += 2) {
-    const double x0 = L0[i + j * n], x1 = L0[i + (j + 1) * n];
+    const double x0 = L0[i + j * ld], x1 = L0[i + (j + 1) * ld];
     a0 += x0 * x0;
     a1 += x1 * x1;
   }
-  for (; j < s; ++j) a0 += L0[i + j * n] * L0[i + j * n];
+  for (; j < s; ++j) a0 += L0[i + j * ld] * L0[i + j * ld];
   double t = (diag[i] - (a0 + a1)) / lambda;
   if (pilot[i]) t = 1.0;
   tau[i] = fmin(fmax(t, kWeightFloor), 1.0);
@@ -328,15 +328,16 @@ __global__ void k_mark(const int64_t* idx, int64_t k, unsigned char* flag) {
 void leverage_estimate(ffk_system* s, const int64_t* pilot, int64_t ns, double lambda, double* tau,
                        hipStream_t st) {
   const int64_t n = s->n;
-  DBuf L0(n * ns * 8), diag(n * 8), flag(n);
-  HIPCHK(hipMemsetAsync(L0.get(), 0, n * ns * 8, st));
+  const int64_t ld = (n + 1) / 2 * 2;   // the panel products move pairs of rows
+  DBuf L0(ld * ns * 8), diag(n * 8), flag(n);
+  HIPCHK(hipMemsetAsync(L0.get(), 0, ld * ns * 8, st));
   std::vector<char> kept;
-  icd_forced(s, pilot, ns, lambda, L0.as<double>(), n, &kept, st);
+  icd_forced(s, pilot, ns, lambda, L0.as<double>(), ld, &kept, st);
   kernel_diag(s, diag.as<double>(), st);
   HIPCHK(hipMemsetAsync(flag.get(), 0, n, st));
   k_mark<<<cdiv(ns, 256), 256, 0, st>>>(pilot, ns, flag.as<unsigned char>());
   LAUNCHCHK();
-  k_leverage<<<cdiv(n, 256), 256, 0, st>>>(L0.as<double>(), n, ns, diag.as<double>(), lambda,
+  k_leverage<<<cdiv(n, 256), 256, 0, st>>>(L0.as<double>(), n, ld, ns, diag.as<double>(), lambda,
                                            flag.as<unsigned char>(), tau);
   LAUNCHCHK();
   HIPCHK(hipStreamSynchronize(st));
