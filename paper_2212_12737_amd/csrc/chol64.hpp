@@ -4,7 +4,7 @@
 // products between 16 x 16 blocks on FP64 MFMA.  What bounds it is the serial
 // chain of 64 pivots; a column-by-column factorization in LDS with three
 // barriers a column spent its time in the barriers: 80 us for the factor and 33
-// more for its inverse, now 35 us for both.
+// more for its inverse, now 30 us for both.
 #pragma once
 
 #include "gemm.hpp"
@@ -25,21 +25,50 @@ __device__ inline double lane_value(double x, int lane) {
   return __hiloint2double(hi, lo);
 }
 
-// s = sqrt(d), ri = 1 / s for d > 0: the hardware's reciprocal square root and
-// two Newton steps, both results corrected by their residuals (the library's
-// square root and divide are a chain twice as long, and 64 of them are serial).
+// s = sqrt(d), ri = 1 / s for 1e-280 < d < 1e280: the hardware's reciprocal
+// square root and two Newton steps, both results corrected by their residuals
+// (the library's square root and divide are a chain twice as long, and 64 of
+// them are serial).
 __device__ inline void sqrt_and_inverse(double d, double& s, double& ri) {
-  if (d < 1e-280 || d > 1e280) {   // the residuals would leave the range
-    s = sqrt(d);
-    ri = 1.0 / s;
-    return;
-  }
   double y = __builtin_amdgcn_rsq(d);
 #pragma unroll
   for (int i = 0; i < 2; ++i) y = fma(0.5 * y, fma(-d * y, y, 1.0), y);
   s = d * y;
   s = fma(fma(-s, s, d), 0.5 * y, s);
   ri = fma(fma(-s, y, 1.0), y, y);
+}
+
+// Cholesky of a 16 x 16 block, row r of it in a[0..15] of the lanes l % 16 = r;
+// ri: the inverses of the pivots' roots; the flagged pivots as bits.  One
+// straight line of code, so that the updates fill the pivots' latency; SAFE
+// takes the library's square root and divide.  Returns whether a pivot was
+// outside the range of sqrt_and_inverse.
+template <bool DROP, bool SAFE>
+__device__ inline bool factor16(double (&a)[16], double (&ri)[16], double thr, unsigned& flagged) {
+  const int r = threadIdx.x & 15;
+  bool range = false;
+  flagged = 0;
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {
+    const double d = lane_value(a[c], c);
+    const bool ok = DROP ? d > thr : (d > 0.0 && d < __builtin_huge_val());
+    double sq, inv;
+    if (SAFE) {
+      sq = sqrt(d);
+      inv = 1.0 / sq;
+    } else {
+      sqrt_and_inverse(d, sq, inv);
+      range |= ok && !(d > 1e-280 && d < 1e280);
+    }
+    const double none = DROP ? 0.0 : 1.0;
+    flagged |= ok ? 0u : 1u << c;
+    ri[c] = ok ? inv : 1.0;
+    const double f = ok ? inv : none;
+    a[c] = r == c ? (ok ? sq : none) : a[c] * f;
+#pragma unroll
+    for (int q = c + 1; q < 16; ++q) a[q] = fma(-a[c], lane_value(a[c], q), a[q]);
+  }
+  return range;
 }
 
 // acc += A B (B[k][col]) or A B^T (NT: B[col][k]) for 16 x 16 blocks; lane l
@@ -88,20 +117,17 @@ __device__ inline void chol64(Chol64& s, double thr) {
     const int c0 = 16 * b;
     if (wave == 0) {
       double a[16], ri[16];
+      auto load = [&]() {
 #pragma unroll
-      for (int c = 0; c < 16; ++c) a[c] = c <= r ? s.T[c0 + r][c0 + c] : 0.0;
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        const double d = lane_value(a[c], c);
-        const bool ok = DROP ? d > thr : (d > 0.0 && isfinite(d));
-        double sq = DROP ? 0.0 : 1.0, inv = sq;
-        if (ok) sqrt_and_inverse(d, sq, inv);
-        ri[c] = ok ? inv : 1.0;
-        a[c] = r == c ? sq : a[c] * inv;
-        if (lane == 0) s.bad[c0 + c] = !ok;
-#pragma unroll
-        for (int q = c + 1; q < 16; ++q) a[q] = fma(-a[c], lane_value(a[c], q), a[q]);
+        for (int c = 0; c < 16; ++c) a[c] = c <= r ? s.T[c0 + r][c0 + c] : 0.0;
+      };
+      unsigned flagged;
+      load();
+      if (factor16<DROP, false>(a, ri, thr, flagged)) {
+        load();
+        factor16<DROP, true>(a, ri, thr, flagged);
       }
+      if (lane < 16) s.bad[c0 + lane] = (flagged >> lane) & 1;
       if (lane < 16) {
 #pragma unroll
         for (int c = 0; c < 16; ++c)

@@ -7,12 +7,14 @@
 
 namespace ffk {
 
-// Tiles of the column-major GEMM.
-typedef Tile64<128, 128, 2, 2, 1, 4> T64L;   // the large tile
-typedef Tile64<64, 64, 2, 2, 1, 4> T64S;     // grids that leave CUs idle with it
-typedef Tile64<128, 64, 4, 1, 1, 4> T64N;    // N <= 64; in place (C = A) is safe: one tile spans the columns
-typedef Tile64<64, 256, 1, 4, 1, 3> T64W;    // in place for N <= 256 (C = A)
-typedef Tile64<256, 64, 4, 1, 1, 3> T64H;    // in place for M = K <= 256 (C = B)
+// Tiles of the column-major GEMM.  16 k between barriers and, where the tile
+// allows it, eight waves in two workgroups a CU: at M = N = 8192, K = 1024 the
+// 128 x 128 tile runs at 63 TFLOP/s with eight waves and 16 k, 51 with four
+// waves and 8 k, 59 and 62 with one of the two changed.
+typedef Tile64<128, 128, 2, 4, 2, 2> T64L;
+typedef Tile64<64, 64, 2, 2, 2, 2> T64S;
+typedef Tile64<128, 64, 4, 2, 2, 2> T64N;
+typedef Tile64<256, 64, 8, 1, 2, 2> T64H;    // in place for M = K <= 256 (C = B)
 
 template <class TL, bool BKC>
 static void launch64(const Gemm64Args& g, EpiCol64 e, int ntn, int ntm, int batch, hipStream_t st) {
@@ -39,9 +41,13 @@ void gemm64(int M, int N, int K, double alpha, const double* A, int64_t lda, con
   g.M = M; g.N = N; g.K = K;
   g.lower_only = lower_only;
   const EpiCol64 e{C, ldc, 0, alpha, beta, 0};
+  // The larger tile where it gives every CU one: at N = 64 = K it is 24
+  // against 17 TFLOP/s at M = 126016 and 9.6 against 11.2 at M = 12544, at M =
+  // 2048, N = 1024, K = 256 22 against 35.  N <= 64 takes a 64-wide tile
+  // always, which is safe in place.
   const int64_t large = (int64_t)cdiv(M, 128) * cdiv(N, 128) / (lower_only ? 2 : 1);
-  if (N <= 64) launch64<T64N>(g, e, b_kcontig, st);
-  else if (large < 256) launch64<T64S>(g, e, b_kcontig, st);
+  if (large < 256) launch64<T64S>(g, e, b_kcontig, st);
+  else if (N <= 64) launch64<T64N>(g, e, b_kcontig, st);
   else launch64<T64L>(g, e, b_kcontig, st);
 }
 
@@ -166,8 +172,8 @@ int64_t potrf_lower(double* A, int64_t n, int64_t lda, hipStream_t st) {
 // diagonal blocks are inverted first, all at once: 64-wide blocks by one
 // kernel, then pairs of them twice, [X11 0; -X22 L21 X11 X22], as batched
 // products.  Then, with C = L below the diagonal blocks, from the first block
-// column on: C_ij <- C_ij X_jj (in place), C_i,<j -= C_ij C_j,<j (one K = 256
-// product over the whole trailing part), and at the end X_k,<k = -X_kk C_k,<k.
+// column on: T = C_>j,j X_jj, C_>j,<j -= T C_j,<j (one K = 256 product over the
+// whole trailing part), C_>j,j <- T, and at the end X_k,<k = -X_kk C_k,<k.
 // Every large product has many tiles of equal depth.  (Block columns from the
 // last on, T = X22 A21, gave at most n / 64 tiles, of depths up to n.)
 void trtri_lower(double* A, int64_t n, int64_t lda, hipStream_t st) {
@@ -177,7 +183,9 @@ void trtri_lower(double* A, int64_t n, int64_t lda, hipStream_t st) {
   LAUNCHCHK();
   k_zero_upper_blocks<<<(unsigned)n, 64, 0, st>>>(A, n, lda);
   LAUNCHCHK();
-  const size_t tb = (size_t)nblk * (NB2 / 2) * (NB2 / 2) * 8;   // products of the pairs: larger at the second level
+  // products of the pairs (the second level's are the larger), later one panel
+  const int64_t ldt = (n + 1) / 2 * 2;
+  const size_t tb = std::max<size_t>((size_t)nblk * (NB2 / 2) * (NB2 / 2) * 8, (size_t)ldt * NB2 * 8);
   DBuf T(tb);
   HIPCHK(hipMemsetAsync(T.get(), 0, tb, st));
   for (int h = NB; h < NB2; h *= 2) {
@@ -198,12 +206,10 @@ void trtri_lower(double* A, int64_t n, int64_t lda, hipStream_t st) {
   for (int64_t j0 = 0; j0 + NB2 < n; j0 += NB2) {
     const int64_t j1 = j0 + NB2;
     double* P = A + j1 + j0 * lda;
-    Gemm64Args g{};
-    g.M = (int)(n - j1); g.N = NB2; g.K = NB2;
-    g.A = P; g.lda = lda;
-    g.B = A + j0 + j0 * lda; g.ldb = lda;
-    launch64<T64W>(g, EpiCol64{P, lda, 0, 1.0, 0.0, 0}, true, st);
-    gemm64((int)(n - j1), (int)j0, NB2, -1.0, P, lda, A + j0, lda, true, 1.0, A + j1, lda, false, st);
+    const int rest = (int)(n - j1);
+    gemm64(rest, NB2, NB2, 1.0, P, lda, A + j0 + j0 * lda, lda, true, 0.0, T.as<double>(), ldt, false, st);
+    gemm64(rest, (int)j0, NB2, -1.0, T.as<double>(), ldt, A + j0, lda, true, 1.0, A + j1, lda, false, st);
+    HIPCHK(hipMemcpy2DAsync(P, lda * 8, T.get(), ldt * 8, (size_t)rest * 8, NB2, hipMemcpyDeviceToDevice, st));
   }
   if (nblk > 1) {   // rows of block k >= 1, all its columns left of the diagonal block, in place
     Gemm64Args g{};
