@@ -104,6 +104,17 @@ class HBuf {
   size_t n_ = 0;
 };
 
+// Compute units of the current device.
+inline int device_cus() {
+  static const int cus = [] {
+    int dev = 0, n = 0;
+    HIPCHK(hipGetDevice(&dev));
+    HIPCHK(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
+    return n;
+  }();
+  return cus;
+}
+
 inline int cdiv(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }
 
 // ----------------------------------------------------------- bf16 helpers ----

@@ -405,11 +405,12 @@ template <> struct DmaMfma<double> {
   }
 };
 
-// Operand segment of the pipelined engine: K-contiguous arrays of T whose row
+// Operand segment of the pipelined engines: K-contiguous arrays of T whose row
 // count is padded to the tile and whose leading dimension (in elements) and K
 // are multiples of 64 bytes; padding is zero.  BF16 operands are in the
-// fragment-major layout (frag_off, with K tiles of 32) and ignore lda/ldb.
-// The lo arrays are used only in the split-BF16 mode.
+// fragment-major layout (frag_off) with lda/32 (ldb/32) K tiles to a row group.
+// K may be less than the leading dimensions: K tiles that are all padding are
+// left out.  The lo arrays are used only in the split-BF16 mode.
 struct SegD {
   const void *Ah, *Al;
   const void *Bh, *Bl;
@@ -432,7 +433,7 @@ struct DmaTile {
 
 template <typename T, class TL, bool X3, class Epi>
 __global__ __launch_bounds__(TL::NT) void gemm_dma_kernel(DmaArgs g, Epi epi) {
-  static_assert(!X3 || sizeof(T) == 2, "the split mode is for bf16 operands");
+  static_assert(sizeof(T) == 2, "bf16 operands (FP32 and FP64: gemm_row_kernel)");
   constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = TL::WN, S = TL::S, NW = WM * WN;
   constexpr int BK = 64 / (int)sizeof(T);               // one 64-byte chunk of each row per K tile
   constexpr int NARR = X3 ? 2 : 1;
@@ -449,12 +450,11 @@ __global__ __launch_bounds__(TL::NT) void gemm_dma_kernel(DmaArgs g, Epi epi) {
   typedef typename DmaMfma<T>::acc_t acc_t;
   __shared__ __attribute__((aligned(1024))) char smem[S * STAGE_BYTES];
 
-  // BF16 operands: the wave index in a scalar register, so every operand
-  // address is a scalar base plus the lane's offset (228 rather than 252
-  // VGPRs on the split 256 x 256 tile).  The FP32 and FP64 loops are left as
-  // they were measured.
+  // the wave index in a scalar register, so every operand address is a scalar
+  // base plus the lane's offset (228 rather than 252 VGPRs on the split 256 x
+  // 256 tile)
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = sizeof(T) == 2 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int tmi, tni, tzi;
   tile_coords<X3 && TM * TN >= 32>(tmi, tni, tzi);
   if (g.lower_only && tni > tmi) return;
@@ -471,17 +471,14 @@ __global__ __launch_bounds__(TL::NT) void gemm_dma_kernel(DmaArgs g, Epi epi) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
 
-  // Row-major operands (FP32, FP64): lane L of a group load takes row L%16,
-  // 16-byte chunk L/16.  BF16 operands are fragment-major (frag_off): the
-  // 1 KB block of a (row group, K tile) is contiguous, lane L takes bytes
-  // 16 L .. 16 L + 15, and whole cache lines move per load.
-  constexpr bool FRAG = sizeof(T) == 2;
-  const int lrow = lane & 15, lchunk = lane >> 4;
+  // fragment-major operands (frag_off): the 1 KB block of a (row group, K
+  // tile) is contiguous, lane L takes bytes 16 L .. 16 L + 15, and whole cache
+  // lines move per load.  lda and ldb give the K tiles of a stored row group,
+  // of which the product may take fewer.
   auto issue = [&](int t) {
     const SegD& sg = (t < t0) ? g.seg[0] : g.seg[1];
     const int64_t tk = (t < t0 ? t : t - t0);
-    const int64_t k0 = tk * BK + lchunk * (16 / (int)sizeof(T));
-    const int64_t KT = sg.K / BK;
+    const int64_t KA = sg.lda / BK, KB = sg.ldb / BK;
     char* st = smem + (t % S) * STAGE_BYTES;
 #pragma unroll
     for (int h = 0; h < NARR; ++h) {
@@ -490,16 +487,13 @@ __global__ __launch_bounds__(TL::NT) void gemm_dma_kernel(DmaArgs g, Epi epi) {
 #pragma unroll
       for (int q = 0; q < QA; ++q) {
         const int grp = wave * QA + q;
-        const T* src = FRAG ? A + (((int64_t)(m0 / 16 + grp) * KT + tk) * 512 + lane * 8)
-                            : A + (int64_t)(m0 + grp * 16 + lrow) * sg.lda + k0;
-        dma16(src, st + h * A_BYTES + grp * GROUP_BYTES);
+        dma16(A + (((int64_t)(m0 / 16 + grp) * KA + tk) * 512 + lane * 8), st + h * A_BYTES + grp * GROUP_BYTES);
       }
 #pragma unroll
       for (int q = 0; q < QB; ++q) {
         const int grp = wave * QB + q;
-        const T* src = FRAG ? B + (((int64_t)(n0 / 16 + grp) * KT + tk) * 512 + lane * 8)
-                            : B + (int64_t)(n0 + grp * 16 + lrow) * sg.ldb + k0;
-        dma16(src, st + NARR * A_BYTES + h * B_BYTES + grp * GROUP_BYTES);
+        dma16(B + (((int64_t)(n0 / 16 + grp) * KB + tk) * 512 + lane * 8),
+              st + NARR * A_BYTES + h * B_BYTES + grp * GROUP_BYTES);
       }
     }
   };
@@ -571,39 +565,140 @@ __global__ __launch_bounds__(TL::NT) void gemm_dma_kernel(DmaArgs g, Epi epi) {
     // all fragment reads are issued before the first MFMA: left to itself the
     // scheduler interleaves them in pairs, each behind a full LDS-latency wait
     __builtin_amdgcn_sched_barrier(0);
-    // FP64: slice-outer order, so consecutive instructions update different
-    // accumulators (measured faster); FP32 and BF16: block-outer order
-    if (sizeof(T) != 8) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int sl = 0; sl < DmaMfma<T>::SLICES; ++sl) {
-            if (X3) {
-              acc[i][j] = DmaMfma<T>::slice(al[X3 ? i : 0], bh[j], acc[i][j], sl);
-              acc[i][j] = DmaMfma<T>::slice(ah[i], bl[X3 ? j : 0], acc[i][j], sl);
-            }
-            acc[i][j] = DmaMfma<T>::slice(ah[i], bh[j], acc[i][j], sl);
-          }
-    } else
-#pragma unroll
-    for (int sl = 0; sl < DmaMfma<T>::SLICES; ++sl) {
-      if (X3) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = DmaMfma<T>::slice(al[X3 ? i : 0], bh[j], acc[i][j], sl);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = DmaMfma<T>::slice(ah[i], bl[X3 ? j : 0], acc[i][j], sl);
+      for (int j = 0; j < TN; ++j) {
+        if (X3) {
+          acc[i][j] = DmaMfma<T>::slice(al[X3 ? i : 0], bh[j], acc[i][j], 0);
+          acc[i][j] = DmaMfma<T>::slice(ah[i], bl[X3 ? j : 0], acc[i][j], 0);
+        }
+        acc[i][j] = DmaMfma<T>::slice(ah[i], bh[j], acc[i][j], 0);
       }
+  }
+  __syncthreads();
+  FragCoord fc{m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane, m0, n0, sizeof(T) == 8, tni, wn, WN, tzi};
+  epi.template run<typename DmaMfma<T>::scalar_t, TM, TN>(acc, fc, smem);
+}
+
+// ---------------------------------------------------------------------------
+// FP32 and FP64 MFMA engine for row-major (K-contiguous) operands, the same
+// direct global->LDS loads: a wave load takes 16 rows x 64 bytes, lane L row
+// L % 16 and 16-byte chunk L / 16, the lane layout of the fragments.
+// Bound by the matrix cores.  A stage holds KS chunks of 64 bytes of K, two
+// stages: at KS = 2 a wave meets a barrier every 64 (FP64) or 128 (FP32) MFMAs
+// of a 64 x 32 tile, and the 128 x 128 tile by eight waves leaves room for two
+// workgroups, 16 waves, on a CU.  K order within an element's sum does not
+// depend on the tile shape.  Against four waves of 64 x 64 with a barrier per
+// chunk and four stages: the FP64 product at M = 42, N = 5000 4.18 -> 2.86 ms
+// (45 TFLOP/s; with the column tiles and K splits below), FP32 at M = 21, N =
+// 10000 1.72 -> 1.54 ms (82), the Gram matrix of the factor at n = 126000, k =
+// 2000 18.4 -> 11.5 ms (49, with the splits on XCDs).
+// BN need not be a power of two: the column tiles can fit the operand's width.
+// ---------------------------------------------------------------------------
+template <int BM_, int BN_, int WM_, int WN_, int KS_>
+struct RowTile {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, KS = KS_;
+  static constexpr int NT = 64 * WM * WN;
+};
+
+// XCDK: the K splits are spread over the XCDs (split z runs on XCD z % 8), so
+// that each XCD streams its own range of K through its L2; gridDim.z must be a
+// multiple of 8.  Otherwise the order of tile_coords<false>.
+template <typename T, class TL, class Epi, bool XCDK = false>
+__global__ __launch_bounds__(TL::NT) void gemm_row_kernel(DmaArgs g, Epi epi) {
+  static_assert(sizeof(T) >= 4, "FP32 or FP64 operands");
+  constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = TL::WN, KS = TL::KS, NW = WM * WN;
+  constexpr int BK = 64 / (int)sizeof(T);
+  constexpr int GA = BM / 16, GB = BN / 16, CHUNK = (GA + GB) * 1024;
+  constexpr int L = KS * (GA + GB);                     // 1 KB wave loads per stage
+  constexpr int Q = (L + NW - 1) / NW;                  // of one wave, at most
+  constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
+  static_assert(TM * WM * 16 == BM && TN * WN * 16 == BN, "16 x 16 blocks per wave");
+  typedef typename DmaMfma<T>::acc_t acc_t;
+  __shared__ __attribute__((aligned(1024))) char smem[2 * KS * CHUNK];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tmi, tni, tzi;
+  if constexpr (XCDK) {
+    const int nt = (int)(gridDim.x * gridDim.y), per = (int)gridDim.z / 8;
+    const int w = ((int)blockIdx.z * (int)gridDim.y + (int)blockIdx.y) * (int)gridDim.x + (int)blockIdx.x;
+    const int idx = w / 8;
+    tzi = w % 8 + 8 * (idx / nt % per);
+    tmi = idx % nt / (int)gridDim.x;
+    tni = idx % nt % (int)gridDim.x;
+  } else {
+    tile_coords<false>(tmi, tni, tzi);
+  }
+  if (g.lower_only && tni > tmi) return;
+  const int m0 = tmi * BM, n0 = tni * BN;
+  const int wm = wave / WN, wn = wave % WN;
+  const int t0 = g.seg[0].K / BK;
+  const int T_ = t0 + (g.nseg > 1 ? g.seg[1].K / BK : 0);
+  const int tb = (int)((int64_t)T_ * tzi / gridDim.z);
+  const int te = (int)((int64_t)T_ * (tzi + 1) / gridDim.z);
+
+  acc_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
+
+  // wave w takes the loads w, w + NW, ...; a load's source in both segments
+  const char *src0[Q], *src1[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int idx = wave + q * NW, grp = idx % (GA + GB);
+    const bool a = grp < GA;
+    const int64_t row = (a ? m0 + grp * 16 : n0 + (grp - GA) * 16) + (lane & 15);
+    const SegD &s0 = g.seg[0], &s1 = g.seg[1];
+    src0[q] = static_cast<const char*>(a ? s0.Ah : s0.Bh) + row * (a ? s0.lda : s0.ldb) * (int)sizeof(T) + (lane >> 4) * 16;
+    src1[q] = static_cast<const char*>(a ? s1.Ah : s1.Bh) + row * (a ? s1.lda : s1.ldb) * (int)sizeof(T) + (lane >> 4) * 16;
+  }
+  auto issue = [&](int s) {   // stage s: chunks tb + s KS ..
+    char* st = smem + (s & 1) * KS * CHUNK;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int idx = wave + q * NW, t = tb + s * KS + idx / (GA + GB);
+      if (idx < L && t < te) {
+        const char* p = t < t0 ? src0[q] + (int64_t)t * 64 : src1[q] + (int64_t)(t - t0) * 64;
+        dma16(p, st + idx * 1024);
+      }
+    }
+  };
+  auto chunk = [&](const char* st) {
+    u4 a[TM], b[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const u4*>(st + (wm * TM + i) * 1024 + lane * 16);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const u4*>(st + (GA + wn * TN + j) * 1024 + lane * 16);
+    // every fragment read before the first MFMA (else they interleave in
+    // pairs, each behind a full LDS latency)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int sl = 0; sl < DmaMfma<T>::SLICES; ++sl)
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = DmaMfma<T>::slice(ah[i], bh[j], acc[i][j], sl);
-    }
+        for (int j = 0; j < TN; ++j) acc[i][j] = DmaMfma<T>::slice(a[i], b[j], acc[i][j], sl);
+  };
+
+  const int full = (te - tb) / KS, left = (te - tb) % KS;
+  if (te > tb) issue(0);
+  for (int s = 0; s < full; ++s) {
+    __builtin_amdgcn_s_waitcnt(VmCnt<0>::v);
+    asm volatile("s_barrier" ::: "memory");
+    issue(s + 1);
+    const char* st = smem + (s & 1) * KS * CHUNK;
+#pragma unroll
+    for (int kc = 0; kc < KS; ++kc) chunk(st + kc * CHUNK);
+  }
+  if (left > 0) {
+    __builtin_amdgcn_s_waitcnt(VmCnt<0>::v);
+    asm volatile("s_barrier" ::: "memory");
+    const char* st = smem + (full & 1) * KS * CHUNK;
+    for (int kc = 0; kc < left; ++kc) chunk(st + kc * CHUNK);
   }
   __syncthreads();
   FragCoord fc{m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane, m0, n0, sizeof(T) == 8, tni, wn, WN, tzi};

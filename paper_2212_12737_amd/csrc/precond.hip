@@ -49,7 +49,7 @@ __global__ void k_gather_rows32(const float* L, int64_t ld, const int64_t* idx, 
 // Factor the nb x nb pivot block T[c][c'] = panel[idx[c], c'] with drops and
 // invert it.  Outputs: diag (PB) of the factor, Linv (PB x PB row-major) = its
 // inverse with a unit diagonal put at dropped positions, kept flags.  One
-// block on one CU: 218 us with three barriers a column, 42 us on 16 x 16
+// block on one CU: 218 us with three barriers a column, 37 us on 16 x 16
 // blocks (chol64.hpp).
 __global__ __launch_bounds__(256) void k_panel_chol(const double* Lp, int64_t ld, const int64_t* idx, int nb,
                                                     double thr, double* diag, double* Linv, unsigned char* kept) {
@@ -260,21 +260,32 @@ constexpr int64_t kGramTile = 128;
 // operand rows (K = ld, zero padding rows), for A and B alike; L holds kp
 // columns (a multiple of the tile) so that every tile row is allocated.  Only
 // tiles on or below the diagonal run, split over K for enough workgroups,
-// and a fixed-order pass sums the splits.
+// and a fixed-order pass sums the splits.  A multiple of eight splits puts each
+// on one XCD, whose L2 then holds the window of L that its tiles walk through
+// together: L is read from HBM about once rather than by every tile.
 static void gram_dma(const double* L, int64_t ld, int64_t k, int64_t kp, double* C, int64_t ldc, hipStream_t st) {
-  typedef DmaTile<kGramTile, kGramTile, 2, 2, 4> TG;
+  typedef RowTile<kGramTile, kGramTile, 2, 4, 2> TG;
   require(kp % kGramTile == 0 && kp >= k && ld % 8 == 0, "gram_dma: operand padding");
   const int64_t nt = kp / kGramTile;
   const int64_t lower = nt * (nt + 1) / 2;
-  int splits = 1;
-  while (lower * splits < 512 && splits < 16 && ld / 8 >= (int64_t)splits * 2 * 64) splits *= 2;
+  // workgroups for eight a CU, at least 64 chunks of K a split, partials of 2 GB at most
+  int splits = 8;
+  while (lower * splits < 2048 && splits < 64 && ld / 8 >= (int64_t)splits * 2 * 64 && splits * k * kp * 16 <= (2ll << 30))
+    splits *= 2;
+  const bool xcd = ld / 8 >= 8 * 64 && splits * k * kp * 8 <= (2ll << 30);
+  if (!xcd) {
+    splits = 1;
+    while (lower * splits < 512 && splits < 16 && ld / 8 >= (int64_t)splits * 2 * 64) splits *= 2;
+  }
   DBuf part((size_t)splits * k * kp * 8);
   DmaArgs g{};
   g.nseg = 1;
   g.lower_only = 1;
   g.seg[0] = SegD{L, nullptr, L, nullptr, ld, ld, (int)ld};
   EpiPart<double> e{part.as<double>(), kp, (int)k, (int)k};
-  gemm_dma_kernel<double, TG, false, EpiPart<double>><<<dim3((unsigned)nt, (unsigned)nt, splits), TG::NT, 0, st>>>(g, e);
+  const dim3 grid((unsigned)nt, (unsigned)nt, splits);
+  if (xcd) gemm_row_kernel<double, TG, EpiPart<double>, true><<<grid, TG::NT, 0, st>>>(g, e);
+  else gemm_row_kernel<double, TG, EpiPart<double>><<<grid, TG::NT, 0, st>>>(g, e);
   LAUNCHCHK();
   k_gram_reduce<<<cdiv(k * k, 256), 256, 0, st>>>(part.as<double>(), splits, k, kp, k * kp, C, ldc);
   LAUNCHCHK();
