@@ -4,11 +4,7 @@
 //  * weighted (leverage / scores): Efraimidis-Spirakis keys log(u_i)/w_i, k largest;
 //    the ordering is (key descending, index ascending), done by a bitonic sort;
 //  * pivoted (incomplete) Cholesky, Algorithm 1: greedy pivot on the largest
-//    remaining diagonal of the Schur complement; each step evaluates one kernel
-//    column, subtracts the Schur correction L[:, :m] L[pivot, :m]^T (a GEMV
-//    over the column-major factor, coalesced thread-per-row), scales by the
-//    pivot and updates the diagonal; the argmax for the next step is fused
-//    into the same pass;
+//    remaining diagonal of the Schur complement, in blocks of pivots (below);
 //  * leverage: ridge-leverage estimates from a uniform pilot set S0,
 //    tau_i = (K_ii - K_iS0 (K_S0S0 + lambda I)^-1 K_S0i) / lambda, obtained as
 //    (K_ii - |row i of L0|^2)/lambda with L0 the incomplete Cholesky factor of
@@ -142,153 +138,455 @@ void select_weighted(int64_t n, const double* w, int64_t k, uint64_t seed, int s
 }
 
 // ---------------------------------------------------------- pivoted ICD ----
-struct Cand {
-  double v;
-  int i;
-};
-__device__ inline Cand better(Cand a, Cand b) { return before(a.v, a.i, b.v, b.i) ? a : b; }
+// Algorithm 1 in blocks of pivots.  One pivot at a time needs the whole factor
+// for every column (K[:, p] - L L[p, :]^T, n m 8 bytes per pivot).  Instead a
+// pool holds the Schur-complement columns of up to kPool candidates, the rows
+// with the largest remaining diagonals: new ones are formed together by one
+// GEMM over the factor, and each block of accepted pivots updates the rest by
+// another.  Within a block the greedy choice is made on the candidates' own
+// small matrix and is exact: every row outside the pool has a diagonal below
+// `bound`, diagonals only fall, so as long as the best candidate is not below
+// the bound it is the best of all rows (ties by index as before).  The block
+// ends when it is, or when the rank test stops the factorization.  What a
+// pivot costs is then a share of a few passes over n x kPool and of a K = m
+// product instead of a pass over the factor: at n = 126000, k = 2000
+// (75 blocks) 415 ms became 73 (57 with the kernel columns in tiles of 64).
+constexpr int kPool = 128;       // candidates (two per lane of the greedy wave)
+constexpr int kBins = 2048;      // histogram of the diagonals, 2^-10 of an octave each
+constexpr int kBinShift = 10;    // of the high word
 
-__device__ inline Cand block_best(Cand c, Cand* sh) {
-  sh[threadIdx.x] = c;
+struct PivState {
+  double best, bound;   // largest remaining diagonal; all rows outside the pool are below
+  int s;                // pivots of the last block
+  int stop;             // the largest diagonal is at the rank threshold
+  int count;            // candidates listed
+  int fresh;            // of them, without a column in the pool
+  int first;            // lowest row with the largest diagonal
+  int pad;
+  int hist[kBins];
+  int list[kPool];      // candidate rows
+  int row[kPool];       // pool: the row of every slot, -1 = free
+  int64_t new_row[kPool];
+  int new_slot[kPool];
+  // the block's pivots: row, slot, pivot value, and the factor's rows at them,
+  // Lt[b][j] = L[pivot j, b] for b < j
+  int prow[kPool], pslot[kPool];
+  double pval[kPool], pinv[kPool];   // and its inverse
+  double Lt[kPool * kPool];
+};
+
+// Columns [m, m + s) of L for this thread's row by forward substitution with
+// the block's pivot rows (the arithmetic and order of Algorithm 1 within the
+// block), the diagonal update and its block maxima.  A selected row has the
+// diagonal -inf.  The rows of Lt are scalar loads.
+__global__ __launch_bounds__(256) void k_piv_panel(double* __restrict__ L, int64_t n, int64_t ld, int64_t m,
+                                                   const double* __restrict__ pool, const PivState* __restrict__ st,
+                                                   double* __restrict__ d, double* __restrict__ pmax) {
+  constexpr int W = 32;
+  __shared__ double sh[256];
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int s = st->s;
+  double dn = -INFINITY;
+  if (i < n) {
+    dn = d[i];
+    bool gone = dn == -INFINITY;
+    double* Li = L + i + m * ld;
+    for (int c0 = 0; c0 < s; c0 += W) {
+      const int w = min(W, s - c0);
+      double r[W];
+#pragma unroll
+      for (int j = 0; j < W; ++j) r[j] = j < w ? pool[i + st->pslot[c0 + j] * ld] : 0.0;
+      for (int b = 0; b < c0; ++b) {
+        const double lb = Li[b * ld];
+        const double* t = st->Lt + b * kPool + c0;
+#pragma unroll
+        for (int j = 0; j < W; ++j) r[j] = fma(-lb, t[j], r[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < W; ++j) {
+        if (j < w) {   // uniform; a break would leave the loop rolled and r in memory
+          const bool own = i == st->prow[c0 + j];
+          const double l = own ? st->pval[c0 + j] : (gone ? 0.0 : r[j] * st->pinv[c0 + j]);
+          gone = gone || own;
+          Li[(c0 + j) * ld] = l;
+          if (!gone) dn = fma(-l, l, dn);
+          const double* t = st->Lt + (c0 + j) * kPool + c0;
+#pragma unroll
+          for (int q = j + 1; q < W; ++q) r[q] = fma(-l, t[q], r[q]);
+        }
+      }
+    }
+    if (gone) dn = -INFINITY;
+    d[i] = dn;
+  }
+  sh[threadIdx.x] = dn;
   __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) sh[threadIdx.x] = better(sh[threadIdx.x], sh[threadIdx.x + o]);
+  for (int o = 128; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + o]);
     __syncthreads();
   }
-  return sh[0];
+  if (threadIdx.x == 0) pmax[blockIdx.x] = sh[0];
 }
 
-// First argmax partials over the initial diagonal.
-__global__ __launch_bounds__(256) void k_argmax_part(const double* d, int64_t n, Cand* part) {
-  __shared__ Cand sh[256];
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  Cand c{-INFINITY, 0x7FFFFFFF};
-  if (i < n) c = Cand{d[i], (int)i};
-  c = block_best(c, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = c;
-}
-
-// Combine partials; choose pivot m or stop; gather row pivot of L[:, :m].
-__global__ __launch_bounds__(256) void k_pivot(const Cand* part, int np, int64_t m, double thr, int64_t* piv,
-                                               double* pivval, int* stop, int* keff, const double* L, int64_t n,
-                                               double* vbuf) {
-  __shared__ Cand sh[256];
-  __shared__ int go;
-  Cand c{-INFINITY, 0x7FFFFFFF};
-  for (int e = threadIdx.x; e < np; e += 256) c = better(c, part[e]);
-  c = block_best(c, sh);
+// Largest diagonal, the rank test, and cleared counters for the next listing.
+__global__ __launch_bounds__(1024) void k_piv_begin(const double* __restrict__ pmax, int np, double thr, PivState* st) {
+  __shared__ double sh[1024];
+  double v = -INFINITY;
+  for (int e = threadIdx.x; e < np; e += 1024) v = fmax(v, pmax[e]);
+  sh[threadIdx.x] = v;
+  __syncthreads();
+  for (int o = 512; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + o]);
+    __syncthreads();
+  }
+  for (int e = threadIdx.x; e < kBins; e += 1024) st->hist[e] = 0;
   if (threadIdx.x == 0) {
-    go = 0;
-    if (*stop == 0) {
-      if (c.i == 0x7FFFFFFF || !(c.v > thr)) {
-        *stop = 1;
-      } else {
-        piv[m] = c.i;
-        *pivval = sqrt(c.v);
-        *keff = (int)(m + 1);
-        go = 1;
-      }
-    }
+    st->best = sh[0];
+    st->stop = !(sh[0] > thr);
+    st->count = 0;
+    st->first = 0x7FFFFFFF;
+  }
+}
+
+// Histogram of the diagonals below the largest, by the high words' distance:
+// bin 0 holds the largest ones.  Diagonals at the rank threshold can never be
+// pivots and are left out.
+__device__ inline int piv_bin(double v, double best) {
+  return (int)((unsigned)(__double2hiint(best) - __double2hiint(v)) >> kBinShift);
+}
+__global__ __launch_bounds__(256) void k_piv_hist(const double* __restrict__ d, int64_t n, double thr, PivState* st) {
+  __shared__ int h[kBins];
+  for (int e = threadIdx.x; e < kBins; e += 256) h[e] = 0;
+  __syncthreads();
+  const double best = st->best;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const double v = d[i];
+    if (!(v > thr)) continue;
+    const int b = piv_bin(v, best);
+    if (b < kBins) atomicAdd(&h[b], 1);
+    if (v == best) atomicMin(&st->first, (int)i);
   }
   __syncthreads();
-  if (!go) return;
-  const int64_t p = c.i;
-  for (int64_t j = threadIdx.x; j < m; j += 256) vbuf[j] = L[p + j * n];
+  for (int e = threadIdx.x; e < kBins; e += 256)
+    if (h[e]) atomicAdd(&st->hist[e], h[e]);
 }
 
-// Column m of L from the raw kernel column stored there; diagonal update and
-// argmax partials for the next step.
-__global__ __launch_bounds__(256) void k_pivchol_update(double* L, int64_t n, int64_t m, const double* vbuf,
-                                                        const double* pivval, const int64_t* piv,
-                                                        unsigned char* sel, double* d, const int* stop,
-                                                        Cand* part) {
-  constexpr int CH = 2048;
-  __shared__ double sv[CH];
-  __shared__ Cand sh[256];
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const bool halted = *stop != 0;   // same value for the whole grid
-  Cand c{-INFINITY, 0x7FFFFFFF};
-  if (halted) {
-    if (i < n) L[i + m * n] = 0.0;
-  } else {
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    for (int64_t j0 = 0; j0 < m; j0 += CH) {   // Schur correction L[i, :m] . L[pivot, :m]
-      const int64_t jn = m - j0 < CH ? m - j0 : CH;
-      __syncthreads();
-      for (int64_t j = threadIdx.x; j < jn; j += 256) sv[j] = vbuf[j0 + j];
-      __syncthreads();
-      if (i < n) {
-        const double* Li = L + i + j0 * n;
-        int64_t j = 0;
-        for (; j + 4 <= jn; j += 4) {
-          s0 += Li[j * n] * sv[j];
-          s1 += Li[(j + 1) * n] * sv[j + 1];
-          s2 += Li[(j + 2) * n] * sv[j + 2];
-          s3 += Li[(j + 3) * n] * sv[j + 3];
-        }
-        for (; j < jn; ++j) s0 += Li[j * n] * sv[j];
-      }
-    }
-    if (i < n) {
-      const int64_t p = piv[m];
-      const double pv = *pivval;
-      const double schur = (s0 + s1) + (s2 + s3);
-      double l;
-      if (i == p) {
-        l = pv;
-        sel[i] = 1;
-      } else if (sel[i]) {
-        l = 0.0;
-      } else {
-        l = (L[i + m * n] - schur) / pv;
-        const double dn = d[i] - l * l;
-        d[i] = dn;
-        c = Cand{dn, (int)i};
-      }
-      L[i + m * n] = l;
+// List the rows of the first bins that together hold at most `most` rows (in
+// any order); if the first bin alone holds more, only the best row.
+__global__ __launch_bounds__(256) void k_piv_list(const double* __restrict__ d, int64_t n, double thr, int most,
+                                                  PivState* st) {
+  __shared__ int sum[256];
+  __shared__ int cut;   // bins taken
+  const int t = threadIdx.x;
+  constexpr int PER = kBins / 256;
+  int own[PER], acc = 0;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    own[e] = st->hist[t * PER + e];
+    acc += own[e];
+  }
+  sum[t] = acc;
+  if (t == 0) cut = 0;
+  __syncthreads();
+  for (int o = 1; o < 256; o <<= 1) {   // inclusive scan
+    const int x = t >= o ? sum[t - o] : 0;
+    __syncthreads();
+    sum[t] += x;
+    __syncthreads();
+  }
+  int before_me = sum[t] - acc;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    before_me += own[e];
+    if (before_me <= most) atomicMax(&cut, t * PER + e + 1);
+  }
+  __syncthreads();
+  const double best = st->best;
+  const int taken = cut;
+  if (blockIdx.x == 0 && t == 0) {
+    if (taken == 0) {
+      st->bound = best;
+      st->list[0] = st->first;
+      st->count = 1;
+    } else {
+      // rows not listed: high word <= that of best - (taken << shift)
+      st->bound = __hiloint2double(__double2hiint(best) - (taken << kBinShift) + 1, 0);
     }
   }
-  c = block_best(c, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = c;
+  if (taken == 0) return;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + t; i < n; i += (int64_t)gridDim.x * 256) {
+    const double v = d[i];
+    if (v > thr && piv_bin(v, best) < taken) st->list[atomicAdd(&st->count, 1)] = (int)i;
+  }
+}
+
+// Match the listed rows (sorted, so that nothing depends on the order of the
+// atomics) with the pool; the others get free slots, then those of rows no
+// longer listed.
+__global__ __launch_bounds__(kPool) void k_piv_match(PivState* st, int slots) {
+  __shared__ int key[kPool], row[kPool], used[kPool], slot_of[kPool], avail[kPool];
+  const int t = threadIdx.x;
+  const int count = st->stop ? 0 : min(st->count, slots);
+  key[t] = t < count ? st->list[t] : 0x7FFFFFFF;
+  row[t] = t < slots ? st->row[t] : -1;
+  used[t] = 0;
+  __syncthreads();
+  for (int kk = 2; kk <= kPool; kk <<= 1)
+    for (int j = kk >> 1; j > 0; j >>= 1) {
+      const int l = t ^ j;
+      if (l > t) {
+        const bool up = (t & kk) == 0;
+        const int a = key[t], b = key[l];
+        if (up ? a > b : a < b) {
+          key[t] = b;
+          key[l] = a;
+        }
+      }
+      __syncthreads();
+    }
+  int mine = -1;   // (slots past the last hold row -1, which is no key)
+#pragma unroll 16
+  for (int q = 0; q < kPool; ++q)
+    if (row[q] == key[t]) mine = q;
+  if (t >= count) mine = -1;
+  slot_of[t] = mine;
+  __syncthreads();
+  if (mine >= 0) used[mine] = 1;
+  __syncthreads();
+  // this entry's rank among the unmatched ones, and this slot's among the
+  // available ones: the free slots, then those whose row is no longer listed
+  const bool fresh = t < count && mine < 0;
+  const bool open = t < slots && row[t] < 0, stale = t < slots && row[t] >= 0 && !used[t];
+  __shared__ unsigned long long bits[3][2];
+  const int w = t >> 6;
+  const unsigned long long bf = __ballot(fresh), bo = __ballot(open), bs = __ballot(stale);
+  if ((t & 63) == 0) {
+    bits[0][w] = bf;
+    bits[1][w] = bo;
+    bits[2][w] = bs;
+  }
+  __syncthreads();
+  auto lower = [&](int e) {   // threads before this one
+    return __popcll(bits[e][w] & ((1ull << (t & 63)) - 1)) + (w ? __popcll(bits[e][0]) : 0);
+  };
+  const int rank = lower(0), pos = lower(open ? 1 : 2);
+  const int nfresh = __popcll(bits[0][0]) + __popcll(bits[0][1]), nopen = __popcll(bits[1][0]) + __popcll(bits[1][1]);
+  if (open) avail[pos] = t;
+  if (stale) avail[nopen + pos] = t;
+  __syncthreads();
+  if (fresh) {
+    const int q = avail[rank];
+    st->row[q] = key[t];
+    st->new_row[rank] = key[t];
+    st->new_slot[rank] = q;
+  }
+  if (t == 0) st->fresh = nfresh;
+}
+
+// G[c][j] = L[rows[c], j0 + j] for j < w, zero for w <= j < ldg and rows of
+// free slots (row-major, ldg)
+template <typename I>
+__global__ void k_piv_rows(const double* __restrict__ L, int64_t ld, int64_t j0, const I* __restrict__ rows, int nr,
+                           int64_t w, int64_t ldg, double* __restrict__ G) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= nr * ldg) return;
+  const int64_t c = e / ldg, j = e % ldg;
+  const int64_t r = rows[c];
+  G[e] = j < w && r >= 0 ? L[r + (j0 + j) * ld] : 0.0;
+}
+
+// pool[:, new_slot[c]] = stage[:, c]
+__global__ __launch_bounds__(256) void k_piv_place(const double* __restrict__ stage, int64_t n, int64_t ld,
+                                                   const PivState* __restrict__ st, double* __restrict__ pool) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) pool[i + st->new_slot[blockIdx.y] * ld] = stage[i + blockIdx.y * ld];
+}
+
+// Largest value of a wave, in every lane: rotations within rows of 16 lanes,
+// then the four rows' values by readlane.
+template <int CTRL> __device__ inline double dpp_move(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ inline double wave_max(double x) {
+  x = fmax(x, dpp_move<0x128>(x));   // row_ror:8, 4, 2, 1
+  x = fmax(x, dpp_move<0x124>(x));
+  x = fmax(x, dpp_move<0x122>(x));
+  x = fmax(x, dpp_move<0x121>(x));
+  double y = -INFINITY;
+#pragma unroll
+  for (int l = 0; l < 64; l += 16) {
+    const int lo = __builtin_amdgcn_readlane(__double2loint(x), l);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(x), l);
+    y = fmax(y, __hiloint2double(hi, lo));
+  }
+  return y;
+}
+
+// The greedy block: the candidates' matrix A[slot][c] = pool[row of c, slot]
+// in LDS, then one wave (lane l: candidates l and l + 64) picks the best
+// candidate, forms its column from the block's earlier ones, and lowers the
+// diagonals, until the bound.  A pivot's row of A becomes its column of L.
+// Bound by the chain argmax -> column -> diagonal, about 2 us a pivot.
+__global__ __launch_bounds__(1024) void k_piv_greedy(const double* __restrict__ pool, int64_t ld,
+                                                     const double* __restrict__ d, double thr, int64_t m, int limit,
+                                                     int slots, PivState* st, int64_t* __restrict__ piv) {
+  __shared__ double A[kPool][kPool];
+  __shared__ int row[kPool];
+  for (int e = threadIdx.x; e < kPool; e += 1024) row[e] = e < slots ? st->row[e] : -1;
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < kPool * kPool / 1024; ++h) {   // all of a thread's loads in flight
+    const int e = threadIdx.x + 1024 * h, p = e / kPool, c = e % kPool;
+    A[p][c] = row[p] >= 0 && row[c] >= 0 ? pool[row[c] + p * ld] : 0.0;
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const int lane = threadIdx.x;
+  const double bound = st->bound;
+  double dc[2];
+  int rc[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    rc[h] = row[lane + 64 * h];
+    dc[h] = rc[h] >= 0 ? d[rc[h]] : -INFINITY;
+    if (rc[h] < 0) rc[h] = 0x7FFFFFFF;
+  }
+  int s = 0, sl0 = 0, sl1 = 0;   // lane b: the slots of pivots b and b + 64
+  auto slot = [&](int b) {
+    return b < 64 ? __builtin_amdgcn_readlane(sl0, b) : __builtin_amdgcn_readlane(sl1, b - 64);
+  };
+  while (s < limit) {
+    // the best candidate: the largest diagonal, then the lowest row of those
+    const double v = wave_max(fmax(dc[0], dc[1]));
+    if (!(v > thr) || (s > 0 && !(v >= bound))) break;
+    int r = min(dc[0] == v ? rc[0] : 0x7FFFFFFF, dc[1] == v ? rc[1] : 0x7FFFFFFF);
+    unsigned long long at = __ballot(r != 0x7FFFFFFF);
+    if (at & (at - 1)) {
+      int low = r;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) low = min(low, __shfl_xor(low, o));
+      at = __ballot(r == low);
+    }
+    const int owner = __ffsll(at) - 1;
+    r = __builtin_amdgcn_readlane(r, owner);
+    const bool upper = dc[1] == v && rc[1] == r;
+    const int p = owner + ((__ballot(upper) >> owner) & 1 ? 64 : 0);
+    const double pv = sqrt(v), pinv = 1.0 / pv;
+    double x0 = A[p][lane], x1 = A[p][lane + 64];
+#pragma unroll 8
+    for (int b = 0; b < s; ++b) {
+      const double* Lb = A[slot(b)];
+      const double lp = Lb[p];
+      x0 = fma(-Lb[lane], lp, x0);
+      x1 = fma(-Lb[lane + 64], lp, x1);
+    }
+    if (lane < s) st->Lt[lane * kPool + s] = A[sl0][p];
+    if (lane + 64 < s) st->Lt[(lane + 64) * kPool + s] = A[sl1][p];
+    x0 = p == lane ? pv : (dc[0] == -INFINITY ? 0.0 : x0 * pinv);
+    x1 = p == lane + 64 ? pv : (dc[1] == -INFINITY ? 0.0 : x1 * pinv);
+    dc[0] = p == lane ? -INFINITY : fma(-x0, x0, dc[0]);
+    dc[1] = p == lane + 64 ? -INFINITY : fma(-x1, x1, dc[1]);
+    __builtin_amdgcn_wave_barrier();
+    A[p][lane] = x0;
+    A[p][lane + 64] = x1;
+    if (lane == (s & 63)) {
+      if (s < 64) sl0 = p;
+      else sl1 = p;
+    }
+    if (lane == 0) {
+      st->prow[s] = r;
+      st->pslot[s] = p;
+      st->pval[s] = pv;
+      st->pinv[s] = pinv;
+      st->row[p] = -1;
+      piv[m + s] = r;
+    }
+    __builtin_amdgcn_wave_barrier();
+    ++s;
+  }
+  if (lane == 0) st->s = s;
 }
 
 int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t st) {
   const int64_t n = s->n;
+  const int64_t ld = (n + 1) / 2 * 2;   // the products move pairs of rows
   const double thr = 1e-12 * max_diag(s, st);
-  DBuf L(n * k * 8), d(n * 8), sel(n), piv(k * 8), vbuf(std::max<int64_t>(k, 1) * 8), scal(64);
+  DBuf L(ld * k * 8), d(n * 8), piv(k * 8), state(sizeof(PivState));
   const int np = cdiv(n, 256);
-  DBuf part(np * sizeof(Cand));
-  HIPCHK(hipMemsetAsync(sel.get(), 0, n, st));
-  HIPCHK(hipMemsetAsync(piv.get(), 0, k * 8, st));
-  HIPCHK(hipMemsetAsync(scal.get(), 0, 64, st));
-  double* pivval = scal.as<double>();
-  int* stop = reinterpret_cast<int*>(scal.as<char>() + 8);
-  int* keff = reinterpret_cast<int*>(scal.as<char>() + 12);
-  kernel_diag(s, d.as<double>(), st);
-  k_argmax_part<<<np, 256, 0, st>>>(d.as<double>(), n, part.as<Cand>());
-  LAUNCHCHK();
-  int hstop = 0;
-  for (int64_t m = 0; m < k; ++m) {
-    k_pivot<<<1, 256, 0, st>>>(part.as<Cand>(), np, m, thr, piv.as<int64_t>(), pivval, stop, keff,
-                               L.as<double>(), n, vbuf.as<double>());
-    LAUNCHCHK();
-    kernel_columns(s, piv.as<int64_t>() + m, 1, L.as<double>() + m * n, n, 0.0, st);
-    k_pivchol_update<<<np, 256, 0, st>>>(L.as<double>(), n, m, vbuf.as<double>(), pivval,
-                                                          piv.as<int64_t>(), sel.as<unsigned char>(),
-                                                          d.as<double>(), stop, part.as<Cand>());
-    LAUNCHCHK();
-    if ((m & 31) == 31) {
-      HIPCHK(hipMemcpyAsync(&hstop, stop, 4, hipMemcpyDeviceToHost, st));
-      HIPCHK(hipStreamSynchronize(st));
-      if (hstop) break;
+  DBuf pmax((size_t)np * 8), pool, stage, G;
+  // the pool and its staging columns, fewer where memory is short
+  int slots = (int)std::min<int64_t>(kPool, n);
+  for (;; slots = std::max(1, slots / 4)) {
+    try {
+      pool.alloc(ld * slots * 8);
+      stage.alloc(ld * slots * 8);
+      G.alloc((size_t)slots * (k + 2) * 8);
+      break;
+    } catch (const Error&) {
+      pool.release();
+      stage.release();
+      if (slots == 1) throw;
     }
   }
-  int hk = 0;
-  HIPCHK(hipMemcpyAsync(&hk, keff, 4, hipMemcpyDeviceToHost, st));
+  PivState* ps = state.as<PivState>();
+  HIPCHK(hipMemsetAsync(ps, 0, sizeof(PivState), st));
+  HIPCHK(hipMemsetAsync(ps->row, 0xFF, sizeof(ps->row), st));   // -1: every slot free
+  kernel_diag(s, d.as<double>(), st);
+  const int scan = std::min(np, 512);
+  int64_t m = 0;
+  bool ran = false;
+  // columns [c, c + nc) of C (n x nc) -= L[:, j0 .. j0 + w) (its rows in G)^T
+  auto subtract = [&](double* C, int nc, int64_t j0, int64_t w) {
+    gemm64((int)n, nc, (int)w, -1.0, L.as<double>() + j0 * ld, ld, G.as<double>(), (w + 1) / 2 * 2, true, 1.0, C, ld,
+           false, st);
+  };
+  auto panel = [&]() {
+    k_piv_panel<<<np, 256, 0, st>>>(L.as<double>(), n, ld, m, pool.as<double>(), ps, d.as<double>(), pmax.as<double>());
+    LAUNCHCHK();
+  };
+  panel();   // no columns yet: the block maxima of the diagonal
+  for (;;) {
+    k_piv_begin<<<1, 1024, 0, st>>>(pmax.as<double>(), np, thr, ps);
+    k_piv_hist<<<scan, 256, 0, st>>>(d.as<double>(), n, thr, ps);
+    k_piv_list<<<scan, 256, 0, st>>>(d.as<double>(), n, thr, slots, ps);
+    k_piv_match<<<1, kPool, 0, st>>>(ps, slots);
+    LAUNCHCHK();
+    struct { int s, stop, count, fresh; } h;
+    HIPCHK(hipMemcpyAsync(&h, &ps->s, sizeof(h), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    const int64_t m0 = m;
+    m += h.s;
+    if (h.stop || m >= k || (ran && h.s == 0)) break;   // (no pivot: only where a value is NaN)
+    ran = true;
+    if (h.s > 0) {
+      const int64_t ldg = (h.s + 1) / 2 * 2;
+      k_piv_rows<int><<<cdiv(slots * ldg, 256), 256, 0, st>>>(L.as<double>(), ld, m0, ps->row, slots, h.s, ldg,
+                                                              G.as<double>());
+      LAUNCHCHK();
+      subtract(pool.as<double>(), slots, m0, h.s);
+    }
+    if (h.fresh > 0) {
+      kernel_columns(s, ps->new_row, h.fresh, stage.as<double>(), ld, 0.0, st);
+      if (m > 0) {
+        const int64_t ldg = (m + 1) / 2 * 2;
+        k_piv_rows<int64_t><<<cdiv(h.fresh * ldg, 256), 256, 0, st>>>(L.as<double>(), ld, 0, ps->new_row, h.fresh, m,
+                                                                      ldg, G.as<double>());
+        LAUNCHCHK();
+        subtract(stage.as<double>(), h.fresh, 0, m);
+      }
+      k_piv_place<<<dim3(np, h.fresh), 256, 0, st>>>(stage.as<double>(), n, ld, ps, pool.as<double>());
+      LAUNCHCHK();
+    }
+    k_piv_greedy<<<1, 1024, 0, st>>>(pool.as<double>(), ld, d.as<double>(), thr, m, (int)std::min<int64_t>(k - m, kPool),
+                                     slots, ps, piv.as<int64_t>());
+    LAUNCHCHK();
+    panel();
+  }
+  if (m > 0) HIPCHK(hipMemcpyAsync(idx_out, piv.get(), m * 8, hipMemcpyDeviceToDevice, st));
   HIPCHK(hipStreamSynchronize(st));
-  if (hk > 0) HIPCHK(hipMemcpyAsync(idx_out, piv.get(), hk * 8, hipMemcpyDeviceToDevice, st));
-  HIPCHK(hipStreamSynchronize(st));
-  return hk;
+  return m;
 }
 
 // ------------------------------------------------------------- leverage ----
