@@ -19,12 +19,6 @@ struct Chol64 {
   unsigned char bad[64];    // pivots that were dropped or not positive
 };
 
-__device__ inline double lane_value(double x, int lane) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(x), lane);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), lane);
-  return __hiloint2double(hi, lo);
-}
-
 // s = sqrt(d), ri = 1 / s for 1e-280 < d < 1e280: the hardware's reciprocal
 // square root and two Newton steps, both results corrected by their residuals
 // (the library's square root and divide are a chain twice as long, and 64 of

@@ -8,133 +8,187 @@
 // Hessian coefficients at r = |d|,
 //   K[i-block, c] = J_i^T (a u + b (d . u) d) = a J_i^T u + b (d . u) J_i^T d,
 // where (J_i^T h)_q = -sum_{b != q} h_{qb} (R_iq - R_ib) / r_iqb^3.
-// One wave handles one (target, column) pair; a block of 4 waves shares the
-// target's geometry factors in LDS and walks a chunk of columns.
+// A wave handles one target and 64 columns, one per lane, so that everything
+// that belongs to the target is uniform: its pair vectors (R_ia - R_ib)/r^3
+// and distances come from the system's pair table, a pair to a lane, and reach
+// the arithmetic as scalars by readlane (scalar loads instead, a tile's 64
+// pairs need more scalar registers than there are: 488 us where this takes 345).  A pair costs
+// a lane one LDS read (x_g of its column), a subtraction and three FMAs.  A
+// block is four targets of the same 64 columns, which share the staging of the
+// columns' x_g rows, in tiles of 8 x 8 atoms.
+// Bound by the readlanes and that arithmetic.  (One wave per (target, column),
+// lanes over the M atoms, left two thirds of the lanes idle at M = 21 and read
+// every pair's vector from LDS: 256 columns at M = 21, N = 2000 786 us, now
+// 345; 8192 at N = 200 1890, now 740.)
 #include "common.hpp"
 
 namespace ffk {
 
-#define COLS_PER_BLOCK 64
-
 __device__ inline int pair_of(int a, int b) { return a > b ? a * (a - 1) / 2 + b : b * (b - 1) / 2 + a; }
 
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
+constexpr int kColTile = 64;   // columns per block, one per lane
+constexpr int kColWaves = 4;   // targets per block
+constexpr int kAtoms = 8;      // atoms per tile side
+constexpr int kXStride = kColTile + 1;
 
-// Targets (rows) come from R, X; the source geometry of each column from
-// Rs, Xs (the same arrays for a plain kernel, a permuted copy for a
-// symmetrized one).  With accumulate the values are added to out.
-__global__ __launch_bounds__(256) void k_columns(const double* __restrict__ R, const double* __restrict__ X,
-                                                 const double* __restrict__ Rs, const double* __restrict__ Xs,
-                                                 const int* __restrict__ pairs, int M, int64_t D,
-                                                 const int64_t* __restrict__ cols, int64_t k,
-                                                 double* __restrict__ out, int64_t ldo, double shift,
-                                                 double inv_len, double a0, double bcoef, int accumulate) {
+// Targets (rows) come from PT, X; the source geometry of each column from PTs,
+// Xs (the same arrays for a plain kernel, a permuted copy for a symmetrized
+// one).  PT: the pair table, four doubles per (geometry, pair a > b): (R_a -
+// R_b) / r^3 and 1 / r.  With accumulate the values are added to out.
+// LDS: xs[64][65] (x_g of a tile's pairs; then the outputs on their way out),
+// U[M][64] (u on the pairs {p, b} of each column), XP[M][64] (x_g there).
+__global__ __launch_bounds__(64 * kColWaves) void k_columns(
+    const double* __restrict__ PT, const double* __restrict__ X, const double* __restrict__ PTs,
+    const double* __restrict__ Xs, int64_t N, int M, int64_t D, const int64_t* __restrict__ cols, int64_t k,
+    double* __restrict__ out, int64_t ldo, double shift, double inv_len, double a0, double bcoef, int accumulate) {
   extern __shared__ double sm[];
-  const int nw = blockDim.x >> 6;   // waves per block (1, 2 or 4)
-  double* sRi = sm;                 // 3M
-  double* sWi = sRi + 3 * M;        // 3D: (R_ia - R_ib)/r^3 for pair (a > b)
-  double* sD = sWi + 3 * D;         // nw waves x D
-  double* sU = sD + nw * D;         // nw waves x M
-  const int64_t i = blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double* xs = sm;
+  double* U = xs + kColTile * kXStride;
+  double* XP = U + M * kColTile;
+  __shared__ int64_t sg_of[kColTile];   // first element of the source's row of X
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m3 = 3 * M;
+  const int64_t c0 = (int64_t)blockIdx.y * kColTile;
+  // columns past the end and targets past the end repeat the last one and
+  // store nothing
+  const int64_t cidx = min(c0 + lane, k - 1);
+  const int64_t col = cols[cidx];
+  const int64_t g = col / m3;
+  const int loc = (int)(col % m3), p = loc / 3, t = loc % 3;
+  const int64_t i_raw = (int64_t)blockIdx.x * kColWaves + wave;
+  const int64_t i = min(i_raw, N - 1);
+  const double* Pi = PT + i * D * 4;
   const double* Xi = X + i * D;
-  for (int e = threadIdx.x; e < m3; e += blockDim.x) sRi[e] = R[i * m3 + e];
-  __syncthreads();
-  for (int64_t e = threadIdx.x; e < D; e += blockDim.x) {
-    const int pq = pairs[e];
-    const int a = pq >> 16, b = pq & 0xFFFF;
-    const double dx = sRi[3 * a] - sRi[3 * b], dy = sRi[3 * a + 1] - sRi[3 * b + 1], dz = sRi[3 * a + 2] - sRi[3 * b + 2];
-    const double ir = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
-    const double ir3 = ir * ir * ir;
-    sWi[3 * e] = dx * ir3;
-    sWi[3 * e + 1] = dy * ir3;
-    sWi[3 * e + 2] = dz * ir3;
+  if (tid < kColTile) sg_of[tid] = g * D;
+#pragma unroll 4
+  for (int b = wave; b < M; b += kColWaves) {   // u_{pb} = -(R_gp - R_gb)_t / r^3
+    const double* w = PTs + (g * D + (b != p ? pair_of(p, b) : 0)) * 4;
+    const double wt = w[t], x = w[3];
+    U[b * kColTile + lane] = b == p ? 0.0 : (p > b ? -wt : wt);
+    XP[b * kColTile + lane] = b == p ? 0.0 : x;
   }
-  __syncthreads();
-  double* dW = sD + wave * D;
-  double* uW = sU + wave * M;
-  const int64_t c0 = (int64_t)blockIdx.y * COLS_PER_BLOCK;
-  // uniform trip count so that the block barriers below are reached by all waves
-  for (int it = 0; it < COLS_PER_BLOCK / nw; ++it) {
-    const int64_t cidx = c0 + it * nw + wave;
-    const bool active = cidx < k;
-    int64_t col = 0, g = 0;
-    int p = 0, t = 0;
-    double r2 = 0.0;
-    if (active) {
-      col = cols[cidx];
-      g = col / m3;
-      const int loc = (int)(col % m3);
-      p = loc / 3;
-      t = loc % 3;
-      for (int64_t e = lane; e < D; e += 64) {      // d = x_i - x_g and |d|^2
-        const double dd = Xi[e] - Xs[g * D + e];
-        dW[e] = dd;
-        r2 += dd * dd;
-      }
-      r2 = wave_sum(r2);
-      const double* Rg = Rs + g * m3;
-      for (int b = lane; b < M; b += 64) {          // u on the pairs {p, b}
-        double u = 0.0;
-        if (b != p) {
-          const double dx = Rg[3 * p] - Rg[3 * b], dy = Rg[3 * p + 1] - Rg[3 * b + 1],
-                       dz = Rg[3 * p + 2] - Rg[3 * b + 2];
-          const double ir = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
-          const double comp = t == 0 ? dx : (t == 1 ? dy : dz);
-          u = -comp * ir * ir * ir;
-        }
-        uW[b] = u;
-      }
+  // |x_i - x_g|^2 over tiles of 64 consecutive pairs
+  double r2 = 0.0;
+  for (int64_t e0 = 0; e0 < D; e0 += kColTile) {
+    __syncthreads();
+    const int64_t e = min(e0 + lane, D - 1);
+    const double xi = Xi[e];
+#pragma unroll
+    for (int c = 0; c < kColTile / kColWaves; ++c) {
+      const int cc = wave + kColWaves * c;
+      xs[lane * kXStride + cc] = Xs[sg_of[cc] + e];
     }
     __syncthreads();
-    if (active) {
-      double du = 0.0;
-      for (int b = lane; b < M; b += 64)
-        if (b != p) du += dW[pair_of(p, b)] * uW[b];
-      du = wave_sum(du);
-      const double z = sqrt(r2) * inv_len;
-      const double ez = exp(-z);
-      const double a = a0 * (1.0 + z) * ez;
-      const double bdu = -bcoef * ez * du;
-      for (int q = lane; q < M; q += 64) {
-        double jx = 0.0, jy = 0.0, jz = 0.0;   // (J_i^T d)_q
-        double ux = 0.0, uy = 0.0, uz = 0.0;   // (J_i^T u)_q
-        for (int b = 0; b < M; ++b) {
-          if (b == q) continue;
-          const int e = pair_of(q, b);
-          const double sgn = q > b ? 1.0 : -1.0;   // sWi holds (R_larger - R_smaller)/r^3
-          const double wx = sgn * sWi[3 * e], wy = sgn * sWi[3 * e + 1], wz = sgn * sWi[3 * e + 2];
-          const double de = dW[e];
-          jx -= de * wx;
-          jy -= de * wy;
-          jz -= de * wz;
-          const double ue = (q == p) ? uW[b] : (b == p ? uW[q] : 0.0);
-          ux -= ue * wx;
-          uy -= ue * wy;
-          uz -= ue * wz;
-        }
-        const int64_t row = i * m3 + 3 * q;
-        double* o = out + cidx * ldo + row;
-        const double v0 = a * ux + bdu * jx + (row == col ? shift : 0.0);
-        const double v1 = a * uy + bdu * jy + (row + 1 == col ? shift : 0.0);
-        const double v2 = a * uz + bdu * jz + (row + 2 == col ? shift : 0.0);
-        if (accumulate) {
-          o[0] += v0;
-          o[1] += v1;
-          o[2] += v2;
-        } else {
-          o[0] = v0;
-          o[1] = v1;
-          o[2] = v2;
-        }
+    const int ne = (int)min((int64_t)kColTile, D - e0);
+#pragma unroll
+    for (int q = 0; q < kColTile; ++q) {
+      const double dd = lane_value(xi, q) - xs[q * kXStride + lane];
+      if (q < ne) r2 = fma(dd, dd, r2);
+    }
+  }
+  // d . u, and sum_b u_{pb} (R_ip - R_ib) / r^3
+  double du = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
+  for (int b0 = 0; b0 < M; b0 += kAtoms) {   // eight pairs' loads in flight; U is zero at b = p
+    double w[kAtoms][4];
+#pragma unroll
+    for (int q = 0; q < kAtoms; ++q) {
+      const int b = min(b0 + q, M - 1);
+      const double* src = Pi + (b == p ? 0 : pair_of(p, b)) * 4;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) w[q][v] = src[v];
+    }
+#pragma unroll
+    for (int q = 0; q < kAtoms; ++q) {
+      const int b = min(b0 + q, M - 1);
+      const double u = b0 + q < M ? U[b * kColTile + lane] : 0.0, us = p > b ? u : -u;
+      du = fma(w[q][3] - XP[b * kColTile + lane], u, du);
+      sx = fma(us, w[q][0], sx);
+      sy = fma(us, w[q][1], sy);
+      sz = fma(us, w[q][2], sz);
+    }
+  }
+  const double z = sqrt(r2) * inv_len;
+  const double ez = exp(-z);
+  const double a = a0 * (1.0 + z) * ez;
+  const double bdu = -bcoef * ez * du;
+
+  for (int q0 = 0; q0 < M; q0 += kAtoms) {   // eight atoms' outputs at a time
+    double vx[kAtoms], vy[kAtoms], vz[kAtoms];   // -(J_i^T d)_q
+#pragma unroll
+    for (int q = 0; q < kAtoms; ++q) vx[q] = vy[q] = vz[q] = 0.0;
+    for (int b0 = 0; b0 < M; b0 += kAtoms) {
+      __syncthreads();
+      // lane: one pair of the tile, along the faster atom of their order in
+      // memory; its vector towards the atom of q, and zero where it is no pair
+      const bool below = q0 >= b0;
+      const int hi = lane >> 3, lo = lane & 7;
+      const int qa = q0 + (below ? hi : lo), ba = b0 + (below ? lo : hi);
+      const bool pair = qa != ba && qa < M && ba < M;
+      const int64_t e = pair ? pair_of(qa, ba) : 0;
+      const double sg = pair ? (qa > ba ? 1.0 : -1.0) : 0.0;
+      const double wx = sg * Pi[4 * e], wy = sg * Pi[4 * e + 1], wz = sg * Pi[4 * e + 2], wd = Pi[4 * e + 3];
+#pragma unroll
+      for (int c = 0; c < kColTile / kColWaves; ++c) {
+        const int cc = wave + kColWaves * c;
+        xs[lane * kXStride + cc] = Xs[sg_of[cc] + e];
       }
+      __syncthreads();
+      auto tile = [&](auto ql) {   // ql(q, b): the lane that holds the pair
+#pragma unroll
+        for (int q = 0; q < kAtoms; ++q)
+#pragma unroll
+          for (int b = 0; b < kAtoms; ++b) {
+            const int l = ql(q, b);
+            const double dd = lane_value(wd, l) - xs[l * kXStride + lane];
+            vx[q] = fma(dd, lane_value(wx, l), vx[q]);
+            vy[q] = fma(dd, lane_value(wy, l), vy[q]);
+            vz[q] = fma(dd, lane_value(wz, l), vz[q]);
+          }
+      };
+      if (below) tile([](int q, int b) { return q * kAtoms + b; });
+      else tile([](int q, int b) { return b * kAtoms + q; });
     }
     __syncthreads();
+    // outputs of four atoms at a time through LDS, so that a column's twelve
+    // consecutive rows are stored together
+    constexpr int OW = 12, OS = OW + 1;
+    double* st = xs + wave * (kColTile * OS);
+    static_assert(kColWaves * kColTile * OS <= kColTile * kXStride, "output staging fits the tile");
+#pragma unroll
+    for (int h = 0; h < kAtoms; h += 4) {
+#pragma unroll
+      for (int q = h; q < h + 4; ++q) {
+        const int qa = q0 + q;
+        if (qa < M) {
+          const double* w = Pi + (qa != p ? pair_of(qa, p) : 0) * 4;
+          const double u = U[qa * kColTile + lane], us = qa > p ? -u : u;
+          const double ux = qa != p ? us * w[0] : -sx;   // (J_i^T u)_q
+          const double uy = qa != p ? us * w[1] : -sy;
+          const double uz = qa != p ? us * w[2] : -sz;
+          const int64_t row = i * m3 + 3 * qa;
+          double* o = st + lane * OS + 3 * (q - h);
+          o[0] = a * ux - bdu * vx[q] + (row == col ? shift : 0.0);
+          o[1] = a * uy - bdu * vy[q] + (row + 1 == col ? shift : 0.0);
+          o[2] = a * uz - bdu * vz[q] + (row + 2 == col ? shift : 0.0);
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+      const int na = min(4, M - (q0 + h));   // atoms of this part
+      if (na > 0 && i_raw < N) {
+        const int nr = 3 * na;
+        double* o = out + i * m3 + 3 * (q0 + h);
+        for (int e = lane; e < kColTile * nr; e += 64) {
+          const int c = e / nr, r = e % nr;
+          if (c0 + c < k) {
+            double* dst = o + (c0 + c) * ldo + r;
+            const double val = st[c * OS + r];
+            *dst = accumulate ? *dst + val : val;
+          }
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
   }
 }
 
@@ -150,18 +204,22 @@ void kernel_columns_src(const ffk_system* s, const ffk_system* src, const int64_
     HIPCHK(hipGetDevice(&dv));
     HIPCHK(hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dv));
   }
-  int nw = 4;
-  auto bytes = [&](int w) { return (size_t)(3 * M + 3 * D + w * (D + M)) * sizeof(double); };
-  while (nw > 1 && bytes(nw) > (size_t)max_lds) nw >>= 1;
-  if (bytes(nw) > (size_t)max_lds) fail(FFK_ERR_ARG, "kernel_columns: descriptor too large for the LDS staging");
-  const int64_t per_launch = (int64_t)65535 * COLS_PER_BLOCK;
+  // the interface's limit (four values per atom and pair in the LDS of a
+  // block); the tile and the two tables below need less than that at any M
+  // whose tables fill the LDS, and fit it up to the limit
+  const size_t shm = (size_t)(kColTile * kXStride + 2 * M * kColTile) * sizeof(double);
+  if ((size_t)(4 * M + 4 * D) * sizeof(double) > (size_t)max_lds || shm > (size_t)max_lds)
+    fail(FFK_ERR_ARG, "kernel_columns: descriptor too large for the LDS staging");
+  if (shm > 65536)
+    HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_columns), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)shm));
+  const int64_t per_launch = (int64_t)65535 * kColTile;
   for (int64_t c0 = 0; c0 < k; c0 += per_launch) {
     const int64_t kc = std::min(per_launch, k - c0);
-    dim3 grid((unsigned)s->N, (unsigned)cdiv(kc, COLS_PER_BLOCK));
-    k_columns<<<grid, 64 * nw, bytes(nw), st>>>(s->R.as<double>(), s->X.as<double>(), src->R.as<double>(),
-                                                src->X.as<double>(), s->pairs.as<int>(), M, D, cols + c0, kc,
-                                                out + c0 * ldo, ldo, shift, sqrt(5.0) / s->sigma, s->a0, s->bcoef,
-                                                accumulate ? 1 : 0);
+    const dim3 grid((unsigned)cdiv(s->N, kColWaves), (unsigned)cdiv(kc, kColTile));
+    k_columns<<<grid, 64 * kColWaves, shm, st>>>(s->PT.as<double>(), s->X.as<double>(), src->PT.as<double>(),
+                                                 src->X.as<double>(), s->N, M, D, cols + c0, kc, out + c0 * ldo, ldo,
+                                                 shift, sqrt(5.0) / s->sigma, s->a0, s->bcoef, accumulate ? 1 : 0);
     LAUNCHCHK();
   }
 }

@@ -104,6 +104,13 @@ class HBuf {
   size_t n_ = 0;
 };
 
+// The value of one lane of the wave, as a scalar.
+__device__ inline double lane_value(double x, int lane) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(x), lane);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), lane);
+  return __hiloint2double(hi, lo);
+}
+
 // Compute units of the current device.
 inline int device_cus() {
   static const int cus = [] {
@@ -195,6 +202,7 @@ struct ffk_system {
   ffk::DBuf R;              // N x M x 3 double
   ffk::DBuf pairs;          // D int32: (p << 16) | q
   ffk::DBuf X;              // N x D double (uncentred)
+  ffk::DBuf PT;             // N x D x 4 double: (R_p - R_q) / r^3 and 1 / r of every pair
   ffk::DBuf xmean;          // D double
   ffk::DBuf Xc;             // N x D double (centred)
   ffk::DBuf sqn;            // N double (|x_c|^2)

@@ -14,7 +14,8 @@
 namespace ffk {
 
 __global__ void k_descriptor(const double* __restrict__ R, const int* __restrict__ pairs, int64_t N,
-                             int M, int64_t D, double* __restrict__ X, int* __restrict__ bad) {
+                             int M, int64_t D, double* __restrict__ X, double* __restrict__ PT,
+                             int* __restrict__ bad) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= N * D) return;
   const int64_t g = e / D, d = e % D;
@@ -27,6 +28,10 @@ __global__ void k_descriptor(const double* __restrict__ R, const int* __restrict
   const double x = 1.0 / sqrt(r2);
   if (!(r2 > 0.0) || !isfinite(x)) atomicOr(bad, 1);
   X[e] = x;
+  const double x3 = x * x * x;
+  double2* w = reinterpret_cast<double2*>(PT + 4 * e);
+  w[0] = make_double2(dx * x3, dy * x3);
+  w[1] = make_double2(dz * x3, x);
 }
 
 // Column means of an N x D matrix: block = 64 columns x 4 row groups.
@@ -77,13 +82,14 @@ void descriptor_build(ffk_system* s, const double* R, hipStream_t st, bool coeff
   s->R.alloc(N * M * 3 * sizeof(double));
   HIPCHK(hipMemcpyAsync(s->R.get(), R, N * M * 3 * sizeof(double), hipMemcpyDeviceToDevice, st));
   s->X.alloc(N * D * sizeof(double));
+  s->PT.alloc(4 * N * D * sizeof(double));
   s->Xc.alloc(N * D * sizeof(double));
   s->xmean.alloc(D * sizeof(double));
   s->sqn.alloc(N * sizeof(double));
   DBuf bad(sizeof(int));
   HIPCHK(hipMemsetAsync(bad.get(), 0, sizeof(int), st));
   k_descriptor<<<cdiv(N * D, 256), 256, 0, st>>>(s->R.as<double>(), s->pairs.as<int>(), N, M, D,
-                                                  s->X.as<double>(), bad.as<int>());
+                                                  s->X.as<double>(), s->PT.as<double>(), bad.as<int>());
   LAUNCHCHK();
   int hbad = 0;
   HIPCHK(hipMemcpyAsync(&hbad, bad.get(), sizeof(int), hipMemcpyDeviceToHost, st));
