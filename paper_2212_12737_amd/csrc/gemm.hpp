@@ -408,14 +408,15 @@ template <> struct DmaMfma<double> {
 // Operand segment of the pipelined engines: K-contiguous arrays of T whose row
 // count is padded to the tile and whose leading dimension (in elements) and K
 // are multiples of 64 bytes; padding is zero.  BF16 operands are in the
-// fragment-major layout (frag_off) with lda/32 (ldb/32) K tiles to a row group.
-// K may be less than the leading dimensions: K tiles that are all padding are
+// fragment-major layout (frag_off) with KT K tiles to a row group and ignore
+// lda/ldb.  K may be less than what is stored: K tiles that are all padding are
 // left out.  The lo arrays are used only in the split-BF16 mode.
 struct SegD {
   const void *Ah, *Al;
   const void *Bh, *Bl;
   int64_t lda, ldb;   // elements
   int K;              // elements, multiple of 64 bytes
+  int KT;             // BF16: K tiles of a stored row group
 };
 struct DmaArgs {
   int nseg;
@@ -473,12 +474,12 @@ __global__ __launch_bounds__(TL::NT) void gemm_dma_kernel(DmaArgs g, Epi epi) {
 
   // fragment-major operands (frag_off): the 1 KB block of a (row group, K
   // tile) is contiguous, lane L takes bytes 16 L .. 16 L + 15, and whole cache
-  // lines move per load.  lda and ldb give the K tiles of a stored row group,
-  // of which the product may take fewer.
+  // lines move per load.  KT: the K tiles of a stored row group, of which the
+  // product may take fewer.
   auto issue = [&](int t) {
     const SegD& sg = (t < t0) ? g.seg[0] : g.seg[1];
     const int64_t tk = (t < t0 ? t : t - t0);
-    const int64_t KA = sg.lda / BK, KB = sg.ldb / BK;
+    const int64_t KT = sg.KT;
     char* st = smem + (t % S) * STAGE_BYTES;
 #pragma unroll
     for (int h = 0; h < NARR; ++h) {
@@ -487,12 +488,12 @@ __global__ __launch_bounds__(TL::NT) void gemm_dma_kernel(DmaArgs g, Epi epi) {
 #pragma unroll
       for (int q = 0; q < QA; ++q) {
         const int grp = wave * QA + q;
-        dma16(A + (((int64_t)(m0 / 16 + grp) * KA + tk) * 512 + lane * 8), st + h * A_BYTES + grp * GROUP_BYTES);
+        dma16(A + (((int64_t)(m0 / 16 + grp) * KT + tk) * 512 + lane * 8), st + h * A_BYTES + grp * GROUP_BYTES);
       }
 #pragma unroll
       for (int q = 0; q < QB; ++q) {
         const int grp = wave * QB + q;
-        dma16(B + (((int64_t)(n0 / 16 + grp) * KB + tk) * 512 + lane * 8),
+        dma16(B + (((int64_t)(n0 / 16 + grp) * KT + tk) * 512 + lane * 8),
               st + NARR * A_BYTES + h * B_BYTES + grp * GROUP_BYTES);
       }
     }

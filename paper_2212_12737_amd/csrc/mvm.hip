@@ -776,7 +776,7 @@ static GemmOut mvm_gemms_dma(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t
   {
     DmaArgs g{};
     g.nseg = 1;
-    g.seg[0] = SegD{o.Uh, o.Ul, o.Xh, o.Xl, Dk, Dk, (int)rup(D, 32)};
+    g.seg[0] = SegD{o.Uh, o.Ul, o.Xh, o.Xl, Dk, Dk, (int)rup(D, 32), (int)(Dk / 32)};
     // rows of the product are sources, columns targets
     const dim3 grid((unsigned)(Ntr / TL1::BN), (unsigned)(Nsr / TL1::BM));
     clk_begin(CLK_GEMM1, st);
@@ -789,8 +789,8 @@ static GemmOut mvm_gemms_dma(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t
   mark(ev, 3, st);
   DmaArgs g{};
   g.nseg = 2;
-  g.seg[0] = SegD{o.dAh, o.dAl, o.UTh, o.UTl, Nsr, Nsr, (int)Nsr};
-  g.seg[1] = SegD{o.Wh, o.Wl, o.XTh, o.XTl, Nsr, Nsr, (int)Nsr};
+  g.seg[0] = SegD{o.dAh, o.dAl, o.UTh, o.UTl, Nsr, Nsr, (int)Nsr, (int)(Nsr / 32)};
+  g.seg[1] = SegD{o.Wh, o.Wl, o.XTh, o.XTl, Nsr, Nsr, (int)Nsr, (int)(Nsr / 32)};
   const int64_t tiles = (Dr / TL2::BN) * (Ntr / TL2::BM);
   static int per_cu = 0;
   if (per_cu == 0) {

@@ -150,7 +150,7 @@ void select_weighted(int64_t n, const double* w, int64_t k, uint64_t seed, int s
 // ends when it is, or when the rank test stops the factorization.  What a
 // pivot costs is then a share of a few passes over n x kPool and of a K = m
 // product instead of a pass over the factor: at n = 126000, k = 2000
-// (75 blocks) 415 ms became 73 (57 with the kernel columns in tiles of 64).
+// 415 ms became 45, of which half is the products that form new candidates.
 constexpr int kPool = 128;       // candidates (two per lane of the greedy wave)
 constexpr int kBins = 2048;      // histogram of the diagonals, 2^-10 of an octave each
 constexpr int kBinShift = 10;    // of the high word
@@ -162,7 +162,7 @@ struct PivState {
   int count;            // candidates listed
   int fresh;            // of them, without a column in the pool
   int first;            // lowest row with the largest diagonal
-  int pad;
+  int ones;             // pivots taken one at a time since the host last looked
   int hist[kBins];
   int list[kPool];      // candidate rows
   int row[kPool];       // pool: the row of every slot, -1 = free
@@ -174,6 +174,185 @@ struct PivState {
   double pval[kPool], pinv[kPool];   // and its inverse
   double Lt[kPool * kPool];
 };
+
+// ---- one pivot at a time: while blocks are short, the passes over the factor
+// cost less than a block's launches
+struct Cand {
+  double v;
+  int i;
+};
+__device__ inline Cand better(Cand a, Cand b) { return before(a.v, a.i, b.v, b.i) ? a : b; }
+
+__device__ inline Cand block_best(Cand c, Cand* sh) {
+  sh[threadIdx.x] = c;
+  __syncthreads();
+  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) sh[threadIdx.x] = better(sh[threadIdx.x], sh[threadIdx.x + o]);
+    __syncthreads();
+  }
+  return sh[0];
+}
+
+// Best rows of blocks of 256 diagonals.
+__global__ __launch_bounds__(256) void k_argmax_part(const double* d, int64_t n, Cand* part) {
+  __shared__ Cand sh[256];
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  Cand c{-INFINITY, 0x7FFFFFFF};
+  if (i < n) c = Cand{d[i], (int)i};
+  c = block_best(c, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = c;
+}
+
+__device__ inline int piv_pair(int a, int b) { return a > b ? a * (a - 1) / 2 + b : b * (b - 1) / 2 + a; }
+__device__ inline double piv_wave_sum(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
+// Pivot m and column m of L.  Every block finds the best row from the partials
+// (the same fixed order everywhere; block 0 writes it down) or that the rank
+// test stops here.  One wave per target geometry then evaluates its 3M rows of
+// the kernel column (lanes are rows; pair vectors from the system's table, PTs
+// and Xs of the source's), subtracts L[:, :m] times the pivot's row, scales, and
+// lowers the diagonals, and the block leaves its best row for the next pivot.
+// A symmetrized kernel takes one launch per group element (pinv maps the
+// column's atom), summed in L[:, m]; the last one finishes.
+// Bound by latency at small m, by reading L later: 19 us a pivot at N = 2000 and
+// small m, where a selection, a column and an update kernel took 33.
+__global__ __launch_bounds__(256) void k_piv_step(const double* __restrict__ PT, const double* __restrict__ X,
+                                                  const double* __restrict__ PTs, const double* __restrict__ Xs,
+                                                  const int32_t* __restrict__ pinv, int64_t N, int M, int64_t D,
+                                                  double inv_len, double a0, double bcoef, int add, int finish,
+                                                  double* __restrict__ L, int64_t ld, int64_t m,
+                                                  double thr, const Cand* __restrict__ part_in, int np_in,
+                                                  PivState* __restrict__ st, int64_t* __restrict__ piv,
+                                                  double* __restrict__ d, Cand* __restrict__ part_out) {
+  extern __shared__ double sm[];
+  constexpr int CH = 512;
+  const int nw = blockDim.x >> 6;
+  double* sv = sm;                       // CH values of the pivot's row
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double* dW = sv + CH + wave * (D + M);
+  double* uW = dW + D;
+  __shared__ Cand sh[256];
+  const int m3 = 3 * M;
+  Cand c{-INFINITY, 0x7FFFFFFF};
+  for (int e = threadIdx.x; e < np_in; e += blockDim.x) c = better(c, part_in[e]);
+  c = block_best(c, sh);
+  const bool go = c.i != 0x7FFFFFFF && c.v > thr;   // the same for the whole grid
+  if (blockIdx.x == 0 && finish) {
+    if (threadIdx.x == 0) {
+      if (go) piv[m] = c.i;
+      if (go) st->ones += 1;
+      else st->stop = 1;
+    }
+    if (go && threadIdx.x < 64) {
+      if (st->row[threadIdx.x] == c.i) st->row[threadIdx.x] = -1;
+      if (st->row[threadIdx.x + 64] == c.i) st->row[threadIdx.x + 64] = -1;
+    }
+  }
+  if (!go) {   // and the next launches stop here too
+    if (finish && threadIdx.x == 0) part_out[blockIdx.x] = Cand{-INFINITY, 0x7FFFFFFF};
+    return;
+  }
+  const double one_val = sqrt(c.v), one_inv = 1.0 / one_val;
+  const int64_t pivot = c.i, g = pivot / m3;
+  const int loc = (int)(pivot % m3), t = loc % 3;
+  const int p = pinv ? pinv[loc / 3] : loc / 3;
+  const int64_t i = (int64_t)blockIdx.x * nw + wave;
+  const bool active = i < N;
+  const double* Pi = PT + (active ? i : 0) * D * 4;
+  double r2 = 0.0, du = 0.0;
+  if (active) {
+#pragma unroll 4
+    for (int64_t e = lane; e < D; e += 64) {
+      const double dd = X[i * D + e] - Xs[g * D + e];
+      dW[e] = dd;
+      r2 = fma(dd, dd, r2);
+    }
+    for (int b = lane; b < M; b += 64) {
+      const double w = PTs[(g * D + (b != p ? piv_pair(p, b) : 0)) * 4 + t];
+      uW[b] = b == p ? 0.0 : (p > b ? -w : w);
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (int b = lane; b < M; b += 64)
+      if (b != p) du = fma(dW[piv_pair(p, b)], uW[b], du);
+    r2 = piv_wave_sum(r2);
+    du = piv_wave_sum(du);
+  }
+  const double z = sqrt(r2) * inv_len;
+  const double ez = exp(-z);
+  const double a = a0 * (1.0 + z) * ez, bdu = -bcoef * ez * du;
+  c = Cand{-INFINITY, 0x7FFFFFFF};
+  for (int o0 = 0; o0 < m3; o0 += 64) {   // uniform: the chunks of the pivot's row below are the block's
+    const int o = o0 + lane;
+    const bool row_ok = active && o < m3;
+    const int q = row_ok ? o / 3 : 0, s = row_ok ? o % 3 : 0;
+    const int64_t row = i * m3 + o;
+    double raw = 0.0;
+    if (row_ok) {
+      double jd = 0.0, ju = 0.0;   // (J^T d)_q and (J^T u)_q, component s
+      constexpr int W = 12;          // pair vectors in flight
+      for (int b0 = 0; b0 < M; b0 += W) {
+        double w[W];
+#pragma unroll
+        for (int x = 0; x < W; ++x) {
+          const int b = min(b0 + x, M - 1);
+          w[x] = Pi[4 * (b != q ? piv_pair(q, b) : 0) + s];
+        }
+#pragma unroll
+        for (int x = 0; x < W; ++x) {
+          const int b = min(b0 + x, M - 1);
+          const bool pair = b != q && b0 + x < M;
+          const double ws = pair ? (q > b ? w[x] : -w[x]) : 0.0;
+          jd = fma(-dW[pair ? piv_pair(q, b) : 0], ws, jd);
+          ju = fma(-(q == p ? uW[b] : (b == p ? uW[q] : 0.0)), ws, ju);
+        }
+      }
+      raw = a * ju + bdu * jd;
+      if (add) raw += L[row + m * ld];
+      if (!finish) L[row + m * ld] = raw;
+    }
+    if (!finish) continue;
+    double s0 = 0.0, s1 = 0.0;
+    for (int64_t j0 = 0; j0 < m; j0 += CH) {
+      const int jn = (int)min((int64_t)CH, m - j0);
+      __syncthreads();
+      for (int j = threadIdx.x; j < jn; j += blockDim.x) sv[j] = L[pivot + (j0 + j) * ld];
+      __syncthreads();
+      if (row_ok) {
+        const double* Li = L + row + j0 * ld;
+        int j = 0;
+#pragma unroll 4
+        for (; j + 2 <= jn; j += 2) {
+          s0 = fma(Li[j * ld], sv[j], s0);
+          s1 = fma(Li[(j + 1) * ld], sv[j + 1], s1);
+        }
+        if (j < jn) s0 = fma(Li[j * ld], sv[j], s0);
+      }
+    }
+    if (row_ok) {
+      double dn = d[row], l = 0.0;
+      if (row == pivot) {
+        l = one_val;
+        d[row] = -INFINITY;
+      } else if (dn != -INFINITY) {
+        l = (raw - (s0 + s1)) * one_inv;
+        dn = fma(-l, l, dn);
+        d[row] = dn;
+        c = better(c, Cand{dn, (int)row});
+      }
+      L[row + m * ld] = l;
+    }
+  }
+  if (!finish) return;
+  __syncthreads();
+  c = block_best(c, sh);
+  if (threadIdx.x == 0) part_out[blockIdx.x] = c;
+}
+
+// ---- blocks of pivots
 
 // Columns [m, m + s) of L for this thread's row by forward substitution with
 // the block's pivot rows (the arithmetic and order of Algorithm 1 within the
@@ -454,9 +633,6 @@ __global__ __launch_bounds__(1024) void k_piv_greedy(const double* __restrict__ 
     if (rc[h] < 0) rc[h] = 0x7FFFFFFF;
   }
   int s = 0, sl0 = 0, sl1 = 0;   // lane b: the slots of pivots b and b + 64
-  auto slot = [&](int b) {
-    return b < 64 ? __builtin_amdgcn_readlane(sl0, b) : __builtin_amdgcn_readlane(sl1, b - 64);
-  };
   while (s < limit) {
     // the best candidate: the largest diagonal, then the lowest row of those
     const double v = wave_max(fmax(dc[0], dc[1]));
@@ -475,13 +651,16 @@ __global__ __launch_bounds__(1024) void k_piv_greedy(const double* __restrict__ 
     const int p = owner + ((__ballot(upper) >> owner) & 1 ? 64 : 0);
     const double pv = sqrt(v), pinv = 1.0 / pv;
     double x0 = A[p][lane], x1 = A[p][lane + 64];
-#pragma unroll 8
-    for (int b = 0; b < s; ++b) {
-      const double* Lb = A[slot(b)];
+    auto earlier = [&](int slot) {
+      const double* Lb = A[slot];
       const double lp = Lb[p];
       x0 = fma(-Lb[lane], lp, x0);
       x1 = fma(-Lb[lane + 64], lp, x1);
-    }
+    };
+#pragma unroll 8
+    for (int b = 0; b < min(s, 64); ++b) earlier(__builtin_amdgcn_readlane(sl0, b));
+#pragma unroll 8
+    for (int b = 64; b < s; ++b) earlier(__builtin_amdgcn_readlane(sl1, b - 64));
     if (lane < s) st->Lt[lane * kPool + s] = A[sl0][p];
     if (lane + 64 < s) st->Lt[(lane + 64) * kPool + s] = A[sl1][p];
     x0 = p == lane ? pv : (dc[0] == -INFINITY ? 0.0 : x0 * pinv);
@@ -516,27 +695,28 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
   DBuf L(ld * k * 8), d(n * 8), piv(k * 8), state(sizeof(PivState));
   const int np = cdiv(n, 256);
   DBuf pmax((size_t)np * 8), pool, stage, G;
+  int slots = 0;
   // the pool and its staging columns, fewer where memory is short
-  int slots = (int)std::min<int64_t>(kPool, n);
-  for (;; slots = std::max(1, slots / 4)) {
-    try {
-      pool.alloc(ld * slots * 8);
-      stage.alloc(ld * slots * 8);
-      G.alloc((size_t)slots * (k + 2) * 8);
-      break;
-    } catch (const Error&) {
-      pool.release();
-      stage.release();
-      if (slots == 1) throw;
+  auto make_pool = [&]() {
+    for (slots = (int)std::min<int64_t>(kPool, n);; slots = std::max(1, slots / 4)) {
+      try {
+        pool.alloc(ld * slots * 8);
+        stage.alloc(ld * slots * 8);
+        G.alloc((size_t)slots * (k + 2) * 8);
+        return;
+      } catch (const Error&) {
+        pool.release();
+        stage.release();
+        if (slots == 1) throw;
+      }
     }
-  }
+  };
   PivState* ps = state.as<PivState>();
   HIPCHK(hipMemsetAsync(ps, 0, sizeof(PivState), st));
   HIPCHK(hipMemsetAsync(ps->row, 0xFF, sizeof(ps->row), st));   // -1: every slot free
   kernel_diag(s, d.as<double>(), st);
   const int scan = std::min(np, 512);
-  int64_t m = 0;
-  bool ran = false;
+  int64_t m = 0, m_pool = 0;   // pivots; the columns of L that the pool's columns already account for
   // columns [c, c + nc) of C (n x nc) -= L[:, j0 .. j0 + w) (its rows in G)^T
   auto subtract = [&](double* C, int nc, int64_t j0, int64_t w) {
     gemm64((int)n, nc, (int)w, -1.0, L.as<double>() + j0 * ld, ld, G.as<double>(), (w + 1) / 2 * 2, true, 1.0, C, ld,
@@ -546,27 +726,88 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
     k_piv_panel<<<np, 256, 0, st>>>(L.as<double>(), n, ld, m, pool.as<double>(), ps, d.as<double>(), pmax.as<double>());
     LAUNCHCHK();
   };
-  panel();   // no columns yet: the block maxima of the diagonal
+  struct { int s, stop, count, fresh, first, ones; } h;
+  auto look = [&]() {
+    HIPCHK(hipMemcpyAsync(&h, &ps->s, sizeof(h), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+  };
+  // up to `want` pivots one at a time (fewer at the rank threshold)
+  const int64_t D = s->D;
+  int nw = 4;
+  auto step_lds = [&](int w) { return (size_t)(512 + w * (D + s->M)) * 8; };
+  while (nw > 1 && step_lds(nw) > 65536) nw >>= 1;
+  const int np1 = cdiv(s->N, nw);
+  DBuf part_a((size_t)std::max(np, np1) * sizeof(Cand)), part_b((size_t)std::max(np, np1) * sizeof(Cand));
+  auto singles = [&](int64_t want) {
+    want = std::min(want, k - m);
+    Cand *in = part_a.as<Cand>(), *out = part_b.as<Cand>();
+    k_argmax_part<<<np, 256, 0, st>>>(d.as<double>(), n, in);
+    LAUNCHCHK();
+    const int S = std::max<int>(1, (int)s->sym.size());
+    for (int64_t e = 0; e < want; ++e) {
+      for (int q = 0; q < S; ++q) {
+        const ffk_system* src = s->sym.empty() ? s : s->sym[q].get();
+        k_piv_step<<<np1, 64 * nw, step_lds(nw), st>>>(
+            s->PT.as<double>(), s->X.as<double>(), src->PT.as<double>(), src->X.as<double>(),
+            s->sym.empty() ? nullptr : s->sym_pinv.as<int32_t>() + (size_t)q * s->M, s->N, s->M, D,
+            sqrt(5.0) / s->sigma, s->a0, s->bcoef, q > 0, q == S - 1, L.as<double>(), ld, m + e, thr, in,
+            e == 0 ? np : np1, ps, piv.as<int64_t>(), d.as<double>(), out);
+        LAUNCHCHK();
+      }
+      std::swap(in, out);
+    }
+  };
+  // Blocks start short (an early pivot lowers a whole class of rows, those of
+  // one coordinate of one atom) and grow past twenty pivots.  A pivot by
+  // itself takes 24 us and a pass over L, a block 300 us and more, and more
+  // with n (M = 22, N = 1005, k = 130: 3.9 ms with three kernels a pivot, 4.1
+  // with blocks from 64 pivots on; M = 12, N = 200, k = 180: 3.7 and 2.1).  So
+  // the first pivots go one at a time, more of them at large n, all where few
+  // would be left for blocks, and kFew after a block of fewer than kShort while
+  // the pass is short (4e8 bytes).
+  constexpr int kFew = 16, kShort = 10;
+  const int64_t first = n >= 32768 ? 112 : 64;
+  int64_t pending = k <= first + 2 * kFew ? k : first;   // pivots to take one at a time next
+  bool running = false;         // a block whose pivot count the host has not read
+  bool filled = false;          // the pool holds columns
   for (;;) {
+    if (pending > 0) {
+      if (running) {
+        look();
+        m += h.s;
+        if (m >= k) break;
+      }
+      singles(pending);
+      look();
+      m += h.ones;
+      if (h.stop || m >= k) break;
+      HIPCHK(hipMemsetAsync(&ps->ones, 0, sizeof(int), st));
+      HIPCHK(hipMemsetAsync(&ps->s, 0, sizeof(int), st));
+      pending = 0;
+      running = false;
+      panel();   // no columns: the block maxima of the diagonal
+    }
+    if (slots == 0) make_pool();
     k_piv_begin<<<1, 1024, 0, st>>>(pmax.as<double>(), np, thr, ps);
     k_piv_hist<<<scan, 256, 0, st>>>(d.as<double>(), n, thr, ps);
     k_piv_list<<<scan, 256, 0, st>>>(d.as<double>(), n, thr, slots, ps);
     k_piv_match<<<1, kPool, 0, st>>>(ps, slots);
     LAUNCHCHK();
-    struct { int s, stop, count, fresh; } h;
-    HIPCHK(hipMemcpyAsync(&h, &ps->s, sizeof(h), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
-    const int64_t m0 = m;
-    m += h.s;
-    if (h.stop || m >= k || (ran && h.s == 0)) break;   // (no pivot: only where a value is NaN)
-    ran = true;
-    if (h.s > 0) {
-      const int64_t ldg = (h.s + 1) / 2 * 2;
-      k_piv_rows<int><<<cdiv(slots * ldg, 256), 256, 0, st>>>(L.as<double>(), ld, m0, ps->row, slots, h.s, ldg,
+    look();
+    if (running) {
+      m += h.s;
+      if (h.s < kShort && (double)n * m * 8.0 < 4e8) pending = kFew;
+    }
+    if (h.stop || m >= k || (running && h.s == 0)) break;   // (no pivot: only where a value is NaN)
+    if (filled && m > m_pool) {
+      const int64_t w = m - m_pool, ldg = (w + 1) / 2 * 2;
+      k_piv_rows<int><<<cdiv(slots * ldg, 256), 256, 0, st>>>(L.as<double>(), ld, m_pool, ps->row, slots, w, ldg,
                                                               G.as<double>());
       LAUNCHCHK();
-      subtract(pool.as<double>(), slots, m0, h.s);
+      subtract(pool.as<double>(), slots, m_pool, w);
     }
+    m_pool = m;
+    filled = true;
     if (h.fresh > 0) {
       kernel_columns(s, ps->new_row, h.fresh, stage.as<double>(), ld, 0.0, st);
       if (m > 0) {
@@ -583,6 +824,7 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
                                      slots, ps, piv.as<int64_t>());
     LAUNCHCHK();
     panel();
+    running = true;
   }
   if (m > 0) HIPCHK(hipMemcpyAsync(idx_out, piv.get(), m * 8, hipMemcpyDeviceToDevice, st));
   HIPCHK(hipStreamSynchronize(st));
