@@ -7,15 +7,13 @@
 //
 // Parameter layout (floats): W1 (H x D row-major), b1 (H), W2 (H x H), b2 (H),
 // w3 (H), b3 (1); after the parameters: input mean (D) and inverse std (D).
+#include <type_traits>
+
 #include "gemm.hpp"
 
 namespace ffk {
 
 __device__ inline float gelu_f(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
-__device__ inline float gelu_grad_f(float x) {
-  return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * 0.39894228040143268f * expf(-0.5f * x * x);
-}
-
 struct Offs {
   int64_t W1, b1, W2, b2, w3, b3, mean, istd, end;
 };
@@ -62,45 +60,6 @@ struct EpiBiasGelu {
   }
 };
 
-// C = acc (row-major, ldc), optionally times gelu'(Zg) elementwise.
-struct EpiStoreF {
-  float* C;
-  int64_t ldc;
-  const float* Zg;   // optional
-  int M, N;
-  template <typename T, int TM, int TN, class Acc>
-  __device__ void run(const Acc (&acc)[TM][TN], const FragCoord& f, char*) const {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int r = f.row(i, v), c = f.col(j);
-          if (r < M && c < N) {
-            float x = (float)acc[i][j][v];
-            if (Zg) x *= gelu_grad_f(Zg[(int64_t)r * ldc + c]);
-            C[(int64_t)r * ldc + c] = x;
-          }
-        }
-  }
-};
-
-template <bool AKC, bool BKC, class Epi>
-static void gemm_f32(int M, int N, int K, const float* A, int64_t sa0, int64_t sa1, const float* B, int64_t sb0,
-                     int64_t sb1, const Epi& e, hipStream_t st) {
-  ScalarArgs<float> g{};
-  g.M = M;
-  g.N = N;
-  g.nseg = 1;
-  g.seg[0] = SegS<float>{A, sa0, sa1, B, sb0, sb1, K};
-  if (N <= 64)
-    gemm_scalar_kernel<float, 128, 64, 16, AKC, BKC, Epi><<<dim3(cdiv(N, 64), cdiv(M, 128)), 256, 0, st>>>(g, e);
-  else
-    gemm_scalar_kernel<float, 128, 128, 16, AKC, BKC, Epi><<<dim3(cdiv(N, 128), cdiv(M, 128)), 256, 0, st>>>(g, e);
-  LAUNCHCHK();
-}
-
 // ----------------------------------------------------------- small kernels ----
 // out[b] = H2[b] . w3 + b3 (one wave per row)
 __global__ __launch_bounds__(256) void k_rowdot(const float* H2, int64_t B, int H, const float* w3, const float* b3,
@@ -115,58 +74,279 @@ __global__ __launch_bounds__(256) void k_rowdot(const float* H2, int64_t B, int 
   if (lane == 0) out[b] = a + b3[0];
 }
 
-// dout = 2 (out - y) / B and loss partials (single block, deterministic)
-__global__ __launch_bounds__(256) void k_loss(const float* out, const float* y, int64_t B, float* dout, float* loss) {
-  __shared__ double sh[256];
-  double a = 0.0;
-  for (int64_t b = threadIdx.x; b < B; b += 256) {
-    const float d = out[b] - y[b];
-    dout[b] = 2.0f * d / (float)B;
-    a += (double)d * d;
+// ------------------------------------------- FP32 forward and backward ----
+// The layers are small (256 x 256 x 256 in training), so what counts is
+// launches, workgroups and latency: a T x T tile (16 or 32) per workgroup, its
+// four waves split K, fragments go from global memory (L2) straight to
+// registers, four 16-wide steps of K in flight, and everything elementwise or
+// reduced rides in the epilogues.  A gradient takes four kernels:
+//   1. H1 = gelu(X W1^T + b1), G1 = gelu'
+//   2. H2 = gelu(H1 W2^T + b2), G2 = w3 gelu', and the partials of out = H2 w3 + b3
+//   3. with dout = 2 (out - y) / B, a scale of the rows:  dZ1 = dout (G2 W2) G1,
+//      g_W2 = (dout G2)^T H1, g_b2, g_w3, g_b3 and the loss
+//   4. g_W1 = dZ1^T X, g_b1
+// At D = 210, H = B = 256 a gradient and Adam step takes 25 us; on 128 x 128
+// tiles (four workgroups to a layer) and twelve kernels it took 404.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // rows of odd length
+
+__device__ inline void gelu_both(float x, float& h, float& g) {
+  const float c = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
+  h = x * c;
+  g = c + x * 0.39894228040143268f * expf(-0.5f * x * x);
+}
+
+// The wave's part of sum_k A(m, k) B(n, k) for the T x T tile at (m0, n0),
+// summed over the waves in red[0].  KC: element (m, k) at A[m lda + k], else
+// at A[k lda + m].  kscale (not null): a factor of every k.  Lane l takes rows
+// l % 16 and k = 16 s + 4 (l / 16) + j in MFMA j of step s.
+template <int T, bool AKC, bool BKC>
+__device__ inline void mlp_tile(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
+                                int M, int N, int K, int m0, int n0, const float* kscale, float (*red)[T][T + 1]) {
+  constexpr int NB = T / 16, U = 4;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 15, kq = 4 * (lane >> 4);
+  const int steps = (K + 15) / 16;
+  const int s0 = steps * wave / 4, s1 = steps * (wave + 1) / 4;
+  f4 acc[NB][NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = f4{0, 0, 0, 0};
+  auto fetch = [&](auto kc, const float* P, int64_t ld, int row, int k) {
+    f4 v;
+    if constexpr (decltype(kc)::value) {
+      const float* src = P + row * ld + k;
+      if (k + 3 < K) {
+        v = *reinterpret_cast<const f4u*>(src);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = k + j < K ? src[j] : 0.f;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float x = P[(int64_t)min(k + j, K - 1) * ld + row];
+        v[j] = k + j < K ? x : 0.f;
+      }
+    }
+    return v;
+  };
+  for (int s = s0; s < s1; s += U) {
+    f4 a[U][NB], b[U][NB];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (s + u < s1) {
+        const int k = 16 * (s + u) + kq;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+          a[u][i] = fetch(std::integral_constant<bool, AKC>(), A, lda, min(m0 + 16 * i + r, M - 1), k);
+          b[u][i] = fetch(std::integral_constant<bool, BKC>(), B, ldb, min(n0 + 16 * i + r, N - 1), k);
+        }
+        if (kscale) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float f = kscale[min(k + j, K - 1)];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) a[u][i][j] *= f;
+          }
+        }
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (s + u < s1) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][q], b[u][j][q], acc[i][j], 0, 0, 0);
+      }
   }
-  sh[threadIdx.x] = a;
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[wave][16 * i + (lane >> 4) * 4 + v][16 * j + r] = acc[i][j][v];
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+}
+template <int T> __device__ inline float mlp_sum(const float (*red)[T][T + 1], int r, int c) {
+  return (red[0][r][c] + red[1][r][c]) + (red[2][r][c] + red[3][r][c]);
+}
+
+// Hout = gelu(Z), Z = X W^T + bias for B rows (K inputs, H outputs); with G,
+// G = gelu'(Z) (times w3 when given); with w3, outp[tile column][row] = the
+// tile's part of Hout . w3.  Hout may be null.
+template <int T>
+__global__ __launch_bounds__(256) void k_mlp_layer(const float* __restrict__ X, const float* __restrict__ W,
+                                                   const float* __restrict__ bias, int B, int K, int H,
+                                                   float* __restrict__ Hout, float* __restrict__ G,
+                                                   const float* __restrict__ w3, float* __restrict__ outp) {
+  __shared__ float red[4][T][T + 1];
+  const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
+  mlp_tile<T, true, true>(X, K, W, K, B, H, K, m0, n0, nullptr, red);
+  for (int e = threadIdx.x; e < T * T; e += 256) {   // T consecutive lanes share a row
+    const int r = m0 + e / T, c = n0 + e % T;
+    float h, g;
+    gelu_both(mlp_sum<T>(red, e / T, e % T) + bias[c], h, g);
+    const float w = w3 ? w3[c] : 1.f;
+    if (r < B) {
+      if (Hout) Hout[(int64_t)r * H + c] = h;
+      if (G) G[(int64_t)r * H + c] = w * g;
+    }
+    if (w3) {
+      float p = h * w;
+#pragma unroll
+      for (int o = T / 2; o > 0; o >>= 1) p += __shfl_xor(p, o);
+      if (e % T == 0 && r < B) outp[(int64_t)blockIdx.x * B + r] = p;
+    }
+  }
+}
+
+__device__ inline float mlp_out(const float* outp, int nt, int64_t B, const float* b3, int64_t b) {
+  float o = b3[0];
+  for (int t0 = 0; t0 < nt; t0 += 16) {   // sixteen loads in flight
+    float p[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) p[t] = outp[min(t0 + t, nt - 1) * B + b];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) o += t0 + t < nt ? p[t] : 0.f;
+  }
+  return o;
+}
+__device__ inline float mlp_dout(float out, float y, int64_t B) { return 2.0f * (out - y) / (float)B; }
+
+__global__ void k_mlp_out(const float* __restrict__ outp, int nt, int64_t B, const float* __restrict__ b3,
+                          float* __restrict__ out) {
+  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (b < B) out[b] = mlp_out(outp, nt, B, b3, b);
+}
+__global__ void k_mlp_dout(const float* __restrict__ outp, int nt, int64_t B, const float* __restrict__ b3,
+                           const float* __restrict__ y, float* __restrict__ dout) {
+  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (b < B) dout[b] = mlp_dout(mlp_out(outp, nt, B, b3, b), y[b], B);
+}
+
+// sums of 16 columns over the B rows of a (and of a2, when given), each row
+// times f[row] (f null: 1): 16 lanes a row, 16 rows at a time, fixed order
+__device__ inline void mlp_colsums(const float* a, const float* a2, int B, int H, int c0, const float* f, float* s1,
+                                   float* s2, float (*sh)[16][17]) {
+  const int c = threadIdx.x & 15, rg = threadIdx.x >> 4;
+  float x = 0.f, x2 = 0.f;
+#pragma unroll 8
+  for (int b = rg; b < B; b += 16) {
+    const float w = f ? f[b] : 1.f;
+    x += w * a[(int64_t)b * H + c0 + c];
+    if (a2) x2 += w * a2[(int64_t)b * H + c0 + c];
+  }
+  sh[0][rg][c] = x;
+  sh[1][rg][c] = x2;
+  __syncthreads();
+  if (threadIdx.x < 32) {
+    const int which = threadIdx.x >> 4;
+    float s = 0.f;
+    for (int q = 0; q < 16; ++q) s += sh[which][q][c];
+    if (which == 0) s1[c0 + c] = s;
+    else if (s2) s2[c0 + c] = s;
+  }
+}
+
+constexpr int kDoutLds = 1024;   // batches up to this form dout in the LDS of every workgroup that needs it
+
+// Step 3 above.  Workgroups: the tiles of dZ1, then those of g_W2, then H / 16
+// for g_b2 and g_w3, then one for the loss and g_b3.  dout: precomputed for
+// batches beyond kDoutLds, else null.
+template <int T>
+__global__ __launch_bounds__(256) void k_mlp_back2(const float* __restrict__ G1, const float* __restrict__ H1,
+                                                   const float* __restrict__ G2, const float* __restrict__ H2,
+                                                   const float* __restrict__ W2, const float* __restrict__ outp, int nt,
+                                                   const float* __restrict__ b3, const float* __restrict__ y,
+                                                   const float* __restrict__ dout, int B, int H,
+                                                   float* __restrict__ dZ1, float* __restrict__ gW2,
+                                                   float* __restrict__ gb2, float* __restrict__ gw3,
+                                                   float* __restrict__ gb3, float* __restrict__ loss) {
+  __shared__ float red[4][T][T + 1];
+  __shared__ float sd[kDoutLds];
+  __shared__ float sh[2][16][17];
+  const int nh = H / T, ntz = nh * ((B + T - 1) / T), ntw = nh * nh;
+  int w = blockIdx.x;
+  if (w < ntz) {
+    const int m0 = w / nh * T, n0 = w % nh * T;
+    if (threadIdx.x < T) {
+      const int b = min(m0 + (int)threadIdx.x, B - 1);
+      sd[threadIdx.x] = dout ? dout[b] : mlp_dout(mlp_out(outp, nt, B, b3, b), y[b], B);
+    }
+    mlp_tile<T, true, false>(G2, H, W2, H, B, H, H, m0, n0, nullptr, red);
+    for (int e = threadIdx.x; e < T * T; e += 256) {
+      const int r = m0 + e / T, c = n0 + e % T;
+      if (r < B) {
+        const int64_t o = (int64_t)r * H + c;
+        dZ1[o] = sd[e / T] * mlp_sum<T>(red, e / T, e % T) * G1[o];
+      }
+    }
+    return;
+  }
+  w -= ntz;
+  const float* f = dout;
+  if (!f) {
+    for (int b = threadIdx.x; b < B; b += 256) sd[b] = mlp_dout(mlp_out(outp, nt, B, b3, b), y[b], B);
+    f = sd;
     __syncthreads();
   }
-  if (threadIdx.x == 0) loss[0] = (float)(sh[0] / (double)B);
-}
-
-// colsum[h] = sum_b A[b][h] * (w ? w[b] : 1)  (thread per column, fixed order)
-__global__ void k_colsum_w(const float* A, int64_t B, int H, const float* w, float* colsum) {
-  const int h = blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= H) return;
-  float a0 = 0.f, a1 = 0.f;
-  int64_t b = 0;
-  for (; b + 2 <= B; b += 2) {
-    a0 += A[b * H + h] * (w ? w[b] : 1.f);
-    a1 += A[(b + 1) * H + h] * (w ? w[b + 1] : 1.f);
+  if (w < ntw) {
+    const int m0 = w / nh * T, n0 = w % nh * T;
+    mlp_tile<T, false, false>(G2, H, H1, H, H, H, B, m0, n0, f, red);
+    for (int e = threadIdx.x; e < T * T; e += 256)
+      gW2[(int64_t)(m0 + e / T) * H + n0 + e % T] = mlp_sum<T>(red, e / T, e % T);
+    return;
   }
-  if (b < B) a0 += A[b * H + h] * (w ? w[b] : 1.f);
-  colsum[h] = a0 + a1;
-}
-
-// dZ2[b][h] = dout[b] * w3[h] * gelu'(Z2[b][h])
-__global__ void k_dz2(const float* dout, const float* w3, const float* Z2, int64_t B, int H, float* dZ2) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= B * H) return;
-  const int64_t b = e / H;
-  const int h = (int)(e % H);
-  dZ2[e] = dout[b] * w3[h] * gelu_grad_f(Z2[e]);
-}
-
-__global__ void k_sum1(const float* a, int64_t n, float* out) {
-  __shared__ double sh[256];
-  double s = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += 256) s += a[i];
-  sh[threadIdx.x] = s;
+  w -= ntw;
+  if (w < H / 16) {
+    mlp_colsums(G2, H2, B, H, 16 * w, f, gb2, gw3, sh);
+    return;
+  }
+  __shared__ double sl[256], sb[256];
+  double l = 0.0, g = 0.0;
+  for (int b = threadIdx.x; b < B; b += 256) {
+    const float d = mlp_out(outp, nt, B, b3, b) - y[b];
+    l += (double)d * d;
+    g += f[b];
+  }
+  sl[threadIdx.x] = l;
+  sb[threadIdx.x] = g;
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+    if ((int)threadIdx.x < o) {
+      sl[threadIdx.x] += sl[threadIdx.x + o];
+      sb[threadIdx.x] += sb[threadIdx.x + o];
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = (float)sh[0];
+  if (threadIdx.x == 0) {
+    loss[0] = (float)(sl[0] / (double)B);
+    gb3[0] = (float)sb[0];
+  }
+}
+
+// Step 4: the tiles of g_W1 = dZ1^T X, then H / 16 workgroups for g_b1.
+template <int T>
+__global__ __launch_bounds__(256) void k_mlp_back1(const float* __restrict__ dZ1, const float* __restrict__ X, int B,
+                                                   int D, int H, float* __restrict__ gW1, float* __restrict__ gb1) {
+  __shared__ float red[4][T][T + 1];
+  __shared__ float sh[2][16][17];
+  const int nd = (D + T - 1) / T, nt = nd * (H / T);
+  const int w = blockIdx.x;
+  if (w < nt) {
+    const int m0 = w / nd * T, n0 = w % nd * T;
+    mlp_tile<T, false, false>(dZ1, H, X, D, H, D, B, m0, n0, nullptr, red);
+    for (int e = threadIdx.x; e < T * T; e += 256) {
+      const int c = n0 + e % T;
+      if (c < D) gW1[(int64_t)(m0 + e / T) * D + c] = mlp_sum<T>(red, e / T, e % T);
+    }
+    return;
+  }
+  mlp_colsums(dZ1, nullptr, B, H, 16 * (w - nt), nullptr, gb1, nullptr, sh);
 }
 
 __global__ void k_adam(float* theta, const float* g, float* m, float* v, int64_t n, float lr, float b1, float b2,
@@ -233,7 +413,12 @@ ffk_mlp* mlp_create(int32_t D, int32_t H, uint64_t seed) {
   return m.release();
 }
 
-// Activations of a batch: Z1, H1, Z2, H2 (B x H each), out, dout (B), dZ2, dZ1 (B x H)
+// Tile edge of the FP32 kernels: 32 where that still makes two workgroups a
+// CU, else 16.
+static int mlp_edge(int64_t M, int64_t N) { return (int64_t)cdiv(M, 32) * cdiv(N, 32) >= 512 ? 32 : 16; }
+
+// Activations of a batch: H1, G1, H2, G2, dZ1 (B x H each), the partials of
+// out (at most H / 16 x B) and dout (B)
 static float* act(const ffk_mlp* net, int64_t B) {
   const int64_t need = (6 * B * net->H + 2 * B) * 4;
   ffk_mlp* m = const_cast<ffk_mlp*>(net);
@@ -241,14 +426,12 @@ static float* act(const ffk_mlp* net, int64_t B) {
   return m->work.as<float>();
 }
 
-static void forward_f32(const ffk_mlp* net, const float* X, int64_t B, float* out, float* Z1, float* H1, float* Z2,
-                        float* H2, hipStream_t st) {
-  const int D = net->D, H = net->H;
-  const Offs o = offs(D, H);
-  const float* th = net->theta.as<float>();
-  gemm_f32<true, true>((int)B, H, D, X, D, 1, th + o.W1, D, 1, EpiBiasGelu{th + o.b1, Z1, H1, nullptr, H, 0, (int)B, H}, st);
-  gemm_f32<true, true>((int)B, H, H, H1, H, 1, th + o.W2, H, 1, EpiBiasGelu{th + o.b2, Z2, H2, nullptr, H, 0, (int)B, H}, st);
-  k_rowdot<<<cdiv(B, 4), 256, 0, st>>>(H2, B, H, th + o.w3, th + o.b3, out);
+static void mlp_layer(const float* X, const float* W, const float* bias, int64_t B, int K, int H, float* Hout, float* G,
+                      const float* w3, float* outp, hipStream_t st) {
+  if (mlp_edge(B, H) == 32)
+    k_mlp_layer<32><<<dim3(H / 32, cdiv(B, 32)), 256, 0, st>>>(X, W, bias, (int)B, K, H, Hout, G, w3, outp);
+  else
+    k_mlp_layer<16><<<dim3(H / 16, cdiv(B, 16)), 256, 0, st>>>(X, W, bias, (int)B, K, H, Hout, G, w3, outp);
   LAUNCHCHK();
 }
 
@@ -297,9 +480,15 @@ static void forward_bf16(const ffk_mlp* net, const bf16_t* Xb, int64_t B, int64_
 
 void mlp_forward(const ffk_mlp* net, const float* X, int64_t B, float* out, int prec, hipStream_t st) {
   if (prec == FFK_FP32) {
-    float* w = act(net, B);
-    const int64_t bh = B * net->H;
-    forward_f32(net, X, B, out, w, w + bh, w + 2 * bh, w + 3 * bh, st);
+    const int D = net->D, H = net->H;
+    const Offs o = offs(D, H);
+    const float* th = net->theta.as<float>();
+    float* H1 = act(net, B);
+    float* outp = H1 + B * H;
+    mlp_layer(X, th + o.W1, th + o.b1, B, D, H, H1, nullptr, nullptr, nullptr, st);
+    mlp_layer(H1, th + o.W2, th + o.b2, B, H, H, nullptr, nullptr, th + o.w3, outp, st);
+    k_mlp_out<<<cdiv(B, 256), 256, 0, st>>>(outp, H / mlp_edge(B, H), B, th + o.b3, out);
+    LAUNCHCHK();
     return;
   }
   const int64_t Dk = rup(net->D, 64), Br = rup(B, 128);
@@ -313,31 +502,31 @@ void mlp_grad(ffk_mlp* net, const float* X, const float* y, int64_t B, float* lo
   const int D = net->D, H = net->H;
   const Offs o = offs(D, H);
   const float* th = net->theta.as<float>();
-  float* w = act(net, B);
   const int64_t bh = B * H;
-  float *Z1 = w, *H1 = w + bh, *Z2 = w + 2 * bh, *H2 = w + 3 * bh, *dZ2 = w + 4 * bh, *dZ1 = w + 5 * bh;
-  float* out = w + 6 * bh;
-  float* dout = out + B;
-  forward_f32(net, X, B, out, Z1, H1, Z2, H2, st);
-  k_loss<<<1, 256, 0, st>>>(out, y, B, dout, loss);
-  LAUNCHCHK();
-  // output layer
-  k_colsum_w<<<cdiv(H, 256), 256, 0, st>>>(H2, B, H, dout, grad + o.w3);
-  LAUNCHCHK();
-  k_sum1<<<1, 256, 0, st>>>(dout, B, grad + o.b3);
-  LAUNCHCHK();
-  // second hidden layer
-  k_dz2<<<cdiv(bh, 256), 256, 0, st>>>(dout, th + o.w3, Z2, B, H, dZ2);
-  LAUNCHCHK();
-  // g_W2[i][j] = sum_b dZ2[b][i] H1[b][j]
-  gemm_f32<false, false>(H, H, (int)B, dZ2, 1, H, H1, 1, H, EpiStoreF{grad + o.W2, H, nullptr, H, H}, st);
-  k_colsum_w<<<cdiv(H, 256), 256, 0, st>>>(dZ2, B, H, nullptr, grad + o.b2);
-  LAUNCHCHK();
-  // dZ1 = (dZ2 W2) o gelu'(Z1)
-  gemm_f32<true, false>((int)B, H, H, dZ2, H, 1, th + o.W2, 1, H, EpiStoreF{dZ1, H, Z1, (int)B, H}, st);
-  // g_W1[i][d] = sum_b dZ1[b][i] X[b][d]
-  gemm_f32<false, false>(H, D, (int)B, dZ1, 1, H, X, 1, D, EpiStoreF{grad + o.W1, D, nullptr, H, D}, st);
-  k_colsum_w<<<cdiv(H, 256), 256, 0, st>>>(dZ1, B, H, nullptr, grad + o.b1);
+  float *H1 = act(net, B), *G1 = H1 + bh, *H2 = H1 + 2 * bh, *G2 = H1 + 3 * bh, *dZ1 = H1 + 4 * bh;
+  float *outp = H1 + 5 * bh, *dout = H1 + 6 * bh;
+  mlp_layer(X, th + o.W1, th + o.b1, B, D, H, H1, G1, nullptr, nullptr, st);
+  mlp_layer(H1, th + o.W2, th + o.b2, B, H, H, H2, G2, th + o.w3, outp, st);
+  const int nt = H / mlp_edge(B, H);
+  if (B > kDoutLds) {
+    k_mlp_dout<<<cdiv(B, 256), 256, 0, st>>>(outp, nt, B, th + o.b3, y, dout);
+    LAUNCHCHK();
+  } else {
+    dout = nullptr;
+  }
+  auto back = [&](auto edge) {
+    constexpr int T = decltype(edge)::value;
+    const int grid = H / T * cdiv(B, T) + H / T * (H / T) + H / 16 + 1;
+    k_mlp_back2<T><<<grid, 256, 0, st>>>(G1, H1, G2, H2, th + o.W2, outp, nt, th + o.b3, y, dout, (int)B, H, dZ1,
+                                         grad + o.W2, grad + o.b2, grad + o.w3, grad + o.b3, loss);
+    LAUNCHCHK();
+  };
+  if (mlp_edge(B, H) == 32) back(std::integral_constant<int, 32>());
+  else back(std::integral_constant<int, 16>());
+  if (mlp_edge(H, D) == 32)
+    k_mlp_back1<32><<<cdiv(D, 32) * (H / 32) + H / 16, 256, 0, st>>>(dZ1, X, (int)B, D, H, grad + o.W1, grad + o.b1);
+  else
+    k_mlp_back1<16><<<cdiv(D, 16) * (H / 16) + H / 16, 256, 0, st>>>(dZ1, X, (int)B, D, H, grad + o.W1, grad + o.b1);
   LAUNCHCHK();
 }
 
