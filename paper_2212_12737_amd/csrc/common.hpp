@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -180,16 +181,6 @@ struct MvmWork {
 
 }  // namespace ffk
 
-namespace ffk {
-// Fixed coefficients and workspaces of a rectangular product K(tgt, src)
-// whose geometries do not change (a permuted copy of a symmetrized system,
-// as the source, against the system itself); valid while tgt is the target.
-struct RectCache {
-  const ffk_system* tgt = nullptr;
-  DBuf Xt, sqt, dA, B, Wn, U, pd, sv, cpart, wpart, G, part;
-};
-}  // namespace ffk
-
 struct ffk_system {
   ffk_ctx* ctx = nullptr;
   int64_t N = 0;
@@ -206,7 +197,8 @@ struct ffk_system {
   ffk::DBuf xmean;          // D double
   ffk::DBuf Xc;             // N x D double (centred)
   ffk::DBuf sqn;            // N double (|x_c|^2)
-  ffk::DBuf Xp64, XpT64;    // X_c as FP64, padded: Nr x Dk and transposed Dr x Nr
+  mutable ffk::DBuf Xp64;   // X_c as FP64, padded: Nr x Dk
+  ffk::DBuf XpT64;          // and transposed: Dr x Nr
   ffk::DBuf Xp32, XpT32;    // the same in FP32
   ffk::DBuf Xch, Xcl;       // N x D bf16 hi/lo
   ffk::DBuf XcTh, XcTl;     // D x N bf16 hi/lo
@@ -221,7 +213,6 @@ struct ffk_system {
   ffk::DBuf sym_perm, sym_pinv;
   ffk::DBuf sym_work;
   int sym_identity = 0;     // index of the identity in the group
-  ffk::RectCache rect;      // used when this system is a permuted copy
   // The symmetrized product as one rectangular product against the stacked
   // permuted copies: sources P_1 R, ..., P_S R (N S geometries, descriptors
   // centred with this system's mean), N x N S coefficient sets, the
@@ -230,6 +221,10 @@ struct ffk_system {
   ffk::CoeffSet stack_coef[4];
   ffk::MvmWork stack_work;
   ffk::DBuf stack_v;
+  // Prediction with this system as the model: workspace (U, N D 8 bytes,
+  // and up to 256 MB or so of parts of G) and the stacked vector, one call at a time.
+  mutable std::mutex predict_lock;
+  mutable ffk::DBuf predict_work, predict_v;
 };
 
 struct ffk_precond {
@@ -279,10 +274,6 @@ void sym_diag(const ffk_system* s, double* d, hipStream_t st);
 // columns.hip -- columns of K(s, src) in the numbering of src (targets from s)
 void kernel_columns_src(const ffk_system* s, const ffk_system* src, const int64_t* cols, int64_t k, double* out,
                         int64_t ldo, double shift, bool accumulate, hipStream_t st);
-// mvm.hip -- y (+)= K(tgt, src) alpha on the FP64 engine; with shift_v, the
-// first (non-accumulating) pass also adds shift * shift_v
-void rect_mvm(const ffk_system* src, const ffk_system* tgt, const double* alpha, double* y, bool accumulate,
-              const double* shift_v, double shift, RectCache* cache, hipStream_t st);
 void permute_atoms(const double* a, const int32_t* p, int64_t N, int M, double* out, hipStream_t st);
 void ensure_coeffs(ffk_system* sys, int prec, hipStream_t st);
 // Coefficient sets of K(t, src) (rows t->N, columns src->N, padded); both
@@ -293,6 +284,16 @@ void ensure_coeffs_pair(const ffk_system* t, const ffk_system* src, CoeffSet* se
 void ensure_lowp_descriptor(ffk_system* sys, int prec, hipStream_t st);
 // Re-centre a system's descriptor with another mean (X_c = X - mean, |x_c|^2).
 void center_with(ffk_system* sys, const double* mean, hipStream_t st);
+// The same for N rows of any matrix X (N x D).
+void center_rows(const double* X, const double* mean, int64_t N, int64_t D, double* Xc, double* sqn, hipStream_t st);
+// mvm.hip -- parts of the FP64 product: U = J v (N x D), pd_j = x_c,j . u_j and
+// the column sums of U (cpart: jv_blocks(N) x D workspace); y = J^T G for N
+// rows; the stacked permuted vector of a symmetrized system.
+int jv_blocks(int64_t N);
+void jv_fp64(const ffk_system* s, const double* v, double* U, double* pd, double* cpart, double* sum, hipStream_t st);
+void jtg_rows(const double* R, const double* G, const double* X, int64_t N, int M, int64_t D, double* y,
+              hipStream_t st);
+void permute_stack(const ffk_system* s, const double* v, double* out, hipStream_t st);
 
 // fused.hip -- the product's two dense steps in one kernel (BF16, D <= 128)
 // Operands of the fused product (layouts as in the two-GEMM form).
@@ -335,13 +336,13 @@ int kernel_mvm_vy(ffk_system* sys, const double* v, double* y, double shift, int
                   double* vy_part);
 void kernel_mvm_phases(ffk_system* sys, const double* v, double* y, double shift, int prec, int iters,
                        double* ms, hipStream_t st);
-void kernel_predict(const ffk_system* train, const ffk_system* test, const double* alpha,
-                    double* F, hipStream_t st);
 // The product with its workspace carved from the device memory [base, base +
 // cap) instead of the system's own: allocates nothing.  The system's
 // coefficients and descriptor copies for prec must already exist.
 void kernel_mvm_scratch(ffk_system* sys, const double* v, double* y, double shift, int prec, hipStream_t st,
                         void* base, size_t cap);
+// predict.hip
+void kernel_predict(const ffk_system* train, const ffk_system* test, const double* alpha, double* F, hipStream_t st);
 // noalloc.hip -- the library's fixed scratch array on each device
 constexpr size_t kScratchBytes = (size_t)128 << 20;
 void scratch_init(int device);        // once per device, with that device current

@@ -9,18 +9,27 @@
 //   B_ij  = b(r) = -25/(3 sigma^4) e^-z,
 // the Matern-5/2 Hessian coefficients H = a I + b d d^T of the force kernel.
 // Reduced-precision copies are derived from the FP64 arrays on first use.
-#include "gemm.hpp"
+#include <algorithm>
+
+#include "smalldot.hpp"
 
 namespace ffk {
 
-__global__ void k_descriptor(const double* __restrict__ R, const int* __restrict__ pairs, int64_t N,
-                             int M, int64_t D, double* __restrict__ X, double* __restrict__ PT,
+// Descriptor, pair table and the copies the system keeps: thread e takes
+// element e of X and of R.
+__global__ void k_descriptor(const double* __restrict__ R, int64_t N, int M, int64_t D, double* __restrict__ X,
+                             double* __restrict__ PT, int* __restrict__ pairs, double* __restrict__ Rcopy,
                              int* __restrict__ bad) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e < N * M * 3) Rcopy[e] = R[e];
   if (e >= N * D) return;
   const int64_t g = e / D, d = e % D;
-  const int pq = pairs[d];
-  const int p = pq >> 16, q = pq & 0xFFFF;
+  // row p of the strict lower triangle starts at p (p - 1) / 2
+  int p = (int)((1.0 + sqrt(1.0 + 8.0 * (double)d)) * 0.5);
+  while ((int64_t)p * (p - 1) / 2 > d) --p;
+  while ((int64_t)p * (p + 1) / 2 <= d) ++p;
+  const int q = (int)(d - (int64_t)p * (p - 1) / 2);
+  if (g == 0) pairs[d] = p << 16 | q;
   const double* Rg = R + g * 3 * M;
   const double dx = Rg[3 * p] - Rg[3 * q], dy = Rg[3 * p + 1] - Rg[3 * q + 1],
                dz = Rg[3 * p + 2] - Rg[3 * q + 2];
@@ -34,17 +43,27 @@ __global__ void k_descriptor(const double* __restrict__ R, const int* __restrict
   w[1] = make_double2(dz * x3, x);
 }
 
-// Column means of an N x D matrix: block = 64 columns x 4 row groups.
-__global__ void k_colmean(const double* __restrict__ X, int64_t N, int64_t D, double* __restrict__ mean) {
-  __shared__ double part[4][64];
-  const int c = threadIdx.x & 63, rg = threadIdx.x >> 6;
-  const int64_t col = (int64_t)blockIdx.x * 64 + c;
+// scale times the sums of the columns of X (N x D) over rows [rows y, rows y +
+// rows), in out[y]: 16 columns a block, 16 rows at a time, eight loads in
+// flight.  (64 columns a block with the whole column to four lanes ran one
+// block per 64 columns whatever N: 127 us at N = 2000, 2.0 ms at N = 20000.)
+__global__ __launch_bounds__(256) void k_colmean(const double* __restrict__ X, int64_t N, int64_t D, int64_t rows,
+                                                 double scale, double* __restrict__ out) {
+  __shared__ double part[16][17];
+  const int c = threadIdx.x & 15, rg = threadIdx.x >> 4;
+  const int64_t col = min((int64_t)blockIdx.x * 16 + c, D - 1);
+  const int64_t r1 = min(((int64_t)blockIdx.y + 1) * rows, N);
   double s = 0.0;
-  if (col < D)
-    for (int64_t r = rg; r < N; r += 4) s += X[r * D + col];
+#pragma unroll 8
+  for (int64_t r = (int64_t)blockIdx.y * rows + rg; r < r1; r += 16) s += X[r * D + col];
   part[rg][c] = s;
   __syncthreads();
-  if (rg == 0 && col < D) mean[col] = ((part[0][c] + part[1][c]) + (part[2][c] + part[3][c])) / (double)N;
+  if (rg == 0 && (int64_t)blockIdx.x * 16 + c < D) {
+    double t = 0.0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) t += part[q][c];
+    out[blockIdx.y * D + col] = t * scale;
+  }
 }
 
 // X_c = X - mean, and |x_c,i|^2 (one block per geometry).
@@ -70,17 +89,8 @@ __global__ void k_center(const double* __restrict__ X, const double* __restrict_
 void descriptor_build(ffk_system* s, const double* R, hipStream_t st, bool coefficients) {
   const int64_t N = s->N, D = s->D;
   const int M = s->M;
-  // pair table
-  std::vector<int> pt(D);
-  {
-    int64_t d = 0;
-    for (int p = 1; p < M; ++p)
-      for (int q = 0; q < p; ++q) pt[d++] = (p << 16) | q;
-  }
   s->pairs.alloc(D * sizeof(int));
-  HIPCHK(hipMemcpyAsync(s->pairs.get(), pt.data(), D * sizeof(int), hipMemcpyHostToDevice, st));
   s->R.alloc(N * M * 3 * sizeof(double));
-  HIPCHK(hipMemcpyAsync(s->R.get(), R, N * M * 3 * sizeof(double), hipMemcpyDeviceToDevice, st));
   s->X.alloc(N * D * sizeof(double));
   s->PT.alloc(4 * N * D * sizeof(double));
   s->Xc.alloc(N * D * sizeof(double));
@@ -88,19 +98,27 @@ void descriptor_build(ffk_system* s, const double* R, hipStream_t st, bool coeff
   s->sqn.alloc(N * sizeof(double));
   DBuf bad(sizeof(int));
   HIPCHK(hipMemsetAsync(bad.get(), 0, sizeof(int), st));
-  k_descriptor<<<cdiv(N * D, 256), 256, 0, st>>>(s->R.as<double>(), s->pairs.as<int>(), N, M, D,
-                                                  s->X.as<double>(), s->PT.as<double>(), bad.as<int>());
+  k_descriptor<<<cdiv(N * std::max<int64_t>(D, 3 * M), 256), 256, 0, st>>>(
+      R, N, M, D, s->X.as<double>(), s->PT.as<double>(), s->pairs.as<int>(), s->R.as<double>(), bad.as<int>());
   LAUNCHCHK();
-  int hbad = 0;
-  HIPCHK(hipMemcpyAsync(&hbad, bad.get(), sizeof(int), hipMemcpyDeviceToHost, st));
-  HIPCHK(hipStreamSynchronize(st));
-  if (hbad) fail(FFK_ERR_NONFINITE, "descriptor_build: coincident atoms or non-finite coordinates");
-  k_colmean<<<cdiv(D, 64), 256, 0, st>>>(s->X.as<double>(), N, D, s->xmean.as<double>());
+  // column means: sums of 512 rows, then the sum of those
+  const int S = cdiv(N, 512);
+  DBuf part(S > 1 ? (size_t)S * D * 8 : 0);
+  k_colmean<<<dim3(cdiv(D, 16), S), 256, 0, st>>>(s->X.as<double>(), N, D, 512, S == 1 ? 1.0 / (double)N : 1.0,
+                                                  S == 1 ? s->xmean.as<double>() : part.as<double>());
   LAUNCHCHK();
+  if (S > 1) {
+    k_colmean<<<dim3(cdiv(D, 16), 1), 256, 0, st>>>(part.as<double>(), S, D, S, 1.0 / (double)N, s->xmean.as<double>());
+    LAUNCHCHK();
+  }
   k_center<<<N, 256, 0, st>>>(s->X.as<double>(), s->xmean.as<double>(), D, s->Xc.as<double>(),
                               s->sqn.as<double>());
   LAUNCHCHK();
   if (coefficients) ensure_coeffs(s, FFK_FP64, st);
+  int hbad = 0;   // looked at once, at the end: nothing above depends on it
+  HIPCHK(hipMemcpyAsync(&hbad, bad.get(), sizeof(int), hipMemcpyDeviceToHost, st));
+  HIPCHK(hipStreamSynchronize(st));
+  if (hbad) fail(FFK_ERR_NONFINITE, "descriptor_build: coincident atoms or non-finite coordinates");
 }
 
 // ------------------------------------------------------------ conversions ----
@@ -199,22 +217,33 @@ void k_split_transpose_launch(const double* a, int64_t rows, int64_t cols, int64
 }
 
 template <typename T>
-static void padded_descriptor(const ffk_system* s, DBuf& P, DBuf& PT, hipStream_t st) {
-  const int64_t N = s->N, D = s->D;
-  const int64_t Nr = pad_rows(N), Dk = rup(D, 64), Dr = pad_rows(D);
+static void padded_rows(const ffk_system* s, DBuf& P, hipStream_t st) {
+  if (P) return;
+  const int64_t Nr = pad_rows(s->N), Dk = rup(s->D, 64);
   P.alloc(Nr * Dk * sizeof(T));
-  k_pad_copy<T><<<cdiv(Nr * Dk, 256), 256, 0, st>>>(s->Xc.as<double>(), N, D, D, Nr, Dk, P.as<T>());
+  k_pad_copy<T><<<cdiv(Nr * Dk, 256), 256, 0, st>>>(s->Xc.as<double>(), s->N, s->D, s->D, Nr, Dk, P.as<T>());
   LAUNCHCHK();
+}
+template <typename T>
+static void padded_columns(const ffk_system* s, DBuf& PT, hipStream_t st) {
+  if (PT) return;
+  const int64_t Nr = pad_rows(s->N), Dr = pad_rows(s->D);
   PT.alloc(Dr * Nr * sizeof(T));
   dim3 grid(cdiv(Nr, 64), cdiv(Dr, 64));
-  k_pad_transpose<T><<<grid, 256, 0, st>>>(s->Xc.as<double>(), N, D, D, Dr, Nr, PT.as<T>());
+  k_pad_transpose<T><<<grid, 256, 0, st>>>(s->Xc.as<double>(), s->N, s->D, s->D, Dr, Nr, PT.as<T>());
   LAUNCHCHK();
 }
 
 void ensure_lowp_descriptor(ffk_system* s, int prec, hipStream_t st) {
   const int64_t N = s->N, D = s->D;
-  if (prec == FFK_FP64 && !s->Xp64) padded_descriptor<double>(s, s->Xp64, s->XpT64, st);
-  if (prec == FFK_FP32 && !s->Xp32) padded_descriptor<float>(s, s->Xp32, s->XpT32, st);
+  if (prec == FFK_FP64) {
+    padded_rows<double>(s, s->Xp64, st);
+    padded_columns<double>(s, s->XpT64, st);
+  }
+  if (prec == FFK_FP32) {
+    padded_rows<float>(s, s->Xp32, st);
+    padded_columns<float>(s, s->XpT32, st);
+  }
   if ((prec == FFK_BF16 || prec == FFK_BF16X3) && !s->Xch) {
     const int64_t Nr = pad_rows(N), Dk = rup(D, 64), Dr = pad_rows(D);
     s->Xch.alloc(Nr * Dk * 2);
@@ -242,6 +271,10 @@ struct EpiCoeffPair {
   int Nt, Ns;
   int64_t ld, diag_off;
   double inv_len, a0, bcoef;   // sqrt(5)/sigma, 5/(3 sigma^2), 25/(3 sigma^4)
+  int mirror;                  // a tile below the diagonal is stored above it too
+  __device__ inline void pair(int r, int c, double gram, double& d, double& b) const {
+    matern_coeffs(c == r + diag_off ? 0.0 : sqr[r] + sqc[c] - 2.0 * gram, inv_len, a0, bcoef, d, b);
+  }
   template <typename T, int TM, int TN, class Acc>
   __device__ void run(const Acc (&acc)[TM][TN], const FragCoord& f, char*) const {
 #pragma unroll
@@ -252,16 +285,58 @@ struct EpiCoeffPair {
         for (int v = 0; v < 4; ++v) {
           const int r = f.row(i, v), c = f.col(j);
           if (r < Nt && c < Ns) {
-            double r2 = sqr[r] + sqc[c] - 2.0 * (double)acc[i][j][v];
-            r2 = (c == r + diag_off || r2 < 0.0) ? 0.0 : r2;
-            const double z = sqrt(r2) * inv_len;
-            const double em = expm1(-z);
-            dA[(int64_t)r * ld + c] = a0 * ((1.0 + z) * em + z);
-            B[(int64_t)r * ld + c] = -bcoef * (em + 1.0);
+            double d, b;
+            pair(r, c, (double)acc[i][j][v], d, b);
+            dA[(int64_t)r * ld + c] = d;
+            B[(int64_t)r * ld + c] = b;
+            if (mirror && f.n0 < f.m0) {
+              dA[(int64_t)c * ld + r] = d;
+              B[(int64_t)c * ld + r] = b;
+            }
           }
         }
   }
 };
+
+// The same for few pairs: a 16 x 16 tile a workgroup, its waves split K, rows
+// straight from L2; the padding (rows to gridDim.y 16, columns to gridDim.x 16)
+// is written as zeros.
+__global__ __launch_bounds__(256) void k_coeff_small(const double* __restrict__ Xt, const double* __restrict__ Xs,
+                                                     int D, EpiCoeffPair e) {
+  __shared__ double red[4][16][17];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r0 = blockIdx.y * 16, c0 = blockIdx.x * 16;
+  const int r = r0 + (threadIdx.x >> 4), c = c0 + (threadIdx.x & 15);
+  double d = 0.0, b = 0.0;
+  if (r0 < e.Nt && c0 < e.Ns) {
+    const int steps = (D + 7) / 8;
+    const double* a[1] = {Xt + (int64_t)min(r0 + (lane & 15), e.Nt - 1) * D};
+    d4 g[1] = {d4{0, 0, 0, 0}}, none[1];
+    rows_dot<1, false>(a, Xs + (int64_t)min(c0 + (lane & 15), e.Ns - 1) * D, nullptr, D, steps * wave / 4,
+                       steps * (wave + 1) / 4, g, none);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[wave][4 * v + (lane >> 4)][lane & 15] = g[0][v];
+    __syncthreads();
+    if (r < e.Nt && c < e.Ns) {
+      const int t = threadIdx.x >> 4, s = threadIdx.x & 15;
+      e.pair(r, c, (red[0][t][s] + red[1][t][s]) + (red[2][t][s] + red[3][t][s]), d, b);
+    }
+  }
+  e.dA[(int64_t)r * e.ld + c] = d;
+  e.B[(int64_t)r * e.ld + c] = b;
+}
+
+// Zeros right of column Ns and below row Nt of two Ntr x ld arrays.
+__global__ void k_zero_padding(double* __restrict__ a, double* __restrict__ b, int64_t Nt, int64_t Ns, int64_t Ntr,
+                               int64_t ld) {
+  const int64_t w = ld - Ns, right = Nt * w;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < right + (Ntr - Nt) * ld;
+       e += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t o = e < right ? e / w * ld + Ns + e % w : Nt * ld + (e - right);
+    a[o] = 0.0;
+    b[o] = 0.0;
+  }
+}
 
 void ensure_coeffs_pair(const ffk_system* t, const ffk_system* src, CoeffSet* sets, int prec, int64_t diag_off,
                         hipStream_t st) {
@@ -271,18 +346,31 @@ void ensure_coeffs_pair(const ffk_system* t, const ffk_system* src, CoeffSet* se
   if (!c64.ready) {
     c64.dA_hi.alloc(Ntr * Nsr * sizeof(double));
     c64.B.alloc(Ntr * Nsr * sizeof(double));
-    HIPCHK(hipMemsetAsync(c64.dA_hi.get(), 0, Ntr * Nsr * sizeof(double), st));
-    HIPCHK(hipMemsetAsync(c64.B.get(), 0, Ntr * Nsr * sizeof(double), st));
-    ScalarArgs<double> g{};
-    g.M = (int)Nt;
-    g.N = (int)Ns;
-    g.nseg = 1;
-    g.seg[0] = SegS<double>{t->Xc.as<double>(), t->D, 1, src->Xc.as<double>(), src->D, 1, (int)t->D};
+    const bool square = t == src && diag_off == 0;
     EpiCoeffPair e{t->sqn.as<double>(), src->sqn.as<double>(), c64.dA_hi.as<double>(), c64.B.as<double>(), (int)Nt,
-                   (int)Ns, Nsr, diag_off, sqrt(5.0) / t->sigma, t->a0, t->bcoef};
-    dim3 grid(cdiv(Ns, 128), cdiv(Nt, 128));
-    gemm_scalar_kernel<double, 128, 128, 16, true, true, EpiCoeffPair><<<grid, 256, 0, st>>>(g, e);
-    LAUNCHCHK();
+                   (int)Ns, Nsr, diag_off, sqrt(5.0) / t->sigma, t->a0, t->bcoef, square};
+    // Up to 1024^2 pairs the small tiles, which fill the GPU at once and need
+    // no padded operands; beyond, where they would read every row from L2 N /
+    // 16 times, the pipelined engine, on and below the diagonal if the matrix
+    // is symmetric.
+    if (Ntr * Nsr <= 1024 * 1024) {
+      k_coeff_small<<<dim3((unsigned)(Nsr / 16), (unsigned)(Ntr / 16)), 256, 0, st>>>(
+          t->Xc.as<double>(), src->Xc.as<double>(), (int)t->D, e);
+      LAUNCHCHK();
+    } else {
+      padded_rows<double>(t, t->Xp64, st);
+      padded_rows<double>(src, src->Xp64, st);
+      k_zero_padding<<<1024, 256, 0, st>>>(e.dA, e.B, Nt, Ns, Ntr, Nsr);
+      LAUNCHCHK();
+      const int64_t Dk = rup(t->D, 64);
+      DmaArgs g{};
+      g.nseg = 1;
+      g.lower_only = square;
+      g.seg[0] = SegD{t->Xp64.get(), nullptr, src->Xp64.get(), nullptr, Dk, Dk, (int)rup(t->D, 8), 0};
+      typedef RowTile<128, 128, 2, 4, 2> TL;
+      gemm_row_kernel<double, TL, EpiCoeffPair><<<dim3(cdiv(Ns, 128), cdiv(Nt, 128)), TL::NT, 0, st>>>(g, e);
+      LAUNCHCHK();
+    }
     c64.ready = true;
   }
   if (prec == FFK_FP64) return;

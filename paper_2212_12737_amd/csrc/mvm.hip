@@ -204,8 +204,7 @@ __device__ inline double block_sum_waves(double x) {
 // the result does not depend on timing.  (One lane per atom left most of the
 // block idle behind a serial loop over M - 1 partners.)
 __device__ inline void jtg_atoms(const double* sR, const double* sG, int64_t g, int M,
-                                 const double* v, double shift, double* y, bool accumulate = false,
-                                 double* vy_part = nullptr) {
+                                 const double* v, double shift, double* y, double* vy_part = nullptr) {
   int L = 1;
   while (L < 64 && 2 * L * M <= (int)blockDim.x) L *= 2;
   const int part = (int)threadIdx.x & (L - 1);
@@ -238,15 +237,9 @@ __device__ inline void jtg_atoms(const double* sR, const double* sG, int64_t g, 
         ay += shift * v[o + 1];
         az += shift * v[o + 2];
       }
-      if (accumulate) {
-        y[o] += ax;
-        y[o + 1] += ay;
-        y[o + 2] += az;
-      } else {
-        y[o] = ax;
-        y[o + 1] = ay;
-        y[o + 2] = az;
-      }
+      y[o] = ax;
+      y[o + 1] = ay;
+      y[o + 2] = az;
       if (vy_part) vy += (ax * v[o] + ay * v[o + 1]) + az * v[o + 2];
     }
   }
@@ -256,11 +249,11 @@ __device__ inline void jtg_atoms(const double* sR, const double* sG, int64_t g, 
   }
 }
 
-// y = J^T G + shift v, or y += J^T G with accumulate (then v is unused).
+// y = J^T G + shift v (v may be null).
 // X: the uncentred descriptor rows, which scale G as it is staged.
 __global__ void k_jtg(const double* __restrict__ R, const double* __restrict__ G, const double* __restrict__ X,
                       const double* __restrict__ v, double shift, int M, int64_t D,
-                      double* __restrict__ y, int accumulate = 0, double* __restrict__ vy_part = nullptr) {
+                      double* __restrict__ y, double* __restrict__ vy_part = nullptr) {
   extern __shared__ double sm[];
   double* sR = sm;
   double* sG = sm + 3 * M;
@@ -271,8 +264,7 @@ __global__ void k_jtg(const double* __restrict__ R, const double* __restrict__ G
     sG[i] = G[g * D + i] * (x * x * x);
   }
   __syncthreads();
-  jtg_atoms(sR, sG, g, M, accumulate ? nullptr : v, shift, y, accumulate != 0,
-            accumulate ? nullptr : vy_part);
+  jtg_atoms(sR, sG, g, M, v, shift, y, vy_part);
 }
 
 // Sum of the n partials p[0..n) by the calling wave: lane l adds l, l + 64,
@@ -360,7 +352,7 @@ __global__ void k_jtg_reduce(const PT* __restrict__ part, int splits, int64_t ro
     }
   }
   __syncthreads();
-  jtg_atoms(sR, sG, g, M, v, shift, y, false, vy_part);
+  jtg_atoms(sR, sG, g, M, v, shift, y, vy_part);
 }
 
 template <typename PT, int CC, typename... A>
@@ -585,55 +577,6 @@ struct EpiG {
   }
 };
 
-// Gram epilogue for a rectangular (target x source) pair -> dA, B (FP64).
-struct EpiCoeffRect {
-  const double *sqr, *sqc;
-  double *dA, *B;
-  int Nr, Nc;
-  double inv_len, a0, bcoef;
-  template <typename T, int TM, int TN, class Acc>
-  __device__ void run(const Acc (&acc)[TM][TN], const FragCoord& f, char*) const {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int r = f.row(i, v), c = f.col(j);
-          if (r < Nr && c < Nc) {
-            double r2 = sqr[r] + sqc[c] - 2.0 * (double)acc[i][j][v];
-            r2 = r2 < 0.0 ? 0.0 : r2;
-            const double z = sqrt(r2) * inv_len;
-            const double em = expm1(-z);
-            dA[(int64_t)r * Nc + c] = a0 * ((1.0 + z) * em + z);
-            B[(int64_t)r * Nc + c] = -bcoef * (em + 1.0);
-          }
-        }
-  }
-};
-
-// Split-K reduction for GEMM 2: G = sum_z part_z + a0 s_c + w_r Xt_r,c (one block per row).
-template <typename PT>
-__global__ __launch_bounds__(256) void k_g_reduce(const PT* __restrict__ part, int splits, int64_t rows, int64_t cols,
-                                                  const double* __restrict__ s, const double* __restrict__ Xt,
-                                                  const double* __restrict__ wpart, int ntn, double a0,
-                                                  double* __restrict__ G) {
-  __shared__ double wsh;
-  const int64_t r = blockIdx.x;
-  if (threadIdx.x < 64) {
-    const double w = wave_sum_parts(wpart + r * ntn, ntn);
-    if (threadIdx.x == 0) wsh = w;
-  }
-  __syncthreads();
-  const double w = wsh;
-  for (int64_t c = threadIdx.x; c < cols; c += blockDim.x) {
-    double acc = 0.0;
-#pragma unroll 4
-    for (int z = 0; z < splits; ++z) acc += (double)part[((int64_t)z * rows + r) * cols + c];
-    G[r * cols + c] = acc + a0 * s[c] + w * Xt[r * cols + c];
-  }
-}
-
 static inline void mark(hipEvent_t* ev, int i, hipStream_t st) {
   if (ev) HIPCHK(hipEventRecord(ev[i], st));
 }
@@ -651,53 +594,6 @@ struct MvmArgs {
   void* part;            // split-K partials
   size_t part_bytes;
 };
-
-template <typename T>
-static void mvm_gemms_scalar(const MvmArgs& a, const T* Xt, const T* Xs, const T* U, const T* dA, const T* Bc, T* Wn,
-                             hipStream_t st, hipEvent_t* ev) {
-  const int Nt = (int)a.Nt, Ns = (int)a.Ns;
-  const int64_t D = a.D;
-  const int ntn = cdiv(Ns, 128);
-  {
-    ScalarArgs<T> g{};
-    g.M = Nt;
-    g.N = Ns;
-    g.nseg = 1;
-    g.seg[0] = SegS<T>{Xt, D, 1, U, D, 1, (int)D};
-    EpiW<T, 128> e{Bc, Ns, a.pd, Wn, Ns, a.wpart, ntn, Nt, Ns};
-    clk_begin(CLK_GEMM1, st);
-    gemm_scalar_kernel<T, 128, 128, 16, true, true, EpiW<T, 128>><<<dim3(ntn, cdiv(Nt, 128)), 256, 0, st>>>(g, e);
-    LAUNCHCHK();
-    clk_end(CLK_GEMM1, st);
-  }
-  mark(ev, 3, st);
-  ScalarArgs<T> g{};
-  g.M = Nt;
-  g.N = (int)D;
-  g.nseg = 2;
-  g.seg[0] = SegS<T>{dA, Ns, 1, U, 1, D, Ns};
-  g.seg[1] = SegS<T>{Wn, Ns, 1, Xs, 1, D, Ns};
-  const int64_t tiles = (int64_t)cdiv(D, 128) * cdiv(Nt, 128);
-  int splits = pick_splits(tiles, 2 * (int64_t)cdiv(Ns, 16));
-  while (splits > 1 && (size_t)splits * Nt * D * sizeof(T) > a.part_bytes) splits >>= 1;
-  if (splits == 1) {
-    EpiG<128> e{a.s, a.Xt64, D, a.wpart, ntn, a.a0, a.G, D, Nt, (int)D};
-    clk_begin(CLK_GEMM2, st);
-    gemm_scalar_kernel<T, 128, 128, 16, true, false, EpiG<128>><<<dim3(cdiv(D, 128), cdiv(Nt, 128)), 256, 0, st>>>(g, e);
-    LAUNCHCHK();
-    clk_end(CLK_GEMM2, st);
-  } else {
-    EpiPart<T> e{static_cast<T*>(a.part), D, Nt, (int)D};
-    clk_begin(CLK_GEMM2, st);
-    gemm_scalar_kernel<T, 128, 128, 16, true, false, EpiPart<T>><<<dim3(cdiv(D, 128), cdiv(Nt, 128), splits), 256, 0, st>>>(g, e);
-    LAUNCHCHK();
-    clk_end(CLK_GEMM2, st);
-    clk_begin(CLK_GEMM2_REDUCE, st);
-    k_g_reduce<T><<<Nt, 256, 0, st>>>(static_cast<const T*>(a.part), splits, Nt, D, a.s, a.Xt64, a.wpart, ntn, a.a0, a.G);
-    LAUNCHCHK();
-    clk_end(CLK_GEMM2_REDUCE, st);
-  }
-}
 
 // Both GEMMs of the product on the pipelined MFMA engine, for element type T
 // (double, float or bf16; X3 = split BF16) and tile shapes TL1 (GEMM 1) and
@@ -1111,7 +1007,7 @@ static void kernel_mvm_core(ffk_system* t, ffk_system* src, CoeffSet* coef, cons
     launch_jtg_reduce(N, D, shj, st, static_cast<const float*>(b.part), -go.splits, N, b.s, t->Xc.as<double>(), xm,
                       b.wpart, go.ntn, t->a0, t->R.as<double>(), v, shift, M, D, y, vy_part);
   else if (go.splits == 1)
-    k_jtg<<<N, tb, shj, st>>>(t->R.as<double>(), b.G, t->X.as<double>(), v, shift, M, D, y, 0, vy_part);
+    k_jtg<<<N, tb, shj, st>>>(t->R.as<double>(), b.G, t->X.as<double>(), v, shift, M, D, y, vy_part);
   else if (prec == FFK_FP64)
     launch_jtg_reduce(N, D, shj, st, static_cast<const double*>(b.part), go.splits, N, b.s, t->Xc.as<double>(), xm,
                       b.wpart, go.ntn, t->a0, t->R.as<double>(), v, shift, M, D, y, vy_part);
@@ -1140,15 +1036,12 @@ __global__ void k_permute_stack(const double* __restrict__ v, const int32_t* __r
 static void stack_mvm(ffk_system* s, const double* v, double* y, double shift, int prec, hipStream_t st,
                       hipEvent_t* ev, double* vy_part) {
   ffk_system* src = s->stack.get();
-  const int S = (int)s->sym.size();
   ensure_coeffs_pair(s, src, s->stack_coef, prec, (int64_t)s->sym_identity * s->N, st);
   ensure_lowp_descriptor(s, prec, st);
   ensure_lowp_descriptor(src, prec, st);
   ensure_work(s->stack_work, src, s->N, s->D, prec, st);
   if (!s->stack_v) s->stack_v.alloc(src->n * 8);
-  k_permute_stack<<<cdiv(src->n, 256), 256, 0, st>>>(v, s->sym_perm.as<int32_t>(), S, s->N, s->M,
-                                                      s->stack_v.as<double>());
-  LAUNCHCHK();
+  permute_stack(s, v, s->stack_v.as<double>(), st);
   kernel_mvm_core(s, src, s->stack_coef, s->stack_v.as<double>(), v, y, shift, prec, st, ev, vy_part,
                   handle_bufs(s->stack_work, prec));
 }
@@ -1222,8 +1115,8 @@ void kernel_mvm_scratch(ffk_system* s, const double* v, double* y, double shift,
   require(prec >= FFK_FP64 && prec <= FFK_BF16X3, "kernel_mvm_noalloc: unknown precision");
   require(s->sym.empty(), "kernel_mvm_noalloc: a symmetrized kernel is not supported");
   const bool prepared = s->coef[prec].ready && s->coef[FFK_FP64].ready &&
-                        (prec == FFK_FP64   ? (bool)s->Xp64
-                         : prec == FFK_FP32 ? (bool)s->Xp32
+                        (prec == FFK_FP64   ? (bool)s->XpT64
+                         : prec == FFK_FP32 ? (bool)s->XpT32
                                             : (bool)s->Xch && (prec == FFK_BF16 || use_fused(prec, s->D, s->N, s->N) ||
                                                                (bool)s->coef[prec].dA_lo));
   require(prepared, "kernel_mvm_noalloc: the system's coefficients for this precision are not built yet "
@@ -1289,7 +1182,7 @@ void kernel_mvm_phases(ffk_system* s, const double* v, double* y, double shift, 
   for (auto& e : ev) (void)hipEventDestroy(e);
 }
 
-// ----------------------------------------------------------- prediction ----
+// ------------------------------------------- parts that prediction shares ----
 __global__ void k_center_with(const double* __restrict__ X, const double* __restrict__ mean, int64_t D,
                               double* __restrict__ Xc, double* __restrict__ sqn) {
   __shared__ double red[256];
@@ -1309,85 +1202,35 @@ __global__ void k_center_with(const double* __restrict__ X, const double* __rest
   if (threadIdx.x == 0) sqn[g] = red[0];
 }
 
+void center_rows(const double* X, const double* mean, int64_t N, int64_t D, double* Xc, double* sqn, hipStream_t st) {
+  k_center_with<<<(unsigned)N, 256, 0, st>>>(X, mean, D, Xc, sqn);
+  LAUNCHCHK();
+}
+
 void center_with(ffk_system* sys, const double* mean, hipStream_t st) {
-  k_center_with<<<(unsigned)sys->N, 256, 0, st>>>(sys->X.as<double>(), mean, sys->D, sys->Xc.as<double>(),
-                                                  sys->sqn.as<double>());
+  center_rows(sys->X.as<double>(), mean, sys->N, sys->D, sys->Xc.as<double>(), sys->sqn.as<double>(), st);
+}
+
+int jv_blocks(int64_t N) { return cdiv(N, jv_group(N)); }
+
+void jv_fp64(const ffk_system* s, const double* v, double* U, double* pd, double* cpart, double* sum, hipStream_t st) {
+  launch_jv<0>(s->N, s->M, st, s->R.as<double>(), s->pairs.as<int>(), v, s->Xc.as<double>(), s->N, s->M, s->D, (void*)U,
+               nullptr, s->D, nullptr, nullptr, (int64_t)0, pd, cpart);
+  LAUNCHCHK();
+  k_colsum_final<<<cdiv(s->D, 4), 256, 0, st>>>(cpart, jv_blocks(s->N), s->D, sum);
   LAUNCHCHK();
 }
 
-// y (+)= K(tgt, src) alpha on the scalar FP64 engine (rectangular: targets
-// and sources are different systems of the same molecule).  The target
-// descriptors are centred with the source mean (the kernel depends on
-// differences only).  With a cache, the coefficients of the pair and the
-// workspaces are kept for the next call with the same target.
-void rect_mvm(const ffk_system* tr, const ffk_system* te, const double* alpha, double* F, bool accumulate,
-              const double* shift_v, double shift, RectCache* cache, hipStream_t st) {
-  require(tr->M == te->M, "kernel product: the two systems differ in molecule size");
-  require(tr->sigma == te->sigma, "kernel product: sigma differs");
-  const int64_t Ns = tr->N, Nt = te->N, D = tr->D;
-  const int M = tr->M;
-  const int nblk = cdiv(Ns, jv_group(Ns));
-  const int ntn = cdiv(Ns, 128);
-  RectCache local;
-  RectCache& c = cache ? *cache : local;
-  if (!cache || c.tgt != te) {
-    c.tgt = nullptr;
-    c.U.alloc(Ns * D * 8);
-    c.pd.alloc(Ns * 8);
-    c.sv.alloc(D * 8);
-    c.cpart.alloc((int64_t)nblk * D * 8);
-    c.Xt.alloc(Nt * D * 8);
-    c.sqt.alloc(Nt * 8);
-    c.dA.alloc(Nt * Ns * 8);
-    c.B.alloc(Nt * Ns * 8);
-    c.Wn.alloc(Nt * Ns * 8);
-    c.wpart.alloc(Nt * ntn * 8);
-    c.G.alloc(Nt * D * 8);
-    c.part.alloc(part_budget(Nt, D));
-    k_center_with<<<Nt, 256, 0, st>>>(te->X.as<double>(), tr->xmean.as<double>(), D, c.Xt.as<double>(),
-                                      c.sqt.as<double>());
-    LAUNCHCHK();
-    ScalarArgs<double> g{};
-    g.M = (int)Nt;
-    g.N = (int)Ns;
-    g.nseg = 1;
-    g.seg[0] = SegS<double>{c.Xt.as<double>(), D, 1, tr->Xc.as<double>(), D, 1, (int)D};
-    EpiCoeffRect e{c.sqt.as<double>(), tr->sqn.as<double>(), c.dA.as<double>(), c.B.as<double>(), (int)Nt,
-                   (int)Ns, sqrt(5.0) / tr->sigma, tr->a0, tr->bcoef};
-    gemm_scalar_kernel<double, 128, 128, 16, true, true, EpiCoeffRect><<<dim3(ntn, cdiv(Nt, 128)), 256, 0, st>>>(g, e);
-    LAUNCHCHK();
-    if (cache) c.tgt = te;
-  }
-  launch_jv<0>(Ns, M, st, tr->R.as<double>(), tr->pairs.as<int>(), alpha, tr->Xc.as<double>(), Ns, M, D, c.U.get(),
-               nullptr, D, nullptr, nullptr, (int64_t)0, c.pd.as<double>(), c.cpart.as<double>());
+void jtg_rows(const double* R, const double* G, const double* X, int64_t N, int M, int64_t D, double* y,
+              hipStream_t st) {
+  k_jtg<<<(unsigned)N, M <= 64 ? 64 : 128, (3 * M + D) * sizeof(double), st>>>(R, G, X, nullptr, 0.0, M, D, y);
   LAUNCHCHK();
-  k_colsum_final<<<cdiv(D, 4), 256, 0, st>>>(c.cpart.as<double>(), nblk, D, c.sv.as<double>());
-  LAUNCHCHK();
-  MvmArgs a{Nt, Ns, D, tr->a0, c.Xt.as<double>(), c.pd.as<double>(), c.sv.as<double>(), c.wpart.as<double>(),
-            c.G.as<double>(), c.part.get(), c.part.bytes()};
-  mvm_gemms_scalar<double>(a, c.Xt.as<double>(), tr->Xc.as<double>(), c.U.as<double>(), c.dA.as<double>(),
-                           c.B.as<double>(), c.Wn.as<double>(), st, nullptr);
-  const int tb = M <= 64 ? 64 : 128;
-  k_jtg<<<Nt, tb, (3 * M + D) * sizeof(double), st>>>(te->R.as<double>(), c.G.as<double>(), te->X.as<double>(),
-                                                      shift_v, shift, M, D, F, accumulate ? 1 : 0);
-  LAUNCHCHK();
-  if (!cache) HIPCHK(hipStreamSynchronize(st));   // the temporaries are freed on return
 }
 
-// F = K(test, train) alpha; a symmetrized training system predicts with
-// sum_q K(test, train_q) (Pi_q alpha), train_q its permuted copies
-void kernel_predict(const ffk_system* tr, const ffk_system* te, const double* alpha, double* F, hipStream_t st) {
-  if (tr->sym.empty()) {
-    rect_mvm(tr, te, alpha, F, false, nullptr, 0.0, nullptr, st);
-    return;
-  }
-  DBuf aq(tr->n * 8);
-  const int M = tr->M;
-  for (size_t q = 0; q < tr->sym.size(); ++q) {
-    permute_atoms(alpha, tr->sym_perm.as<int32_t>() + q * M, tr->N, M, aq.as<double>(), st);
-    rect_mvm(tr->sym[q].get(), te, aq.as<double>(), F, q > 0, nullptr, 0.0, nullptr, st);
-  }
-  HIPCHK(hipStreamSynchronize(st));
+void permute_stack(const ffk_system* s, const double* v, double* out, hipStream_t st) {
+  const int S = (int)s->sym.size();
+  k_permute_stack<<<cdiv(s->n * S, 256), 256, 0, st>>>(v, s->sym_perm.as<int32_t>(), S, s->N, s->M, out);
+  LAUNCHCHK();
 }
 
 }  // namespace ffk

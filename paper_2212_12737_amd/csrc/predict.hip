@@ -1,0 +1,263 @@
+// Force prediction F = K(test, train) alpha (section 2.1), FP64.
+//
+// With U = J alpha over the N training geometries, T test geometries x_t
+// (centred with the training mean: the kernel sees differences only) and the
+// product's algebra,
+//   P = X_t U^T, W = B o (P - 1 pd^T), G = dA U - W X_c + diag(W 1) X_t + a(0) 1 (1^T U),
+// a workgroup takes 16 or 32 test geometries and 16 or 64 training ones through
+// all of it: the Gram products that give dA and B and those that give P share
+// the rows of X_t; dA and W stay in LDS and are the left operand of its part of
+// G.  Nothing of size T x N reaches memory, only the parts of G, which a second
+// kernel sums in a fixed order.  Bound by latency for a few test geometries
+// and by reading the training rows from L2 for hundreds.  A prediction (with the
+// test system's setup) against the same products as separate scalar GEMMs on
+// 128-row tiles with T x N results in memory: 442 -> 95 us at M = 21, N = 2000,
+// T = 1; 1894 -> 438 us at M = 42, N = 5000, T = 200, of it 269 us this kernel
+// (26 TFLOP/s).
+#include <type_traits>
+
+#include "smalldot.hpp"
+
+namespace ffk {
+
+struct PredictArgs {
+  const double *Xt, *sqt;         // centred test rows (T x D), |x_t|^2
+  const double *Xs, *sqs;         // centred training rows (N x D), |x_s|^2
+  const double *U, *pd;           // J alpha (N x D), x_s . u_s
+  double* part;                   // chunks x T x D parts of G
+  double* wpart;                  // T x chunks row sums of W
+  int T, N, D, chunks, tiles;
+  double inv_len, a0, bcoef;
+};
+
+// TB blocks of 16 test geometries; CB blocks of 16 training ones (1: the four
+// waves split K = D; 4: a block each).  Workgroups: the test tiles of a chunk
+// of training geometries run one after the other on one XCD (workgroup w on XCD
+// w % 8), which reads the chunk's rows into its L2 once.
+template <int TB, int CB>
+__global__ __launch_bounds__(256) void k_predict_part(PredictArgs g) {
+  constexpr int CH = 16 * CB, TR = 16 * TB;
+  __shared__ double sA[TR][CH + 1], sW[TR][CH + 1];
+  __shared__ double red[CB == 1 ? 4 : 1][2][CB == 1 ? TR : 1][17];
+  __shared__ double rsum[4][TR];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c16 = lane & 15, q16 = lane >> 4;
+  const int idx = blockIdx.x / 8, chunk = idx / g.tiles * 8 + blockIdx.x % 8;
+  const int t0 = idx % g.tiles * TR, s0 = chunk * CH;
+  if (chunk >= g.chunks) return;
+  const int D = g.D, steps = (D + 7) / 8;
+  const double* a[TB];
+#pragma unroll
+  for (int i = 0; i < TB; ++i) a[i] = g.Xt + (int64_t)min(t0 + 16 * i + c16, g.T - 1) * D;
+  const int64_t srow = min(s0 + (CB == 1 ? 0 : 16 * wave) + c16, g.N - 1);
+  d4 gm[TB], pm[TB];
+#pragma unroll
+  for (int i = 0; i < TB; ++i) gm[i] = pm[i] = d4{0, 0, 0, 0};
+  rows_dot<TB, true>(a, g.Xs + srow * D, g.U + srow * D, D, CB == 1 ? steps * wave / 4 : 0,
+                     CB == 1 ? steps * (wave + 1) / 4 : steps, gm, pm);
+  // dA and -W of one (test, training) pair into LDS; returns W
+  auto pair = [&](int t, int s, double gram, double p) {
+    double dA = 0.0, w = 0.0;
+    if (t0 + t < g.T && s0 + s < g.N) {
+      double B;
+      matern_coeffs(g.sqt[t0 + t] + g.sqs[s0 + s] - 2.0 * gram, g.inv_len, g.a0, g.bcoef, dA, B);
+      w = B * (p - g.pd[s0 + s]);
+    }
+    sA[t][s] = dA;
+    sW[t][s] = -w;
+    return w;
+  };
+  auto sum16 = [](double x) {
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o);
+    return x;
+  };
+  if constexpr (CB == 1) {
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        red[wave][0][16 * i + 4 * v + q16][c16] = gm[i][v];
+        red[wave][1][16 * i + 4 * v + q16][c16] = pm[i][v];
+      }
+    __syncthreads();
+    for (int t = threadIdx.x >> 4; t < TR; t += 16) {
+      double x[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) x[h] = (red[0][h][t][c16] + red[1][h][t][c16]) + (red[2][h][t][c16] + red[3][h][t][c16]);
+      const double w = sum16(pair(t, c16, x[0], x[1]));
+      if (c16 == 0) rsum[0][t] = w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int t = 16 * i + 4 * v + q16;
+        const double w = sum16(pair(t, 16 * wave + c16, gm[i][v], pm[i][v]));
+        if (c16 == 0) rsum[wave][t] = w;
+      }
+  }
+  __syncthreads();
+  if (threadIdx.x < TR && t0 + (int)threadIdx.x < g.T) {
+    double w = rsum[0][threadIdx.x];
+    if (CB > 1) w = (w + rsum[1][threadIdx.x]) + (rsum[2][threadIdx.x] + rsum[3][threadIdx.x]);
+    g.wpart[(int64_t)(t0 + threadIdx.x) * g.chunks + chunk] = w;
+  }
+  // this chunk's part of G: a wave takes every fourth block of 16 columns;
+  // training rows past the end read the last one, against zeros of dA and W
+  double* out = g.part + (int64_t)chunk * g.T * D;
+  constexpr int Q = CH / 4 < 8 ? CH / 4 : 8, KB = CH / 4 / Q;   // steps of four training rows in flight, batches
+  struct Rows { double u[Q], x[Q]; };
+  auto load = [&](int d0, int kb, Rows& r) {
+    const int d = min(d0 + c16, D - 1);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int64_t s = min(s0 + 4 * (kb * Q + q) + q16, g.N - 1);
+      r.u[q] = g.U[s * D + d];
+      r.x[q] = g.Xs[s * D + d];
+    }
+  };
+  Rows r[2];
+  if (16 * wave < D) load(16 * wave, 0, r[0]);
+  auto block = [&](int d0, auto first) {   // first: the buffer that holds its first batch
+    constexpr int F = decltype(first)::value;
+    d4 ga[TB], gw[TB];
+#pragma unroll
+    for (int i = 0; i < TB; ++i) ga[i] = gw[i] = d4{0, 0, 0, 0};
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      Rows& cur = r[(F + kb) & 1];
+      Rows& nxt = r[(F + kb + 1) & 1];
+      if (kb + 1 < KB) load(d0, kb + 1, nxt);
+      else if (d0 + 64 < D) load(d0 + 64, 0, nxt);
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int i = 0; i < TB; ++i) {
+          const int k = 4 * (kb * Q + q) + q16;
+          ga[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(sA[16 * i + c16][k], cur.u[q], ga[i], 0, 0, 0);
+          gw[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(sW[16 * i + c16][k], cur.x[q], gw[i], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int t = t0 + 16 * i + 4 * v + q16;
+        if (t < g.T && d0 + c16 < D) out[(int64_t)t * D + d0 + c16] = ga[i][v] + gw[i][v];
+      }
+  };
+  for (int d0 = 16 * wave; d0 < D; d0 += 128) {
+    block(d0, std::integral_constant<int, 0>());
+    if (d0 + 64 < D) block(d0 + 64, std::integral_constant<int, KB & 1>());
+  }
+}
+
+// G[t, d] = sum of the chunks' parts + a0 s_d + w_t x_t,d: one workgroup per
+// test geometry and 64 columns, its sixteen waves each sum every sixteenth
+// chunk (eight loads in flight), then meet in a fixed order.
+__global__ __launch_bounds__(1024) void k_predict_reduce(const double* __restrict__ part, int chunks, int64_t T, int D,
+                                                         const double* __restrict__ wpart, const double* __restrict__ s,
+                                                         const double* __restrict__ Xt, double a0,
+                                                         double* __restrict__ G) {
+  __shared__ double sh[16][64];
+  __shared__ double shw[16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t t = blockIdx.y;
+  const int d0 = blockIdx.x * 64, d = min(d0 + lane, D - 1);
+  const double* p = part + t * D + d;
+  double acc = 0.0, w = 0.0;
+  for (int z0 = wave; z0 < chunks; z0 += 16 * 8) {
+    double v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = p[(int64_t)min(z0 + 16 * e, chunks - 1) * T * D];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc += z0 + 16 * e < chunks ? v[e] : 0.0;
+  }
+  for (int z = wave * 64 + lane; z < chunks; z += 1024) w += wpart[t * chunks + z];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) w += __shfl_xor(w, o);
+  sh[wave][lane] = acc;
+  if (lane == 0) shw[wave] = w;
+  __syncthreads();
+  if (wave == 0 && d0 + lane < D) {
+    double a = 0.0, ws = 0.0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      a += sh[q][lane];
+      ws += shw[q];
+    }
+    G[t * D + d] = a + a0 * s[d] + ws * Xt[t * D + d];
+  }
+}
+
+template <int TB, int CB>
+static void launch_part(const PredictArgs& g, hipStream_t st) {
+  const int groups = cdiv(g.chunks, 8);
+  k_predict_part<TB, CB><<<(unsigned)(8 * groups * g.tiles), 256, 0, st>>>(g);
+  LAUNCHCHK();
+}
+
+// F = K(te, src) v for sources whose descriptors are centred with `mean`, with
+// the model's workspace (held by the caller until the stream is done).
+static void predict_from(const ffk_system* src, const double* mean, const ffk_system* te, const double* v, double* F,
+                         DBuf& work, hipStream_t st) {
+  const int64_t N = src->N, D = src->D;
+  const int M = src->M;
+  // test geometries at a time: up to 512, fewer where the parts of G would
+  // take more than 256 MB
+  const int64_t most = (256ll << 20) / ((int64_t)cdiv(N, 64) * D * 8) / 32 * 32;
+  const int64_t batch = std::min<int64_t>(te->N, std::min<int64_t>(512, std::max<int64_t>(32, most)));
+  const int TB = batch > 16 ? 2 : 1;
+  const int tiles = cdiv(batch, 16 * TB);
+  // 64 training geometries a workgroup where that gives every CU one
+  const int CB = (int64_t)tiles * cdiv(N, 64) >= 256 ? 4 : 1;
+  const int chunks = cdiv(N, 16 * CB);
+  int64_t off = 0;
+  auto take = [&](int64_t doubles) {
+    const int64_t o = off;
+    off += (doubles + 31) / 32 * 32;
+    return o;
+  };
+  const int64_t oU = take(N * D), opd = take(N), os = take(D), ocp = take((int64_t)jv_blocks(N) * D);
+  const int64_t oXt = take(batch * D), osq = take(batch), owp = take(batch * chunks), oG = take(batch * D);
+  const int64_t opart = take((int64_t)chunks * batch * D);
+  work.ensure(off * 8);
+  double* w = work.as<double>();
+  jv_fp64(src, v, w + oU, w + opd, w + ocp, w + os, st);
+  for (int64_t b0 = 0; b0 < te->N; b0 += batch) {
+    const int T = (int)std::min<int64_t>(batch, te->N - b0);
+    center_rows(te->X.as<double>() + b0 * D, mean, T, D, w + oXt, w + osq, st);
+    PredictArgs g{w + oXt, w + osq, src->Xc.as<double>(), src->sqn.as<double>(), w + oU, w + opd, w + opart, w + owp,
+                  T, (int)N, (int)D, chunks, cdiv(T, 16 * TB), sqrt(5.0) / src->sigma, src->a0, src->bcoef};
+    if (TB == 1 && CB == 1) launch_part<1, 1>(g, st);
+    else if (TB == 1) launch_part<1, 4>(g, st);
+    else if (CB == 1) launch_part<2, 1>(g, st);
+    else launch_part<2, 4>(g, st);
+    k_predict_reduce<<<dim3(cdiv(D, 64), T), 1024, 0, st>>>(w + opart, chunks, T, (int)D, w + owp, w + os, w + oXt,
+                                                            src->a0, w + oG);
+    LAUNCHCHK();
+    jtg_rows(te->R.as<double>() + b0 * 3 * M, w + oG, te->X.as<double>() + b0 * D, T, M, D, F + b0 * 3 * M, st);
+  }
+  HIPCHK(hipStreamSynchronize(st));   // the workspace may be the next call's, on another stream
+}
+
+// F = K(test, train) alpha; a symmetrized training system predicts with its
+// stacked permuted copies, sum_q K(test, P_q train) (Pi_q alpha)
+void kernel_predict(const ffk_system* tr, const ffk_system* te, const double* alpha, double* F, hipStream_t st) {
+  require(tr->M == te->M, "kernel product: the two systems differ in molecule size");
+  require(tr->sigma == te->sigma, "kernel product: sigma differs");
+  // The workspace stays with the model (releasing and mapping it anew cost
+  // milliseconds a call); calls that share the model take turns.
+  std::lock_guard<std::mutex> lock(tr->predict_lock);
+  if (tr->sym.empty()) {
+    predict_from(tr, tr->xmean.as<double>(), te, alpha, F, tr->predict_work, st);
+    return;
+  }
+  tr->predict_v.ensure(tr->stack->n * 8);
+  permute_stack(tr, alpha, tr->predict_v.as<double>(), st);
+  predict_from(tr->stack.get(), tr->xmean.as<double>(), te, tr->predict_v.as<double>(), F, tr->predict_work, st);
+}
+
+}  // namespace ffk
