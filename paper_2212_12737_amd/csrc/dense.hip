@@ -7,15 +7,15 @@
 
 namespace ffk {
 
-// Tiles of the column-major GEMM.  16 k between barriers and, where the tile
-// allows it, eight waves in two workgroups a CU: at M = N = 8192, K = 1024 the
-// 128 x 128 tile runs at 63 TFLOP/s with eight waves and 16 k, 51 with four
-// waves and 8 k, 59 and 62 with one of the two changed.
-typedef Tile64<128, 128, 2, 4, 2, 2> T64L;
-typedef Tile64<64, 64, 2, 2, 2, 2> T64S;
-typedef Tile64<128, 64, 4, 2, 2, 2> T64N;
-typedef Tile64<128, 32, 4, 1, 2, 3> T64R;    // N <= 32: bound by reading A, three stages
-typedef Tile64<256, 64, 8, 1, 2, 2> T64H;    // in place for M = K <= 256 (C = B) or N <= 64 (C = A)
+// Tiles of the column-major GEMM: 16 k between barriers and, where the tile
+// allows it, eight waves in two workgroups a CU.  At M = N = 8192, K = 1024 the
+// 128 x 128 tile runs at 67 TFLOP/s with eight waves, 66 with four (64 x 64
+// each), 62 with 32 k and one workgroup a CU, 64 as 256 x 128 by one workgroup.
+typedef Tile64<128, 128, 2, 4, 2> T64L;
+typedef Tile64<64, 64, 2, 2, 2> T64S;
+typedef Tile64<128, 64, 4, 2, 2> T64N;
+typedef Tile64<128, 32, 4, 1, 2> T64R;    // N <= 32
+typedef Tile64<256, 64, 8, 1, 2> T64H;    // in place for M = K <= 256 (C = B) or N <= 64 (C = A)
 
 template <class TL, bool BKC>
 static void launch64(const Gemm64Args& g, EpiCol64 e, int ntn, int ntm, int batch, hipStream_t st) {

@@ -586,15 +586,18 @@ __global__ __launch_bounds__(TL::NT) void gemm_dma_kernel(DmaArgs g, Epi epi) {
 // FP32 and FP64 MFMA engine for row-major (K-contiguous) operands, the same
 // direct global->LDS loads: a wave load takes 16 rows x 64 bytes, lane L row
 // L % 16 and 16-byte chunk L / 16, the lane layout of the fragments.
-// Bound by the matrix cores.  A stage holds KS chunks of 64 bytes of K, two
-// stages: at KS = 2 a wave meets a barrier every 64 (FP64) or 128 (FP32) MFMAs
-// of a 64 x 32 tile, and the 128 x 128 tile by eight waves leaves room for two
-// workgroups, 16 waves, on a CU.  K order within an element's sum does not
-// depend on the tile shape.  Against four waves of 64 x 64 with a barrier per
-// chunk and four stages: the FP64 product at M = 42, N = 5000 4.18 -> 2.86 ms
-// (45 TFLOP/s; with the column tiles and K splits below), FP32 at M = 21, N =
-// 10000 1.72 -> 1.54 ms (82), the Gram matrix of the factor at n = 126000, k =
-// 2000 18.4 -> 11.5 ms (49, with the splits on XCDs).
+// Bound by the matrix cores.  A stage holds two chunks of 64 bytes of K, two
+// stages: a wave meets a barrier every 64 (FP64) or 128 (FP32) MFMAs of a 64 x
+// 32 tile, and the 128 x 128 tile by eight waves leaves room for two
+// workgroups, 16 waves, on a CU (at most 128 registers: hence the bound of four
+// waves a SIMD).  Fragments are double-buffered in registers; read right before
+// their MFMAs, the waves of both workgroups met in the same phase and the
+// matrix cores idled 30% of the time.  K order within an element's sum does not
+// depend on the tile shape.  Four waves of 64 x 64 with a barrier per chunk and
+// four stages, eight waves with two chunks, and now: the FP64 product at M =
+// 42, N = 5000 4.18, 2.86, 2.42 ms (53 TFLOP/s; matrix cores busy 77% of GEMM
+// 2); FP32 at M = 21, N = 10000 1.72, 1.54, 1.55 ms; the Gram matrix of the
+// factor at n = 126000, k = 2000 18.4, 11.5, 10.3 ms.
 // BN need not be a power of two: the column tiles can fit the operand's width.
 // ---------------------------------------------------------------------------
 template <int BM_, int BN_, int WM_, int WN_, int KS_>
@@ -607,15 +610,15 @@ struct RowTile {
 // that each XCD streams its own range of K through its L2; gridDim.z must be a
 // multiple of 8.  Otherwise the order of tile_coords<false>.
 template <typename T, class TL, class Epi, bool XCDK = false>
-__global__ __launch_bounds__(TL::NT) void gemm_row_kernel(DmaArgs g, Epi epi) {
+__global__ __launch_bounds__(TL::NT, TL::NT == 512 ? 4 : 1) void gemm_row_kernel(DmaArgs g, Epi epi) {
   static_assert(sizeof(T) >= 4, "FP32 or FP64 operands");
   constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = TL::WN, KS = TL::KS, NW = WM * WN;
   constexpr int BK = 64 / (int)sizeof(T);
   constexpr int GA = BM / 16, GB = BN / 16, CHUNK = (GA + GB) * 1024;
-  constexpr int L = KS * (GA + GB);                     // 1 KB wave loads per stage
-  constexpr int Q = (L + NW - 1) / NW;                  // of one wave, at most
+  constexpr int QA = (KS * GA + NW - 1) / NW, QB = (KS * GB + NW - 1) / NW;   // 1 KB loads of a wave per stage
   constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
   static_assert(TM * WM * 16 == BM && TN * WN * 16 == BN, "16 x 16 blocks per wave");
+  static_assert(KS == 2, "the fragments of a stage's chunks alternate between two sets");
   typedef typename DmaMfma<T>::acc_t acc_t;
   __shared__ __attribute__((aligned(1024))) char smem[2 * KS * CHUNK];
 
@@ -646,60 +649,73 @@ __global__ __launch_bounds__(TL::NT) void gemm_row_kernel(DmaArgs g, Epi epi) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
 
-  // wave w takes the loads w, w + NW, ...; a load's source in both segments
-  const char *src0[Q], *src1[Q];
+  // wave w takes the loads w, w + NW, ... of a stage of each operand; the
+  // second segment has the first's leading dimensions and lies at a distance
+  const char *pa[QA], *pb[QB];
 #pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const int idx = wave + q * NW, grp = idx % (GA + GB);
-    const bool a = grp < GA;
-    const int64_t row = (a ? m0 + grp * 16 : n0 + (grp - GA) * 16) + (lane & 15);
-    const SegD &s0 = g.seg[0], &s1 = g.seg[1];
-    src0[q] = static_cast<const char*>(a ? s0.Ah : s0.Bh) + row * (a ? s0.lda : s0.ldb) * (int)sizeof(T) + (lane >> 4) * 16;
-    src1[q] = static_cast<const char*>(a ? s1.Ah : s1.Bh) + row * (a ? s1.lda : s1.ldb) * (int)sizeof(T) + (lane >> 4) * 16;
-  }
+  for (int q = 0; q < QA; ++q)
+    pa[q] = static_cast<const char*>(g.seg[0].Ah) +
+            (m0 + (wave + q * NW) % GA * 16 + (lane & 15)) * g.seg[0].lda * (int64_t)sizeof(T) + (lane >> 4) * 16;
+#pragma unroll
+  for (int q = 0; q < QB; ++q)
+    pb[q] = static_cast<const char*>(g.seg[0].Bh) +
+            (n0 + (wave + q * NW) % GB * 16 + (lane & 15)) * g.seg[0].ldb * (int64_t)sizeof(T) + (lane >> 4) * 16;
+  const int64_t da = (int64_t)((uintptr_t)g.seg[1].Ah - (uintptr_t)g.seg[0].Ah) - (int64_t)t0 * 64;
+  const int64_t db = (int64_t)((uintptr_t)g.seg[1].Bh - (uintptr_t)g.seg[0].Bh) - (int64_t)t0 * 64;
   auto issue = [&](int s) {   // stage s: chunks tb + s KS ..
     char* st = smem + (s & 1) * KS * CHUNK;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int idx = wave + q * NW, t = tb + s * KS + idx / (GA + GB);
-      if (idx < L && t < te) {
-        const char* p = t < t0 ? src0[q] + (int64_t)t * 64 : src1[q] + (int64_t)(t - t0) * 64;
-        dma16(p, st + idx * 1024);
-      }
+    for (int q = 0; q < QA; ++q) {
+      const int idx = wave + q * NW, kc = idx / GA, t = tb + s * KS + kc;
+      if (idx < KS * GA && t < te) dma16(pa[q] + ((int64_t)t * 64 + (t < t0 ? 0 : da)), st + kc * CHUNK + idx % GA * 1024);
+    }
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      const int idx = wave + q * NW, kc = idx / GB, t = tb + s * KS + kc;
+      if (idx < KS * GB && t < te) dma16(pb[q] + ((int64_t)t * 64 + (t < t0 ? 0 : db)), st + kc * CHUNK + (GA + idx % GB) * 1024);
     }
   };
-  auto chunk = [&](const char* st) {
-    u4 a[TM], b[TN];
+  struct Frag { u4 a[TM], b[TN]; };
+  auto read = [&](int s, int kc, Frag& f) {
+    const char* st = smem + (s & 1) * KS * CHUNK + kc * CHUNK;
 #pragma unroll
-    for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const u4*>(st + (wm * TM + i) * 1024 + lane * 16);
+    for (int i = 0; i < TM; ++i) f.a[i] = *reinterpret_cast<const u4*>(st + (wm * TM + i) * 1024 + lane * 16);
 #pragma unroll
-    for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const u4*>(st + (GA + wn * TN + j) * 1024 + lane * 16);
-    // every fragment read before the first MFMA (else they interleave in
-    // pairs, each behind a full LDS latency)
+    for (int j = 0; j < TN; ++j) f.b[j] = *reinterpret_cast<const u4*>(st + (GA + wn * TN + j) * 1024 + lane * 16);
+  };
+  auto mul = [&](const Frag& f) {
+    // the reads of the next fragments stay before these MFMAs
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int sl = 0; sl < DmaMfma<T>::SLICES; ++sl)
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = DmaMfma<T>::slice(a[i], b[j], acc[i][j], sl);
+        for (int j = 0; j < TN; ++j) acc[i][j] = DmaMfma<T>::slice(f.a[i], f.b[j], acc[i][j], sl);
+    __builtin_amdgcn_sched_barrier(0);
   };
 
-  const int full = (te - tb) / KS, left = (te - tb) % KS;
-  if (te > tb) issue(0);
-  for (int s = 0; s < full; ++s) {
-    __builtin_amdgcn_s_waitcnt(VmCnt<0>::v);
-    asm volatile("s_barrier" ::: "memory");
-    issue(s + 1);
-    const char* st = smem + (s & 1) * KS * CHUNK;
-#pragma unroll
-    for (int kc = 0; kc < KS; ++kc) chunk(st + kc * CHUNK);
-  }
-  if (left > 0) {
-    __builtin_amdgcn_s_waitcnt(VmCnt<0>::v);
-    asm volatile("s_barrier" ::: "memory");
-    const char* st = smem + (full & 1) * KS * CHUNK;
-    for (int kc = 0; kc < left; ++kc) chunk(st + kc * CHUNK);
+  // Software pipeline: a chunk's fragments are read while the MFMAs of the one
+  // before it run.  At a stage's last chunk the wave has its fragments in
+  // registers; past the barrier every wave has, so the next stage's data is
+  // complete and this stage's buffer free for the one after it.  The last
+  // stage may lack its second chunk: it is read (whatever the LDS holds) but
+  // not multiplied.
+  const int n = te - tb, ns = (n + KS - 1) / KS;
+  if (ns > 0) issue(0);
+  asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+  if (ns > 1) issue(1);
+  Frag f0, f1;
+  if (ns > 0) read(0, 0, f0);
+  for (int s = 0; s < ns; ++s) {
+    read(s, 1, f1);
+    mul(f0);
+    if (s + 1 < ns) {
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      if (s + 2 < ns) issue(s + 2);
+      read(s + 1, 0, f0);
+    }
+    if (2 * s + 1 < n) mul(f1);
   }
   __syncthreads();
   FragCoord fc{m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane, m0, n0, sizeof(T) == 8, tni, wn, WN, tzi};

@@ -22,20 +22,23 @@
 // k past K reads zeros.  Pointers must be 16-byte aligned, leading dimensions
 // even; a k-contiguous B of odd K needs finite values at k = K (the zeros of
 // A meet them).
-// Bound by the FP64 matrix cores.  Against the engine that loads element by
-// element through registers, bounds-checked (it ran the same products at 18
-// TFLOP/s): 50 TFLOP/s on the group updates of the incomplete Cholesky (n =
-// 126000, N = 256, K to 1792), 40 on the K = 256 trailing updates at n = 12600.
+// Bound by the FP64 matrix cores (72 TFLOP/s reached by a large library
+// product).  Fragments are double-buffered in registers: read right before
+// their MFMAs, the waves of both workgroups of a CU met in the same phase and
+// the matrix cores idled through the reads.  With 128 x 128 tiles, read first
+// and now: M = N = 8192, K = 1024 54 -> 67 TFLOP/s; n = 12544, K = 256 51 -> 56;
+// M = 126016, N = 256, K = 1024 59 -> 64; 64 x 64 tiles at M = 2048, N = 1024, K
+// = 256 33 -> 41.
 #pragma once
 
 #include "gemm.hpp"
 
 namespace ffk {
 
-// BM x BN block tile by WM x WN waves; KS chunks of 8 k per stage, S stages.
-template <int BM_, int BN_, int WM_, int WN_, int KS_, int S_>
+// BM x BN block tile by WM x WN waves; KS chunks of 8 k per stage, two stages.
+template <int BM_, int BN_, int WM_, int WN_, int KS_>
 struct Tile64 {
-  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, KS = KS_, S = S_;
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, KS = KS_;
   static constexpr int NT = 64 * WM * WN;
 };
 
@@ -65,17 +68,18 @@ struct EpiCol64 {
 
 template <class TL, bool BKC>
 __global__ __launch_bounds__(TL::NT) void k_gemm64(Gemm64Args g, EpiCol64 e) {
-  constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = TL::WN, KS = TL::KS, S = TL::S, NW = WM * WN;
+  constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = TL::WN, KS = TL::KS, NW = WM * WN;
   constexpr int BK = 8 * KS;
   constexpr int A_CHUNK = BM * 64, B_CHUNK = BN * 64;      // bytes of 8 k of a tile
   constexpr int STAGE = KS * (A_CHUNK + B_CHUNK);
   constexpr int LA = BM / 16 * KS, LB = BN / 16 * KS;      // 1 KB wave loads per stage
   static_assert(LA % NW == 0 && LB % NW == 0, "loads must split evenly over the waves");
   constexpr int QA = LA / NW, QB = LB / NW, LPT = QA + QB;
-  static_assert(LPT * (S - 2) < 64, "vmcnt holds at most 63 loads in flight");
+  static_assert(LPT < 64, "vmcnt holds at most 63 loads in flight");
+  static_assert(KS % 2 == 0, "fragments alternate between two sets");
   constexpr int MB = BM / WM / 16, NB = BN / WN / 16;      // 16-row blocks per wave
   static_assert(MB % 2 == 0 && (BKC || NB % 2 == 0), "pairs of blocks");
-  __shared__ __attribute__((aligned(1024))) char smem[S * STAGE];
+  __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -126,7 +130,7 @@ __global__ __launch_bounds__(TL::NT) void k_gemm64(Gemm64Args g, EpiCol64 e) {
   const int64_t stepA = (int64_t)BK * g.lda, stepB = BKC ? BK : (int64_t)BK * g.ldb;
   const int T = (K + BK - 1) / BK;
   auto issue = [&](int t) {
-    char* st = smem + (t % S) * STAGE;
+    char* st = smem + (t & 1) * STAGE;
     const int left = K - t * BK;   // k < left is valid in this stage
 #pragma unroll
     for (int q = 0; q < QA; ++q) {
@@ -146,44 +150,60 @@ __global__ __launch_bounds__(TL::NT) void k_gemm64(Gemm64Args g, EpiCol64 e) {
 #pragma unroll
     for (int j = 0; j < MB; ++j) acc[i][j] = d4{0, 0, 0, 0};
 
+  struct Frag { u4 m[2][MB / 2], n[BKC ? 1 : 2][BKC ? NB : NB / 2]; };
+  auto read = [&](int t, int kc, Frag& f) {
+    const char* st = smem + (t & 1) * STAGE;
+    const char* sa = st + kc * A_CHUNK + wm * (MB / 2) * 2048 + lane * 16;
+    const char* sb = st + KS * A_CHUNK + kc * B_CHUNK + wn * NB * 1024 + lane * 16;
 #pragma unroll
-  for (int s = 0; s < S - 1; ++s)
-    if (s < T) issue(s);
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int p = 0; p < MB / 2; ++p) f.m[s][p] = *reinterpret_cast<const u4*>(sa + p * 2048 + s * 1024);
+    if constexpr (BKC) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) f.n[0][i] = *reinterpret_cast<const u4*>(sb + i * 1024);
+    } else {
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int p = 0; p < NB / 2; ++p) f.n[s][p] = *reinterpret_cast<const u4*>(sb + p * 2048 + s * 1024);
+    }
+  };
+  auto mul = [&](const Frag& f) {
+    // the reads of the next fragments stay before these MFMAs
+    __builtin_amdgcn_sched_barrier(0);
+    auto half = [](const u4& v, int h) { return __hiloint2double((int)v[2 * h + 1], (int)v[2 * h]); };
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+          const double a = BKC ? half(f.n[0][i], s) : half(f.n[BKC ? 0 : s][BKC ? 0 : i / 2], i & 1);
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, half(f.m[s][j / 2], j & 1), acc[i][j], 0, 0, 0);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Software pipeline: a chunk's fragments are read while the MFMAs of the one
+  // before it run.  At a stage's last chunk the wave has its fragments in
+  // registers; past the barrier every wave has, so the next stage's data is
+  // complete and this stage's buffer free for the one after it.
+  if (T > 0) issue(0);
+  if (T > 1) issue(1);
+  if (T > 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LPT) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+  Frag f[2];
+  if (T > 0) read(0, 0, f[0]);
   for (int t = 0; t < T; ++t) {
-    if (S > 2 && t + S - 2 < T) __builtin_amdgcn_s_waitcnt(VmCnt<LPT * (S > 2 ? S - 2 : 0)>::v);
-    else __builtin_amdgcn_s_waitcnt(VmCnt<0>::v);
-    asm volatile("s_barrier" ::: "memory");
-    if (t + S - 1 < T) issue(t + S - 1);
-    const char* st = smem + (t % S) * STAGE;
 #pragma unroll
     for (int kc = 0; kc < KS; ++kc) {
-      u4 fm[2][MB / 2], fn[BKC ? 1 : 2][BKC ? NB : NB / 2];
-      const char* sa = st + kc * A_CHUNK + wm * (MB / 2) * 2048 + lane * 16;
-      const char* sb = st + KS * A_CHUNK + kc * B_CHUNK + wn * NB * 1024 + lane * 16;
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int p = 0; p < MB / 2; ++p) fm[s][p] = *reinterpret_cast<const u4*>(sa + p * 2048 + s * 1024);
-      if constexpr (BKC) {
-#pragma unroll
-        for (int i = 0; i < NB; ++i) fn[0][i] = *reinterpret_cast<const u4*>(sb + i * 1024);
-      } else {
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-          for (int p = 0; p < NB / 2; ++p) fn[s][p] = *reinterpret_cast<const u4*>(sb + p * 2048 + s * 1024);
+      if (kc + 1 < KS) read(t, kc + 1, f[(kc + 1) & 1]);
+      else if (t + 1 < T) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (t + 2 < T) issue(t + 2);
+        read(t + 1, 0, f[0]);
       }
-      __builtin_amdgcn_sched_barrier(0);
-      auto half = [](const u4& v, int h) { return __hiloint2double((int)v[2 * h + 1], (int)v[2 * h]); };
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-          for (int j = 0; j < MB; ++j) {
-            const double a = BKC ? half(fn[0][i], s) : half(fn[BKC ? 0 : s][BKC ? 0 : i / 2], i & 1);
-            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, half(fm[s][j / 2], j & 1), acc[i][j], 0, 0, 0);
-          }
+      mul(f[kc & 1]);
     }
   }
 

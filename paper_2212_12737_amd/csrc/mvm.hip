@@ -767,7 +767,9 @@ static GemmOut mvm_gemms_row(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t
 }
 
 // Column tile of the FP32 and FP64 GEMM 2: the width of 128, 112 and 96 that
-// leaves the least padding past D (and stays inside the padded rows Dr).
+// leaves the least padding past D (and stays inside the padded rows Dr).  112
+// columns take four waves in FP64 (at M = 21, N = 2000 74 us against 89 by
+// eight, whose fragments spill) and eight in FP32 (N = 10000: 1032 against 1066).
 static int gemm2_width(int64_t D, int64_t Dr) {
   int best = 128;
   for (int w : {112, 96})
@@ -785,7 +787,7 @@ static GemmOut mvm_gemms_wide(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_
   else
     splits = gemm2_splits_fp64((int64_t)cdiv(a.D, w) * cdiv(a.Nt, 128), 2 * cdiv(a.Ns, 8), a.Nt, a.D,
                                2.0 * 128 * w * 2.0 * a.Ns);
-  if (w == 112) return mvm_gemms_row<T, TL1, RowTile<128, 112, 8, 1, 2>>(a, Ntr, Nsr, Dk, splits, o, st, ev);
+  if (w == 112) return mvm_gemms_row<T, TL1, RowTile<128, 112, sizeof(T) == 4 ? 8 : 4, 1, 2>>(a, Ntr, Nsr, Dk, splits, o, st, ev);
   if (w == 96) return mvm_gemms_row<T, TL1, RowTile<128, 96, 4, 2, 2>>(a, Ntr, Nsr, Dk, splits, o, st, ev);
   return mvm_gemms_row<T, TL1, RowTile<128, 128, 2, 4, 2>>(a, Ntr, Nsr, Dk, splits, o, st, ev);
 }
