@@ -418,10 +418,18 @@ struct SegD {
   int K;              // elements, multiple of 64 bytes
   int KT;             // BF16: K tiles of a stored row group
 };
+// Items of a Gram product: K in `ranges` ranges, workgroup w on range w %
+// ranges (eight: one per XCD, whose L2 then holds the window of the operand that
+// its tiles walk through together) as that range's item w / ranges: the first
+// `whole` lower tiles in one piece each, the others in `parts`.
+struct GramMap {
+  int ranges, whole, parts;
+};
 struct DmaArgs {
   int nseg;
   SegD seg[2];
   int lower_only;   // square tiles strictly above the diagonal do nothing (symmetric products)
+  GramMap gram;
 };
 
 // Tile shape of the pipelined engine: BM x BN block tile computed by WM x WN
@@ -597,7 +605,7 @@ __global__ __launch_bounds__(TL::NT) void gemm_dma_kernel(DmaArgs g, Epi epi) {
 // four stages, eight waves with two chunks, and now: the FP64 product at M =
 // 42, N = 5000 4.18, 2.86, 2.42 ms (53 TFLOP/s; matrix cores busy 77% of GEMM
 // 2); FP32 at M = 21, N = 10000 1.72, 1.54, 1.55 ms; the Gram matrix of the
-// factor at n = 126000, k = 2000 18.4, 11.5, 10.3 ms.
+// factor at n = 126000, k = 2000 18.4, 11.5, 10.3 ms (8.5 in GramMap's items).
 // BN need not be a power of two: the column tiles can fit the operand's width.
 // ---------------------------------------------------------------------------
 template <int BM_, int BN_, int WM_, int WN_, int KS_>
@@ -606,10 +614,9 @@ struct RowTile {
   static constexpr int NT = 64 * WM * WN;
 };
 
-// XCDK: the K splits are spread over the XCDs (split z runs on XCD z % 8), so
-// that each XCD streams its own range of K through its L2; gridDim.z must be a
-// multiple of 8.  Otherwise the order of tile_coords<false>.
-template <typename T, class TL, class Epi, bool XCDK = false>
+// GRAM: the lower tiles of a symmetric product in the items of GramMap.
+// Otherwise the order of tile_coords<false>.
+template <typename T, class TL, class Epi, bool GRAM = false>
 __global__ __launch_bounds__(TL::NT, TL::NT == 512 ? 4 : 1) void gemm_row_kernel(DmaArgs g, Epi epi) {
   static_assert(sizeof(T) >= 4, "FP32 or FP64 operands");
   constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = TL::WN, KS = TL::KS, NW = WM * WN;
@@ -625,23 +632,29 @@ __global__ __launch_bounds__(TL::NT, TL::NT == 512 ? 4 : 1) void gemm_row_kernel
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int tmi, tni, tzi;
-  if constexpr (XCDK) {
-    const int nt = (int)(gridDim.x * gridDim.y), per = (int)gridDim.z / 8;
-    const int w = ((int)blockIdx.z * (int)gridDim.y + (int)blockIdx.y) * (int)gridDim.x + (int)blockIdx.x;
-    const int idx = w / 8;
-    tzi = w % 8 + 8 * (idx / nt % per);
-    tmi = idx % nt / (int)gridDim.x;
-    tni = idx % nt % (int)gridDim.x;
+  int part = 0, parts = 1;
+  if constexpr (GRAM) {
+    const int x = (int)blockIdx.x % g.gram.ranges, j = (int)blockIdx.x / g.gram.ranges, rest = j - g.gram.whole;
+    const int t = rest < 0 ? j : g.gram.whole + rest / g.gram.parts;
+    tmi = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+    while ((tmi + 1) * (tmi + 2) / 2 <= t) ++tmi;
+    while (tmi * (tmi + 1) / 2 > t) --tmi;
+    tni = t - tmi * (tmi + 1) / 2;
+    tzi = x * (int)(gridDim.x / g.gram.ranges) + j;
+    part = rest < 0 ? x : x * g.gram.parts + rest % g.gram.parts;
+    parts = rest < 0 ? g.gram.ranges : g.gram.ranges * g.gram.parts;
   } else {
     tile_coords<false>(tmi, tni, tzi);
+    part = tzi;
+    parts = (int)gridDim.z;
   }
   if (g.lower_only && tni > tmi) return;
   const int m0 = tmi * BM, n0 = tni * BN;
   const int wm = wave / WN, wn = wave % WN;
   const int t0 = g.seg[0].K / BK;
   const int T_ = t0 + (g.nseg > 1 ? g.seg[1].K / BK : 0);
-  const int tb = (int)((int64_t)T_ * tzi / gridDim.z);
-  const int te = (int)((int64_t)T_ * (tzi + 1) / gridDim.z);
+  const int tb = (int)((int64_t)T_ * part / parts);
+  const int te = (int)((int64_t)T_ * (part + 1) / parts);
 
   acc_t acc[TM][TN];
 #pragma unroll
@@ -768,6 +781,23 @@ template <typename PT> struct EpiPart {
           const int r = f.row(i, v), c = f.col(j);
           if (r < rows && c < cols) base[(int64_t)r * ldp + c] = (PT)acc[i][j][v];
         }
+  }
+};
+
+// The tile as the registers hold it, one after the other by split index: a
+// wave's store is 512 contiguous bytes.
+template <int BM, int BN> struct EpiTile {
+  double* part;
+  template <typename T, int TM, int TN, class Acc>
+  __device__ void run(const Acc (&acc)[TM][TN], const FragCoord& f, char*) const {
+    const int wave = ((f.wm0 - f.m0) / (16 * TM)) * f.nwcol + f.wcol;
+    double* base = part + (int64_t)f.split * BM * BN + (int64_t)wave * TM * TN * 256 + f.lane;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) base[((i * TN + j) * 4 + v) * 64] = acc[i][j][v];
   }
 };
 

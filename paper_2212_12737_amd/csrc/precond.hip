@@ -239,55 +239,69 @@ static void gram_cols(const TI* L, int64_t n, int64_t ld, int64_t k, double* C, 
   LAUNCHCHK();
 }
 
-// core[r + c ldc] = sum_z part[z][r][c] for r >= c (the lower triangle),
-// from the split-K partials of gram_dma (plane = k ldp doubles per split)
-__global__ void k_gram_reduce(const double* __restrict__ part, int splits, int64_t k, int64_t ldp, int64_t plane,
-                              double* __restrict__ C, int64_t ldc) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= k * k) return;
-  const int64_t r = e / k, c = e % k;
-  if (r < c) return;
-  double a = 0.0;
-  for (int z = 0; z < splits; ++z) a += part[(int64_t)z * plane + r * ldp + c];
-  C[r + c * ldc] = a;
-}
-
 // Rows of the Gram operand are padded to this (the tile of gram_dma).
 constexpr int64_t kGramTile = 128;
+typedef RowTile<kGramTile, kGramTile, 2, 4, 2> TileG;
+
+// core[r + c ldc], the lower triangle, from the tiles that gram_dma left as
+// registers held them: the sum over a tile's pieces in their order.  A
+// workgroup takes 1024 elements of a tile (blockIdx.x / 16).
+__global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ part, GramMap m, int items, int k,
+                                                     double* __restrict__ C, int64_t ldc) {
+  constexpr int TM = TileG::BM / TileG::WM / 16, TN = TileG::BN / TileG::WN / 16;
+  const int t = blockIdx.x / 16;
+  int tm = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+  while ((tm + 1) * (tm + 2) / 2 <= t) ++tm;
+  while (tm * (tm + 1) / 2 > t) --tm;
+  const int tn = t - tm * (tm + 1) / 2;
+  const int parts = t < m.whole ? 1 : m.parts;
+  const int64_t first = t < m.whole ? t : m.whole + (int64_t)(t - m.whole) * m.parts;
+  const int e0 = (int)(blockIdx.x % 16) * 1024 + threadIdx.x;
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int x = 0; x < m.ranges; ++x)
+    for (int p = 0; p < parts; ++p)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        a[q] += part[(x * (int64_t)items + first + p) * TileG::BM * TileG::BN + e0 + 256 * q];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = e0 + 256 * q, lane = e & 63, v = e >> 6 & 3, b = e >> 8;
+    const int j = b % TN, i = b / TN % TM, w = b / (TN * TM);
+    const int r = tm * TileG::BM + (w / TileG::WN * TM + i) * 16 + 4 * v + (lane >> 4);
+    const int c = tn * TileG::BN + (w % TileG::WN * TN + j) * 16 + (lane & 15);
+    if (r < k && c <= r) C[r + c * ldc] = a[q];
+  }
+}
 
 // Lower triangle of core = L^T L from the FP64 factor on the pipelined FP64
 // MFMA engine.  The columns of the column-major L are the K-contiguous
 // operand rows (K = ld, zero padding rows), for A and B alike; L holds kp
 // columns (a multiple of the tile) so that every tile row is allocated.  Only
-// tiles on or below the diagonal run, split over K for enough workgroups,
-// and a fixed-order pass sums the splits.  A multiple of eight splits puts each
-// on one XCD, whose L2 then holds the window of L that its tiles walk through
-// together: L is read from HBM about once rather than by every tile.
+// tiles on or below the diagonal run, each in eight ranges of K (one per XCD),
+// and a fixed-order pass sums them.  Tiles past the last full round of two
+// workgroups a CU are cut further, so that they too fill the chip: 136 tiles on
+// 64 places an XCD took five rounds of sixteenths (CUs busy 83%), now two of
+// eighths and one of an eighth of that.  n = 126000, k = 2000: 10.3 -> 8.5 ms (59
+// TFLOP/s), and 0.2 GB of pieces instead of 0.5.
 static void gram_dma(const double* L, int64_t ld, int64_t k, int64_t kp, double* C, int64_t ldc, hipStream_t st) {
-  typedef RowTile<kGramTile, kGramTile, 2, 4, 2> TG;
   require(kp % kGramTile == 0 && kp >= k && ld % 8 == 0, "gram_dma: operand padding");
-  const int64_t nt = kp / kGramTile;
-  const int64_t lower = nt * (nt + 1) / 2;
-  // workgroups for eight a CU, at least 64 chunks of K a split, partials of 2 GB at most
-  int splits = 8;
-  while (lower * splits < 2048 && splits < 64 && ld / 8 >= (int64_t)splits * 2 * 64 && splits * k * kp * 16 <= (2ll << 30))
-    splits *= 2;
-  const bool xcd = ld / 8 >= 8 * 64 && splits * k * kp * 8 <= (2ll << 30);
-  if (!xcd) {
-    splits = 1;
-    while (lower * splits < 512 && splits < 16 && ld / 8 >= (int64_t)splits * 2 * 64) splits *= 2;
-  }
-  DBuf part((size_t)splits * k * kp * 8);
+  const int64_t nt = kp / kGramTile, tiles = nt * (nt + 1) / 2, chunks = ld / 8;
+  const int ranges = chunks >= 8 * 64 && tiles <= 1000 ? 8 : 1;   // pieces of 2 GB at most, then about those of core
+  const int64_t places = std::max(1, 2 * device_cus() / ranges);
+  const int64_t whole = tiles / places * places, rest = tiles - whole;
+  int parts = 1;   // at least 32 chunks of K each
+  for (int s = 2; s <= 16 && chunks / ranges >= 32ll * s; ++s)
+    if (cdiv(rest * s, places) * (int64_t)parts < cdiv(rest * parts, places) * (int64_t)s) parts = s;
+  const int64_t items = whole + rest * parts;
+  DBuf part((size_t)(ranges * items * kGramTile * kGramTile * 8));
   DmaArgs g{};
   g.nseg = 1;
-  g.lower_only = 1;
   g.seg[0] = SegD{L, nullptr, L, nullptr, ld, ld, (int)ld};
-  EpiPart<double> e{part.as<double>(), kp, (int)k, (int)k};
-  const dim3 grid((unsigned)nt, (unsigned)nt, splits);
-  if (xcd) gemm_row_kernel<double, TG, EpiPart<double>, true><<<grid, TG::NT, 0, st>>>(g, e);
-  else gemm_row_kernel<double, TG, EpiPart<double>><<<grid, TG::NT, 0, st>>>(g, e);
+  g.gram = GramMap{ranges, (int)whole, parts};
+  typedef EpiTile<kGramTile, kGramTile> Epi;
+  gemm_row_kernel<double, TileG, Epi, true><<<(unsigned)(ranges * items), TileG::NT, 0, st>>>(g, Epi{part.as<double>()});
   LAUNCHCHK();
-  k_gram_reduce<<<cdiv(k * k, 256), 256, 0, st>>>(part.as<double>(), splits, k, kp, k * kp, C, ldc);
+  k_gram_reduce<<<(unsigned)(16 * tiles), 256, 0, st>>>(part.as<double>(), g.gram, (int)items, (int)k, C, ldc);
   LAUNCHCHK();
   HIPCHK(hipStreamSynchronize(st));   // before the partials are freed
 }
