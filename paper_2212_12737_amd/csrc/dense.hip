@@ -91,24 +91,28 @@ constexpr int NB = 64, NB2 = 256;
 __global__ __launch_bounds__(256) void k_potf2(double* A, int jb, int64_t lda, int64_t j0, int64_t* info,
                                                double* Linv) {
   __shared__ Chol64 s;
-  for (int e = threadIdx.x; e < NB * NB; e += 256) {
-    const int r = e % NB, c = e / NB;
-    s.T[r][c] = r < jb && c <= r ? A[r + c * lda] : (r == c ? 1.0 : 0.0);
+  const int r = threadIdx.x % NB, cq = threadIdx.x / NB;   // a thread's elements: row r, columns cq + 4 q
+  double t[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) t[q] = A[min(r, jb - 1) + min(cq + 4 * q, jb - 1) * lda];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int c = cq + 4 * q;
+    s.T[r][c] = r < jb && c <= r ? t[q] : (r == c ? 1.0 : 0.0);
   }
   __syncthreads();
-  chol64<false>(s, 0.0);
-  if (threadIdx.x == 0) {
-    int bad = -1;
-    for (int c = NB - 1; c >= 0; --c)
-      if (s.bad[c]) bad = c;
-    if (bad >= 0) atomicMin(reinterpret_cast<unsigned long long*>(info), (unsigned long long)(j0 + bad));
-  }
-  tri64_inverse(s);
+  chol64_inverse<false>(s, 0.0);
   __syncthreads();
-  for (int e = threadIdx.x; e < NB * NB; e += 256) {
-    const int r = e % NB, c = e / NB;
+  if (threadIdx.x < 64) {
+    const unsigned long long bad = __ballot(s.bad[threadIdx.x] != 0);
+    if (threadIdx.x == 0 && bad)
+      atomicMin(reinterpret_cast<unsigned long long*>(info), (unsigned long long)(j0 + __ffsll((long long)bad) - 1));
+  }
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int c = cq + 4 * q, e = threadIdx.x + 256 * q;
     if (r < jb && c < jb) A[r + c * lda] = r >= c ? s.T[r][c] : 0.0;
-    Linv[e] = s.X[e / NB][e % NB];
+    Linv[e] = s.inverse(e / NB, e % NB);
   }
 }
 
@@ -119,18 +123,22 @@ __global__ __launch_bounds__(256) void k_tri64(double* A, int64_t n, int64_t lda
   const int64_t j0 = (int64_t)blockIdx.x * NB;
   const int jb = (int)min((int64_t)NB, n - j0);
   double* D = A + j0 + j0 * lda;
-  for (int e = threadIdx.x; e < NB * NB; e += 256) {
-    const int r = e % NB, c = e / NB;
-    s.T[r][c] = r < jb && c <= r ? D[r + c * lda] : (r == c ? 1.0 : 0.0);
+  const int r = threadIdx.x % NB, cq = threadIdx.x / NB;
+  double t[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) t[q] = D[min(r, jb - 1) + min(cq + 4 * q, jb - 1) * lda];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int c = cq + 4 * q;
+    s.T[r][c] = r < jb && c <= r ? t[q] : (r == c ? 1.0 : 0.0);
   }
-  __syncthreads();
-  tri64_diag(s);
   __syncthreads();
   tri64_inverse(s);
   __syncthreads();
-  for (int e = threadIdx.x; e < jb * NB; e += 256) {
-    const int r = e % NB, c = e / NB;
-    if (r < jb) D[r + c * lda] = s.X[r][c];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int c = cq + 4 * q;
+    if (r < jb && c < jb) D[r + c * lda] = s.inverse(r, c);
   }
 }
 

@@ -49,20 +49,29 @@ __global__ void k_gather_rows32(const float* L, int64_t ld, const int64_t* idx, 
 // Factor the nb x nb pivot block T[c][c'] = panel[idx[c], c'] with drops and
 // invert it.  Outputs: diag (PB) of the factor, Linv (PB x PB row-major) = its
 // inverse with a unit diagonal put at dropped positions, kept flags.  One
-// block on one CU: 218 us with three barriers a column, 37 us on 16 x 16
-// blocks (chol64.hpp).
+// block on one CU: 218 us with three barriers a column, 25 us in panels of 16
+// (chol64.hpp).
 __global__ __launch_bounds__(256) void k_panel_chol(const double* Lp, int64_t ld, const int64_t* idx, int nb,
                                                     double thr, double* diag, double* Linv, unsigned char* kept) {
   __shared__ Chol64 s;
-  for (int e = threadIdx.x; e < PB * PB; e += 256) {
-    const int r = e % PB, c = e / PB;
-    s.T[r][c] = (r < nb && c <= r) ? Lp[idx[r] + (int64_t)c * ld] : (r == c ? 1.0 : 0.0);
+  const int r = threadIdx.x % PB, cq = threadIdx.x / PB;   // a thread's elements: row r, columns cq + 4 q
+  const double* row = Lp + idx[min(r, nb - 1)];
+  double t[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) t[q] = row[min(cq + 4 * q, nb - 1) * ld];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int c = cq + 4 * q;
+    s.T[r][c] = (r < nb && c <= r) ? t[q] : (r == c ? 1.0 : 0.0);
   }
   __syncthreads();
-  chol64<true>(s, thr);
-  tri64_inverse(s);
+  chol64_inverse<true>(s, thr);
   __syncthreads();
-  for (int e = threadIdx.x; e < PB * PB; e += 256) Linv[e] = s.X[e / PB][e % PB];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int e = threadIdx.x + 256 * q;
+    Linv[e] = s.inverse(e / PB, e % PB);
+  }
   if ((int)threadIdx.x < nb) {
     diag[threadIdx.x] = s.T[threadIdx.x][threadIdx.x];
     kept[threadIdx.x] = s.bad[threadIdx.x] ? 0 : 1;
