@@ -14,6 +14,7 @@ namespace ffk {
 typedef Tile64<128, 128, 2, 4, 2> T64L;
 typedef Tile64<64, 64, 2, 2, 2> T64S;
 typedef Tile64<128, 64, 4, 2, 2> T64N;
+typedef Tile64<128, 96, 4, 1, 2> T64W;    // 64 < N <= 96, B k-contiguous
 typedef Tile64<128, 32, 4, 1, 2> T64R;    // N <= 32
 typedef Tile64<256, 64, 8, 1, 2> T64H;    // in place for M = K <= 256 (C = B) or N <= 64 (C = A)
 
@@ -47,12 +48,14 @@ void gemm64(int M, int N, int K, double alpha, const double* A, int64_t lda, con
   // 2048, N = 1024, K = 256 22 against 35.  N <= 64 takes a tile
   // that spans the columns always, which is safe in place; the taller one where
   // it too gives every CU a tile and a half (M = 126016, N = 64, K = 192: 42
-  // against 38).
+  // against 38).  65 to 96 columns have a tile of their own width: 203 against
+  // 330 us at M = 126000 and depths about 1000, where the selection meets them.
   const int64_t large = (int64_t)cdiv(M, 128) * cdiv(N, 128) / (lower_only ? 2 : 1);
   if (large < 256) launch64<T64S>(g, e, b_kcontig, st);
   else if (N <= 32) launch64<T64R>(g, e, b_kcontig, st);
   else if (N <= 64 && large >= 768) launch64<T64H>(g, e, b_kcontig, st);
   else if (N <= 64) launch64<T64N>(g, e, b_kcontig, st);
+  else if (N <= 96) launch64<T64W>(g, e, b_kcontig, st);
   else launch64<T64L>(g, e, b_kcontig, st);
 }
 

@@ -603,89 +603,122 @@ __device__ inline double wave_max(double x) {
   return y;
 }
 
-// The greedy block: the candidates' matrix A[slot][c] = pool[row of c, slot]
-// in LDS, then one wave (lane l: candidates l and l + 64) picks the best
-// candidate, forms its column from the block's earlier ones, and lowers the
-// diagonals, until the bound.  A pivot's row of A becomes its column of L.
-// Bound by the chain argmax -> column -> diagonal, about 2 us a pivot.
-__global__ __launch_bounds__(1024) void k_piv_greedy(const double* __restrict__ pool, int64_t ld,
+// A[q][c] = pool[row of slot c, slot q]: 16384 scattered reads, a few per CU (by
+// the greedy block's own CU they took 40 us).
+__global__ __launch_bounds__(kPool) void k_piv_gather(const double* __restrict__ pool, int64_t ld, int slots,
+                                                      const PivState* __restrict__ st, double* __restrict__ A) {
+  const int q = blockIdx.x, c = threadIdx.x;
+  const int rq = q < slots ? st->row[q] : -1, rc = c < slots ? st->row[c] : -1;
+  A[q * kPool + c] = rq >= 0 && rc >= 0 ? pool[rc + q * ld] : 0.0;
+}
+
+__device__ inline unsigned wave_max(unsigned x) {
+  x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, true));
+  x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xF, 0xF, true));
+  x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xF, 0xF, true));
+  x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xF, 0xF, true));
+  unsigned y = 0;
+#pragma unroll
+  for (int l = 0; l < 64; l += 16) y = max(y, (unsigned)__builtin_amdgcn_readlane((int)x, l));
+  return y;
+}
+
+constexpr int kGreedy = 512;   // threads of k_piv_greedy
+
+// The greedy block on the candidates' matrix A[slot][c] = pool[row of c, slot]:
+// picks the best candidate, scales its row of A to its column of L over the
+// candidates, and lowers the diagonals and the rest of A, until the bound.
+// Wave w of eight holds the rows of the slots 16 w .. 16 w + 15 in registers
+// (lane l: candidates l and l + 64); the diagonals, and so the choice of the
+// pivot, are every wave's own, so that a pivot costs one barrier, behind which
+// all read its column.  The choice looks at the diagonals' high words, and at
+// all of them only where those tie.  Bound by the chain argmax -> root -> column -> diagonal: one wave
+// that gathered A itself and formed each column from the earlier ones in LDS
+// took 81 us a block of 34, now 34 and 5 for the gather.
+__global__ __launch_bounds__(kGreedy) void k_piv_greedy(const double* __restrict__ A,
                                                      const double* __restrict__ d, double thr, int64_t m, int limit,
                                                      int slots, PivState* st, int64_t* __restrict__ piv) {
-  __shared__ double A[kPool][kPool];
-  __shared__ int row[kPool];
-  for (int e = threadIdx.x; e < kPool; e += 1024) row[e] = e < slots ? st->row[e] : -1;
+  constexpr int RW = kPool / (kGreedy / 64);
+  __shared__ double L[kPool][kPool];   // the pivots' columns
+  __shared__ int row[kPool], slot_of[kPool];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int e = threadIdx.x; e < kPool; e += kGreedy) row[e] = e < slots ? st->row[e] : -1;
   __syncthreads();
-#pragma unroll
-  for (int h = 0; h < kPool * kPool / 1024; ++h) {   // all of a thread's loads in flight
-    const int e = threadIdx.x + 1024 * h, p = e / kPool, c = e % kPool;
-    A[p][c] = row[p] >= 0 && row[c] >= 0 ? pool[row[c] + p * ld] : 0.0;
-  }
-  __syncthreads();
-  if (threadIdx.x >= 64) return;
-  const int lane = threadIdx.x;
-  const double bound = st->bound;
-  double dc[2];
+  double a[RW][2], dc[2];
   int rc[2];
+  const double bound = st->bound;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     rc[h] = row[lane + 64 * h];
     dc[h] = rc[h] >= 0 ? d[rc[h]] : -INFINITY;
+#pragma unroll
+    for (int j = 0; j < RW; ++j) a[j][h] = A[(RW * wave + j) * kPool + lane + 64 * h];
     if (rc[h] < 0) rc[h] = 0x7FFFFFFF;
   }
-  int s = 0, sl0 = 0, sl1 = 0;   // lane b: the slots of pivots b and b + 64
+  int s = 0;
   while (s < limit) {
     // the best candidate: the largest diagonal, then the lowest row of those
-    const double v = wave_max(fmax(dc[0], dc[1]));
-    if (!(v > thr) || (s > 0 && !(v >= bound))) break;
-    int r = min(dc[0] == v ? rc[0] : 0x7FFFFFFF, dc[1] == v ? rc[1] : 0x7FFFFFFF);
-    unsigned long long at = __ballot(r != 0x7FFFFFFF);
-    if (at & (at - 1)) {
-      int low = r;
+    const unsigned k0 = dc[0] > 0.0 ? (unsigned)__double2hiint(dc[0]) : 0u;
+    const unsigned k1 = dc[1] > 0.0 ? (unsigned)__double2hiint(dc[1]) : 0u;
+    const unsigned top = wave_max(max(k0, k1));
+    const unsigned long long at0 = __ballot(k0 == top), at1 = __ballot(k1 == top);
+    double v;
+    int r, p;
+    if (__popcll(at0) + __popcll(at1) == 1) {
+      const int owner = __ffsll(at0 | at1) - 1;
+      v = lane_value(at1 ? dc[1] : dc[0], owner);
+      r = __builtin_amdgcn_readlane(at1 ? rc[1] : rc[0], owner);
+      p = owner + (at1 ? 64 : 0);
+    } else {
+      v = wave_max(fmax(dc[0], dc[1]));
+      r = min(dc[0] == v ? rc[0] : 0x7FFFFFFF, dc[1] == v ? rc[1] : 0x7FFFFFFF);
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) low = min(low, __shfl_xor(low, o));
-      at = __ballot(r == low);
+      for (int o = 32; o > 0; o >>= 1) r = min(r, __shfl_xor(r, o));
+      const unsigned long long lower = __ballot(dc[0] == v && rc[0] == r), upper = __ballot(dc[1] == v && rc[1] == r);
+      p = lower ? __ffsll(lower) - 1 : __ffsll(upper) + 63;   // (none where all diagonals are NaN: v is no pivot)
     }
-    const int owner = __ffsll(at) - 1;
-    r = __builtin_amdgcn_readlane(r, owner);
-    const bool upper = dc[1] == v && rc[1] == r;
-    const int p = owner + ((__ballot(upper) >> owner) & 1 ? 64 : 0);
-    const double pv = sqrt(v), pinv = 1.0 / pv;
-    double x0 = A[p][lane], x1 = A[p][lane + 64];
-    auto earlier = [&](int slot) {
-      const double* Lb = A[slot];
-      const double lp = Lb[p];
-      x0 = fma(-Lb[lane], lp, x0);
-      x1 = fma(-Lb[lane + 64], lp, x1);
-    };
-#pragma unroll 8
-    for (int b = 0; b < min(s, 64); ++b) earlier(__builtin_amdgcn_readlane(sl0, b));
-#pragma unroll 8
-    for (int b = 64; b < s; ++b) earlier(__builtin_amdgcn_readlane(sl1, b - 64));
-    if (lane < s) st->Lt[lane * kPool + s] = A[sl0][p];
-    if (lane + 64 < s) st->Lt[(lane + 64) * kPool + s] = A[sl1][p];
-    x0 = p == lane ? pv : (dc[0] == -INFINITY ? 0.0 : x0 * pinv);
-    x1 = p == lane + 64 ? pv : (dc[1] == -INFINITY ? 0.0 : x1 * pinv);
-    dc[0] = p == lane ? -INFINITY : fma(-x0, x0, dc[0]);
-    dc[1] = p == lane + 64 ? -INFINITY : fma(-x1, x1, dc[1]);
-    __builtin_amdgcn_wave_barrier();
-    A[p][lane] = x0;
-    A[p][lane + 64] = x1;
-    if (lane == (s & 63)) {
-      if (s < 64) sl0 = p;
-      else sl1 = p;
+    if (!(v > thr) || (s > 0 && !(v >= bound))) break;
+    r = __builtin_amdgcn_readfirstlane(r);
+    if (wave == p / RW) {
+      double x[2] = {a[0][0], a[0][1]};
+#pragma unroll
+      for (int j = 1; j < RW; ++j)
+        if (p % RW == j) {
+          x[0] = a[j][0];
+          x[1] = a[j][1];
+        }
+      const double pv = sqrt(v), pinv = 1.0 / pv;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        L[s][lane + 64 * h] = p == lane + 64 * h ? pv : (dc[h] == -INFINITY ? 0.0 : x[h] * pinv);
+      if (lane == 0) {
+        slot_of[s] = p;
+        st->prow[s] = r;
+        st->pslot[s] = p;
+        st->pval[s] = pv;
+        st->pinv[s] = pinv;
+        st->row[p] = -1;
+        piv[m + s] = r;
+      }
     }
-    if (lane == 0) {
-      st->prow[s] = r;
-      st->pslot[s] = p;
-      st->pval[s] = pv;
-      st->pinv[s] = pinv;
-      st->row[p] = -1;
-      piv[m + s] = r;
+    __syncthreads();
+    const double x[2] = {L[s][lane], L[s][lane + 64]};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) dc[h] = p == lane + 64 * h ? -INFINITY : fma(-x[h], x[h], dc[h]);
+#pragma unroll
+    for (int j = 0; j < RW; ++j) {
+      const double lq = L[s][RW * wave + j];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) a[j][h] = fma(-x[h], lq, a[j][h]);
     }
-    __builtin_amdgcn_wave_barrier();
     ++s;
   }
-  if (lane == 0) st->s = s;
+  // the pivots' columns at the later pivots
+  for (int e = threadIdx.x; e < s * kPool; e += kGreedy) {
+    const int b = e / kPool, c = e % kPool;
+    if (b < c && c < s) st->Lt[e] = L[b][slot_of[c]];
+  }
+  if (threadIdx.x == 0) st->s = s;
 }
 
 int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t st) {
@@ -694,7 +727,7 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
   const double thr = 1e-12 * max_diag(s, st);
   DBuf L(ld * k * 8), d(n * 8), piv(k * 8), state(sizeof(PivState));
   const int np = cdiv(n, 256);
-  DBuf pmax((size_t)np * 8), pool, stage, G;
+  DBuf pmax((size_t)np * 8), A(kPool * kPool * 8), pool, stage, G;
   int slots = 0;
   // the pool and its staging columns, fewer where memory is short
   auto make_pool = [&]() {
@@ -820,7 +853,8 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
       k_piv_place<<<dim3(np, h.fresh), 256, 0, st>>>(stage.as<double>(), n, ld, ps, pool.as<double>());
       LAUNCHCHK();
     }
-    k_piv_greedy<<<1, 1024, 0, st>>>(pool.as<double>(), ld, d.as<double>(), thr, m, (int)std::min<int64_t>(k - m, kPool),
+    k_piv_gather<<<kPool, kPool, 0, st>>>(pool.as<double>(), ld, slots, ps, A.as<double>());
+    k_piv_greedy<<<1, kGreedy, 0, st>>>(A.as<double>(), d.as<double>(), thr, m, (int)std::min<int64_t>(k - m, kPool),
                                      slots, ps, piv.as<int64_t>());
     LAUNCHCHK();
     panel();
