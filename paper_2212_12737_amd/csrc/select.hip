@@ -175,6 +175,27 @@ struct PivState {
   double Lt[kPool * kPool];
 };
 
+// What the host reads of a block, in pinned memory: the pivots behind the greedy
+// kernel's event, the others behind the matching's.
+struct PivHost {
+  int s, stop, fresh;
+};
+class PivEvent {
+ public:
+  PivEvent() { HIPCHK(hipEventCreateWithFlags(&e_, hipEventDisableTiming)); }
+  ~PivEvent() {   // (what the host buffer's kernels still write comes first)
+    (void)hipEventSynchronize(e_);
+    (void)hipEventDestroy(e_);
+  }
+  PivEvent(const PivEvent&) = delete;
+  PivEvent& operator=(const PivEvent&) = delete;
+  void record(hipStream_t st) { HIPCHK(hipEventRecord(e_, st)); }
+  void wait() { HIPCHK(hipEventSynchronize(e_)); }
+
+ private:
+  hipEvent_t e_;
+};
+
 // ---- one pivot at a time: while blocks are short, the passes over the factor
 // cost less than a block's launches
 struct Cand {
@@ -502,7 +523,7 @@ __global__ __launch_bounds__(256) void k_piv_list(const double* __restrict__ d, 
 // Match the listed rows (sorted, so that nothing depends on the order of the
 // atomics) with the pool; the others get free slots, then those of rows no
 // longer listed.
-__global__ __launch_bounds__(kPool) void k_piv_match(PivState* st, int slots) {
+__global__ __launch_bounds__(kPool) void k_piv_match(PivState* st, int slots, PivHost* host) {
   __shared__ int key[kPool], row[kPool], used[kPool], slot_of[kPool], avail[kPool];
   const int t = threadIdx.x;
   const int count = st->stop ? 0 : min(st->count, slots);
@@ -559,7 +580,11 @@ __global__ __launch_bounds__(kPool) void k_piv_match(PivState* st, int slots) {
     st->new_row[rank] = key[t];
     st->new_slot[rank] = q;
   }
-  if (t == 0) st->fresh = nfresh;
+  if (t == 0) {
+    st->fresh = nfresh;
+    host->fresh = nfresh;
+    host->stop = st->stop;
+  }
 }
 
 // G[c][j] = L[rows[c], j0 + j] for j < w, zero for w <= j < ldg and rows of
@@ -637,7 +662,7 @@ constexpr int kGreedy = 512;   // threads of k_piv_greedy
 // took 81 us a block of 34, now 34 and 5 for the gather.
 __global__ __launch_bounds__(kGreedy) void k_piv_greedy(const double* __restrict__ A,
                                                      const double* __restrict__ d, double thr, int64_t m, int limit,
-                                                     int slots, PivState* st, int64_t* __restrict__ piv) {
+                                                     int slots, PivState* st, int64_t* __restrict__ piv, PivHost* host) {
   constexpr int RW = kPool / (kGreedy / 64);
   __shared__ double L[kPool][kPool];   // the pivots' columns
   __shared__ int row[kPool], slot_of[kPool];
@@ -718,7 +743,10 @@ __global__ __launch_bounds__(kGreedy) void k_piv_greedy(const double* __restrict
     const int b = e / kPool, c = e % kPool;
     if (b < c && c < s) st->Lt[e] = L[b][slot_of[c]];
   }
-  if (threadIdx.x == 0) st->s = s;
+  if (threadIdx.x == 0) {
+    st->s = s;
+    host->s = s;
+  }
 }
 
 int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t st) {
@@ -803,11 +831,17 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
   int64_t pending = k <= first + 2 * kFew ? k : first;   // pivots to take one at a time next
   bool running = false;         // a block whose pivot count the host has not read
   bool filled = false;          // the pool holds columns
+  // The host reads a block's pivots while the diagonals are listed, and what is
+  // new in the pool while its columns are brought up to date (one read of both,
+  // after the listing, left the GPU idle for 40 us a block).
+  HBuf host;
+  PivHost* hp = nullptr;
+  PivEvent greedy_done, match_done;
   for (;;) {
     if (pending > 0) {
       if (running) {
-        look();
-        m += h.s;
+        greedy_done.wait();
+        m += hp->s;
         if (m >= k) break;
       }
       singles(pending);
@@ -815,23 +849,29 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
       m += h.ones;
       if (h.stop || m >= k) break;
       HIPCHK(hipMemsetAsync(&ps->ones, 0, sizeof(int), st));
-      HIPCHK(hipMemsetAsync(&ps->s, 0, sizeof(int), st));
       pending = 0;
       running = false;
+      HIPCHK(hipMemsetAsync(&ps->s, 0, sizeof(int), st));
       panel();   // no columns: the block maxima of the diagonal
     }
-    if (slots == 0) make_pool();
+    if (slots == 0) {
+      make_pool();
+      host.ensure(sizeof(PivHost));
+      hp = host.as<PivHost>();
+    }
     k_piv_begin<<<1, 1024, 0, st>>>(pmax.as<double>(), np, thr, ps);
     k_piv_hist<<<scan, 256, 0, st>>>(d.as<double>(), n, thr, ps);
     k_piv_list<<<scan, 256, 0, st>>>(d.as<double>(), n, thr, slots, ps);
-    k_piv_match<<<1, kPool, 0, st>>>(ps, slots);
+    k_piv_match<<<1, kPool, 0, st>>>(ps, slots, hp);
     LAUNCHCHK();
-    look();
+    match_done.record(st);
     if (running) {
-      m += h.s;
-      if (h.s < kShort && (double)n * m * 8.0 < 4e8) pending = kFew;
+      greedy_done.wait();
+      const int got = hp->s;
+      m += got;
+      if (got < kShort && (double)n * m * 8.0 < 4e8) pending = kFew;
+      if (m >= k || got == 0) break;   // (no pivot: at the rank threshold, or where a value is NaN)
     }
-    if (h.stop || m >= k || (running && h.s == 0)) break;   // (no pivot: only where a value is NaN)
     if (filled && m > m_pool) {
       const int64_t w = m - m_pool, ldg = (w + 1) / 2 * 2;
       k_piv_rows<int><<<cdiv(slots * ldg, 256), 256, 0, st>>>(L.as<double>(), ld, m_pool, ps->row, slots, w, ldg,
@@ -839,6 +879,10 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
       LAUNCHCHK();
       subtract(pool.as<double>(), slots, m_pool, w);
     }
+    match_done.wait();
+    h.stop = hp->stop;
+    h.fresh = hp->fresh;
+    if (h.stop) break;
     m_pool = m;
     filled = true;
     if (h.fresh > 0) {
@@ -855,8 +899,9 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
     }
     k_piv_gather<<<kPool, kPool, 0, st>>>(pool.as<double>(), ld, slots, ps, A.as<double>());
     k_piv_greedy<<<1, kGreedy, 0, st>>>(A.as<double>(), d.as<double>(), thr, m, (int)std::min<int64_t>(k - m, kPool),
-                                     slots, ps, piv.as<int64_t>());
+                                     slots, ps, piv.as<int64_t>(), hp);
     LAUNCHCHK();
+    greedy_done.record(st);
     panel();
     running = true;
   }
