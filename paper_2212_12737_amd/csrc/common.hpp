@@ -149,6 +149,10 @@ struct ffk_ctx {
   int device = 0;
   std::string last_error;
   ffk::HBuf host_scratch;          // pinned readback area
+  // A build's flag of bad geometries, which its kernels raise in pinned memory;
+  // builds take turns.
+  std::mutex flag_lock;
+  ffk::HBuf flag;
 };
 
 namespace ffk {
@@ -287,10 +291,12 @@ void center_with(ffk_system* sys, const double* mean, hipStream_t st);
 // The same for N rows of any matrix X (N x D).
 void center_rows(const double* X, const double* mean, int64_t N, int64_t D, double* Xc, double* sqn, hipStream_t st);
 // mvm.hip -- parts of the FP64 product: U = J v (N x D), pd_j = x_c,j . u_j and
-// the column sums of U (cpart: jv_blocks(N) x D workspace); y = J^T G for N
+// the column sums of U (cpart: jv_blocks(N) x D workspace), and beside these rows
+// of X centred with mean; y = J^T G for N
 // rows; the stacked permuted vector of a symmetrized system.
 int jv_blocks(int64_t N);
-void jv_fp64(const ffk_system* s, const double* v, double* U, double* pd, double* cpart, double* sum, hipStream_t st);
+void jv_fp64(const ffk_system* s, const double* v, double* U, double* pd, double* cpart, double* sum, const double* X,
+             const double* mean, int64_t rows, double* Xc, double* sqn, hipStream_t st);
 void jtg_rows(const double* R, const double* G, const double* X, int64_t N, int M, int64_t D, double* y,
               hipStream_t st);
 void permute_stack(const ffk_system* s, const double* v, double* out, hipStream_t st);

@@ -15,6 +15,29 @@
 
 namespace ffk {
 
+// Pair d of the strict lower triangle, whose row p starts at p (p - 1) / 2.
+__device__ inline void pair_of(int64_t d, int& p, int& q) {
+  p = (int)((1.0 + sqrt(1.0 + 8.0 * (double)d)) * 0.5);
+  while ((int64_t)p * (p - 1) / 2 > d) --p;
+  while ((int64_t)p * (p + 1) / 2 <= d) ++p;
+  q = (int)(d - (int64_t)p * (p - 1) / 2);
+}
+
+// x of the pair (p, q) of one geometry and its entry of the pair table; flags
+// coincident atoms and what is not finite.
+__device__ inline double descriptor_entry(const double* Rg, int p, int q, double* PT, int* bad) {
+  const double dx = Rg[3 * p] - Rg[3 * q], dy = Rg[3 * p + 1] - Rg[3 * q + 1],
+               dz = Rg[3 * p + 2] - Rg[3 * q + 2];
+  const double r2 = dx * dx + dy * dy + dz * dz;
+  const double x = 1.0 / sqrt(r2);
+  if (!(r2 > 0.0) || !isfinite(x)) *bad = 1;
+  const double x3 = x * x * x;
+  double2* w = reinterpret_cast<double2*>(PT);
+  w[0] = make_double2(dx * x3, dy * x3);
+  w[1] = make_double2(dz * x3, x);
+  return x;
+}
+
 // Descriptor, pair table and the copies the system keeps: thread e takes
 // element e of X and of R.
 __global__ void k_descriptor(const double* __restrict__ R, int64_t N, int M, int64_t D, double* __restrict__ X,
@@ -24,23 +47,61 @@ __global__ void k_descriptor(const double* __restrict__ R, int64_t N, int M, int
   if (e < N * M * 3) Rcopy[e] = R[e];
   if (e >= N * D) return;
   const int64_t g = e / D, d = e % D;
-  // row p of the strict lower triangle starts at p (p - 1) / 2
-  int p = (int)((1.0 + sqrt(1.0 + 8.0 * (double)d)) * 0.5);
-  while ((int64_t)p * (p - 1) / 2 > d) --p;
-  while ((int64_t)p * (p + 1) / 2 <= d) ++p;
-  const int q = (int)(d - (int64_t)p * (p - 1) / 2);
+  int p, q;
+  pair_of(d, p, q);
   if (g == 0) pairs[d] = p << 16 | q;
-  const double* Rg = R + g * 3 * M;
-  const double dx = Rg[3 * p] - Rg[3 * q], dy = Rg[3 * p + 1] - Rg[3 * q + 1],
-               dz = Rg[3 * p + 2] - Rg[3 * q + 2];
-  const double r2 = dx * dx + dy * dy + dz * dz;
-  const double x = 1.0 / sqrt(r2);
-  if (!(r2 > 0.0) || !isfinite(x)) atomicOr(bad, 1);
-  X[e] = x;
-  const double x3 = x * x * x;
-  double2* w = reinterpret_cast<double2*>(PT + 4 * e);
-  w[0] = make_double2(dx * x3, dy * x3);
-  w[1] = make_double2(dz * x3, x);
+  X[e] = descriptor_entry(R + g * 3 * M, p, q, PT + 4 * e, bad);
+}
+
+// The same of at most kFewRows geometries with their mean, centred rows and
+// norms, in one block: a thread takes pairs of all geometries.  (Apart,
+// with a flag cleared and copied by the GPU, a prediction of one geometry waited
+// for their launches: 95 us, 76 with this one, the flag in pinned memory and one
+// launch fewer in kernel_predict, at M = 21, N = 2000.)
+constexpr int kFewRows = 8;
+__global__ __launch_bounds__(1024) void k_descriptor_few(const double* __restrict__ R, int N, int M, int64_t D,
+                                                         double* __restrict__ X, double* __restrict__ PT,
+                                                         int* __restrict__ pairs, double* __restrict__ Rcopy,
+                                                         double* __restrict__ mean, double* __restrict__ Xc,
+                                                         double* __restrict__ sqn, int* __restrict__ bad) {
+  __shared__ double red[16][kFewRows];
+  for (int e = threadIdx.x; e < N * M * 3; e += 1024) Rcopy[e] = R[e];
+  double sq[kFewRows] = {};
+  for (int64_t d = threadIdx.x; d < D; d += 1024) {
+    int p, q;
+    pair_of(d, p, q);
+    pairs[d] = p << 16 | q;
+    double x[kFewRows], sum = 0.0;
+#pragma unroll
+    for (int g = 0; g < kFewRows; ++g)
+      if (g < N) {
+        x[g] = descriptor_entry(R + (int64_t)g * 3 * M, p, q, PT + 4 * (g * D + d), bad);
+        X[g * D + d] = x[g];
+        sum += x[g];
+      }
+    const double mu = sum * (1.0 / (double)N);
+    mean[d] = mu;
+#pragma unroll
+    for (int g = 0; g < kFewRows; ++g)
+      if (g < N) {
+        const double c = x[g] - mu;
+        Xc[g * D + d] = c;
+        sq[g] += c * c;
+      }
+  }
+#pragma unroll
+  for (int g = 0; g < kFewRows; ++g) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sq[g] += __shfl_xor(sq[g], o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][g] = sq[g];
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < N) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) t += red[w][threadIdx.x];
+    sqn[threadIdx.x] = t;
+  }
 }
 
 // scale times the sums of the columns of X (N x D) over rows [rows y, rows y +
@@ -96,29 +157,42 @@ void descriptor_build(ffk_system* s, const double* R, hipStream_t st, bool coeff
   s->Xc.alloc(N * D * sizeof(double));
   s->xmean.alloc(D * sizeof(double));
   s->sqn.alloc(N * sizeof(double));
-  DBuf bad(sizeof(int));
-  HIPCHK(hipMemsetAsync(bad.get(), 0, sizeof(int), st));
-  k_descriptor<<<cdiv(N * std::max<int64_t>(D, 3 * M), 256), 256, 0, st>>>(
-      R, N, M, D, s->X.as<double>(), s->PT.as<double>(), s->pairs.as<int>(), s->R.as<double>(), bad.as<int>());
-  LAUNCHCHK();
   // column means: sums of 512 rows, then the sum of those
   const int S = cdiv(N, 512);
   DBuf part(S > 1 ? (size_t)S * D * 8 : 0);
-  k_colmean<<<dim3(cdiv(D, 16), S), 256, 0, st>>>(s->X.as<double>(), N, D, 512, S == 1 ? 1.0 / (double)N : 1.0,
-                                                  S == 1 ? s->xmean.as<double>() : part.as<double>());
-  LAUNCHCHK();
-  if (S > 1) {
-    k_colmean<<<dim3(cdiv(D, 16), 1), 256, 0, st>>>(part.as<double>(), S, D, S, 1.0 / (double)N, s->xmean.as<double>());
+  std::lock_guard<std::mutex> lock(s->ctx->flag_lock);
+  s->ctx->flag.ensure(sizeof(int));
+  int* bad = s->ctx->flag.as<int>();   // looked at once, at the end: nothing below depends on it
+  *bad = 0;
+  // up to some 10^4 elements: a block's 1024 threads take eight pairs each
+  if (N <= kFewRows && N * std::max<int64_t>(D, 3 * M) <= 8192) {
+    k_descriptor_few<<<1, 1024, 0, st>>>(R, (int)N, M, D, s->X.as<double>(), s->PT.as<double>(), s->pairs.as<int>(),
+                                         s->R.as<double>(), s->xmean.as<double>(), s->Xc.as<double>(),
+                                         s->sqn.as<double>(), bad);
+    LAUNCHCHK();
+  } else {
+    k_descriptor<<<cdiv(N * std::max<int64_t>(D, 3 * M), 256), 256, 0, st>>>(
+        R, N, M, D, s->X.as<double>(), s->PT.as<double>(), s->pairs.as<int>(), s->R.as<double>(), bad);
+    LAUNCHCHK();
+    k_colmean<<<dim3(cdiv(D, 16), S), 256, 0, st>>>(s->X.as<double>(), N, D, 512, S == 1 ? 1.0 / (double)N : 1.0,
+                                                    S == 1 ? s->xmean.as<double>() : part.as<double>());
+    LAUNCHCHK();
+    if (S > 1) {
+      k_colmean<<<dim3(cdiv(D, 16), 1), 256, 0, st>>>(part.as<double>(), S, D, S, 1.0 / (double)N,
+                                                      s->xmean.as<double>());
+      LAUNCHCHK();
+    }
+    k_center<<<N, 256, 0, st>>>(s->X.as<double>(), s->xmean.as<double>(), D, s->Xc.as<double>(), s->sqn.as<double>());
     LAUNCHCHK();
   }
-  k_center<<<N, 256, 0, st>>>(s->X.as<double>(), s->xmean.as<double>(), D, s->Xc.as<double>(),
-                              s->sqn.as<double>());
-  LAUNCHCHK();
-  if (coefficients) ensure_coeffs(s, FFK_FP64, st);
-  int hbad = 0;   // looked at once, at the end: nothing above depends on it
-  HIPCHK(hipMemcpyAsync(&hbad, bad.get(), sizeof(int), hipMemcpyDeviceToHost, st));
+  try {
+    if (coefficients) ensure_coeffs(s, FFK_FP64, st);
+  } catch (...) {
+    (void)hipStreamSynchronize(st);   // before the flag is another build's
+    throw;
+  }
   HIPCHK(hipStreamSynchronize(st));
-  if (hbad) fail(FFK_ERR_NONFINITE, "descriptor_build: coincident atoms or non-finite coordinates");
+  if (*bad) fail(FFK_ERR_NONFINITE, "descriptor_build: coincident atoms or non-finite coordinates");
 }
 
 // ------------------------------------------------------------ conversions ----

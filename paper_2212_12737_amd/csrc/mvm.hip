@@ -158,9 +158,9 @@ static void launch_jv(int64_t N, int M, hipStream_t st, A... args) {
 // butterfly combines the lanes.  (Eight loads per lane in flight, with the
 // ones past the end clamped and masked, made it slower at M = 60, N = 20000:
 // 16.5 -> 19.9 us; at N = 2000 it sits at a 6 us floor either way.)
-__global__ __launch_bounds__(256) void k_colsum_final(const double* __restrict__ part, int nblk, int64_t D,
-                                                      double* __restrict__ s) {
-  const int64_t col = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+__device__ inline void colsum_four(const double* __restrict__ part, int nblk, int64_t D, int64_t col0,
+                                   double* __restrict__ s) {
+  const int64_t col = col0 + (threadIdx.x >> 6);
   const int q = threadIdx.x & 63;
   double a0 = 0.0, a1 = 0.0;
   if (col < D) {
@@ -175,6 +175,10 @@ __global__ __launch_bounds__(256) void k_colsum_final(const double* __restrict__
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off);
   if (q == 0 && col < D) s[col] = t;
+}
+__global__ __launch_bounds__(256) void k_colsum_final(const double* __restrict__ part, int nblk, int64_t D,
+                                                      double* __restrict__ s) {
+  colsum_four(part, nblk, D, (int64_t)blockIdx.x * 4, s);
 }
 
 // Sum of x over a block of 64, 128 or 256 lanes: wave butterflies, then the
@@ -1185,10 +1189,9 @@ void kernel_mvm_phases(ffk_system* s, const double* v, double* y, double shift, 
 }
 
 // ------------------------------------------- parts that prediction shares ----
-__global__ void k_center_with(const double* __restrict__ X, const double* __restrict__ mean, int64_t D,
-                              double* __restrict__ Xc, double* __restrict__ sqn) {
+__device__ inline void center_row(const double* __restrict__ X, const double* __restrict__ mean, int64_t D, int64_t g,
+                                  double* __restrict__ Xc, double* __restrict__ sqn) {
   __shared__ double red[256];
-  const int64_t g = blockIdx.x;
   double s = 0.0;
   for (int64_t d = threadIdx.x; d < D; d += blockDim.x) {
     const double v = X[g * D + d] - mean[d];
@@ -1203,6 +1206,10 @@ __global__ void k_center_with(const double* __restrict__ X, const double* __rest
   }
   if (threadIdx.x == 0) sqn[g] = red[0];
 }
+__global__ void k_center_with(const double* __restrict__ X, const double* __restrict__ mean, int64_t D,
+                              double* __restrict__ Xc, double* __restrict__ sqn) {
+  center_row(X, mean, D, blockIdx.x, Xc, sqn);
+}
 
 void center_rows(const double* X, const double* mean, int64_t N, int64_t D, double* Xc, double* sqn, hipStream_t st) {
   k_center_with<<<(unsigned)N, 256, 0, st>>>(X, mean, D, Xc, sqn);
@@ -1215,11 +1222,23 @@ void center_with(ffk_system* sys, const double* mean, hipStream_t st) {
 
 int jv_blocks(int64_t N) { return cdiv(N, jv_group(N)); }
 
-void jv_fp64(const ffk_system* s, const double* v, double* U, double* pd, double* cpart, double* sum, hipStream_t st) {
+// The column sums of jv_fp64's partials (the first blocks) beside the centring of
+// test rows: neither needs the other, and each alone is mostly its launch.
+__global__ __launch_bounds__(256) void k_sum_and_center(const double* __restrict__ part, int nblk, int64_t D,
+                                                        double* __restrict__ s, const double* __restrict__ X,
+                                                        const double* __restrict__ mean, double* __restrict__ Xc,
+                                                        double* __restrict__ sqn) {
+  const int64_t nc = (D + 3) / 4;
+  if (blockIdx.x < nc) colsum_four(part, nblk, D, (int64_t)blockIdx.x * 4, s);
+  else center_row(X, mean, D, blockIdx.x - nc, Xc, sqn);
+}
+
+void jv_fp64(const ffk_system* s, const double* v, double* U, double* pd, double* cpart, double* sum, const double* X,
+             const double* mean, int64_t rows, double* Xc, double* sqn, hipStream_t st) {
   launch_jv<0>(s->N, s->M, st, s->R.as<double>(), s->pairs.as<int>(), v, s->Xc.as<double>(), s->N, s->M, s->D, (void*)U,
                nullptr, s->D, nullptr, nullptr, (int64_t)0, pd, cpart);
   LAUNCHCHK();
-  k_colsum_final<<<cdiv(s->D, 4), 256, 0, st>>>(cpart, jv_blocks(s->N), s->D, sum);
+  k_sum_and_center<<<(unsigned)(cdiv(s->D, 4) + rows), 256, 0, st>>>(cpart, jv_blocks(s->N), s->D, sum, X, mean, Xc, sqn);
   LAUNCHCHK();
 }
 

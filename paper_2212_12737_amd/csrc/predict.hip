@@ -225,10 +225,10 @@ static void predict_from(const ffk_system* src, const double* mean, const ffk_sy
   const int64_t opart = take((int64_t)chunks * batch * D);
   work.ensure(off * 8);
   double* w = work.as<double>();
-  jv_fp64(src, v, w + oU, w + opd, w + ocp, w + os, st);
+  jv_fp64(src, v, w + oU, w + opd, w + ocp, w + os, te->X.as<double>(), mean, batch, w + oXt, w + osq, st);
   for (int64_t b0 = 0; b0 < te->N; b0 += batch) {
     const int T = (int)std::min<int64_t>(batch, te->N - b0);
-    center_rows(te->X.as<double>() + b0 * D, mean, T, D, w + oXt, w + osq, st);
+    if (b0 > 0) center_rows(te->X.as<double>() + b0 * D, mean, T, D, w + oXt, w + osq, st);
     PredictArgs g{w + oXt, w + osq, src->Xc.as<double>(), src->sqn.as<double>(), w + oU, w + opd, w + opart, w + owp,
                   T, (int)N, (int)D, chunks, cdiv(T, 16 * TB), sqrt(5.0) / src->sigma, src->a0, src->bcoef};
     if (TB == 1 && CB == 1) launch_part<1, 1>(g, st);
