@@ -301,6 +301,14 @@ void jtg_rows(const double* R, const double* G, const double* X, int64_t N, int 
               hipStream_t st);
 void permute_stack(const ffk_system* s, const double* v, double* out, hipStream_t st);
 
+// predict.hip -- both dense steps of the FP64 product against few sources in one
+// kernel: chunks x Nt x D parts of G and the Nt x chunks row sums of W.
+// product_few_chunks: how many (at most D), 0 where the GEMMs are to run.
+int product_few_chunks(int64_t Nt, int64_t Ns, int64_t D, size_t part_bytes);
+void product_few(const double* Xt, const double* Xs, const double* U, int64_t ldu, const double* pd, const double* dA,
+                 const double* B, int64_t ldc, int64_t Nt, int64_t Ns, int64_t D, int chunks, double* part,
+                 double* wpart, hipStream_t st);
+
 // fused.hip -- the product's two dense steps in one kernel (BF16, D <= 128)
 // Operands of the fused product (layouts as in the two-GEMM form).
 struct FusedArgs {

@@ -935,10 +935,11 @@ static void kernel_mvm_core(ffk_system* t, ffk_system* src, CoeffSet* coef, cons
   const int nblk = cdiv(Ns, jv_group(Ns));
   double* pd = b.pd;
   double* cp = b.spart;
+  const int few = prec == FFK_FP64 ? product_few_chunks(N, Ns, D, b.part_bytes) : 0;
   clk_begin(CLK_JV, st);
   if (prec == FFK_FP64)
     launch_jv<0>(Ns, M, st, src->R.as<double>(), src->pairs.as<int>(), vs, src->Xc.as<double>(), Ns, M, D,
-                 b.U, nullptr, ldu, b.UT, nullptr, Nsr, pd, cp);
+                 b.U, nullptr, ldu, few ? nullptr : b.UT, nullptr, Nsr, pd, cp);
   else if (prec == FFK_FP32)
     launch_jv<1>(Ns, M, st, src->R.as<double>(), src->pairs.as<int>(), vs, src->Xc.as<double>(), Ns, M, D,
                  b.U, nullptr, ldu, b.UT, nullptr, Nsr, pd, cp);
@@ -965,7 +966,14 @@ static void kernel_mvm_core(ffk_system* t, ffk_system* src, CoeffSet* coef, cons
   o.Bc = cs.B.get();
   o.Uh = b.U; o.UTh = b.UT; o.Wh = b.Wh;
   // GEMM 1 takes the targets' descriptor, GEMM 2 the sources' (transposed)
-  if (prec == FFK_FP64) {
+  if (few) {
+    clk_begin(CLK_FUSED, st);
+    // (G is not formed: its buffer takes the row sums)
+    product_few(t->Xc.as<double>(), src->Xc.as<double>(), static_cast<const double*>(b.U), ldu, pd,
+                cs.dA_hi.as<double>(), cs.B.as<double>(), Nsr, N, Ns, D, few, static_cast<double*>(b.part), b.G, st);
+    clk_end(CLK_FUSED, st);
+    mark(ev, 3, st);
+  } else if (prec == FFK_FP64) {
     o.Xh = t->Xp64.get(); o.XTh = src->XpT64.get();
     go = mvm_gemms_for<double, false, double>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
   } else if (prec == FFK_FP32) {
@@ -1009,7 +1017,11 @@ static void kernel_mvm_core(ffk_system* t, ffk_system* src, CoeffSet* coef, cons
   const size_t shj = (3 * M + D + 1) * sizeof(double);
   const double* xm = t->xmean.as<double>();
   clk_begin(CLK_JTG, st);
-  if (go.splits < 0)
+  if (few) {
+    launch_jtg_reduce(N, D, shj, st, static_cast<const double*>(b.part), few, N, b.s, t->Xc.as<double>(), xm,
+                      static_cast<const double*>(b.G), few, t->a0, t->R.as<double>(), v, shift, M, D, y,
+                      vy_part);
+  } else if (go.splits < 0)
     launch_jtg_reduce(N, D, shj, st, static_cast<const float*>(b.part), -go.splits, N, b.s, t->Xc.as<double>(), xm,
                       b.wpart, go.ntn, t->a0, t->R.as<double>(), v, shift, M, D, y, vy_part);
   else if (go.splits == 1)

@@ -13,7 +13,7 @@
 // test system's setup) against the same products as separate scalar GEMMs on
 // 128-row tiles with T x N results in memory: 442 -> 95 us at M = 21, N = 2000,
 // T = 1; 1894 -> 438 us at M = 42, N = 5000, T = 200, of it 269 us this kernel
-// (26 TFLOP/s).
+// (26 TFLOP/s).  The FP64 product of small systems runs it too (product_few).
 #include <type_traits>
 
 #include "smalldot.hpp"
@@ -28,13 +28,17 @@ struct PredictArgs {
   double* wpart;                  // T x chunks row sums of W
   int T, N, D, chunks, tiles;
   double inv_len, a0, bcoef;
+  int64_t ldu;                    // of U
+  const double *dA, *B;           // KNOWN: the coefficients (T x N, ldc)
+  int64_t ldc;
 };
 
 // TB blocks of 16 test geometries; CB blocks of 16 training ones (1: the four
 // waves split K = D; 4: a block each).  Workgroups: the test tiles of a chunk
 // of training geometries run one after the other on one XCD (workgroup w on XCD
-// w % 8), which reads the chunk's rows into its L2 once.
-template <int TB, int CB>
+// w % 8), which reads the chunk's rows into its L2 once.  KNOWN: a product whose
+// coefficients are at hand, so that of the Gram products only P is left.
+template <int TB, int CB, bool KNOWN>
 __global__ __launch_bounds__(256) void k_predict_part(PredictArgs g) {
   constexpr int CH = 16 * CB, TR = 16 * TB;
   __shared__ double sA[TR][CH + 1], sW[TR][CH + 1];
@@ -53,14 +57,34 @@ __global__ __launch_bounds__(256) void k_predict_part(PredictArgs g) {
   d4 gm[TB], pm[TB];
 #pragma unroll
   for (int i = 0; i < TB; ++i) gm[i] = pm[i] = d4{0, 0, 0, 0};
-  rows_dot<TB, true>(a, g.Xs + srow * D, g.U + srow * D, D, CB == 1 ? steps * wave / 4 : 0,
-                     CB == 1 ? steps * (wave + 1) / 4 : steps, gm, pm);
+  const int k0 = CB == 1 ? steps * wave / 4 : 0, k1 = CB == 1 ? steps * (wave + 1) / 4 : steps;
+  constexpr int PB = CB == 1 ? 1 : 4;   // this thread's pairs of a block of test geometries
+  double known[KNOWN ? TB : 1][PB][2];
+  if constexpr (KNOWN) {
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+      for (int v = 0; v < PB; ++v) {
+        const int t = t0 + 16 * i + (CB == 1 ? (int)threadIdx.x >> 4 : 4 * v + q16);
+        const int64_t e = (int64_t)min(t, g.T - 1) * g.ldc + min(s0 + (CB == 1 ? 0 : 16 * wave) + c16, g.N - 1);
+        known[i][v][0] = g.dA[e];
+        known[i][v][1] = g.B[e];
+      }
+    rows_dot<TB, false>(a, g.U + srow * g.ldu, nullptr, D, k0, k1, pm, gm);
+  } else {
+    rows_dot<TB, true>(a, g.Xs + srow * D, g.U + srow * g.ldu, D, k0, k1, gm, pm);
+  }
   // dA and -W of one (test, training) pair into LDS; returns W
-  auto pair = [&](int t, int s, double gram, double p) {
+  auto pair = [&](int i, int v, int t, int s, double gram, double p) {
     double dA = 0.0, w = 0.0;
     if (t0 + t < g.T && s0 + s < g.N) {
       double B;
-      matern_coeffs(g.sqt[t0 + t] + g.sqs[s0 + s] - 2.0 * gram, g.inv_len, g.a0, g.bcoef, dA, B);
+      if constexpr (KNOWN) {
+        dA = known[i][v][0];
+        B = known[i][v][1];
+      } else {
+        matern_coeffs(g.sqt[t0 + t] + g.sqs[s0 + s] - 2.0 * gram, g.inv_len, g.a0, g.bcoef, dA, B);
+      }
       w = B * (p - g.pd[s0 + s]);
     }
     sA[t][s] = dA;
@@ -77,15 +101,17 @@ __global__ __launch_bounds__(256) void k_predict_part(PredictArgs g) {
     for (int i = 0; i < TB; ++i)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        red[wave][0][16 * i + 4 * v + q16][c16] = gm[i][v];
+        if (!KNOWN) red[wave][0][16 * i + 4 * v + q16][c16] = gm[i][v];
         red[wave][1][16 * i + 4 * v + q16][c16] = pm[i][v];
       }
     __syncthreads();
-    for (int t = threadIdx.x >> 4; t < TR; t += 16) {
-      double x[2];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) x[h] = (red[0][h][t][c16] + red[1][h][t][c16]) + (red[2][h][t][c16] + red[3][h][t][c16]);
-      const double w = sum16(pair(t, c16, x[0], x[1]));
+    for (int i = 0; i < TB; ++i) {
+      const int t = 16 * i + (threadIdx.x >> 4);
+      double x[2] = {0.0, 0.0};
+#pragma unroll
+      for (int h = KNOWN ? 1 : 0; h < 2; ++h) x[h] = (red[0][h][t][c16] + red[1][h][t][c16]) + (red[2][h][t][c16] + red[3][h][t][c16]);
+      const double w = sum16(pair(i, 0, t, c16, x[0], x[1]));
       if (c16 == 0) rsum[0][t] = w;
     }
   } else {
@@ -94,7 +120,7 @@ __global__ __launch_bounds__(256) void k_predict_part(PredictArgs g) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int t = 16 * i + 4 * v + q16;
-        const double w = sum16(pair(t, 16 * wave + c16, gm[i][v], pm[i][v]));
+        const double w = sum16(pair(i, v, t, 16 * wave + c16, gm[i][v], pm[i][v]));
         if (c16 == 0) rsum[wave][t] = w;
       }
   }
@@ -114,7 +140,7 @@ __global__ __launch_bounds__(256) void k_predict_part(PredictArgs g) {
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       const int64_t s = min(s0 + 4 * (kb * Q + q) + q16, g.N - 1);
-      r.u[q] = g.U[s * D + d];
+      r.u[q] = g.U[s * g.ldu + d];
       r.x[q] = g.Xs[s * D + d];
     }
   };
@@ -192,11 +218,33 @@ __global__ __launch_bounds__(1024) void k_predict_reduce(const double* __restric
   }
 }
 
-template <int TB, int CB>
+template <int TB, int CB, bool KNOWN = false>
 static void launch_part(const PredictArgs& g, hipStream_t st) {
   const int groups = cdiv(g.chunks, 8);
-  k_predict_part<TB, CB><<<(unsigned)(8 * groups * g.tiles), 256, 0, st>>>(g);
+  k_predict_part<TB, CB, KNOWN><<<(unsigned)(8 * groups * g.tiles), 256, 0, st>>>(g);
   LAUNCHCHK();
+}
+
+// One kernel where its workgroups (16 targets, 16 sources up to 256 of them and
+// 64 beyond) find a CU each; with D <= 128, whose GEMMs have few tiles too, up to
+// 1024 sources.  One kernel against the GEMMs, us a product: M = 9, N = 200 19,
+// 29; M = 21, N = 250 22, 40; M = 56, N = 512 111, 154; but M = 56, N = 600 233,
+// 174; M = 9, N = 1000 29, 42; M = 16, N = 1024 45, 53; M = 21, N = 1000 61, 59.
+// (32 targets a workgroup took 10 to 25% longer from M = 21 on.)
+int product_few_chunks(int64_t Nt, int64_t Ns, int64_t D, size_t part_bytes) {
+  int chunks = cdiv(Ns, Ns <= 256 ? 16 : 64);
+  if (chunks > 16 || (D > 128 && (int64_t)chunks * cdiv(Nt, 16) > device_cus())) return 0;
+  if (chunks > 8) chunks = 16;   // (counts that the reduction is compiled for; those past the sources are zeros)
+  return chunks <= D && (size_t)(chunks * Nt * D * 8) <= part_bytes ? chunks : 0;
+}
+
+void product_few(const double* Xt, const double* Xs, const double* U, int64_t ldu, const double* pd, const double* dA,
+                 const double* B, int64_t ldc, int64_t Nt, int64_t Ns, int64_t D, int chunks, double* part,
+                 double* wpart, hipStream_t st) {
+  const PredictArgs g{Xt, nullptr, Xs, nullptr, U, pd, part, wpart, (int)Nt, (int)Ns, (int)D, chunks, cdiv(Nt, 16),
+                      0.0, 0.0, 0.0, ldu, dA, B, ldc};
+  if (Ns <= 256) launch_part<1, 1, true>(g, st);
+  else launch_part<1, 4, true>(g, st);
 }
 
 // F = K(te, src) v for sources whose descriptors are centred with `mean`, with
@@ -209,9 +257,10 @@ static void predict_from(const ffk_system* src, const double* mean, const ffk_sy
   // take more than 256 MB
   const int64_t most = (256ll << 20) / ((int64_t)cdiv(N, 64) * D * 8) / 32 * 32;
   const int64_t batch = std::min<int64_t>(te->N, std::min<int64_t>(512, std::max<int64_t>(32, most)));
-  const int TB = batch > 16 ? 2 : 1;
+  // 32 test and 64 training geometries a workgroup where that gives every CU
+  // one, else 16 test ones, and 16 training ones where even so some have none
+  const int TB = batch > 16 && (int64_t)cdiv(batch, 32) * cdiv(N, 64) >= 256 ? 2 : 1;
   const int tiles = cdiv(batch, 16 * TB);
-  // 64 training geometries a workgroup where that gives every CU one
   const int CB = (int64_t)tiles * cdiv(N, 64) >= 256 ? 4 : 1;
   const int chunks = cdiv(N, 16 * CB);
   int64_t off = 0;
@@ -230,10 +279,10 @@ static void predict_from(const ffk_system* src, const double* mean, const ffk_sy
     const int T = (int)std::min<int64_t>(batch, te->N - b0);
     if (b0 > 0) center_rows(te->X.as<double>() + b0 * D, mean, T, D, w + oXt, w + osq, st);
     PredictArgs g{w + oXt, w + osq, src->Xc.as<double>(), src->sqn.as<double>(), w + oU, w + opd, w + opart, w + owp,
-                  T, (int)N, (int)D, chunks, cdiv(T, 16 * TB), sqrt(5.0) / src->sigma, src->a0, src->bcoef};
-    if (TB == 1 && CB == 1) launch_part<1, 1>(g, st);
+                  T, (int)N, (int)D, chunks, cdiv(T, 16 * TB), sqrt(5.0) / src->sigma, src->a0, src->bcoef,
+                  D, nullptr, nullptr, 0};
+    if (CB == 1) launch_part<1, 1>(g, st);
     else if (TB == 1) launch_part<1, 4>(g, st);
-    else if (CB == 1) launch_part<2, 1>(g, st);
     else launch_part<2, 4>(g, st);
     k_predict_reduce<<<dim3(cdiv(D, 64), T), 1024, 0, st>>>(w + opart, chunks, T, (int)D, w + owp, w + os, w + oXt,
                                                             src->a0, w + oG);
