@@ -226,7 +226,7 @@ struct ffk_system {
   ffk::MvmWork stack_work;
   ffk::DBuf stack_v;
   // Prediction with this system as the model: workspace (U, N D 8 bytes,
-  // and up to 256 MB or so of parts of G) and the stacked vector, one call at a time.
+  // and up to 512 MB of parts of G) and the stacked vector, one call at a time.
   mutable std::mutex predict_lock;
   mutable ffk::DBuf predict_work, predict_v;
 };
@@ -292,8 +292,8 @@ void center_with(ffk_system* sys, const double* mean, hipStream_t st);
 void center_rows(const double* X, const double* mean, int64_t N, int64_t D, double* Xc, double* sqn, hipStream_t st);
 // mvm.hip -- parts of the FP64 product: U = J v (N x D), pd_j = x_c,j . u_j and
 // the column sums of U (cpart: jv_blocks(N) x D workspace), and beside these rows
-// of X centred with mean; y = J^T G for N
-// rows; the stacked permuted vector of a symmetrized system.
+// of X centred with mean; y = J^T G for N rows; the stacked permuted vector of a
+// symmetrized system.
 int jv_blocks(int64_t N);
 void jv_fp64(const ffk_system* s, const double* v, double* U, double* pd, double* cpart, double* sum, const double* X,
              const double* mean, int64_t rows, double* Xc, double* sqn, hipStream_t st);

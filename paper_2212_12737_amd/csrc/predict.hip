@@ -12,8 +12,9 @@
 // and by reading the training rows from L2 for hundreds.  A prediction (with the
 // test system's setup) against the same products as separate scalar GEMMs on
 // 128-row tiles with T x N results in memory: 442 -> 95 us at M = 21, N = 2000,
-// T = 1; 1894 -> 438 us at M = 42, N = 5000, T = 200, of it 269 us this kernel
-// (26 TFLOP/s).  The FP64 product of small systems runs it too (product_few).
+// T = 1; 1894 -> 438 us at M = 42, N = 5000, T = 200, and 360 since two
+// workgroups fit a CU and their last round is a full one (205 us in this kernel, 34
+// TFLOP/s).  The FP64 product of small systems runs it too (product_few).
 #include <type_traits>
 
 #include "smalldot.hpp"
@@ -25,12 +26,13 @@ struct PredictArgs {
   const double *Xs, *sqs;         // centred training rows (N x D), |x_s|^2
   const double *U, *pd;           // J alpha (N x D), x_s . u_s
   double* part;                   // chunks x T x D parts of G
-  double* wpart;                  // T x chunks row sums of W
+  double* wpart;                  // T x chunks row sums of W (stride planes)
   int T, N, D, chunks, tiles;
   double inv_len, a0, bcoef;
   int64_t ldu;                    // of U
   const double *dA, *B;           // KNOWN: the coefficients (T x N, ldc)
   int64_t ldc;
+  int planes;                     // parts of G altogether: the stride of wpart
 };
 
 // TB blocks of 16 test geometries; CB blocks of 16 training ones (1: the four
@@ -39,7 +41,7 @@ struct PredictArgs {
 // w % 8), which reads the chunk's rows into its L2 once.  KNOWN: a product whose
 // coefficients are at hand, so that of the Gram products only P is left.
 template <int TB, int CB, bool KNOWN>
-__global__ __launch_bounds__(256) void k_predict_part(PredictArgs g) {
+__global__ __launch_bounds__(256, TB == 2 ? 2 : 1) void k_predict_part(PredictArgs g) {
   constexpr int CH = 16 * CB, TR = 16 * TB;
   __shared__ double sA[TR][CH + 1], sW[TR][CH + 1];
   __shared__ double red[CB == 1 ? 4 : 1][2][CB == 1 ? TR : 1][17];
@@ -128,7 +130,7 @@ __global__ __launch_bounds__(256) void k_predict_part(PredictArgs g) {
   if (threadIdx.x < TR && t0 + (int)threadIdx.x < g.T) {
     double w = rsum[0][threadIdx.x];
     if (CB > 1) w = (w + rsum[1][threadIdx.x]) + (rsum[2][threadIdx.x] + rsum[3][threadIdx.x]);
-    g.wpart[(int64_t)(t0 + threadIdx.x) * g.chunks + chunk] = w;
+    g.wpart[(int64_t)(t0 + threadIdx.x) * g.planes + chunk] = w;
   }
   // this chunk's part of G: a wave takes every fourth block of 16 columns;
   // training rows past the end read the last one, against zeros of dA and W
@@ -151,6 +153,9 @@ __global__ __launch_bounds__(256) void k_predict_part(PredictArgs g) {
     d4 ga[TB], gw[TB];
 #pragma unroll
     for (int i = 0; i < TB; ++i) ga[i] = gw[i] = d4{0, 0, 0, 0};
+    // dA and W are read anew for each block: kept in registers they took 128 of
+    // them, and a CU one workgroup
+    if (TB == 2) asm volatile("" ::: "memory");
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
       Rows& cur = r[(F + kb) & 1];
@@ -242,7 +247,7 @@ void product_few(const double* Xt, const double* Xs, const double* U, int64_t ld
                  const double* B, int64_t ldc, int64_t Nt, int64_t Ns, int64_t D, int chunks, double* part,
                  double* wpart, hipStream_t st) {
   const PredictArgs g{Xt, nullptr, Xs, nullptr, U, pd, part, wpart, (int)Nt, (int)Ns, (int)D, chunks, cdiv(Nt, 16),
-                      0.0, 0.0, 0.0, ldu, dA, B, ldc};
+                      0.0, 0.0, 0.0, ldu, dA, B, ldc, chunks};
   if (Ns <= 256) launch_part<1, 1, true>(g, st);
   else launch_part<1, 4, true>(g, st);
 }
@@ -253,16 +258,28 @@ static void predict_from(const ffk_system* src, const double* mean, const ffk_sy
                          DBuf& work, hipStream_t st) {
   const int64_t N = src->N, D = src->D;
   const int M = src->M;
-  // test geometries at a time: up to 512, fewer where the parts of G would
-  // take more than 256 MB
+  // test geometries at a time: up to 512, fewer where the parts of G in chunks of
+  // 64 training geometries would take more than 256 MB (those of 16, of at most a
+  // third of them, may double that)
   const int64_t most = (256ll << 20) / ((int64_t)cdiv(N, 64) * D * 8) / 32 * 32;
-  const int64_t batch = std::min<int64_t>(te->N, std::min<int64_t>(512, std::max<int64_t>(32, most)));
+  const int64_t limit = std::min<int64_t>(512, std::max<int64_t>(32, most));
+  const int64_t batch = std::min<int64_t>(te->N, (cdiv(te->N, cdiv(te->N, limit)) + 31) / 32 * 32);   // of about one size
   // 32 test and 64 training geometries a workgroup where that gives every CU
   // one, else 16 test ones, and 16 training ones where even so some have none
   const int TB = batch > 16 && (int64_t)cdiv(batch, 32) * cdiv(N, 64) >= 256 ? 2 : 1;
   const int tiles = cdiv(batch, 16 * TB);
   const int CB = (int64_t)tiles * cdiv(N, 64) >= 256 ? 4 : 1;
-  const int chunks = cdiv(N, 16 * CB);
+  // Workgroups of 32 and 64 past an XCD's last full round of two a CU, if they
+  // fill less than half of one, are cut to 16 and 16: at M = 42, N = 5000, T = 200
+  // 70 of them on 64 places took two rounds.
+  int chunks = cdiv(N, 16 * CB);
+  const int64_t places = device_cus() / 4, most_xcd = (int64_t)tiles * cdiv(chunks, 8);
+  int64_t tail = 0;   // training geometries in the smaller workgroups
+  if (TB == 2 && most_xcd > places && most_xcd % places < places / 2) {
+    chunks = (int)std::min<int64_t>(chunks, most_xcd / places * places / tiles * 8);
+    tail = std::max<int64_t>(0, N - 64ll * chunks);
+  }
+  const int planes = chunks + cdiv(tail, 16);
   int64_t off = 0;
   auto take = [&](int64_t doubles) {
     const int64_t o = off;
@@ -270,8 +287,8 @@ static void predict_from(const ffk_system* src, const double* mean, const ffk_sy
     return o;
   };
   const int64_t oU = take(N * D), opd = take(N), os = take(D), ocp = take((int64_t)jv_blocks(N) * D);
-  const int64_t oXt = take(batch * D), osq = take(batch), owp = take(batch * chunks), oG = take(batch * D);
-  const int64_t opart = take((int64_t)chunks * batch * D);
+  const int64_t oXt = take(batch * D), osq = take(batch), owp = take(batch * planes), oG = take(batch * D);
+  const int64_t opart = take((int64_t)planes * batch * D);
   work.ensure(off * 8);
   double* w = work.as<double>();
   jv_fp64(src, v, w + oU, w + opd, w + ocp, w + os, te->X.as<double>(), mean, batch, w + oXt, w + osq, st);
@@ -279,12 +296,22 @@ static void predict_from(const ffk_system* src, const double* mean, const ffk_sy
     const int T = (int)std::min<int64_t>(batch, te->N - b0);
     if (b0 > 0) center_rows(te->X.as<double>() + b0 * D, mean, T, D, w + oXt, w + osq, st);
     PredictArgs g{w + oXt, w + osq, src->Xc.as<double>(), src->sqn.as<double>(), w + oU, w + opd, w + opart, w + owp,
-                  T, (int)N, (int)D, chunks, cdiv(T, 16 * TB), sqrt(5.0) / src->sigma, src->a0, src->bcoef,
-                  D, nullptr, nullptr, 0};
+                  T, (int)(N - tail), (int)D, chunks, cdiv(T, 16 * TB), sqrt(5.0) / src->sigma, src->a0, src->bcoef,
+                  D, nullptr, nullptr, 0, planes};
     if (CB == 1) launch_part<1, 1>(g, st);
     else if (TB == 1) launch_part<1, 4>(g, st);
     else launch_part<2, 4>(g, st);
-    k_predict_reduce<<<dim3(cdiv(D, 64), T), 1024, 0, st>>>(w + opart, chunks, T, (int)D, w + owp, w + os, w + oXt,
+    if (tail > 0) {
+      const int64_t r = N - tail;
+      g.Xs += r * D; g.sqs += r; g.U += r * D; g.pd += r;
+      g.part += (int64_t)chunks * T * D;
+      g.wpart += chunks;
+      g.N = (int)tail;
+      g.chunks = planes - chunks;
+      g.tiles = cdiv(T, 16);
+      launch_part<1, 1>(g, st);
+    }
+    k_predict_reduce<<<dim3(cdiv(D, 64), T), 1024, 0, st>>>(w + opart, planes, T, (int)D, w + owp, w + os, w + oXt,
                                                             src->a0, w + oG);
     LAUNCHCHK();
     jtg_rows(te->R.as<double>() + b0 * 3 * M, w + oG, te->X.as<double>() + b0 * D, T, M, D, F + b0 * 3 * M, st);

@@ -41,7 +41,8 @@ def geometries(M, N, seed):
 
 
 @pytest.mark.parametrize("M,N,T", [(3, 1, 1), (4, 15, 2), (5, 17, 16), (6, 63, 17), (7, 65, 33), (12, 300, 1), (9, 130, 48),
-                                   (5, 1400, 400), (4, 70, 513), (3, 3, 1030), (30, 40, 5)])
+                                   (5, 1400, 400), (4, 70, 513), (3, 3, 1030), (30, 40, 5), (3, 5000, 200),
+                                   (4, 2200, 500), (3, 1700, 700)])
 def test_prediction_at_tile_edges(ffk, ctx, M, N, T):
     print("predict", M, N, T, flush=True)
     R, Rt = geometries(M, N, 1), geometries(M, T, 2)
