@@ -10,8 +10,6 @@
 // barriers a column, 30 us with diagonal blocks of 16 and readlane, now 18.
 #pragma once
 
-#include <utility>
-
 #include "gemm.hpp"
 
 namespace ffk {
@@ -24,14 +22,6 @@ struct Chol64 {
   unsigned char bad[64];    // pivots that were dropped or not positive
   __device__ double inverse(int r, int c) const { return c >> 4 > r >> 4 ? 0.0 : X[r][c]; }
 };
-
-// f(0), f(1) .. as compile-time constants.
-template <int A, int N, class F> __device__ inline void static_for(F&& f) {
-  if constexpr (A < N) {
-    f(std::integral_constant<int, A>());
-    static_for<A + 1, N>(f);
-  }
-}
 
 // The value of lane N of each row of 16 lanes, in the whole row.
 template <int N> __device__ inline double row_value(double x) {

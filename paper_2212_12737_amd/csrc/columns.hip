@@ -10,16 +10,15 @@
 // where (J_i^T h)_q = -sum_{b != q} h_{qb} (R_iq - R_ib) / r_iqb^3.
 // A wave handles one target and 64 columns, one per lane, so that everything
 // that belongs to the target is uniform: its pair vectors (R_ia - R_ib)/r^3
-// and distances come from the system's pair table, a pair to a lane, and reach
-// the arithmetic as scalars by readlane (scalar loads instead, a tile's 64
-// pairs need more scalar registers than there are: 488 us where this takes 345).  A pair costs
-// a lane one LDS read (x_g of its column), a subtraction and three FMAs.  A
-// block is four targets of the same 64 columns, which share the staging of the
-// columns' x_g rows, in tiles of 8 x 8 atoms.
-// Bound by the readlanes and that arithmetic.  (One wave per (target, column),
-// lanes over the M atoms, left two thirds of the lanes idle at M = 21 and read
-// every pair's vector from LDS: 256 columns at M = 21, N = 2000 786 us, now
-// 345; 8192 at N = 200 1890, now 740.)
+// and distances come from the system's pair table, sixteen pairs to a register
+// (the same in each row of 16 lanes), and reach the arithmetic as the DPP operand
+// of the FMA itself.  A pair costs a lane one LDS read (x_g of its column) and four
+// FMAs.  A block is four targets of the same 64 columns, which share the staging
+// of the columns' x_g rows, in tiles of 8 x 8 atoms.
+// Bound by the LDS reads and that arithmetic.  256 columns at M = 21, N = 2000:
+// 786 us with one wave per (target, column), lanes over the M atoms, two thirds
+// of them idle; 488 with scalar loads, for which there are too few scalar
+// registers; 345 with a pair to a lane and two readlanes a value; now 302.
 #include "common.hpp"
 
 namespace ffk {
@@ -31,11 +30,41 @@ constexpr int kColWaves = 4;   // targets per block
 constexpr int kAtoms = 8;      // atoms per tile side
 constexpr int kXStride = kColTile + 1;
 
+// d_j += w_d (of lane L_j of each row of 16), then v += w d_j: four pairs, of which
+// the first two have their vectors in A and the others in B (x, y, z, d).  By
+// hand, as the compiler broadcasts with a move of its own; a value that the
+// vector unit has just written may not be a DPP operand for two cycles.
+template <int L0, int L1, int L2, int L3>
+__device__ inline void four_pairs(double (&d)[4], double& vx, double& vy, double& vz, const double (&A)[4],
+                                  const double (&B)[4], double one) {
+#define FFK_PAIR(D, W, L)                                                       \
+  "v_fmac_f64_dpp %[" D "], %[" W "3], %[one] row_newbcast:%[" L "] row_mask:0xf bank_mask:0xf\n\t"    \
+  "v_fmac_f64_dpp %[vx], %[" W "0], %[" D "] row_newbcast:%[" L "] row_mask:0xf bank_mask:0xf\n\t"     \
+  "v_fmac_f64_dpp %[vy], %[" W "1], %[" D "] row_newbcast:%[" L "] row_mask:0xf bank_mask:0xf\n\t"     \
+  "v_fmac_f64_dpp %[vz], %[" W "2], %[" D "] row_newbcast:%[" L "] row_mask:0xf bank_mask:0xf\n\t"
+  asm("s_nop 1\n\t" FFK_PAIR("d0", "a", "l0") FFK_PAIR("d1", "a", "l1") FFK_PAIR("d2", "b", "l2")
+          FFK_PAIR("d3", "b", "l3")
+      : [d0] "+v"(d[0]), [d1] "+v"(d[1]), [d2] "+v"(d[2]), [d3] "+v"(d[3]), [vx] "+v"(vx), [vy] "+v"(vy), [vz] "+v"(vz)
+      : [a0] "v"(A[0]), [a1] "v"(A[1]), [a2] "v"(A[2]), [a3] "v"(A[3]), [b0] "v"(B[0]), [b1] "v"(B[1]),
+        [b2] "v"(B[2]), [b3] "v"(B[3]), [one] "v"(one), [l0] "n"(L0), [l1] "n"(L1), [l2] "n"(L2), [l3] "n"(L3));
+#undef FFK_PAIR
+}
+// d_j += w of lane L + j of each row of 16.
+template <int L> __device__ inline void four_differences(double (&d)[4], double w, double one) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %4, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %4, %5 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %4, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+      : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]), "+v"(d[3])
+      : "v"(w), "v"(one), "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3));
+}
+
 // Targets (rows) come from PT, X; the source geometry of each column from PTs,
 // Xs (the same arrays for a plain kernel, a permuted copy for a symmetrized
 // one).  PT: the pair table, four doubles per (geometry, pair a > b): (R_a -
 // R_b) / r^3 and 1 / r.  With accumulate the values are added to out.
-// LDS: xs[64][65] (x_g of a tile's pairs; then the outputs on their way out),
+// LDS: xs[64][65] (-x_g of a tile's pairs; then the outputs on their way out),
 // U[M][64] (u on the pairs {p, b} of each column), XP[M][64] (x_g there).
 __global__ __launch_bounds__(64 * kColWaves) void k_columns(
     const double* __restrict__ PT, const double* __restrict__ X, const double* __restrict__ PTs,
@@ -68,24 +97,33 @@ __global__ __launch_bounds__(64 * kColWaves) void k_columns(
     U[b * kColTile + lane] = b == p ? 0.0 : (p > b ? -wt : wt);
     XP[b * kColTile + lane] = b == p ? 0.0 : x;
   }
+  double one = 1.0;
+  asm("" : "+v"(one));   // in a register
   // |x_i - x_g|^2 over tiles of 64 consecutive pairs
   double r2 = 0.0;
   for (int64_t e0 = 0; e0 < D; e0 += kColTile) {
     __syncthreads();
     const int64_t e = min(e0 + lane, D - 1);
-    const double xi = Xi[e];
+    double xi[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) xi[h] = Xi[min(e0 + 16 * h + (lane & 15), D - 1)];
 #pragma unroll
     for (int c = 0; c < kColTile / kColWaves; ++c) {
       const int cc = wave + kColWaves * c;
-      xs[lane * kXStride + cc] = Xs[sg_of[cc] + e];
+      xs[lane * kXStride + cc] = -Xs[sg_of[cc] + e];
     }
     __syncthreads();
     const int ne = (int)min((int64_t)kColTile, D - e0);
+    static_for<0, kColTile / 4>([&](auto J) {
+      constexpr int q = 4 * decltype(J)::value;
+      double d[4];
 #pragma unroll
-    for (int q = 0; q < kColTile; ++q) {
-      const double dd = lane_value(xi, q) - xs[q * kXStride + lane];
-      if (q < ne) r2 = fma(dd, dd, r2);
-    }
+      for (int j = 0; j < 4; ++j) d[j] = xs[(q + j) * kXStride + lane];
+      four_differences<q % 16>(d, xi[q / 16], one);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (q + j < ne) r2 = fma(d[j], d[j], r2);
+    });
   }
   // d . u, and sum_b u_{pb} (R_ip - R_ib) / r^3
   double du = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
@@ -119,35 +157,48 @@ __global__ __launch_bounds__(64 * kColWaves) void k_columns(
     for (int q = 0; q < kAtoms; ++q) vx[q] = vy[q] = vz[q] = 0.0;
     for (int b0 = 0; b0 < M; b0 += kAtoms) {
       __syncthreads();
-      // lane: one pair of the tile, along the faster atom of their order in
-      // memory; its vector towards the atom of q, and zero where it is no pair
+      // the tile's pair l, along the faster atom of their order in memory: its
+      // vector towards the atom of q, and zero where it is no pair
       const bool below = q0 >= b0;
-      const int hi = lane >> 3, lo = lane & 7;
-      const int qa = q0 + (below ? hi : lo), ba = b0 + (below ? lo : hi);
-      const bool pair = qa != ba && qa < M && ba < M;
-      const int64_t e = pair ? pair_of(qa, ba) : 0;
-      const double sg = pair ? (qa > ba ? 1.0 : -1.0) : 0.0;
-      const double wx = sg * Pi[4 * e], wy = sg * Pi[4 * e + 1], wz = sg * Pi[4 * e + 2], wd = Pi[4 * e + 3];
+      auto pair = [&](int l, double& sg) {
+        const int hi = l >> 3, lo = l & 7;
+        const int qa = q0 + (below ? hi : lo), ba = b0 + (below ? lo : hi);
+        const bool is = qa != ba && qa < M && ba < M;
+        sg = is ? (qa > ba ? 1.0 : -1.0) : 0.0;
+        return is ? pair_of(qa, ba) : 0;
+      };
+      double sg;
+      double w[4][4];   // of the pairs 16 h + lane % 16: the vector and 1 / r
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        const double* src = Pi + 4 * (int64_t)pair(16 * h + (lane & 15), sg);
+#pragma unroll
+        for (int v = 0; v < 3; ++v) w[h][v] = sg * src[v];
+        w[h][3] = src[3];
+      }
+      const int64_t e = pair(lane, sg);
 #pragma unroll
       for (int c = 0; c < kColTile / kColWaves; ++c) {
         const int cc = wave + kColWaves * c;
-        xs[lane * kXStride + cc] = Xs[sg_of[cc] + e];
+        xs[lane * kXStride + cc] = -Xs[sg_of[cc] + e];
       }
       __syncthreads();
-      auto tile = [&](auto ql) {   // ql(q, b): the lane that holds the pair
+      // four partners b of an atom q at a time
+      auto tile = [&](auto order) {
+        static_for<0, 2 * kAtoms>([&](auto J) {
+          constexpr int q = decltype(J)::value / 2, b = decltype(J)::value % 2 * 4;
+          constexpr bool rows = decltype(order)::value;   // the pairs of an atom q follow one another
+          constexpr int l = rows ? q % 2 * kAtoms + b : q;
+          if (decltype(J)::value % 4 == 0) __builtin_amdgcn_sched_barrier(0);   // sixteen pairs' reads in flight
+          double d[4];
 #pragma unroll
-        for (int q = 0; q < kAtoms; ++q)
-#pragma unroll
-          for (int b = 0; b < kAtoms; ++b) {
-            const int l = ql(q, b);
-            const double dd = lane_value(wd, l) - xs[l * kXStride + lane];
-            vx[q] = fma(dd, lane_value(wx, l), vx[q]);
-            vy[q] = fma(dd, lane_value(wy, l), vy[q]);
-            vz[q] = fma(dd, lane_value(wz, l), vz[q]);
-          }
+          for (int j = 0; j < 4; ++j) d[j] = xs[(rows ? q * kAtoms + b + j : (b + j) * kAtoms + q) * kXStride + lane];
+          if constexpr (rows) four_pairs<l, l + 1, l + 2, l + 3>(d, vx[q], vy[q], vz[q], w[q / 2], w[q / 2], one);
+          else four_pairs<l, l + kAtoms, l, l + kAtoms>(d, vx[q], vy[q], vz[q], w[b / 2], w[b / 2 + 1], one);
+        });
       };
-      if (below) tile([](int q, int b) { return q * kAtoms + b; });
-      else tile([](int q, int b) { return b * kAtoms + q; });
+      if (below) tile(std::true_type());
+      else tile(std::false_type());
     }
     __syncthreads();
     // outputs of four atoms at a time through LDS, so that a column's twelve

@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstring>
 #include <memory>
+#include <type_traits>
 #include <mutex>
 #include <stdexcept>
 #include <string>
@@ -110,6 +111,14 @@ __device__ inline double lane_value(double x, int lane) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(x), lane);
   const int hi = __builtin_amdgcn_readlane(__double2hiint(x), lane);
   return __hiloint2double(hi, lo);
+}
+
+// f(0), f(1) .. as compile-time constants.
+template <int A, int N, class F> __device__ inline void static_for(F&& f) {
+  if constexpr (A < N) {
+    f(std::integral_constant<int, A>());
+    static_for<A + 1, N>(f);
+  }
 }
 
 // Compute units of the current device.
