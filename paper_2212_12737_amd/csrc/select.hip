@@ -233,14 +233,17 @@ __device__ inline double piv_wave_sum(double v) {
 
 // Pivot m and column m of L.  Every block finds the best row from the partials
 // (the same fixed order everywhere; block 0 writes it down) or that the rank
-// test stops here.  One wave per target geometry then evaluates its 3M rows of
-// the kernel column (lanes are rows; pair vectors from the system's table, PTs
-// and Xs of the source's), subtracts L[:, :m] times the pivot's row, scales, and
+// test stops here.  One wave per 64 of a target geometry's 3M rows then evaluates
+// them of the kernel column (lanes are rows; pair vectors from the system's table,
+// PTs and Xs of the source's), subtracts L[:, :m] times the pivot's row, scales, and
 // lowers the diagonals, and the block leaves its best row for the next pivot.
 // A symmetrized kernel takes one launch per group element (pinv maps the
 // column's atom), summed in L[:, m]; the last one finishes.
 // Bound by latency at small m, by reading L later: 19 us a pivot at N = 2000 and
-// small m, where a selection, a column and an update kernel took 33.
+// small m, where a selection, a column and an update kernel took 33.  With all of a
+// geometry's rows in one wave and eight loads of L in flight instead of sixteen
+// 69 pivots at M = 24, N = 1092 took 1.63 ms, now 1.44 (130 at M = 22, N = 1005
+// 3.62 and 2.89).
 __global__ __launch_bounds__(256) void k_piv_step(const double* __restrict__ PT, const double* __restrict__ X,
                                                   const double* __restrict__ PTs, const double* __restrict__ Xs,
                                                   const int32_t* __restrict__ pinv, int64_t N, int M, int64_t D,
@@ -281,7 +284,8 @@ __global__ __launch_bounds__(256) void k_piv_step(const double* __restrict__ PT,
   const int64_t pivot = c.i, g = pivot / m3;
   const int loc = (int)(pivot % m3), t = loc % 3;
   const int p = pinv ? pinv[loc / 3] : loc / 3;
-  const int64_t i = (int64_t)blockIdx.x * nw + wave;
+  const int nch = (m3 + 63) / 64;   // waves of a geometry
+  const int64_t task = (int64_t)blockIdx.x * nw + wave, i = task / nch;
   const bool active = i < N;
   const double* Pi = PT + (active ? i : 0) * D * 4;
   double r2 = 0.0, du = 0.0;
@@ -306,8 +310,8 @@ __global__ __launch_bounds__(256) void k_piv_step(const double* __restrict__ PT,
   const double ez = exp(-z);
   const double a = a0 * (1.0 + z) * ez, bdu = -bcoef * ez * du;
   c = Cand{-INFINITY, 0x7FFFFFFF};
-  for (int o0 = 0; o0 < m3; o0 += 64) {   // uniform: the chunks of the pivot's row below are the block's
-    const int o = o0 + lane;
+  {
+    const int o = (int)(task % nch) * 64 + lane;
     const bool row_ok = active && o < m3;
     const int q = row_ok ? o / 3 : 0, s = row_ok ? o % 3 : 0;
     const int64_t row = i * m3 + o;
@@ -335,22 +339,27 @@ __global__ __launch_bounds__(256) void k_piv_step(const double* __restrict__ PT,
       if (add) raw += L[row + m * ld];
       if (!finish) L[row + m * ld] = raw;
     }
-    if (!finish) continue;
+    if (!finish) return;
+    constexpr int B = 16;   // columns of L in flight
     double s0 = 0.0, s1 = 0.0;
     for (int64_t j0 = 0; j0 < m; j0 += CH) {
       const int jn = (int)min((int64_t)CH, m - j0);
       __syncthreads();
-      for (int j = threadIdx.x; j < jn; j += blockDim.x) sv[j] = L[pivot + (j0 + j) * ld];
+      for (int j = threadIdx.x; j < (jn + B - 1) / B * B; j += blockDim.x)
+        sv[j] = j < jn ? L[pivot + (j0 + j) * ld] : 0.0;
       __syncthreads();
       if (row_ok) {
         const double* Li = L + row + j0 * ld;
-        int j = 0;
-#pragma unroll 4
-        for (; j + 2 <= jn; j += 2) {
-          s0 = fma(Li[j * ld], sv[j], s0);
-          s1 = fma(Li[(j + 1) * ld], sv[j + 1], s1);
+        for (int j = 0; j < jn; j += B) {   // columns past the last read that one, against zeros
+          double v[B];
+#pragma unroll
+          for (int x = 0; x < B; ++x) v[x] = Li[min(j + x, jn - 1) * ld];
+#pragma unroll
+          for (int x = 0; x < B; x += 2) {
+            s0 = fma(v[x], sv[j + x], s0);
+            s1 = fma(v[x + 1], sv[j + x + 1], s1);
+          }
         }
-        if (j < jn) s0 = fma(Li[j * ld], sv[j], s0);
       }
     }
     if (row_ok) {
@@ -367,7 +376,6 @@ __global__ __launch_bounds__(256) void k_piv_step(const double* __restrict__ PT,
       L[row + m * ld] = l;
     }
   }
-  if (!finish) return;
   __syncthreads();
   c = block_best(c, sh);
   if (threadIdx.x == 0) part_out[blockIdx.x] = c;
@@ -797,7 +805,7 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
   int nw = 4;
   auto step_lds = [&](int w) { return (size_t)(512 + w * (D + s->M)) * 8; };
   while (nw > 1 && step_lds(nw) > 65536) nw >>= 1;
-  const int np1 = cdiv(s->N, nw);
+  const int np1 = cdiv(s->N * cdiv(3 * s->M, 64), nw);
   DBuf part_a((size_t)std::max(np, np1) * sizeof(Cand)), part_b((size_t)std::max(np, np1) * sizeof(Cand));
   auto singles = [&](int64_t want) {
     want = std::min(want, k - m);

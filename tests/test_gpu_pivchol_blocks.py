@@ -83,3 +83,14 @@ def test_symmetrized_kernel(ffk, ctx):
     ffk.set_symmetries(ctx, S, perms)
     piv = ffk.nystrom_select(ctx, S, "pivchol", 150).cpu().numpy()
     check_greedy(osym.dense_sym_kernel(s.R, perms, SIGMA), piv, 150)
+
+
+@pytest.mark.parametrize("M,N,k", [(21, 3, 17), (22, 3, 16), (22, 5, 33), (43, 2, 31)])
+def test_single_pivots_of_large_molecules(ffk, ctx, M, N, k):
+    """Rows of one to three waves a geometry, columns of L around a batch of sixteen."""
+    print("pivchol singles", M, N, k, flush=True)
+    s = synth.make_system(M, N, 0.08, True, 990 + M, 991 + M, 992 + M)
+    S = ffk.descriptor_build(ctx, torch.as_tensor(s.R, device="cuda"), SIGMA)
+    piv = ffk.nystrom_select(ctx, S, "pivchol", k).cpu().numpy()
+    assert len(piv) <= k and len(set(piv.tolist())) == len(piv)
+    check_greedy(ok.dense_kernel(s.R, SIGMA), piv, k)
