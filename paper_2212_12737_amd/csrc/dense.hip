@@ -65,8 +65,7 @@ static void gemm64_in32_t(int M, int N, int K, double alpha, View32 A, View32 B,
   ScalarArgs<float> g{};
   g.M = M;
   g.N = N;
-  g.nseg = 1;
-  g.seg[0] = SegS<float>{A.p, A.s0, A.s1, B.p, B.s0, B.s1, K};
+  g.seg = SegS<float>{A.p, A.s0, A.s1, B.p, B.s0, B.s1, K};
   EpiAxpby<double> e{C, scm, scn, M, N, alpha, beta};
   dim3 grid(cdiv(N, 128), cdiv(M, 128));
   gemm_scalar_kernel<double, 128, 128, 16, AKC, BKC, EpiAxpby<double>, float><<<grid, 256, 0, st>>>(g, e);

@@ -1,8 +1,7 @@
 // MFMA GEMM engines for gfx950.
 //
-// Both engines compute a BM x BN tile of  acc = sum_k A(m, k) B(n, k)  (an
-// "A B^T" product) with 256 threads = 4 wave64s in a 2 x 2 arrangement; each
-// wave owns a (BM/2) x (BN/2) sub-tile made of 16 x 16 MFMA blocks.  Operand
+// Every engine computes a BM x BN tile of  acc = sum_k A(m, k) B(n, k)  (an
+// "A B^T" product); a wave owns a sub-tile made of 16 x 16 MFMA blocks.  Operand
 // lane layout (all three instructions): lane l supplies row l%16 and the
 // K-slice l/16.  Output lane layout: lane l, register v holds column l%16 and
 // row 4*(l/16) + v for the FP32-output instructions, but row 4*v + l/16 for
@@ -10,18 +9,26 @@
 // After the K loop the engine hands the accumulators to an epilogue functor,
 // which does all stores (and any fused elementwise work and row reductions).
 //
-// ScalarEngine<T>: T = double (v_mfma_f64_16x16x4_f64) or float
-//   (v_mfma_f32_16x16x4_f32).  One operand element per lane per instruction, so
-//   operands may be K-contiguous or M-contiguous strided views; LDS tiles are
-//   stored [k][m] with 16 elements of padding per row.  Bounds are checked.
+// gemm_row_kernel: FP32 and FP64 products of padded row-major operands (the
+//   kernel product, its coefficients, the Gram matrix of the factor).
 //
-// Bf16Engine: v_mfma_f32_16x16x32_bf16, FP32 accumulation, optional split
-//   mode (X3) that adds hi*hi + hi*lo + lo*hi.  Operands are K-contiguous bf16
-//   arrays whose row count is padded to a multiple of BM (or BN) and whose
-//   leading dimension is padded to a multiple of BK with zeros, so tiles are
-//   loaded with unpredicated 16-byte vectors.  LDS tiles are [m][k] with 8
-//   elements of row padding, which makes the 16-byte operand reads of one
-//   16-lane group hit distinct banks.
+// gemm_dma_kernel: BF16 and split-BF16 products of fragment-major operands.
+//
+// gemm_scalar_kernel: double (v_mfma_f64_16x16x4_f64) arithmetic on strided
+//   views whose stored type may be narrower: the low-memory build, whose factor
+//   is held in FP32.  One operand element per lane per instruction, so operands
+//   may be K-contiguous or M-contiguous; LDS tiles are stored [k][m] with 16
+//   elements of padding per row.  Bounds are checked.  4 waves, 2 x 2.
+//
+// gemm_bf16_kernel: v_mfma_f32_16x16x32_bf16, FP32 accumulation, optional split
+//   mode (X3) that adds hi*hi + hi*lo + lo*hi (the score network).  Operands are
+//   K-contiguous bf16 arrays whose row count is padded to a multiple of BM (or
+//   BN) and whose leading dimension is padded to a multiple of BK with zeros, so
+//   tiles are loaded with unpredicated 16-byte vectors.  LDS tiles are [m][k]
+//   with 8 elements of row padding, which makes the 16-byte operand reads of one
+//   16-lane group hit distinct banks.  4 waves, 2 x 2.
+//
+// FP64 products of column-major operands are in gemm64.hpp.
 #pragma once
 
 #include "common.hpp"
@@ -67,7 +74,7 @@ struct FragCoord {
   __device__ inline int col(int tn) const { return wn0 + tn * 16 + (lane & 15); }
 };
 
-// Operand segment of a scalar GEMM: element (m, k) at p[m*s0 + k*s1].  The
+// Operands of the strided GEMM: element (m, k) at p[m*s0 + k*s1].  The
 // stored type TI may be narrower than the compute type (float -> double is exact).
 template <typename TI> struct SegS {
   const TI* A; int64_t sa0, sa1;
@@ -77,21 +84,12 @@ template <typename TI> struct SegS {
 
 template <typename TI> struct ScalarArgs {
   int M, N;
-  int nseg;
-  SegS<TI> seg[2];
-  bool lower_only;   // skip tiles whose columns all exceed their rows
-  bool a_lower;      // A(m, k) = 0 for k > m (restricts the K range per tile)
+  SegS<TI> seg;
 };
 
 // ---------------------------------------------------------------------------
-// Scalar-operand MFMA engine (FP64 / FP32)
+// Strided-operand MFMA engine (FP64 arithmetic)
 // ---------------------------------------------------------------------------
-// Conversion of a stored operand element to the compute type; bf16_t is the
-// raw 16-bit pattern of a bfloat16, not an integer.
-template <typename T, typename TI> __device__ inline T to_compute(TI x) { return (T)x; }
-template <> __device__ inline double to_compute<double, bf16_t>(bf16_t x) { return (double)bf2f(x); }
-template <> __device__ inline float to_compute<float, bf16_t>(bf16_t x) { return bf2f(x); }
-
 template <typename T, int BM, int BN, int BK, bool AKC, bool BKC, class Epi, typename TI = T>
 __global__ __launch_bounds__(256) void gemm_scalar_kernel(ScalarArgs<TI> g, Epi epi) {
   constexpr int PAD = 16;
@@ -105,15 +103,9 @@ __global__ __launch_bounds__(256) void gemm_scalar_kernel(ScalarArgs<TI> g, Epi 
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  if (g.lower_only && n0 > m0 + BM - 1) return;
   const int wm0 = (wave >> 1) * (BM / 2), wn0 = (wave & 1) * (BN / 2);
-
-  // tiles of every segment, walked as one sequence
-  int kend0 = g.seg[0].K;
-  if (g.a_lower) kend0 = min(kend0, m0 + BM);
-  const int t0 = (kend0 + BK - 1) / BK;
-  const int t1 = g.nseg > 1 ? (g.seg[1].K + BK - 1) / BK : 0;
-  const int T_ = t0 + t1;
+  const SegS<TI>& s = g.seg;
+  const int T_ = (s.K + BK - 1) / BK;
 
   acc_t acc[TM][TN];
 #pragma unroll
@@ -123,17 +115,14 @@ __global__ __launch_bounds__(256) void gemm_scalar_kernel(ScalarArgs<TI> g, Epi 
 
   T ra[EA], rb[EB];
   auto load = [&](int t) {
-    const SegS<TI>& s = (t < t0) ? g.seg[0] : g.seg[1];
-    const bool tri = g.a_lower && t < t0;
-    const int k0 = (t < t0 ? t : t - t0) * BK;
-    const int Kl = (t < t0) ? kend0 : s.K;
+    const int k0 = t * BK;
 #pragma unroll
     for (int i = 0; i < EA; ++i) {
       const int e = tid + 256 * i;
       const int mm = AKC ? e / BK : e % BM;
       const int kk = AKC ? e % BK : e / BM;
       const int m = m0 + mm, k = k0 + kk;
-      ra[i] = (m < g.M && k < Kl && !(tri && k > m)) ? to_compute<T>(s.A[(int64_t)m * s.sa0 + (int64_t)k * s.sa1]) : T(0);
+      ra[i] = (m < g.M && k < s.K) ? (T)(s.A[(int64_t)m * s.sa0 + (int64_t)k * s.sa1]) : T(0);
     }
 #pragma unroll
     for (int i = 0; i < EB; ++i) {
@@ -141,7 +130,7 @@ __global__ __launch_bounds__(256) void gemm_scalar_kernel(ScalarArgs<TI> g, Epi 
       const int nn = BKC ? e / BK : e % BN;
       const int kk = BKC ? e % BK : e / BN;
       const int n = n0 + nn, k = k0 + kk;
-      rb[i] = (n < g.N && k < Kl) ? to_compute<T>(s.B[(int64_t)n * s.sb0 + (int64_t)k * s.sb1]) : T(0);
+      rb[i] = (n < g.N && k < s.K) ? (T)(s.B[(int64_t)n * s.sb0 + (int64_t)k * s.sb1]) : T(0);
     }
   };
   auto store = [&](int buf) {
@@ -161,17 +150,14 @@ __global__ __launch_bounds__(256) void gemm_scalar_kernel(ScalarArgs<TI> g, Epi 
     }
   };
 
-  // split-K: block z of gridDim.z takes a contiguous range of the tiles
-  const int tb = (int)((int64_t)T_ * blockIdx.z / gridDim.z);
-  const int te = (int)((int64_t)T_ * (blockIdx.z + 1) / gridDim.z);
-  if (te > tb) {
-    load(tb);
+  if (T_ > 0) {
+    load(0);
     store(0);
   }
   __syncthreads();
-  for (int t = tb; t < te; ++t) {
-    const int buf = (t - tb) & 1;
-    if (t + 1 < te) load(t + 1);
+  for (int t = 0; t < T_; ++t) {
+    const int buf = t & 1;
+    if (t + 1 < T_) load(t + 1);
 #pragma unroll
     for (int k4 = 0; k4 < BK / 4; ++k4) {
       T a[TM], b[TN];
@@ -185,10 +171,10 @@ __global__ __launch_bounds__(256) void gemm_scalar_kernel(ScalarArgs<TI> g, Epi 
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = Mfma16<T>::run(a[i], b[j], acc[i][j]);
     }
-    if (t + 1 < te) store(buf ^ 1);
+    if (t + 1 < T_) store(buf ^ 1);
     __syncthreads();
   }
-  FragCoord fc{m0 + wm0, n0 + wn0, lane, m0, n0, sizeof(T) == 8, (int)blockIdx.x, wave & 1, 2, (int)blockIdx.z};
+  FragCoord fc{m0 + wm0, n0 + wn0, lane, m0, n0, sizeof(T) == 8, (int)blockIdx.x, wave & 1, 2, 0};
   epi.template run<T, TM, TN>(acc, fc, reinterpret_cast<char*>(&As[0][0][0]));
 }
 

@@ -803,13 +803,13 @@ static GemmOut mvm_gemms_wide(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_
 // the other's main loop (at N = 20000: GEMM 1 2.02 -> 1.66 ms, GEMM 2 2.89 ->
 // 2.46 ms against 256 x 256 by 8 waves, which fills a CU alone).  Split BF16
 // (hi and lo operands) fills a CU either way and takes the larger tile
-// below.  FP32 and FP64 stay at 128 x 128, which measured faster.
+// below.  FP32 and FP64 (gemm_row_kernel) take 64 x 64 by four waves and 128 x
+// 128 by eight, two workgroups a CU, and for GEMM 2 the width that fits D.
 typedef DmaTile<64, 64, 2, 2, 4> TileM;        // GEMM 1 of small N: 4x more workgroups
 // The same tile in split BF16 with two stages: its hi and lo operands take 16
 // KB a stage, so four stages held a CU to two workgroups, and at N = 2000
 // (seven K steps) the 1024 tiles ran in two rounds.  GEMM 1 19.9 -> 17.6 us
-// at M = 21, N = 2000; single BF16 (14.4 against 13.4 us), FP32 and FP64
-// keep four stages.
+// at M = 21, N = 2000; single BF16 keeps four (14.4 against 13.4 us).
 typedef DmaTile<64, 64, 2, 2, 2> TileMX3;
 typedef DmaTile<256, 128, 4, 2, 3> TileL;      // BF16 and split BF16, large N
 typedef DmaTile<64, 256, 1, 4, 3> TileW2;      // GEMM 2 of small N: one tile spans D <= 256 columns

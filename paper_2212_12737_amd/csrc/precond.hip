@@ -241,8 +241,7 @@ static void gram_cols(const TI* L, int64_t n, int64_t ld, int64_t k, double* C, 
   ScalarArgs<TI> g{};
   g.M = (int)k;
   g.N = (int)k;
-  g.nseg = 1;
-  g.seg[0] = SegS<TI>{L, ld, 1, L, ld, 1, (int)n};
+  g.seg = SegS<TI>{L, ld, 1, L, ld, 1, (int)n};
   EpiStore64 e{C, ldc, (int)k, (int)k};
   gemm_scalar_kernel<double, 128, 128, 16, true, true, EpiStore64, TI><<<dim3(cdiv(k, 128), cdiv(k, 128)), 256, 0, st>>>(g, e);
   LAUNCHCHK();
