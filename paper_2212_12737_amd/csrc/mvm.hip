@@ -691,17 +691,20 @@ static GemmOut mvm_gemms_dma(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t
   g.nseg = 2;
   g.seg[0] = SegD{o.dAh, o.dAl, o.UTh, o.UTl, Nsr, Nsr, (int)Nsr, (int)(Nsr / 32)};
   g.seg[1] = SegD{o.Wh, o.Wl, o.XTh, o.XTl, Nsr, Nsr, (int)Nsr, (int)(Nsr / 32)};
-  const int64_t tiles = (Dr / TL2::BN) * (Ntr / TL2::BM);
+  // the split count is that of 256-column tiles also where two of 128 share a CU
+  constexpr int CW = TL2::BM == 64 ? 256 : TL2::BN;
+  const int64_t tiles = (Dr / CW) * (Ntr / TL2::BM);
   static int per_cu = 0;
   if (per_cu == 0) {
     int nb = 0;
     HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_dma_kernel<T, TL2, X3, EpiPart<CT>>, TL2::NT, 0));
+    nb = nb * TL2::BN / CW;
     per_cu = nb > 0 ? nb : 1;
   }
-  const double t_tile = 2.0 * TL2::BM * TL2::BN * 2.0 * Nsr * (X3 ? 3 : 1) / (1.2e15 / 256.0);
+  const double t_tile = 2.0 * TL2::BM * CW * 2.0 * Nsr * (X3 ? 3 : 1) / (1.2e15 / 256.0);
   int splits = gemm2_splits(tiles, 2 * Nsr / 32, N, D, per_cu, t_tile);
   while (splits > 1 && (size_t)splits * N * D * sizeof(CT) > a.part_bytes) splits >>= 1;
-  const dim3 grid((unsigned)(Dr / TL2::BN), (unsigned)(Ntr / TL2::BM), (unsigned)splits);
+  const dim3 grid((unsigned)cdiv(D, TL2::BN), (unsigned)(Ntr / TL2::BM), (unsigned)splits);
   if (splits == 1) {
     EpiG<TL2::BM> e{a.s, a.Xt64, D, a.wpart, ntn, a.a0, a.G, D, (int)N, (int)D};
     clk_begin(CLK_GEMM2, st);
@@ -797,7 +800,7 @@ static GemmOut mvm_gemms_wide(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_
 }
 
 // Tile shapes.  Small N: 64 x 64 (GEMM 1) and 128 x 128 (GEMM 2; BF16: 64 x
-// 256) by 4 waves, where the grid would otherwise leave CUs idle.  Large N:
+// 128) by 4 waves, where the grid would otherwise leave CUs idle.  Large N:
 // single BF16 uses 256 x 128 by 8 waves of 64 x 64 with three stages; that
 // is 72 KB of LDS, so two workgroups share a CU and one's epilogue overlaps
 // the other's main loop (at N = 20000: GEMM 1 2.02 -> 1.66 ms, GEMM 2 2.89 ->
@@ -812,7 +815,19 @@ typedef DmaTile<64, 64, 2, 2, 4> TileM;        // GEMM 1 of small N: 4x more wor
 // at M = 21, N = 2000; single BF16 keeps four (14.4 against 13.4 us).
 typedef DmaTile<64, 64, 2, 2, 2> TileMX3;
 typedef DmaTile<256, 128, 4, 2, 3> TileL;      // BF16 and split BF16, large N
-typedef DmaTile<64, 256, 1, 4, 3> TileW2;      // GEMM 2 of small N: one tile spans D <= 256 columns
+// GEMM 2 of small N, bound by the latency of its loads (16 K steps a workgroup
+// at N = 2000): two workgroups of 64 x 128 a CU overlap, where one of 64 x 256
+// did not, and columns past D's last 128 are left out.  Split BF16 with two
+// stages, so that three fit: M = 25, N = 1500 (D = 300) 29.9 -> 21.5 us, M = 45,
+// N = 1200 42.2 -> 28.5, M = 26, N = 3000 85 -> 52; M = 21, N = 2000 22.0 -> 20.6
+// with the coefficients in the last-level cache, no change from HBM.  Single
+// BF16 with three (two: 16.5 us): M = 21, N = 2000 15.3 -> 14.5 us, N = 4000
+// 33.9 -> 30.1; but where the 64 x 256 tiles, of which two fit, are more than
+// one and a half a CU they stay (M = 60, N = 4000 196 us against 214, M = 35, N =
+// 2500 30.4 against 33.6; at one and a half, M = 25, N = 1500, 15.9 against 15.5).
+typedef DmaTile<64, 128, 2, 2, 3> TileW2;
+typedef DmaTile<64, 128, 2, 2, 2> TileW2X3;
+typedef DmaTile<64, 256, 1, 4, 3> TileW2L;
 // Split BF16 at large N: 256 x 256 by 8 waves of 64 x 128, two stages (128
 // KB of LDS, one workgroup per CU).  Against 256 x 128 (three stages) at M =
 // 60, N = 20000: GEMM 1 4.53 -> 3.98 ms, GEMM 2 7.25 -> 6.49 ms; 5% and 4%
@@ -833,11 +848,12 @@ static GemmOut mvm_gemms_for(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t
                              hipStream_t st, hipEvent_t* ev) {
   const bool small = a.Nt < kLargeN;
   if constexpr (sizeof(T) == 2 && X3) {
-    // one 256-wide GEMM 2 tile reads [dA | -W] once instead of once per 128
-    // columns (split BF16 at N = 2000, D = 210: 30 -> 27 us)
-    if (small) return mvm_gemms_dma<T, X3, CT, TileMX3, TileW2>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
+    if (small) return mvm_gemms_dma<T, X3, CT, TileMX3, TileW2X3>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
     return mvm_gemms_dma<T, X3, CT, TileX3G1, TileX3G2>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
   } else if constexpr (sizeof(T) == 2) {
+    const int64_t wide = (Dr / 256) * (Ntr / 64);
+    if (small && 2 * wide * pick_splits(wide, 2 * Nsr / 32, 256) > 3 * (int64_t)device_cus())
+      return mvm_gemms_dma<T, X3, CT, TileM, TileW2L>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
     if (small) return mvm_gemms_dma<T, X3, CT, TileM, TileW2>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
     return mvm_gemms_dma<T, X3, CT, TileL, TileL>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
   } else {
