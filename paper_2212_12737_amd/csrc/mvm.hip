@@ -814,6 +814,11 @@ typedef DmaTile<64, 64, 2, 2, 4> TileM;        // GEMM 1 of small N: 4x more wor
 // (seven K steps) the 1024 tiles ran in two rounds.  GEMM 1 19.9 -> 17.6 us
 // at M = 21, N = 2000; single BF16 keeps four (14.4 against 13.4 us).
 typedef DmaTile<64, 64, 2, 2, 2> TileMX3;
+// GEMM 1 in split BF16, bound by the bytes it brings to LDS, on 128 x 64 (a
+// quarter less) where these tiles give four workgroups a CU: M = 60, N = 4000
+// 211 -> 174 us, M = 45, N = 3600 114 -> 99, M = 21, N = 4000 45 -> 43; with
+// three a CU (M = 35, N = 2500) 39 -> 41.
+typedef DmaTile<128, 64, 4, 1, 2> TileTX3;
 typedef DmaTile<256, 128, 4, 2, 3> TileL;      // BF16 and split BF16, large N
 // GEMM 2 of small N, bound by the latency of its loads (16 K steps a workgroup
 // at N = 2000): two workgroups of 64 x 128 a CU overlap, where one of 64 x 256
@@ -848,6 +853,8 @@ static GemmOut mvm_gemms_for(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t
                              hipStream_t st, hipEvent_t* ev) {
   const bool small = a.Nt < kLargeN;
   if constexpr (sizeof(T) == 2 && X3) {
+    if (small && (Nsr / 128) * (Ntr / 64) >= 4 * (int64_t)device_cus())
+      return mvm_gemms_dma<T, X3, CT, TileTX3, TileW2X3>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
     if (small) return mvm_gemms_dma<T, X3, CT, TileMX3, TileW2X3>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
     return mvm_gemms_dma<T, X3, CT, TileX3G1, TileX3G2>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
   } else if constexpr (sizeof(T) == 2) {
