@@ -668,8 +668,17 @@ struct GemmOut {
   int splits, ntn;
 };
 
+// K splits of the BF16 GEMM 2, counted on tiles of BM x BN of which a CU holds
+// per_cu.  Below 4096 geometries these are 64 x 256 whatever tile the product
+// takes, so that the choice of a tile changes no bit of the result.
+template <int BM, int BN>
+static int gemm2_splits_bf16(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t Dr, int per_cu, bool x3) {
+  const double t_tile = 2.0 * BM * BN * 2.0 * Nsr * (x3 ? 3 : 1) / (1.2e15 / 256.0);
+  return gemm2_splits((Dr / BN) * (Ntr / BM), 2 * Nsr / 32, a.Nt, a.D, per_cu, t_tile);
+}
+
 template <typename T, bool X3, typename CT, class TL1, class TL2>
-static GemmOut mvm_gemms_dma(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t Dk, int64_t Dr, const DmaOps& o,
+static GemmOut mvm_gemms_dma(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t Dk, int splits, const DmaOps& o,
                              hipStream_t st, hipEvent_t* ev) {
   const int64_t N = a.Nt, Ns = a.Ns, D = a.D;
   const int ntn = (int)(Nsr / TL1::BM);   // row-sum partials per row of W (source tiles)
@@ -691,18 +700,6 @@ static GemmOut mvm_gemms_dma(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t
   g.nseg = 2;
   g.seg[0] = SegD{o.dAh, o.dAl, o.UTh, o.UTl, Nsr, Nsr, (int)Nsr, (int)(Nsr / 32)};
   g.seg[1] = SegD{o.Wh, o.Wl, o.XTh, o.XTl, Nsr, Nsr, (int)Nsr, (int)(Nsr / 32)};
-  // the split count is that of 256-column tiles also where two of 128 share a CU
-  constexpr int CW = TL2::BM == 64 ? 256 : TL2::BN;
-  const int64_t tiles = (Dr / CW) * (Ntr / TL2::BM);
-  static int per_cu = 0;
-  if (per_cu == 0) {
-    int nb = 0;
-    HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_dma_kernel<T, TL2, X3, EpiPart<CT>>, TL2::NT, 0));
-    nb = nb * TL2::BN / CW;
-    per_cu = nb > 0 ? nb : 1;
-  }
-  const double t_tile = 2.0 * TL2::BM * CW * 2.0 * Nsr * (X3 ? 3 : 1) / (1.2e15 / 256.0);
-  int splits = gemm2_splits(tiles, 2 * Nsr / 32, N, D, per_cu, t_tile);
   while (splits > 1 && (size_t)splits * N * D * sizeof(CT) > a.part_bytes) splits >>= 1;
   const dim3 grid((unsigned)cdiv(D, TL2::BN), (unsigned)(Ntr / TL2::BM), (unsigned)splits);
   if (splits == 1) {
@@ -827,12 +824,22 @@ typedef DmaTile<256, 128, 4, 2, 3> TileL;      // BF16 and split BF16, large N
 // N = 1200 42.2 -> 28.5, M = 26, N = 3000 85 -> 52; M = 21, N = 2000 22.0 -> 20.6
 // with the coefficients in the last-level cache, no change from HBM.  Single
 // BF16 with three (two: 16.5 us): M = 21, N = 2000 15.3 -> 14.5 us, N = 4000
-// 33.9 -> 30.1; but where the 64 x 256 tiles, of which two fit, are more than
-// one and a half a CU they stay (M = 60, N = 4000 196 us against 214, M = 35, N =
-// 2500 30.4 against 33.6; at one and a half, M = 25, N = 1500, 15.9 against 15.5).
+// 33.9 -> 30.1.
 typedef DmaTile<64, 128, 2, 2, 3> TileW2;
 typedef DmaTile<64, 128, 2, 2, 2> TileW2X3;
-typedef DmaTile<64, 256, 1, 4, 3> TileW2L;
+// 128 x 128 moves a third less to LDS and is taken where there are one and a
+// half a CU (gemm2_is_tall).  Whole products, systems in turn, 64 -> 128 rows:
+// split BF16 M = 35, N = 2500 141 -> 125 us, M = 60, N = 2000 214 -> 184, M = 30, N
+// = 3600 209 -> 172, M = 60, N = 4000 752 -> 589 (at fewer a CU M = 45, N = 1200
+// 83 -> 87, M = 21, N = 4000 137 -> 143); single BF16 (against 64 x 256) M = 35, N
+// = 2500 91.9 -> 88.3, M = 48, N = 3000 162 -> 150, M = 60, N = 4000 427 -> 414
+// (eight waves with three stages 408, but M = 48 158, M = 60, N = 2000 129
+// against 123).
+typedef DmaTile<128, 128, 2, 2, 3> TileW3;
+typedef DmaTile<128, 128, 2, 4, 2> TileW3X3;
+static bool gemm2_is_tall(int64_t D, int64_t Ntr, int splits) {
+  return 2 * cdiv(D, 128) * (Ntr / 128) * splits >= 3 * (int64_t)device_cus();
+}
 // Split BF16 at large N: 256 x 256 by 8 waves of 64 x 128, two stages (128
 // KB of LDS, one workgroup per CU).  Against 256 x 128 (three stages) at M =
 // 60, N = 20000: GEMM 1 4.53 -> 3.98 ms, GEMM 2 7.25 -> 6.49 ms; 5% and 4%
@@ -853,16 +860,26 @@ static GemmOut mvm_gemms_for(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t
                              hipStream_t st, hipEvent_t* ev) {
   const bool small = a.Nt < kLargeN;
   if constexpr (sizeof(T) == 2 && X3) {
-    if (small && (Nsr / 128) * (Ntr / 64) >= 4 * (int64_t)device_cus())
-      return mvm_gemms_dma<T, X3, CT, TileTX3, TileW2X3>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
-    if (small) return mvm_gemms_dma<T, X3, CT, TileMX3, TileW2X3>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
-    return mvm_gemms_dma<T, X3, CT, TileX3G1, TileX3G2>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
+    if (!small) {
+      const int s = gemm2_splits_bf16<256, 256>(a, Ntr, Nsr, Dr, 1, true);
+      return mvm_gemms_dma<T, X3, CT, TileX3G1, TileX3G2>(a, Ntr, Nsr, Dk, s, o, st, ev);
+    }
+    const int s = gemm2_splits_bf16<64, 256>(a, Ntr, Nsr, Dr, 1, true);
+    const bool tall1 = (Nsr / 128) * (Ntr / 64) >= 4 * (int64_t)device_cus();
+    if (gemm2_is_tall(a.D, Ntr, s)) {
+      if (tall1) return mvm_gemms_dma<T, X3, CT, TileTX3, TileW3X3>(a, Ntr, Nsr, Dk, s, o, st, ev);
+      return mvm_gemms_dma<T, X3, CT, TileMX3, TileW3X3>(a, Ntr, Nsr, Dk, s, o, st, ev);
+    }
+    if (tall1) return mvm_gemms_dma<T, X3, CT, TileTX3, TileW2X3>(a, Ntr, Nsr, Dk, s, o, st, ev);
+    return mvm_gemms_dma<T, X3, CT, TileMX3, TileW2X3>(a, Ntr, Nsr, Dk, s, o, st, ev);
   } else if constexpr (sizeof(T) == 2) {
-    const int64_t wide = (Dr / 256) * (Ntr / 64);
-    if (small && 2 * wide * pick_splits(wide, 2 * Nsr / 32, 256) > 3 * (int64_t)device_cus())
-      return mvm_gemms_dma<T, X3, CT, TileM, TileW2L>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
-    if (small) return mvm_gemms_dma<T, X3, CT, TileM, TileW2>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
-    return mvm_gemms_dma<T, X3, CT, TileL, TileL>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
+    if (!small) {
+      const int s = gemm2_splits_bf16<256, 128>(a, Ntr, Nsr, Dr, 2, false);
+      return mvm_gemms_dma<T, X3, CT, TileL, TileL>(a, Ntr, Nsr, Dk, s, o, st, ev);
+    }
+    const int s = gemm2_splits_bf16<64, 256>(a, Ntr, Nsr, Dr, 2, false);
+    if (gemm2_is_tall(a.D, Ntr, s)) return mvm_gemms_dma<T, X3, CT, TileM, TileW3>(a, Ntr, Nsr, Dk, s, o, st, ev);
+    return mvm_gemms_dma<T, X3, CT, TileM, TileW2>(a, Ntr, Nsr, Dk, s, o, st, ev);
   } else {
     if (small) return mvm_gemms_wide<T, RowTile<64, 64, 2, 2, 2>>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
     return mvm_gemms_wide<T, RowTile<128, 128, 2, 4, 2>>(a, Ntr, Nsr, Dk, Dr, o, st, ev);
