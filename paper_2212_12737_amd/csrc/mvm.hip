@@ -862,6 +862,14 @@ static GemmOut mvm_gemms_for(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t
   if constexpr (sizeof(T) == 2 && X3) {
     if (!small) {
       const int s = gemm2_splits_bf16<256, 256>(a, Ntr, Nsr, Dr, 1, true);
+      // a mostly empty last round of 256 x 256 tiles in a GEMM 1 of few K steps
+      // costs more than the smaller tile's bytes: M = 18, N = 4654 196 -> 179 us
+      // a product, M = 21, N = 5000 224 -> 210, M = 24, N = 7000 454 -> 434, M =
+      // 32, N = 5000 316 -> 306; in full rounds M = 32, N = 8000 596 -> 618, at D =
+      // 1770 N = 5000 853 -> 858
+      const int64_t tiles1 = (Nsr / 256) * (Ntr / 256), cus = device_cus();
+      if (a.D <= 512 && 5 * tiles1 < 4 * cus * ((tiles1 + cus - 1) / cus))
+        return mvm_gemms_dma<T, X3, CT, TileTX3, TileX3G2>(a, Ntr, Nsr, Dk, s, o, st, ev);
       return mvm_gemms_dma<T, X3, CT, TileX3G1, TileX3G2>(a, Ntr, Nsr, Dk, s, o, st, ev);
     }
     const int s = gemm2_splits_bf16<64, 256>(a, Ntr, Nsr, Dr, 1, true);
