@@ -451,7 +451,20 @@ __global__ __launch_bounds__(TL::NT) void gemm_dma_kernel(DmaArgs g, Epi epi) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int tmi, tni, tzi;
-  tile_coords<X3 && TM * TN >= 32>(tmi, tni, tzi);
+  // the 64 x 128 tiles of up to 32 row tiles over the whole grid too: an XCD's 32
+  // CUs then hold about one K split, both column tiles of a row beside each
+  // other, and read its rows of B from their L2.  M = 21, N = 2000 56.8 -> 55.2
+  // us a split-BF16 product (systems in turn), 45.0 -> 43.9 in single BF16; N =
+  // 300 26.9 -> 25.9.  With more row tiles it is slower (BF16 N = 4000 90.8 -> 94.6),
+  // and on the 128 x 128 tile (M = 60, N = 2000 122 -> 128).
+  if constexpr (X3 && TM * TN >= 32) {
+    tile_coords<true>(tmi, tni, tzi);
+  } else if constexpr (BM == 64 && BN == 128) {
+    if (gridDim.y <= 32) tile_coords<true>(tmi, tni, tzi);
+    else tile_coords<false>(tmi, tni, tzi);
+  } else {
+    tile_coords<false>(tmi, tni, tzi);
+  }
   if (g.lower_only && tni > tmi) return;
   const int m0 = tmi * BM, n0 = tni * BN;
   const int wm = wave / WN, wn = wave % WN;
