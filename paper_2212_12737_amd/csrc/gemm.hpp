@@ -420,9 +420,10 @@ struct DmaArgs {
 
 // Tile shape of the pipelined engine: BM x BN block tile computed by WM x WN
 // waves (each (BM/WM) x (BN/WN)), S pipeline stages.
-template <int BM_, int BN_, int WM_, int WN_, int S_>
+template <int BM_, int BN_, int WM_, int WN_, int S_, bool HH_ = false>
 struct DmaTile {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, S = S_;
+  static constexpr bool HH = HH_;   // split BF16: hi*hi, hi*lo, lo*hi, the order of large wave tiles, not the reverse
   static constexpr int NT = 64 * WM * WN;
 };
 
@@ -577,6 +578,12 @@ __global__ __launch_bounds__(TL::NT) void gemm_dma_kernel(DmaArgs g, Epi epi) {
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
+        if constexpr (X3 && TL::HH) {
+          acc[i][j] = DmaMfma<T>::slice(ah[i], bh[j], acc[i][j], 0);
+          acc[i][j] = DmaMfma<T>::slice(ah[i], bl[j], acc[i][j], 0);
+          acc[i][j] = DmaMfma<T>::slice(al[i], bh[j], acc[i][j], 0);
+          continue;
+        }
         if (X3) {
           acc[i][j] = DmaMfma<T>::slice(al[X3 ? i : 0], bh[j], acc[i][j], 0);
           acc[i][j] = DmaMfma<T>::slice(ah[i], bl[X3 ? j : 0], acc[i][j], 0);

@@ -816,6 +816,7 @@ typedef DmaTile<64, 64, 2, 2, 2> TileMX3;
 // 211 -> 174 us, M = 45, N = 3600 114 -> 99, M = 21, N = 4000 45 -> 43; with
 // three a CU (M = 35, N = 2500) 39 -> 41.
 typedef DmaTile<128, 64, 4, 1, 2> TileTX3;
+typedef DmaTile<128, 64, 4, 1, 2, true> TileTX3L;   // the same above 4096 geometries, in the order of the 256 x 256 tile
 typedef DmaTile<256, 128, 4, 2, 3> TileL;      // BF16 and split BF16, large N
 // GEMM 2 of small N, bound by the latency of its loads (16 K steps a workgroup
 // at N = 2000): two workgroups of 64 x 128 a CU overlap, where one of 64 x 256
@@ -869,7 +870,7 @@ static GemmOut mvm_gemms_for(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t
       // 1770 N = 5000 853 -> 858
       const int64_t tiles1 = (Nsr / 256) * (Ntr / 256), cus = device_cus();
       if (a.D <= 512 && 5 * tiles1 < 4 * cus * ((tiles1 + cus - 1) / cus))
-        return mvm_gemms_dma<T, X3, CT, TileTX3, TileX3G2>(a, Ntr, Nsr, Dk, s, o, st, ev);
+        return mvm_gemms_dma<T, X3, CT, TileTX3L, TileX3G2>(a, Ntr, Nsr, Dk, s, o, st, ev);
       return mvm_gemms_dma<T, X3, CT, TileX3G1, TileX3G2>(a, Ntr, Nsr, Dk, s, o, st, ev);
     }
     const int s = gemm2_splits_bf16<64, 256>(a, Ntr, Nsr, Dr, 1, true);
