@@ -30,6 +30,8 @@ constexpr int kColWaves = 4;   // targets per block
 constexpr int kAtoms = 8;      // atoms per tile side
 constexpr int kXStride = kColTile + 1;
 
+static size_t columns_lds(int M) { return (size_t)(kColTile * kXStride + 2 * M * kColTile) * sizeof(double); }
+
 // d_j += w_d (of lane L_j of each row of 16), then v += w d_j: four pairs, of which
 // the first two have their vectors in A and the others in B (x, y, z, d).  By
 // hand, as the compiler broadcasts with a move of its own; a value that the
@@ -243,24 +245,29 @@ __global__ __launch_bounds__(64 * kColWaves) void k_columns(
   }
 }
 
-// Columns of K(s, src) in the source numbering (src = s for the plain kernel).
-void kernel_columns_src(const ffk_system* s, const ffk_system* src, const int64_t* cols, int64_t k, double* out,
-                        int64_t ldo, double shift, bool accumulate, hipStream_t st) {
-  if (k <= 0) return;
-  const int M = s->M;
-  const int64_t D = s->D;
+// The interface's limit on the molecule: four values per atom and pair in the LDS
+// of a block.  The columns' kernel (a tile and two tables of 64 values an atom) and
+// the selection's need less than that at every M it allows.
+void require_columns_fit(const ffk_system* s) {
   static int max_lds = 0;
   if (max_lds == 0) {
     int dv = 0;
     HIPCHK(hipGetDevice(&dv));
     HIPCHK(hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dv));
   }
-  // the interface's limit (four values per atom and pair in the LDS of a
-  // block); the tile and the two tables below need less than that at any M
-  // whose tables fill the LDS, and fit it up to the limit
-  const size_t shm = (size_t)(kColTile * kXStride + 2 * M * kColTile) * sizeof(double);
-  if ((size_t)(4 * M + 4 * D) * sizeof(double) > (size_t)max_lds || shm > (size_t)max_lds)
+  const size_t limit = (size_t)(4 * s->M + 4 * s->D) * sizeof(double);
+  if (limit > (size_t)max_lds || columns_lds(s->M) > (size_t)max_lds)
     fail(FFK_ERR_ARG, "kernel_columns: descriptor too large for the LDS staging");
+}
+
+// Columns of K(s, src) in the source numbering (src = s for the plain kernel).
+void kernel_columns_src(const ffk_system* s, const ffk_system* src, const int64_t* cols, int64_t k, double* out,
+                        int64_t ldo, double shift, bool accumulate, hipStream_t st) {
+  if (k <= 0) return;
+  const int M = s->M;
+  const int64_t D = s->D;
+  require_columns_fit(s);
+  const size_t shm = columns_lds(M);
   if (shm > 65536)
     HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_columns), hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)shm));

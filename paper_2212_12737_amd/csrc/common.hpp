@@ -375,6 +375,8 @@ void* scratch_ptr(int device);        // nullptr before scratch_init
 // out[:, c] = K[:, cols[c]] + shift * e_{cols[c]}, column-major with leading dimension ldo.
 void kernel_columns(const ffk_system* sys, const int64_t* cols, int64_t k, double* out,
                     int64_t ldo, double shift, hipStream_t st);
+// Refuses (FFK_ERR_ARG) a molecule whose columns do not fit the LDS.
+void require_columns_fit(const ffk_system* sys);
 void kernel_diag(const ffk_system* sys, double* d, hipStream_t st);
 double max_diag(ffk_system* sys, hipStream_t st);
 

@@ -758,6 +758,7 @@ __global__ __launch_bounds__(kGreedy) void k_piv_greedy(const double* __restrict
 }
 
 int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t st) {
+  require_columns_fit(s);   // before any pivot: the single pivots' kernel would take larger molecules
   const int64_t n = s->n;
   const int64_t ld = (n + 1) / 2 * 2;   // the products move pairs of rows
   const double thr = 1e-12 * max_diag(s, st);
