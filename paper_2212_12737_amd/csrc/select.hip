@@ -513,7 +513,9 @@ __global__ __launch_bounds__(256) void k_piv_list(const double* __restrict__ d, 
   const int taken = cut;
   if (blockIdx.x == 0 && t == 0) {
     if (taken == 0) {
-      st->bound = best;
+      // (the next double up: rows outside the pool may be at best itself, so that
+      // after this pivot none of the pool may be taken before them)
+      st->bound = __longlong_as_double(__double_as_longlong(best) + 1);
       st->list[0] = st->first;
       st->count = 1;
     } else {
