@@ -245,18 +245,152 @@ __global__ __launch_bounds__(64 * kColWaves) void k_columns(
   }
 }
 
-// The interface's limit on the molecule: four values per atom and pair in the LDS
-// of a block.  The columns' kernel (a tile and two tables of 64 values an atom) and
-// the selection's need less than that at every M it allows.
-void require_columns_fit(const ffk_system* s) {
+__device__ inline double wave_sum(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
+// The same for few columns: a wave takes one (target, column) pair, lanes over the
+// pairs and then over the atoms; a block of up to four waves shares the target's
+// geometry factors in LDS and walks 64 columns.  Arguments as for k_columns, from the
+// geometries R, Rs.
+__global__ __launch_bounds__(256) void k_columns_few(
+    const double* __restrict__ R, const double* __restrict__ X, const double* __restrict__ Rs,
+    const double* __restrict__ Xs, const int* __restrict__ pairs, int M, int64_t D, const int64_t* __restrict__ cols,
+    int64_t k, double* __restrict__ out, int64_t ldo, double shift, double inv_len, double a0, double bcoef,
+    int accumulate) {
+  extern __shared__ double sm[];
+  const int nw = blockDim.x >> 6;   // waves per block (1, 2 or 4)
+  double* sRi = sm;                 // 3M
+  double* sWi = sRi + 3 * M;        // 3D: (R_ia - R_ib)/r^3 for pair (a > b)
+  double* sD = sWi + 3 * D;         // nw waves x D
+  double* sU = sD + nw * D;         // nw waves x M
+  const int64_t i = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m3 = 3 * M;
+  const double* Xi = X + i * D;
+  for (int e = threadIdx.x; e < m3; e += blockDim.x) sRi[e] = R[i * m3 + e];
+  __syncthreads();
+  for (int64_t e = threadIdx.x; e < D; e += blockDim.x) {
+    const int pq = pairs[e];
+    const int a = pq >> 16, b = pq & 0xFFFF;
+    const double dx = sRi[3 * a] - sRi[3 * b], dy = sRi[3 * a + 1] - sRi[3 * b + 1], dz = sRi[3 * a + 2] - sRi[3 * b + 2];
+    const double ir = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
+    const double ir3 = ir * ir * ir;
+    sWi[3 * e] = dx * ir3;
+    sWi[3 * e + 1] = dy * ir3;
+    sWi[3 * e + 2] = dz * ir3;
+  }
+  __syncthreads();
+  double* dW = sD + wave * D;
+  double* uW = sU + wave * M;
+  const int64_t c0 = (int64_t)blockIdx.y * kColTile;
+  // uniform trip count so that the block barriers below are reached by all waves
+  const int cols_here = (int)min((int64_t)kColTile, k - c0);
+  for (int it = 0; it < cols_here; it += nw) {
+    const int64_t cidx = c0 + it + wave;
+    const bool active = it + wave < cols_here;
+    int64_t col = 0, g = 0;
+    int p = 0, t = 0;
+    double r2 = 0.0;
+    if (active) {
+      col = cols[cidx];
+      g = col / m3;
+      const int loc = (int)(col % m3);
+      p = loc / 3;
+      t = loc % 3;
+      for (int64_t e = lane; e < D; e += 64) {      // d = x_i - x_g and |d|^2
+        const double dd = Xi[e] - Xs[g * D + e];
+        dW[e] = dd;
+        r2 += dd * dd;
+      }
+      r2 = wave_sum(r2);
+      const double* Rg = Rs + g * m3;
+      for (int b = lane; b < M; b += 64) {          // u on the pairs {p, b}
+        double u = 0.0;
+        if (b != p) {
+          const double dx = Rg[3 * p] - Rg[3 * b], dy = Rg[3 * p + 1] - Rg[3 * b + 1],
+                       dz = Rg[3 * p + 2] - Rg[3 * b + 2];
+          const double ir = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
+          const double comp = t == 0 ? dx : (t == 1 ? dy : dz);
+          u = -comp * ir * ir * ir;
+        }
+        uW[b] = u;
+      }
+    }
+    __syncthreads();
+    if (active) {
+      double du = 0.0;
+      for (int b = lane; b < M; b += 64)
+        if (b != p) du += dW[pair_of(p, b)] * uW[b];
+      du = wave_sum(du);
+      const double z = sqrt(r2) * inv_len;
+      const double ez = exp(-z);
+      const double a = a0 * (1.0 + z) * ez;
+      const double bdu = -bcoef * ez * du;
+      for (int q = lane; q < M; q += 64) {
+        double jx = 0.0, jy = 0.0, jz = 0.0;   // (J_i^T d)_q
+        double ux = 0.0, uy = 0.0, uz = 0.0;   // (J_i^T u)_q
+        for (int b = 0; b < M; ++b) {
+          if (b == q) continue;
+          const int e = pair_of(q, b);
+          const double sgn = q > b ? 1.0 : -1.0;   // sWi holds (R_larger - R_smaller)/r^3
+          const double wx = sgn * sWi[3 * e], wy = sgn * sWi[3 * e + 1], wz = sgn * sWi[3 * e + 2];
+          const double de = dW[e];
+          jx -= de * wx;
+          jy -= de * wy;
+          jz -= de * wz;
+          const double ue = (q == p) ? uW[b] : (b == p ? uW[q] : 0.0);
+          ux -= ue * wx;
+          uy -= ue * wy;
+          uz -= ue * wz;
+        }
+        const int64_t row = i * m3 + 3 * q;
+        double* o = out + cidx * ldo + row;
+        const double v0 = a * ux + bdu * jx + (row == col ? shift : 0.0);
+        const double v1 = a * uy + bdu * jy + (row + 1 == col ? shift : 0.0);
+        const double v2 = a * uz + bdu * jz + (row + 2 == col ? shift : 0.0);
+        if (accumulate) {
+          o[0] += v0;
+          o[1] += v1;
+          o[2] += v2;
+        } else {
+          o[0] = v0;
+          o[1] = v1;
+          o[2] = v2;
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
+static int max_lds_bytes() {
   static int max_lds = 0;
   if (max_lds == 0) {
     int dv = 0;
     HIPCHK(hipGetDevice(&dv));
     HIPCHK(hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dv));
   }
+  return max_lds;
+}
+
+// Whether k columns are few: k_columns takes as long for one as for 64.  The call,
+// us, by waves of one column and by lanes: M = 21, N = 2000, k = 1 53 and 103, 12 88 and
+// 106, 16 104 and 105, 24 135 and 110; M = 60, N = 2000, k = 1 200 and 584, 12 466 and
+// 594, 24 818 and 617; M = 100, N = 200, k = 1 98 and 685, 16 660 and 700, 24 967 and
+// 703; M = 30, N = 5000, k = 16 234 and 324, 24 322 and 330; M = 9, N = 200, k = 16 53 and
+// 57, 24 60 and 59.  With few atoms most lanes of such a wave idle: M = 5, N = 20000,
+// k = 4 122 and 157, 6 164 and 158; M = 3, N = 10, k = 4 43 and 45, 8 46 and 45.
+static bool few_columns(int64_t k, int M) { return k <= (M < 8 ? 4 : 16); }
+
+// The interface's limit on the molecule: four values per atom and pair in the LDS
+// of a block.  The columns' kernel (a tile and two tables of 64 values an atom) and
+// the selection's need less than that at every M it allows.
+void require_columns_fit(const ffk_system* s) {
   const size_t limit = (size_t)(4 * s->M + 4 * s->D) * sizeof(double);
-  if (limit > (size_t)max_lds || columns_lds(s->M) > (size_t)max_lds)
+  if (limit > (size_t)max_lds_bytes() || columns_lds(s->M) > (size_t)max_lds_bytes())
     fail(FFK_ERR_ARG, "kernel_columns: descriptor too large for the LDS staging");
 }
 
@@ -267,11 +401,21 @@ void kernel_columns_src(const ffk_system* s, const ffk_system* src, const int64_
   const int M = s->M;
   const int64_t D = s->D;
   require_columns_fit(s);
+  const int64_t per_launch = (int64_t)65535 * kColTile;
+  if (few_columns(k, M)) {
+    int nw = 4;
+    auto bytes = [&](int w) { return (size_t)(3 * M + 3 * D + w * (D + M)) * sizeof(double); };
+    while (nw > 1 && bytes(nw) > (size_t)max_lds_bytes()) nw >>= 1;
+    k_columns_few<<<(unsigned)s->N, 64 * nw, bytes(nw), st>>>(
+        s->R.as<double>(), s->X.as<double>(), src->R.as<double>(), src->X.as<double>(), s->pairs.as<int>(), M, D, cols,
+        k, out, ldo, shift, sqrt(5.0) / s->sigma, s->a0, s->bcoef, accumulate ? 1 : 0);
+    LAUNCHCHK();
+    return;
+  }
   const size_t shm = columns_lds(M);
   if (shm > 65536)
     HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_columns), hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)shm));
-  const int64_t per_launch = (int64_t)65535 * kColTile;
   for (int64_t c0 = 0; c0 < k; c0 += per_launch) {
     const int64_t kc = std::min(per_launch, k - c0);
     const dim3 grid((unsigned)cdiv(s->N, kColWaves), (unsigned)cdiv(kc, kColTile));
