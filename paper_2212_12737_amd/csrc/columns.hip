@@ -402,26 +402,26 @@ void kernel_columns_src(const ffk_system* s, const ffk_system* src, const int64_
   const int64_t D = s->D;
   require_columns_fit(s);
   const int64_t per_launch = (int64_t)65535 * kColTile;
-  if (few_columns(k, M)) {
-    int nw = 4;
-    auto bytes = [&](int w) { return (size_t)(3 * M + 3 * D + w * (D + M)) * sizeof(double); };
-    while (nw > 1 && bytes(nw) > (size_t)max_lds_bytes()) nw >>= 1;
-    k_columns_few<<<(unsigned)s->N, 64 * nw, bytes(nw), st>>>(
-        s->R.as<double>(), s->X.as<double>(), src->R.as<double>(), src->X.as<double>(), s->pairs.as<int>(), M, D, cols,
-        k, out, ldo, shift, sqrt(5.0) / s->sigma, s->a0, s->bcoef, accumulate ? 1 : 0);
-    LAUNCHCHK();
-    return;
-  }
+  // (without the pair tables, for which memory may be short, any number goes as few do)
+  const bool few = few_columns(k, M) || !pair_table(s, st) || !pair_table(src, st);
+  int nw = 4;   // waves of a block of k_columns_few
+  auto few_lds = [&](int w) { return (size_t)(3 * M + 3 * D + w * (D + M)) * sizeof(double); };
+  while (nw > 1 && few_lds(nw) > (size_t)max_lds_bytes()) nw >>= 1;
   const size_t shm = columns_lds(M);
-  if (shm > 65536)
+  if (!few && shm > 65536)
     HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_columns), hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)shm));
   for (int64_t c0 = 0; c0 < k; c0 += per_launch) {
     const int64_t kc = std::min(per_launch, k - c0);
-    const dim3 grid((unsigned)cdiv(s->N, kColWaves), (unsigned)cdiv(kc, kColTile));
-    k_columns<<<grid, 64 * kColWaves, shm, st>>>(s->PT.as<double>(), s->X.as<double>(), src->PT.as<double>(),
-                                                 src->X.as<double>(), s->N, M, D, cols + c0, kc, out + c0 * ldo, ldo,
-                                                 shift, sqrt(5.0) / s->sigma, s->a0, s->bcoef, accumulate ? 1 : 0);
+    const unsigned tiles = (unsigned)cdiv(kc, kColTile);
+    if (few)
+      k_columns_few<<<dim3((unsigned)s->N, tiles), 64 * nw, few_lds(nw), st>>>(
+          s->R.as<double>(), s->X.as<double>(), src->R.as<double>(), src->X.as<double>(), s->pairs.as<int>(), M, D,
+          cols + c0, kc, out + c0 * ldo, ldo, shift, sqrt(5.0) / s->sigma, s->a0, s->bcoef, accumulate ? 1 : 0);
+    else
+      k_columns<<<dim3((unsigned)cdiv(s->N, kColWaves), tiles), 64 * kColWaves, shm, st>>>(
+          s->PT.as<double>(), s->X.as<double>(), src->PT.as<double>(), src->X.as<double>(), s->N, M, D, cols + c0, kc,
+          out + c0 * ldo, ldo, shift, sqrt(5.0) / s->sigma, s->a0, s->bcoef, accumulate ? 1 : 0);
     LAUNCHCHK();
   }
 }

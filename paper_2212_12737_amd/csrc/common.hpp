@@ -206,7 +206,7 @@ struct ffk_system {
   ffk::DBuf R;              // N x M x 3 double
   ffk::DBuf pairs;          // D int32: (p << 16) | q
   ffk::DBuf X;              // N x D double (uncentred)
-  ffk::DBuf PT;             // N x D x 4 double: (R_p - R_q) / r^3 and 1 / r of every pair
+  mutable ffk::DBuf PT;     // N x D x 4 double: (R_p - R_q) / r^3 and 1 / r of every pair (pair_table)
   ffk::DBuf xmean;          // D double
   ffk::DBuf Xc;             // N x D double (centred)
   ffk::DBuf sqn;            // N double (|x_c|^2)
@@ -287,6 +287,9 @@ void sym_diag(const ffk_system* s, double* d, hipStream_t st);
 // columns.hip -- columns of K(s, src) in the numbering of src (targets from s)
 void kernel_columns_src(const ffk_system* s, const ffk_system* src, const int64_t* cols, int64_t k, double* out,
                         int64_t ldo, double shift, bool accumulate, hipStream_t st);
+// descriptor.hip -- the pair table PT of a system, formed when its columns first ask for
+// it.  False: it would take more than a sixteenth of the free device memory.
+bool pair_table(const ffk_system* s, hipStream_t st);
 void permute_atoms(const double* a, const int32_t* p, int64_t N, int M, double* out, hipStream_t st);
 void ensure_coeffs(ffk_system* sys, int prec, hipStream_t st);
 // Coefficient sets of K(t, src) (rows t->N, columns src->N, padded); both

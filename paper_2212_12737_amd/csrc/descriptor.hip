@@ -23,26 +23,20 @@ __device__ inline void pair_of(int64_t d, int& p, int& q) {
   q = (int)(d - (int64_t)p * (p - 1) / 2);
 }
 
-// x of the pair (p, q) of one geometry and its entry of the pair table; flags
-// coincident atoms and what is not finite.
-__device__ inline double descriptor_entry(const double* Rg, int p, int q, double* PT, int* bad) {
+// x of the pair (p, q) of one geometry; flags coincident atoms and what is not finite.
+__device__ inline double descriptor_entry(const double* Rg, int p, int q, int* bad) {
   const double dx = Rg[3 * p] - Rg[3 * q], dy = Rg[3 * p + 1] - Rg[3 * q + 1],
                dz = Rg[3 * p + 2] - Rg[3 * q + 2];
   const double r2 = dx * dx + dy * dy + dz * dz;
   const double x = 1.0 / sqrt(r2);
   if (!(r2 > 0.0) || !isfinite(x)) *bad = 1;
-  const double x3 = x * x * x;
-  double2* w = reinterpret_cast<double2*>(PT);
-  w[0] = make_double2(dx * x3, dy * x3);
-  w[1] = make_double2(dz * x3, x);
   return x;
 }
 
-// Descriptor, pair table and the copies the system keeps: thread e takes
-// element e of X and of R.
+// Descriptor, pairs and the copies the system keeps: thread e takes element e of X
+// and of R.
 __global__ void k_descriptor(const double* __restrict__ R, int64_t N, int M, int64_t D, double* __restrict__ X,
-                             double* __restrict__ PT, int* __restrict__ pairs, double* __restrict__ Rcopy,
-                             int* __restrict__ bad) {
+                             int* __restrict__ pairs, double* __restrict__ Rcopy, int* __restrict__ bad) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e < N * M * 3) Rcopy[e] = R[e];
   if (e >= N * D) return;
@@ -50,7 +44,42 @@ __global__ void k_descriptor(const double* __restrict__ R, int64_t N, int M, int
   int p, q;
   pair_of(d, p, q);
   if (g == 0) pairs[d] = p << 16 | q;
-  X[e] = descriptor_entry(R + g * 3 * M, p, q, PT + 4 * e, bad);
+  X[e] = descriptor_entry(R + g * 3 * M, p, q, bad);
+}
+
+// The pair table: (R_p - R_q) / r^3 and 1 / r of every pair of every geometry.
+__global__ void k_pair_table(const double* __restrict__ R, const int* __restrict__ pairs, int64_t N, int M, int64_t D,
+                             double2* __restrict__ PT) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= N * D) return;
+  const int64_t g = e / D;
+  const int pq = pairs[e % D], p = pq >> 16, q = pq & 0xFFFF;
+  const double* Rg = R + g * 3 * M;
+  const double dx = Rg[3 * p] - Rg[3 * q], dy = Rg[3 * p + 1] - Rg[3 * q + 1],
+               dz = Rg[3 * p + 2] - Rg[3 * q + 2];
+  const double x = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
+  const double x3 = x * x * x;
+  PT[2 * e] = make_double2(dx * x3, dy * x3);
+  PT[2 * e + 1] = make_double2(dz * x3, x);
+}
+
+// Twice the size of the descriptor and its centred copy (1.1 GB at M = 60, N =
+// 20000), which products, predictions and the stacked copies of a symmetrized system
+// do not need: so it is formed here, and where it would be a large part of what
+// is left, the columns do without (kernel_columns_src).
+bool pair_table(const ffk_system* s, hipStream_t st) {
+  if (s->PT) return true;
+  const size_t bytes = (size_t)(4 * s->N * s->D) * sizeof(double);
+  size_t free_bytes = 0, total = 0;
+  HIPCHK(hipMemGetInfo(&free_bytes, &total));
+  if (bytes > free_bytes / 16) return false;
+  DBuf t(bytes);
+  k_pair_table<<<cdiv(s->N * s->D, 256), 256, 0, st>>>(s->R.as<double>(), s->pairs.as<int>(), s->N, s->M, s->D,
+                                                       t.as<double2>());
+  LAUNCHCHK();
+  HIPCHK(hipStreamSynchronize(st));   // the next call may come on another stream
+  s->PT = std::move(t);
+  return true;
 }
 
 // The same of at most kFewRows geometries with their mean, centred rows and
@@ -60,10 +89,10 @@ __global__ void k_descriptor(const double* __restrict__ R, int64_t N, int M, int
 // launch fewer in kernel_predict, at M = 21, N = 2000.)
 constexpr int kFewRows = 8;
 __global__ __launch_bounds__(1024) void k_descriptor_few(const double* __restrict__ R, int N, int M, int64_t D,
-                                                         double* __restrict__ X, double* __restrict__ PT,
-                                                         int* __restrict__ pairs, double* __restrict__ Rcopy,
-                                                         double* __restrict__ mean, double* __restrict__ Xc,
-                                                         double* __restrict__ sqn, int* __restrict__ bad) {
+                                                         double* __restrict__ X, int* __restrict__ pairs,
+                                                         double* __restrict__ Rcopy, double* __restrict__ mean,
+                                                         double* __restrict__ Xc, double* __restrict__ sqn,
+                                                         int* __restrict__ bad) {
   __shared__ double red[16][kFewRows];
   for (int e = threadIdx.x; e < N * M * 3; e += 1024) Rcopy[e] = R[e];
   double sq[kFewRows] = {};
@@ -75,7 +104,7 @@ __global__ __launch_bounds__(1024) void k_descriptor_few(const double* __restric
 #pragma unroll
     for (int g = 0; g < kFewRows; ++g)
       if (g < N) {
-        x[g] = descriptor_entry(R + (int64_t)g * 3 * M, p, q, PT + 4 * (g * D + d), bad);
+        x[g] = descriptor_entry(R + (int64_t)g * 3 * M, p, q, bad);
         X[g * D + d] = x[g];
         sum += x[g];
       }
@@ -153,7 +182,6 @@ void descriptor_build(ffk_system* s, const double* R, hipStream_t st, bool coeff
   s->pairs.alloc(D * sizeof(int));
   s->R.alloc(N * M * 3 * sizeof(double));
   s->X.alloc(N * D * sizeof(double));
-  s->PT.alloc(4 * N * D * sizeof(double));
   s->Xc.alloc(N * D * sizeof(double));
   s->xmean.alloc(D * sizeof(double));
   s->sqn.alloc(N * sizeof(double));
@@ -166,13 +194,12 @@ void descriptor_build(ffk_system* s, const double* R, hipStream_t st, bool coeff
   *bad = 0;
   // up to some 10^4 elements: a block's 1024 threads take eight pairs each
   if (N <= kFewRows && N * std::max<int64_t>(D, 3 * M) <= 8192) {
-    k_descriptor_few<<<1, 1024, 0, st>>>(R, (int)N, M, D, s->X.as<double>(), s->PT.as<double>(), s->pairs.as<int>(),
-                                         s->R.as<double>(), s->xmean.as<double>(), s->Xc.as<double>(),
-                                         s->sqn.as<double>(), bad);
+    k_descriptor_few<<<1, 1024, 0, st>>>(R, (int)N, M, D, s->X.as<double>(), s->pairs.as<int>(), s->R.as<double>(),
+                                         s->xmean.as<double>(), s->Xc.as<double>(), s->sqn.as<double>(), bad);
     LAUNCHCHK();
   } else {
     k_descriptor<<<cdiv(N * std::max<int64_t>(D, 3 * M), 256), 256, 0, st>>>(
-        R, N, M, D, s->X.as<double>(), s->PT.as<double>(), s->pairs.as<int>(), s->R.as<double>(), bad);
+        R, N, M, D, s->X.as<double>(), s->pairs.as<int>(), s->R.as<double>(), bad);
     LAUNCHCHK();
     k_colmean<<<dim3(cdiv(D, 16), S), 256, 0, st>>>(s->X.as<double>(), N, D, 512, S == 1 ? 1.0 / (double)N : 1.0,
                                                     S == 1 ? s->xmean.as<double>() : part.as<double>());

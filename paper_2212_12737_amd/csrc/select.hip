@@ -839,7 +839,10 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
   // the pass is short (4e8 bytes).
   constexpr int kFew = 16, kShort = 10;
   const int64_t first = n >= 32768 ? 112 : 64;
-  int64_t pending = k <= first + 2 * kFew ? k : first;   // pivots to take one at a time next
+  bool tables = pair_table(s, st);   // which the single pivots' kernel reads
+  for (const auto& q : s->sym) tables = tables && pair_table(q.get(), st);
+  int64_t pending = !tables ? 0 : k <= first + 2 * kFew ? k : first;   // pivots to take one at a time next
+  if (!tables) panel();   // no columns: the block maxima of the diagonal
   bool running = false;         // a block whose pivot count the host has not read
   bool filled = false;          // the pool holds columns
   // The host reads a block's pivots while the diagonals are listed, and what is
@@ -880,7 +883,7 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
       greedy_done.wait();
       const int got = hp->s;
       m += got;
-      if (got < kShort && (double)n * m * 8.0 < 4e8) pending = kFew;
+      if (tables && got < kShort && (double)n * m * 8.0 < 4e8) pending = kFew;
       if (m >= k || got == 0) break;   // (no pivot: at the rank threshold, or where a value is NaN)
     }
     if (filled && m > m_pool) {
