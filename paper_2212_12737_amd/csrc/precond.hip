@@ -294,14 +294,21 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ 
 static void gram_dma(const double* L, int64_t ld, int64_t k, int64_t kp, double* C, int64_t ldc, hipStream_t st) {
   require(kp % kGramTile == 0 && kp >= k && ld % 8 == 0, "gram_dma: operand padding");
   const int64_t nt = kp / kGramTile, tiles = nt * (nt + 1) / 2, chunks = ld / 8;
-  const int ranges = chunks >= 8 * 64 && tiles <= 1000 ? 8 : 1;   // pieces of 2 GB at most, then about those of core
+  int ranges = chunks >= 8 * 64 && tiles <= 1000 ? 8 : 1;   // pieces of 2 GB at most, then about those of core
   const int64_t places = std::max(1, 2 * device_cus() / ranges);
-  const int64_t whole = tiles / places * places, rest = tiles - whole;
+  int64_t whole = tiles / places * places, rest = tiles - whole;
   int parts = 1;   // at least 32 chunks of K each
   for (int s = 2; s <= 16 && chunks / ranges >= 32ll * s; ++s)
     if (cdiv(rest * s, places) * (int64_t)parts < cdiv(rest * parts, places) * (int64_t)s) parts = s;
-  const int64_t items = whole + rest * parts;
-  DBuf part((size_t)(ranges * items * kGramTile * kGramTile * 8));
+  int64_t items = whole + rest * parts;
+  DBuf part;
+  try {
+    part.alloc((size_t)(ranges * items * kGramTile * kGramTile * 8));
+  } catch (const Error&) {   // memory is short: every tile in one piece, half the size of core
+    ranges = parts = 1;
+    whole = items = tiles;
+    part.alloc((size_t)(items * kGramTile * kGramTile * 8));
+  }
   DmaArgs g{};
   g.nseg = 1;
   g.seg[0] = SegD{L, nullptr, L, nullptr, ld, ld, (int)ld};
