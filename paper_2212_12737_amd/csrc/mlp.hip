@@ -478,12 +478,51 @@ static void forward_bf16(const ffk_mlp* net, const bf16_t* Xb, int64_t B, int64_
   HIPCHK(hipStreamSynchronize(st));   // temporaries are freed on return
 }
 
+// Whether a forward pass is large: whose tiles of 128 x 128 (64 wide for H = 64) make two
+// a CU, or one with a first layer that is deep.  Tiles of 32 from L2 read every operand
+// four times as often, and are ahead only where the larger ones leave CUs idle.  A
+// pass by tiles of 32 and through LDS, us: D = 1770, H = 1024, B = 8192 1059 and 601; D =
+// 210, H = 256, B = 32768 210 and 166; one tile a CU, D = 861, H = 256, B = 16384 254 and
+// 201, but D = 210, H = 512, B = 8192 161 and 195.
+static bool forward_through_lds(int64_t B, int D, int H) {
+  const int64_t tiles = (int64_t)cdiv(B, 128) * cdiv(H, 128), cus = device_cus();
+  return tiles >= 2 * cus || (tiles >= cus && D >= 512);
+}
+
+// Hout = gelu(X W^T + bias) through LDS: 128 x 128 tiles (64 wide for H = 64).
+static void mlp_layer_lds(const float* X, const float* W, const float* bias, int64_t B, int K, int H, float* Hout,
+                          hipStream_t st) {
+  ScalarArgs<float> g{};
+  g.M = (int)B;
+  g.N = H;
+  g.seg = SegS<float>{X, K, 1, W, K, 1, K};
+  const EpiBiasGelu e{bias, nullptr, Hout, nullptr, H, 0, (int)B, H};
+  // three of the wider tiles share a CU, so that a few past that many start alone (D =
+  // 36, H = 128, B = 100000 179 us, 146 by the narrower)
+  const int64_t wide = (int64_t)cdiv(H, 128) * cdiv(B, 128), cus = device_cus();
+  if (H <= 64 || (wide > 3 * cus && wide <= 4 * cus))
+    gemm_scalar_kernel<float, 128, 64, 16, true, true, EpiBiasGelu>
+        <<<dim3(cdiv(H, 64), cdiv(B, 128)), 256, 0, st>>>(g, e);
+  else
+    gemm_scalar_kernel<float, 128, 128, 16, true, true, EpiBiasGelu>
+        <<<dim3(cdiv(H, 128), cdiv(B, 128)), 256, 0, st>>>(g, e);
+  LAUNCHCHK();
+}
+
 void mlp_forward(const ffk_mlp* net, const float* X, int64_t B, float* out, int prec, hipStream_t st) {
   if (prec == FFK_FP32) {
     const int D = net->D, H = net->H;
     const Offs o = offs(D, H);
     const float* th = net->theta.as<float>();
     float* H1 = act(net, B);
+    if (forward_through_lds(B, D, H)) {
+      float* H2 = H1 + B * H;
+      mlp_layer_lds(X, th + o.W1, th + o.b1, B, D, H, H1, st);
+      mlp_layer_lds(H1, th + o.W2, th + o.b2, B, H, H, H2, st);
+      k_rowdot<<<cdiv(B, 4), 256, 0, st>>>(H2, B, H, th + o.w3, th + o.b3, out);
+      LAUNCHCHK();
+      return;
+    }
     float* outp = H1 + B * H;
     mlp_layer(X, th + o.W1, th + o.b1, B, D, H, H1, nullptr, nullptr, nullptr, st);
     mlp_layer(H1, th + o.W2, th + o.b2, B, H, H, nullptr, nullptr, th + o.w3, outp, st);
