@@ -234,8 +234,9 @@ struct ffk_system {
   ffk::CoeffSet stack_coef[4];
   ffk::MvmWork stack_work;
   ffk::DBuf stack_v;
-  // Prediction with this system as the model: workspace (U, N D 8 bytes,
-  // and up to 512 MB of parts of G) and the stacked vector, one call at a time.
+  // Prediction with this system as the model: workspace (U, N D 8 bytes, and up to 512
+  // MB of parts of G; large ones U, its transpose and up to 512 MB of coefficients and
+  // rows) and the stacked vector, kept until the system is freed; one call at a time.
   mutable std::mutex predict_lock;
   mutable ffk::DBuf predict_work, predict_v;
 };
@@ -298,6 +299,11 @@ void ensure_coeffs(ffk_system* sys, int prec, hipStream_t st);
 void ensure_coeffs_pair(const ffk_system* t, const ffk_system* src, CoeffSet* sets, int prec, int64_t diag_off,
                         hipStream_t st);
 void ensure_lowp_descriptor(ffk_system* sys, int prec, hipStream_t st);
+// Coefficients of T rows Xc (T x D, |x|^2: sq) against src, whose padded copies exist:
+// padded copy of the rows in Xp (Tr x Dk), dA and B (Tr x ld), and zeros in the
+// padding of these and of W (Tr x ld).
+void rect_coeffs(const ffk_system* src, const double* Xc, const double* sq, int64_t T, int64_t Tr, int64_t ld,
+                 double* Xp, double* dA, double* B, double* W, hipStream_t st);
 // Re-centre a system's descriptor with another mean (X_c = X - mean, |x_c|^2).
 void center_with(ffk_system* sys, const double* mean, hipStream_t st);
 // The same for N rows of any matrix X (N x D).
@@ -312,6 +318,26 @@ void jv_fp64(const ffk_system* s, const double* v, double* U, double* pd, double
 void jtg_rows(const double* R, const double* G, const double* X, int64_t N, int M, int64_t D, double* y,
               hipStream_t st);
 void permute_stack(const ffk_system* s, const double* v, double* out, hipStream_t st);
+// The FP64 product on the GEMMs for T rows of another system (geometries R,
+// descriptors X), whose T x N coefficients are made for the call: y = K(rows, src) v,
+// `mean` centring both.  work: product_rows_bytes(N, D, most) for up to `most` rows.
+// With first, J v is formed there; without it is that of the last call.
+size_t product_rows_bytes(int64_t N, int64_t D, int64_t most);
+void product_rows(const ffk_system* src, const double* mean, const double* v, const double* R, const double* X,
+                  int64_t T, int64_t most, bool first, double* y, void* work, hipStream_t st);
+// The FP64 product on the GEMMs against T rows of another system (geometries R,
+// descriptors X), whose T x N coefficients are made for the call: y = K(rows, src) v,
+// `mean` centring both.  work: product_rows_bytes(src->N, src->D, most) for up to
+// `most` rows; with first, J v is formed there, without it is the last call's.
+size_t product_rows_bytes(int64_t N, int64_t D, int64_t most);
+void product_rows(const ffk_system* src, const double* mean, const double* v, const double* R, const double* X,
+                  int64_t T, int64_t most, bool first, double* y, void* work, hipStream_t st);
+// descriptor.hip -- coefficients dA, B (ld columns) of T padded rows Xt (|x|^2: sqt)
+// against the padded copy of src; zeros past T and past the sources.
+void rect_coeffs(const ffk_system* src, const double* Xt, const double* sqt, int64_t T, int64_t Ttr, int64_t ld,
+                 double* dA, double* B, hipStream_t st);
+// X_c rows (N x D) into a zero-padded Nr x ld array.
+void pad_rows_copy(const double* Xc, int64_t N, int64_t D, int64_t Nr, int64_t ld, double* out, hipStream_t st);
 
 // predict.hip -- both dense steps of the FP64 product against few sources in one
 // kernel: chunks x Nt x D parts of G and the Nt x chunks row sums of W.

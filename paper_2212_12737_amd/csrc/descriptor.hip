@@ -439,6 +439,34 @@ __global__ void k_zero_padding(double* __restrict__ a, double* __restrict__ b, i
   }
 }
 
+// The coefficients of e (e.Nt padded to Ntr rows) from the padded rows Xt and Xs.
+static void coeff_gemm(const double* Xt, const double* Xs, int64_t D, int64_t Ntr, bool lower_only,
+                       const EpiCoeffPair& e, hipStream_t st) {
+  k_zero_padding<<<1024, 256, 0, st>>>(e.dA, e.B, e.Nt, e.Ns, Ntr, e.ld);
+  LAUNCHCHK();
+  const int64_t Dk = rup(D, 64);
+  DmaArgs g{};
+  g.nseg = 1;
+  g.lower_only = lower_only;
+  g.seg[0] = SegD{Xt, nullptr, Xs, nullptr, Dk, Dk, (int)rup(D, 8), 0};
+  typedef RowTile<128, 128, 2, 4, 2> TL;
+  gemm_row_kernel<double, TL, EpiCoeffPair><<<dim3(cdiv(e.Ns, 128), cdiv(e.Nt, 128)), TL::NT, 0, st>>>(g, e);
+  LAUNCHCHK();
+}
+
+void rect_coeffs(const ffk_system* src, const double* Xc, const double* sq, int64_t T, int64_t Tr, int64_t ld,
+                 double* Xp, double* dA, double* B, double* W, hipStream_t st) {
+  const int64_t D = src->D, Dk = rup(D, 64);
+  k_pad_copy<double><<<cdiv(Tr * Dk, 256), 256, 0, st>>>(Xc, T, D, D, Tr, Dk, Xp);
+  LAUNCHCHK();
+  k_zero_padding<<<1024, 256, 0, st>>>(W, W, T, src->N, Tr, ld);
+  LAUNCHCHK();
+  // (no row is a source: no column is at row + diag_off)
+  const EpiCoeffPair e{sq, src->sqn.as<double>(), dA, B, (int)T, (int)src->N, ld, INT64_MIN / 2,
+                       sqrt(5.0) / src->sigma, src->a0, src->bcoef, 0};
+  coeff_gemm(Xp, src->Xp64.as<double>(), D, Tr, false, e, st);
+}
+
 void ensure_coeffs_pair(const ffk_system* t, const ffk_system* src, CoeffSet* sets, int prec, int64_t diag_off,
                         hipStream_t st) {
   const int64_t Nt = t->N, Ns = src->N;
@@ -461,16 +489,7 @@ void ensure_coeffs_pair(const ffk_system* t, const ffk_system* src, CoeffSet* se
     } else {
       padded_rows<double>(t, t->Xp64, st);
       padded_rows<double>(src, src->Xp64, st);
-      k_zero_padding<<<1024, 256, 0, st>>>(e.dA, e.B, Nt, Ns, Ntr, Nsr);
-      LAUNCHCHK();
-      const int64_t Dk = rup(t->D, 64);
-      DmaArgs g{};
-      g.nseg = 1;
-      g.lower_only = square;
-      g.seg[0] = SegD{t->Xp64.get(), nullptr, src->Xp64.get(), nullptr, Dk, Dk, (int)rup(t->D, 8), 0};
-      typedef RowTile<128, 128, 2, 4, 2> TL;
-      gemm_row_kernel<double, TL, EpiCoeffPair><<<dim3(cdiv(Ns, 128), cdiv(Nt, 128)), TL::NT, 0, st>>>(g, e);
-      LAUNCHCHK();
+      coeff_gemm(t->Xp64.as<double>(), src->Xp64.as<double>(), t->D, Ntr, square, e, st);
     }
     c64.ready = true;
   }

@@ -1309,6 +1309,83 @@ void jtg_rows(const double* R, const double* G, const double* X, int64_t N, int 
   LAUNCHCHK();
 }
 
+// Workspace of product_rows in doubles from base on (null: only its size, in bytes).
+struct RowsBufs {
+  double *U, *UT, *pd, *s, *spart, *Xt, *Xp, *sq, *dA, *B, *W, *wpart, *G, *part;
+  size_t part_bytes;
+};
+static size_t carve_rows(int64_t N, int64_t D, int64_t most, double* base, RowsBufs* b) {
+  const int64_t Nsr = pad_rows(N), Tr = pad_rows(most), Dk = rup(D, 64), Dr = pad_rows(D);
+  int64_t off = 0;
+  auto take = [&](int64_t doubles) {
+    const int64_t o = off;
+    off += (doubles + 31) / 32 * 32;
+    return base + o;
+  };
+  RowsBufs r;
+  r.U = take(Nsr * Dk);
+  r.UT = take(Dr * Nsr);
+  r.pd = take(Nsr);
+  r.s = take(D);
+  r.spart = take(jv_blocks(N) * D);
+  r.Xt = take(most * D);
+  r.Xp = take(Tr * Dk);
+  r.sq = take(most);
+  r.dA = take(Tr * Nsr);
+  r.B = take(Tr * Nsr);
+  r.W = take(Tr * Nsr);
+  r.wpart = take(most * (Nsr / 64));
+  r.G = take(most * D);
+  const int64_t part = std::min<int64_t>(4 * most * D, 16 << 20);   // four K splits up to 128 MB of them
+  r.part_bytes = (size_t)part * 8;
+  r.part = take(part);
+  if (b) *b = r;
+  return (size_t)off * 8;
+}
+
+size_t product_rows_bytes(int64_t N, int64_t D, int64_t most) { return carve_rows(N, D, most, nullptr, nullptr); }
+
+void product_rows(const ffk_system* src_, const double* mean, const double* v, const double* R, const double* X,
+                  int64_t T, int64_t most, bool first, double* y, void* work, hipStream_t st) {
+  ffk_system* src = const_cast<ffk_system*>(src_);   // its padded copies are formed as for a product
+  const int64_t N = src->N, D = src->D;
+  const int M = src->M;
+  const int64_t Nsr = pad_rows(N), Tr = pad_rows(T), Dk = rup(D, 64), Dr = pad_rows(D);
+  RowsBufs b;
+  carve_rows(N, D, most, static_cast<double*>(work), &b);
+  if (first) {
+    ensure_lowp_descriptor(src, FFK_FP64, st);
+    zero_fill(b.U, Nsr * Dk * 8, st);
+    zero_fill(b.UT, Dr * Nsr * 8, st);
+    launch_jv<0>(N, M, st, src->R.as<double>(), src->pairs.as<int>(), v, src->Xc.as<double>(), N, M, D, (void*)b.U,
+                 nullptr, Dk, (void*)b.UT, nullptr, Nsr, b.pd, b.spart);
+    LAUNCHCHK();
+    k_colsum_final<<<cdiv(D, 4), 256, 0, st>>>(b.spart, jv_blocks(N), D, b.s);
+    LAUNCHCHK();
+  }
+  center_rows(X, mean, T, D, b.Xt, b.sq, st);
+  rect_coeffs(src, b.Xt, b.sq, T, Tr, Nsr, b.Xp, b.dA, b.B, b.W, st);
+  const MvmArgs a{T, N, D, src->a0, b.Xt, b.pd, b.s, b.wpart, b.G, b.part, b.part_bytes};
+  DmaOps o{};
+  o.dAh = b.dA;
+  o.Bc = b.B;
+  o.Uh = b.U;
+  o.UTh = b.UT;
+  o.Wh = b.W;
+  o.Xh = b.Xp;
+  o.XTh = src->XpT64.get();
+  const GemmOut go = mvm_gemms_for<double, false, double>(a, Tr, Nsr, Dk, Dr, o, st, nullptr);
+  const size_t shj = (3 * M + D + 1) * sizeof(double);
+  const double* none = nullptr;
+  double* no_part = nullptr;
+  if (go.splits == 1)
+    k_jtg<<<(unsigned)T, M <= 64 ? 64 : 128, shj, st>>>(R, b.G, X, none, 0.0, M, D, y, no_part);
+  else
+    launch_jtg_reduce(T, D, shj, st, static_cast<const double*>(b.part), go.splits, T, b.s, b.Xt, mean, b.wpart,
+                      go.ntn, src->a0, R, none, 0.0, M, D, y, no_part);
+  LAUNCHCHK();
+}
+
 void permute_stack(const ffk_system* s, const double* v, double* out, hipStream_t st) {
   const int S = (int)s->sym.size();
   k_permute_stack<<<cdiv(s->n * S, 256), 256, 0, st>>>(v, s->sym_perm.as<int32_t>(), S, s->N, s->M, out);

@@ -252,12 +252,48 @@ void product_few(const double* Xt, const double* Xs, const double* U, int64_t ld
   else launch_part<1, 4, true>(g, st);
 }
 
+// Whether a prediction is large: then the T x N coefficients and the product's GEMMs,
+// which keep their tiles' rows in LDS, take less than k_predict_part, which reads them
+// from L2 for every tile (28 TFLOP/s at D <= 861, 12 to 17 where rows are longer).
+// Kernel and GEMMs, us: M = 60, N = 20000, T = 100 2284 and 2489, 200 3964 and 2850, 1600
+// 28105 and 11174; M = 100, N = 10000, T = 64 2373 and 2890, 100 3905 and 2976; M = 100, N
+// = 3000, T = 200 1438 and 1656, 300 2283 and 1809; M = 42, N = 20000, T = 400 2157 and
+// 2428, 600 3100 and 2387.  Where N is far above D the coefficients cost more than the
+// parts of G: M = 21, N = 20000, T = 4000 4185 and 6900; M = 30, T = 1600 3660 and 4048.
+static bool predict_by_gemms(int64_t T, int64_t N, int64_t D) {
+  return (double)T * N * D >= (D >= 1024 ? 4e9 : 8e9) && 32 * D >= N;
+}
+
 // F = K(te, src) v for sources whose descriptors are centred with `mean`, with
-// the model's workspace (held by the caller until the stream is done).
+// the model's workspace (held by the caller until the stream is done); by the GEMMs.
+static void predict_large(const ffk_system* src, const double* mean, const ffk_system* te, const double* v, double* F,
+                          DBuf& work, hipStream_t st) {
+  const int64_t N = src->N, D = src->D;
+  const int M = src->M;
+  // test geometries at a time: 512 MB of what there is of them, in batches of about one size
+  const int64_t row = (int64_t)(product_rows_bytes(N, D, 1 << 17) - product_rows_bytes(N, D, 1 << 16)) >> 16;
+  const int64_t limit = std::max<int64_t>(128, (512ll << 20) / row / 128 * 128);
+  const int64_t most = cdiv(te->N, cdiv(te->N, limit));
+  work.ensure(product_rows_bytes(N, D, most));
+  for (int64_t b0 = 0; b0 < te->N; b0 += most)
+    product_rows(src, mean, v, te->R.as<double>() + b0 * 3 * M, te->X.as<double>() + b0 * D,
+                 std::min(most, te->N - b0), most, b0 == 0, F + b0 * 3 * M, work.get(), st);
+  HIPCHK(hipStreamSynchronize(st));   // the workspace may be the next call's, on another stream
+}
+
+// The same by k_predict_part, or by the GEMMs where the prediction is large.
 static void predict_from(const ffk_system* src, const double* mean, const ffk_system* te, const double* v, double* F,
                          DBuf& work, hipStream_t st) {
   const int64_t N = src->N, D = src->D;
   const int M = src->M;
+  if (predict_by_gemms(te->N, N, D)) {
+    try {
+      predict_large(src, mean, te, v, F, work, st);
+      return;
+    } catch (const Error& e) {   // memory is short: the kernel below needs less
+      if (e.status != FFK_ERR_OOM) throw;
+    }
+  }
   // test geometries at a time: up to 512, fewer where the parts of G in chunks of
   // 64 training geometries would take more than 256 MB (those of 16, of at most a
   // third of them, may double that)
