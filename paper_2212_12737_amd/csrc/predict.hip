@@ -186,27 +186,29 @@ __global__ __launch_bounds__(256, TB == 2 ? 2 : 1) void k_predict_part(PredictAr
 }
 
 // G[t, d] = sum of the chunks' parts + a0 s_d + w_t x_t,d: one workgroup per
-// test geometry and 64 columns, its sixteen waves each sum every sixteenth
-// chunk (eight loads in flight), then meet in a fixed order.
-__global__ __launch_bounds__(1024) void k_predict_reduce(const double* __restrict__ part, int chunks, int64_t T, int D,
+// test geometry and 64 columns, its W = 16 waves each sum every sixteenth chunk
+// (eight loads in flight), then meet in a fixed order.  Four waves where there are
+// no more chunks.
+template <int W>
+__global__ __launch_bounds__(64 * W) void k_predict_reduce(const double* __restrict__ part, int chunks, int64_t T, int D,
                                                          const double* __restrict__ wpart, const double* __restrict__ s,
                                                          const double* __restrict__ Xt, double a0,
                                                          double* __restrict__ G) {
-  __shared__ double sh[16][64];
-  __shared__ double shw[16];
+  __shared__ double sh[W][64];
+  __shared__ double shw[W];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t t = blockIdx.y;
   const int d0 = blockIdx.x * 64, d = min(d0 + lane, D - 1);
   const double* p = part + t * D + d;
   double acc = 0.0, w = 0.0;
-  for (int z0 = wave; z0 < chunks; z0 += 16 * 8) {
+  for (int z0 = wave; z0 < chunks; z0 += W * 8) {
     double v[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = p[(int64_t)min(z0 + 16 * e, chunks - 1) * T * D];
+    for (int e = 0; e < 8; ++e) v[e] = p[(int64_t)min(z0 + W * e, chunks - 1) * T * D];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc += z0 + 16 * e < chunks ? v[e] : 0.0;
+    for (int e = 0; e < 8; ++e) acc += z0 + W * e < chunks ? v[e] : 0.0;
   }
-  for (int z = wave * 64 + lane; z < chunks; z += 1024) w += wpart[t * chunks + z];
+  for (int z = wave * 64 + lane; z < chunks; z += 64 * W) w += wpart[t * chunks + z];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) w += __shfl_xor(w, o);
   sh[wave][lane] = acc;
@@ -215,7 +217,7 @@ __global__ __launch_bounds__(1024) void k_predict_reduce(const double* __restric
   if (wave == 0 && d0 + lane < D) {
     double a = 0.0, ws = 0.0;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < W; ++q) {
       a += sh[q][lane];
       ws += shw[q];
     }
@@ -294,11 +296,15 @@ static void predict_from(const ffk_system* src, const double* mean, const ffk_sy
       if (e.status != FFK_ERR_OOM) throw;
     }
   }
-  // test geometries at a time: up to 512, fewer where the parts of G in chunks of
+  // Test geometries at a time: up to 512, fewer where the parts of G in chunks of
   // 64 training geometries would take more than 256 MB (those of 16, of at most a
-  // third of them, may double that)
-  const int64_t most = (256ll << 20) / ((int64_t)cdiv(N, 64) * D * 8) / 32 * 32;
-  const int64_t limit = std::min<int64_t>(512, std::max<int64_t>(32, most));
+  // third of them, may double that), and more while they take no more than 16 MB: a
+  // batch of a small model is its four launches (M = 3, N = 5, T = 12000: 372 us in batches
+  // of 512, 80 before there were batches), while larger parts leave the last-level cache
+  // (M = 42, N = 2000, T = 4000: 1.88 ms, 2.23 with 128 MB of them).
+  const int64_t row = (int64_t)cdiv(N, 64) * D * 8;
+  const int64_t limit = std::max(std::min<int64_t>(512, std::max<int64_t>(32, (256ll << 20) / row / 32 * 32)),
+                                 std::min<int64_t>(32768, (16ll << 20) / row / 32 * 32));
   const int64_t batch = std::min<int64_t>(te->N, (cdiv(te->N, cdiv(te->N, limit)) + 31) / 32 * 32);   // of about one size
   // 32 test and 64 training geometries a workgroup where that gives every CU
   // one, else 16 test ones, and 16 training ones where even so some have none
@@ -311,8 +317,9 @@ static void predict_from(const ffk_system* src, const double* mean, const ffk_sy
   int chunks = cdiv(N, 16 * CB);
   const int64_t places = device_cus() / 4, most_xcd = (int64_t)tiles * cdiv(chunks, 8);
   int64_t tail = 0;   // training geometries in the smaller workgroups
-  if (TB == 2 && most_xcd > places && most_xcd % places < places / 2) {
-    chunks = (int)std::min<int64_t>(chunks, most_xcd / places * places / tiles * 8);
+  const int64_t in_full = most_xcd / places * places / tiles * 8;   // chunks of the full rounds (none of many tiles)
+  if (TB == 2 && most_xcd % places < places / 2 && in_full > 0) {
+    chunks = (int)std::min<int64_t>(chunks, in_full);
     tail = std::max<int64_t>(0, N - 64ll * chunks);
   }
   const int planes = chunks + cdiv(tail, 16);
@@ -347,8 +354,13 @@ static void predict_from(const ffk_system* src, const double* mean, const ffk_sy
       g.tiles = cdiv(T, 16);
       launch_part<1, 1>(g, st);
     }
-    k_predict_reduce<<<dim3(cdiv(D, 64), T), 1024, 0, st>>>(w + opart, planes, T, (int)D, w + owp, w + os, w + oXt,
-                                                            src->a0, w + oG);
+    auto reduce = [&](auto waves) {
+      constexpr int W = decltype(waves)::value;
+      k_predict_reduce<W><<<dim3(cdiv(D, 64), T), 64 * W, 0, st>>>(w + opart, planes, T, (int)D, w + owp, w + os,
+                                                                   w + oXt, src->a0, w + oG);
+    };
+    if (planes <= 4) reduce(std::integral_constant<int, 4>());
+    else reduce(std::integral_constant<int, 16>());
     LAUNCHCHK();
     jtg_rows(te->R.as<double>() + b0 * 3 * M, w + oG, te->X.as<double>() + b0 * D, T, M, D, F + b0 * 3 * M, st);
   }
