@@ -428,7 +428,7 @@ void gemm64_in32(int M, int N, int K, double alpha, View32 A, View32 B, double b
 // lda even, >= n). Returns the index of the first failing pivot or -1.
 int64_t potrf_lower(double* A, int64_t n, int64_t lda, hipStream_t st);
 // In-place inverse of the lower-triangular n x n column-major matrix A (16-byte
-// aligned, lda even, >= n; for odd n it clears the padding row n).
+// aligned, lda even, >= n; for odd n > 64 it clears the padding row n).
 void trtri_lower(double* A, int64_t n, int64_t lda, hipStream_t st);
 
 // reduce.hip -- deterministic two-stage reductions; `part` holds >= kRedParts doubles.

@@ -196,6 +196,7 @@ void trtri_lower(double* A, int64_t n, int64_t lda, hipStream_t st) {
   const int64_t nblk = cdiv(n, NB2);
   k_tri64<<<cdiv(n, NB), 256, 0, st>>>(A, n, lda);
   LAUNCHCHK();
+  if (n <= NB) return;   // one block, and nothing beside it (labels at n = 9: 116 us with the rest's launches, now 93)
   k_zero_upper_blocks<<<(unsigned)n, 64, 0, st>>>(A, n, lda);
   LAUNCHCHK();
   // products of the pairs (the second level's are the larger), later one panel
@@ -203,7 +204,7 @@ void trtri_lower(double* A, int64_t n, int64_t lda, hipStream_t st) {
   const size_t tb = std::max<size_t>((size_t)nblk * (NB2 / 2) * (NB2 / 2) * 8, (size_t)ldt * NB2 * 8);
   DBuf T(tb);
   HIPCHK(hipMemsetAsync(T.get(), 0, tb, st));
-  for (int h = NB; h < NB2; h *= 2) {
+  for (int h = NB; h < NB2 && h < n; h *= 2) {
     const int pairs = cdiv(n, 2 * h);
     const int64_t step = 2 * h * (1 + lda);   // from one pair to the next
     Gemm64Args g{};
