@@ -145,7 +145,7 @@ __device__ inline void mlp_tile(const float* __restrict__ A, int64_t lda, const 
         if (kscale) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            const float f = kscale[min(k + j, K - 1)];
+            const float f = k + j < K ? kscale[min(k + j, K - 1)] : 0.f;   // (not the last one: 0 times infinity)
 #pragma unroll
             for (int i = 0; i < NB; ++i) a[u][i][j] *= f;
           }
