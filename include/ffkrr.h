@@ -165,12 +165,13 @@ typedef enum {
   FFK_CLK_COLSUM = 1,      /* column sums 1^T U */
   FFK_CLK_GEMM1 = 2,       /* P = X_c U^T with the fused W / row-sum epilogue */
   FFK_CLK_GEMM2 = 3,       /* [dA | -W] [U ; X_c] (split-K partials or G epilogue) */
-  FFK_CLK_GEMM2_REDUCE = 4,/* split-K reduction with the G epilogue */
+  FFK_CLK_GEMM2_REDUCE = 4,/* predictions: the sum of the parts of G (products sum them in J^T G) */
   FFK_CLK_JTG = 5,         /* y = J^T G + shift v */
   FFK_CLK_GEMV_T = 6,      /* preconditioner apply: L^T r partials (one pass over L) */
   FFK_CLK_GEMV_N = 7,      /* preconditioner apply: L t partials (one pass over L) */
   FFK_CLK_CORE = 8,        /* preconditioner apply: the two k x k triangular products */
-  FFK_CLK_FUSED = 9,       /* BF16 products at short D (<= 96; <= 128 up to N^2 = 4096^2): both GEMMs in one kernel */
+  FFK_CLK_FUSED = 9,       /* both GEMMs in one kernel: BF16 products at short D (<= 96; <= 128 up to N^2 =
+                              4096^2), FP64 products of few geometries, predictions except large ones */
   FFK_CLK_COUNT = 10
 } ffk_clock;
 ffk_status ffk_clock_enable(ffk_ctx* ctx, int32_t stride);

@@ -341,6 +341,7 @@ static void predict_from(const ffk_system* src, const double* mean, const ffk_sy
     PredictArgs g{w + oXt, w + osq, src->Xc.as<double>(), src->sqn.as<double>(), w + oU, w + opd, w + opart, w + owp,
                   T, (int)(N - tail), (int)D, chunks, cdiv(T, 16 * TB), sqrt(5.0) / src->sigma, src->a0, src->bcoef,
                   D, nullptr, nullptr, 0, planes};
+    clk_begin(CLK_FUSED, st);
     if (CB == 1) launch_part<1, 1>(g, st);
     else if (TB == 1) launch_part<1, 4>(g, st);
     else launch_part<2, 4>(g, st);
@@ -354,14 +355,17 @@ static void predict_from(const ffk_system* src, const double* mean, const ffk_sy
       g.tiles = cdiv(T, 16);
       launch_part<1, 1>(g, st);
     }
+    clk_end(CLK_FUSED, st);
     auto reduce = [&](auto waves) {
       constexpr int W = decltype(waves)::value;
       k_predict_reduce<W><<<dim3(cdiv(D, 64), T), 64 * W, 0, st>>>(w + opart, planes, T, (int)D, w + owp, w + os,
                                                                    w + oXt, src->a0, w + oG);
     };
+    clk_begin(CLK_GEMM2_REDUCE, st);
     if (planes <= 4) reduce(std::integral_constant<int, 4>());
     else reduce(std::integral_constant<int, 16>());
     LAUNCHCHK();
+    clk_end(CLK_GEMM2_REDUCE, st);
     jtg_rows(te->R.as<double>() + b0 * 3 * M, w + oG, te->X.as<double>() + b0 * D, T, M, D, F + b0 * 3 * M, st);
   }
   HIPCHK(hipStreamSynchronize(st));   // the workspace may be the next call's, on another stream
