@@ -376,14 +376,34 @@ static int max_lds_bytes() {
   return max_lds;
 }
 
-// Whether k columns are few: k_columns takes as long for one as for 64.  The call,
-// us, by waves of one column and by lanes: M = 21, N = 2000, k = 1 53 and 103, 12 88 and
-// 106, 16 104 and 105, 24 135 and 110; M = 60, N = 2000, k = 1 200 and 584, 12 466 and
-// 594, 24 818 and 617; M = 100, N = 200, k = 1 98 and 685, 16 660 and 700, 24 967 and
-// 703; M = 30, N = 5000, k = 16 234 and 324, 24 322 and 330; M = 9, N = 200, k = 16 53 and
-// 57, 24 60 and 59.  With few atoms most lanes of such a wave idle: M = 5, N = 20000,
-// k = 4 122 and 157, 6 164 and 158; M = 3, N = 10, k = 4 43 and 45, 8 46 and 45.
-static bool few_columns(int64_t k, int M) { return k <= (M < 8 ? 4 : 16); }
+// LDS of a block of k_columns_few, and the waves (1, 2 or 4) that fit.
+static size_t few_lds(int w, int M, int64_t D) { return (size_t)(3 * M + 3 * D + w * (D + M)) * sizeof(double); }
+static int few_waves(int M, int64_t D) {
+  int nw = 4;
+  while (nw > 1 && few_lds(nw, M, D) > (size_t)max_lds_bytes()) nw >>= 1;
+  return nw;
+}
+
+// Whether k columns are few: k_columns takes as long for one as for 64, k_columns_few a
+// step for every nw of them, in rounds of the blocks that fit the CUs' LDS.  A step takes
+// a tenth to a twelfth of a round of k_columns where molecules are large; from 16 or 24
+// columns on, fewer of small molecules, most of whose lanes idle, the arithmetic
+// decides.  The call, us, few and k_columns: M = 100, N = 1000, k = 4 866 and 753, N = 200,
+// k = 10 564 and 701, 14 754 and 705; M = 80, N = 500, k = 10 433 and 466, 14 578 and 464; M =
+// 70, N = 2000, k = 10 830 and 758; M = 64, N = 1000, k = 12 277 and 329, 14 343 and 331; M =
+// 60, N = 2000, k = 12 466 and 589, 20 734 and 617; M = 43, N = 3000, k = 16 269 and 379, 24
+// 371 and 393; M = 30, N = 5000, k = 24 306 and 317; M = 21, N = 2000, k = 1 53 and 103, 14
+// 101 and 104, 20 117 and 106, N = 100, k = 24 74 and 87; M = 9, N = 200, k = 12 53 and 59;
+// M = 8, N = 100, k = 8 52 and 51; M = 5, N = 20000, k = 4 112 and 159, 8 178 and 156.
+static bool few_columns(int64_t k, int M, int64_t D, int64_t N) {
+  if (k > (M < 8 ? 4 : M < 12 ? 12 : M < 24 && N > 512 ? 16 : 24)) return false;
+  const int64_t cus = device_cus(), lds = max_lds_bytes();
+  const int nw = few_waves(M, D);
+  const int64_t rounds = cdiv(N, cus * std::min<int64_t>(8, lds / (int64_t)few_lds(nw, M, D)));
+  const int64_t tiles = cdiv(cdiv(N, kColWaves), cus * std::min<int64_t>(8, lds / (int64_t)columns_lds(M)));
+  const int steps = nw == 1 || (nw == 4 && D < 2200) ? 12 : 10;   // of a round
+  return rounds * cdiv(k, nw) <= steps * tiles;
+}
 
 // The interface's limit on the molecule: four values per atom and pair in the LDS
 // of a block.  The columns' kernel (a tile and two tables of 64 values an atom) and
@@ -403,10 +423,8 @@ void kernel_columns_src(const ffk_system* s, const ffk_system* src, const int64_
   require_columns_fit(s);
   const int64_t per_launch = (int64_t)65535 * kColTile;
   // (without the pair tables, for which memory may be short, any number goes as few do)
-  const bool few = few_columns(k, M) || !pair_table(s, st) || !pair_table(src, st);
-  int nw = 4;   // waves of a block of k_columns_few
-  auto few_lds = [&](int w) { return (size_t)(3 * M + 3 * D + w * (D + M)) * sizeof(double); };
-  while (nw > 1 && few_lds(nw) > (size_t)max_lds_bytes()) nw >>= 1;
+  const bool few = few_columns(k, M, D, s->N) || !pair_table(s, st) || !pair_table(src, st);
+  const int nw = few_waves(M, D);
   const size_t shm = columns_lds(M);
   if (!few && shm > 65536)
     HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_columns), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -415,7 +433,7 @@ void kernel_columns_src(const ffk_system* s, const ffk_system* src, const int64_
     const int64_t kc = std::min(per_launch, k - c0);
     const unsigned tiles = (unsigned)cdiv(kc, kColTile);
     if (few)
-      k_columns_few<<<dim3((unsigned)s->N, tiles), 64 * nw, few_lds(nw), st>>>(
+      k_columns_few<<<dim3((unsigned)s->N, tiles), 64 * nw, few_lds(nw, M, D), st>>>(
           s->R.as<double>(), s->X.as<double>(), src->R.as<double>(), src->X.as<double>(), s->pairs.as<int>(), M, D,
           cols + c0, kc, out + c0 * ldo, ldo, shift, sqrt(5.0) / s->sigma, s->a0, s->bcoef, accumulate ? 1 : 0);
     else
