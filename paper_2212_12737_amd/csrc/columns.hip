@@ -387,16 +387,19 @@ static int few_waves(int M, int64_t D) {
 // Whether k columns are few: k_columns takes as long for one as for 64, k_columns_few a
 // step for every nw of them, in rounds of the blocks that fit the CUs' LDS.  A step takes
 // a tenth to a twelfth of a round of k_columns where molecules are large; from 16 or 24
-// columns on, fewer of small molecules, most of whose lanes idle, the arithmetic
-// decides.  The call, us, few and k_columns: M = 100, N = 1000, k = 4 866 and 753, N = 200,
-// k = 10 564 and 701, 14 754 and 705; M = 80, N = 500, k = 10 433 and 466, 14 578 and 464; M =
-// 70, N = 2000, k = 10 830 and 758; M = 64, N = 1000, k = 12 277 and 329, 14 343 and 331; M =
-// 60, N = 2000, k = 12 466 and 589, 20 734 and 617; M = 43, N = 3000, k = 16 269 and 379, 24
-// 371 and 393; M = 30, N = 5000, k = 24 306 and 317; M = 21, N = 2000, k = 1 53 and 103, 14
-// 101 and 104, 20 117 and 106, N = 100, k = 24 74 and 87; M = 9, N = 200, k = 12 53 and 59;
-// M = 8, N = 100, k = 8 52 and 51; M = 5, N = 20000, k = 4 112 and 159, 8 178 and 156.
+// columns on (up to 48 of few targets, which leave CUs idle either way), fewer of small
+// molecules, most of whose lanes idle, the arithmetic decides.  The call, us, by
+// k_columns_few and k_columns: M = 100, N = 1000, k = 4 866 and 753, N = 200, k = 10 564 and
+// 701, 14 754 and 705; M = 80, N = 500, k = 10 433 and 466, 14 578 and 464; M = 70, N = 2000,
+// k = 10 830 and 758; M = 64, N = 1000, k = 12 277 and 329, 14 343 and 331; M = 60, N = 2000,
+// k = 12 466 and 589, 20 734 and 617; M = 43, N = 3000, k = 16 269 and 379, 24 371 and 393,
+// N = 100, k = 48 172 and 193; M = 30, N = 5000, k = 24 306 and 317, N = 500, k = 32 109 and
+// 119, 48 144 and 123; M = 21, N = 2000, k = 1 53 and 103, 14 101 and 104, 20 117 and 106, N
+// = 100, k = 24 74 and 87; M = 9, N = 200, k = 12 53 and 59; M = 8, N = 100, k = 8 52 and 51;
+// M = 5, N = 20000, k = 4 112 and 159, 8 178 and 156.
 static bool few_columns(int64_t k, int M, int64_t D, int64_t N) {
-  if (k > (M < 8 ? 4 : M < 12 ? 12 : M < 24 && N > 512 ? 16 : 24)) return false;
+  const int many = N > 512 ? (M < 24 ? 16 : 24) : M < 16 ? 16 : M < 24 ? 24 : M < 36 ? 32 : 48;
+  if (k > (M < 8 ? 4 : M < 12 ? 12 : many)) return false;
   const int64_t cus = device_cus(), lds = max_lds_bytes();
   const int nw = few_waves(M, D);
   const int64_t rounds = cdiv(N, cus * std::min<int64_t>(8, lds / (int64_t)few_lds(nw, M, D)));

@@ -32,7 +32,7 @@ def test_columns_on_both_sides_of_the_rule(ctx, M, N):
     K = ok.dense_kernel(s.R, SIGMA)
     S = ffk.descriptor_build(ctx, torch.as_tensor(s.R, device="cuda"), SIGMA)
     rng = np.random.Generator(np.random.PCG64([M, N]))
-    for k in (1, 2, 4, 5, 12, 13, 16, 17, 24, 25, 33):
+    for k in (1, 2, 4, 5, 12, 13, 16, 17, 24, 25, 32, 33, 48, 49):
         cols = rng.integers(0, S.n, size=k)
         C = ffk.kernel_columns(ctx, S, torch.from_numpy(cols)).cpu().numpy()
         err = np.linalg.norm(C - K[:, cols]) / np.linalg.norm(K[:, cols])
