@@ -14,19 +14,19 @@
 //
 // gemm_dma_kernel: BF16 and split-BF16 products of fragment-major operands.
 //
-// gemm_scalar_kernel: double (v_mfma_f64_16x16x4_f64) arithmetic on strided
-//   views whose stored type may be narrower: the low-memory build, whose factor
-//   is held in FP32.  One operand element per lane per instruction, so operands
-//   may be K-contiguous or M-contiguous; LDS tiles are stored [k][m] with 16
-//   elements of padding per row.  Bounds are checked.  4 waves, 2 x 2.
+// gemm_scalar_kernel: products of strided views, in double (v_mfma_f64_16x16x4_f64;
+//   the stored type may be narrower: the low-memory build, whose factor is held in
+//   FP32) or float (v_mfma_f32_16x16x4_f32; the score network's large FP32 layers).
+//   One operand element per lane per instruction, so operands may be K-contiguous
+//   or M-contiguous; LDS tiles are stored [k][m] with 16 elements of padding per
+//   row.  Bounds are checked.  4 waves, 2 x 2.
 //
-// gemm_bf16_kernel: v_mfma_f32_16x16x32_bf16, FP32 accumulation, optional split
-//   mode (X3) that adds hi*hi + hi*lo + lo*hi (the score network).  Operands are
-//   K-contiguous bf16 arrays whose row count is padded to a multiple of BM (or
-//   BN) and whose leading dimension is padded to a multiple of BK with zeros, so
-//   tiles are loaded with unpredicated 16-byte vectors.  LDS tiles are [m][k]
-//   with 8 elements of row padding, which makes the 16-byte operand reads of one
-//   16-lane group hit distinct banks.  4 waves, 2 x 2.
+// gemm_bf16_kernel: v_mfma_f32_16x16x32_bf16, FP32 accumulation (the score network).
+//   Operands are K-contiguous bf16 arrays whose row count is padded to a multiple of
+//   BM (or BN) and whose leading dimension is padded to a multiple of BK with zeros,
+//   so tiles are loaded with unpredicated 16-byte vectors.  LDS tiles are [m][k] with
+//   8 elements of row padding, which makes the 16-byte operand reads of one 16-lane
+//   group hit distinct banks.  4 waves, 2 x 2.
 //
 // FP64 products of column-major operands are in gemm64.hpp.
 #pragma once
@@ -88,7 +88,7 @@ template <typename TI> struct ScalarArgs {
 };
 
 // ---------------------------------------------------------------------------
-// Strided-operand MFMA engine (FP64 arithmetic)
+// Strided-operand MFMA engine (FP64 or FP32 arithmetic)
 // ---------------------------------------------------------------------------
 template <typename T, int BM, int BN, int BK, bool AKC, bool BKC, class Epi, typename TI = T>
 __global__ __launch_bounds__(256) void gemm_scalar_kernel(ScalarArgs<TI> g, Epi epi) {
@@ -179,35 +179,28 @@ __global__ __launch_bounds__(256) void gemm_scalar_kernel(ScalarArgs<TI> g, Epi 
 }
 
 // ---------------------------------------------------------------------------
-// BF16 MFMA engine (optionally 3-product split)
+// BF16 MFMA engine
 // ---------------------------------------------------------------------------
-struct SegB {
-  const bf16_t *Ah, *Al;   // rows padded to BM multiple, ld multiple of BK
-  const bf16_t *Bh, *Bl;
+struct Bf16Args {
+  const bf16_t *A, *B;     // rows padded to a BM (BN) multiple, ld a multiple of BK
   int64_t lda, ldb;
   int K;                   // multiple of BK (padded)
 };
-struct Bf16Args {
-  int nseg;
-  SegB seg[2];
-};
 
-template <int BM, int BN, int BK, bool X3, class Epi>
+template <int BM, int BN, int BK, class Epi>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(Bf16Args g, Epi epi) {
   constexpr int PAD = 8;
   constexpr int LDS_ROW = BK + PAD;
   constexpr int VA = BM * BK / 8 / 256;   // 16-byte vectors per thread
   constexpr int VB = BN * BK / 8 / 256;
   constexpr int TM = BM / 32, TN = BN / 32;
-  constexpr int NARR = X3 ? 2 : 1;
-  __shared__ bf16_t As[NARR][BM * LDS_ROW];
-  __shared__ bf16_t Bs[NARR][BN * LDS_ROW];
+  __shared__ bf16_t As[BM * LDS_ROW];
+  __shared__ bf16_t Bs[BN * LDS_ROW];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
   const int wm0 = (wave >> 1) * (BM / 2), wn0 = (wave & 1) * (BN / 2);
-  const int t0 = g.seg[0].K / BK;
-  const int T_ = t0 + (g.nseg > 1 ? g.seg[1].K / BK : 0);
+  const int T_ = g.K / BK;
 
   f4 acc[TM][TN];
 #pragma unroll
@@ -215,90 +208,67 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(Bf16Args g, Epi epi) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f4{0, 0, 0, 0};
 
-  u4 ra[NARR][VA], rb[NARR][VB];
+  u4 ra[VA], rb[VB];
   auto load = [&](int t) {
-    const SegB& s = (t < t0) ? g.seg[0] : g.seg[1];
-    const int k0 = (t < t0 ? t : t - t0) * BK;
+    const int k0 = t * BK;
 #pragma unroll
     for (int i = 0; i < VA; ++i) {
       const int e = tid + 256 * i;
       const int mm = e / (BK / 8), kv = e % (BK / 8);
-      const int64_t off = (int64_t)(m0 + mm) * s.lda + k0 + kv * 8;
-      ra[0][i] = *reinterpret_cast<const u4*>(s.Ah + off);
-      if (X3) ra[NARR - 1][i] = *reinterpret_cast<const u4*>(s.Al + off);
+      ra[i] = *reinterpret_cast<const u4*>(g.A + (int64_t)(m0 + mm) * g.lda + k0 + kv * 8);
     }
 #pragma unroll
     for (int i = 0; i < VB; ++i) {
       const int e = tid + 256 * i;
       const int nn = e / (BK / 8), kv = e % (BK / 8);
-      const int64_t off = (int64_t)(n0 + nn) * s.ldb + k0 + kv * 8;
-      rb[0][i] = *reinterpret_cast<const u4*>(s.Bh + off);
-      if (X3) rb[NARR - 1][i] = *reinterpret_cast<const u4*>(s.Bl + off);
+      rb[i] = *reinterpret_cast<const u4*>(g.B + (int64_t)(n0 + nn) * g.ldb + k0 + kv * 8);
     }
   };
   auto store = [&]() {
 #pragma unroll
-    for (int h = 0; h < NARR; ++h) {
+    for (int i = 0; i < VA; ++i) {
+      const int e = tid + 256 * i;
+      const int mm = e / (BK / 8), kv = e % (BK / 8);
+      *reinterpret_cast<u4*>(&As[mm * LDS_ROW + kv * 8]) = ra[i];
+    }
 #pragma unroll
-      for (int i = 0; i < VA; ++i) {
-        const int e = tid + 256 * i;
-        const int mm = e / (BK / 8), kv = e % (BK / 8);
-        *reinterpret_cast<u4*>(&As[h][mm * LDS_ROW + kv * 8]) = ra[h][i];
-      }
-#pragma unroll
-      for (int i = 0; i < VB; ++i) {
-        const int e = tid + 256 * i;
-        const int nn = e / (BK / 8), kv = e % (BK / 8);
-        *reinterpret_cast<u4*>(&Bs[h][nn * LDS_ROW + kv * 8]) = rb[h][i];
-      }
+    for (int i = 0; i < VB; ++i) {
+      const int e = tid + 256 * i;
+      const int nn = e / (BK / 8), kv = e % (BK / 8);
+      *reinterpret_cast<u4*>(&Bs[nn * LDS_ROW + kv * 8]) = rb[i];
     }
   };
 
-  const int tb = (int)((int64_t)T_ * blockIdx.z / gridDim.z);
-  const int te = (int)((int64_t)T_ * (blockIdx.z + 1) / gridDim.z);
-  if (te > tb) {
-    load(tb);
+  if (T_ > 0) {
+    load(0);
     store();
   }
   __syncthreads();
-  for (int t = tb; t < te; ++t) {
-    if (t + 1 < te) load(t + 1);
+  for (int t = 0; t < T_; ++t) {
+    if (t + 1 < T_) load(t + 1);
 #pragma unroll
     for (int kk = 0; kk < BK / 32; ++kk) {
       const int ko = kk * 32 + 8 * (lane >> 4);
-      u4 ah[TM], bh[TN];
-      u4 al[X3 ? TM : 1], bl[X3 ? TN : 1];
+      u4 a[TM], b[TN];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int r = wm0 + i * 16 + (lane & 15);
-        ah[i] = *reinterpret_cast<const u4*>(&As[0][r * LDS_ROW + ko]);
-        if (X3) al[i] = *reinterpret_cast<const u4*>(&As[NARR - 1][r * LDS_ROW + ko]);
-      }
+      for (int i = 0; i < TM; ++i)
+        a[i] = *reinterpret_cast<const u4*>(&As[(wm0 + i * 16 + (lane & 15)) * LDS_ROW + ko]);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int r = wn0 + j * 16 + (lane & 15);
-        bh[j] = *reinterpret_cast<const u4*>(&Bs[0][r * LDS_ROW + ko]);
-        if (X3) bl[j] = *reinterpret_cast<const u4*>(&Bs[NARR - 1][r * LDS_ROW + ko]);
-      }
+      for (int j = 0; j < TN; ++j)
+        b[j] = *reinterpret_cast<const u4*>(&Bs[(wn0 + j * 16 + (lane & 15)) * LDS_ROW + ko]);
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          if (X3) {
-            acc[i][j] = mfma_bf16(al[i], bh[j], acc[i][j]);
-            acc[i][j] = mfma_bf16(ah[i], bl[X3 ? j : 0], acc[i][j]);
-          }
-          acc[i][j] = mfma_bf16(ah[i], bh[j], acc[i][j]);
-        }
+        for (int j = 0; j < TN; ++j) acc[i][j] = mfma_bf16(a[i], b[j], acc[i][j]);
     }
     __syncthreads();
-    if (t + 1 < te) {
+    if (t + 1 < T_) {
       store();
       __syncthreads();
     }
   }
-  FragCoord fc{m0 + wm0, n0 + wn0, lane, m0, n0, false, (int)blockIdx.x, wave & 1, 2, (int)blockIdx.z};
-  epi.template run<float, TM, TN>(acc, fc, reinterpret_cast<char*>(&As[0][0]));
+  FragCoord fc{m0 + wm0, n0 + wn0, lane, m0, n0, false, (int)blockIdx.x, wave & 1, 2, 0};
+  epi.template run<float, TM, TN>(acc, fc, reinterpret_cast<char*>(&As[0]));
 }
 
 // ---------------------------------------------------------------------------
@@ -414,7 +384,7 @@ struct GramMap {
 struct DmaArgs {
   int nseg;
   SegD seg[2];
-  int lower_only;   // square tiles strictly above the diagonal do nothing (symmetric products)
+  int lower_only;   // gemm_row_kernel: square tiles strictly above the diagonal do nothing (symmetric products)
   GramMap gram;
 };
 
@@ -466,7 +436,6 @@ __global__ __launch_bounds__(TL::NT) void gemm_dma_kernel(DmaArgs g, Epi epi) {
   } else {
     tile_coords<false>(tmi, tni, tzi);
   }
-  if (g.lower_only && tni > tmi) return;
   const int m0 = tmi * BM, n0 = tni * BN;
   const int wm = wave / WN, wn = wave % WN;
   const int t0 = g.seg[0].K / BK;

@@ -32,10 +32,9 @@ static Offs offs(int D, int H) {
 }
 
 // --------------------------------------------------------------- epilogues ----
-// Z = acc + bias[c]; H = gelu(Z) (row-major, ld), Z stored when requested.
+// H = gelu(acc + bias[c]) (row-major, ld), in FP32 or bf16.
 struct EpiBiasGelu {
   const float* bias;
-  float* Z;
   float* Hout;
   bf16_t* Hbf;   // optional bf16 copy of H (ldb)
   int64_t ld, ldb;
@@ -52,7 +51,6 @@ struct EpiBiasGelu {
           if (r < M && c < N) {
             const float z = (float)acc[i][j][v] + bias[c];
             const float h = gelu_f(z);
-            if (Z) Z[(int64_t)r * ld + c] = z;
             if (Hout) Hout[(int64_t)r * ld + c] = h;
             if (Hbf) Hbf[(int64_t)r * ldb + c] = f2bf(h);
           }
@@ -458,19 +456,15 @@ static void forward_bf16(const ffk_mlp* net, const bf16_t* Xb, int64_t B, int64_
   DBuf h1b(Br * Hk * 2), h2(Br * H * 4);
   HIPCHK(hipMemsetAsync(h1b.get(), 0, Br * Hk * 2, st));
   {
-    Bf16Args g{};
-    g.nseg = 1;
-    g.seg[0] = SegB{Xb, nullptr, w1, nullptr, Dk, Dk, (int)Dk};
-    EpiBiasGelu e{th + o.b1, nullptr, nullptr, h1b.as<bf16_t>(), 0, Hk, (int)B, H};
-    gemm_bf16_kernel<128, 128, 64, false, EpiBiasGelu><<<dim3(Hr / 128, Br / 128), 256, 0, st>>>(g, e);
+    const Bf16Args g{Xb, w1, Dk, Dk, (int)Dk};
+    EpiBiasGelu e{th + o.b1, nullptr, h1b.as<bf16_t>(), 0, Hk, (int)B, H};
+    gemm_bf16_kernel<128, 128, 64, EpiBiasGelu><<<dim3(Hr / 128, Br / 128), 256, 0, st>>>(g, e);
     LAUNCHCHK();
   }
   {
-    Bf16Args g{};
-    g.nseg = 1;
-    g.seg[0] = SegB{h1b.as<bf16_t>(), nullptr, w2, nullptr, Hk, Hk, (int)Hk};
-    EpiBiasGelu e{th + o.b2, nullptr, h2.as<float>(), nullptr, H, 0, (int)B, H};
-    gemm_bf16_kernel<128, 128, 64, false, EpiBiasGelu><<<dim3(Hr / 128, Br / 128), 256, 0, st>>>(g, e);
+    const Bf16Args g{h1b.as<bf16_t>(), w2, Hk, Hk, (int)Hk};
+    EpiBiasGelu e{th + o.b2, h2.as<float>(), nullptr, H, 0, (int)B, H};
+    gemm_bf16_kernel<128, 128, 64, EpiBiasGelu><<<dim3(Hr / 128, Br / 128), 256, 0, st>>>(g, e);
     LAUNCHCHK();
   }
   k_rowdot<<<cdiv(B, 4), 256, 0, st>>>(h2.as<float>(), B, H, th + o.w3, th + o.b3, out);
@@ -496,7 +490,7 @@ static void mlp_layer_lds(const float* X, const float* W, const float* bias, int
   g.M = (int)B;
   g.N = H;
   g.seg = SegS<float>{X, K, 1, W, K, 1, K};
-  const EpiBiasGelu e{bias, nullptr, Hout, nullptr, H, 0, (int)B, H};
+  const EpiBiasGelu e{bias, Hout, nullptr, H, 0, (int)B, H};
   // three of the wider tiles share a CU, so that a few past that many start alone (D =
   // 36, H = 128, B = 100000 179 us, 146 by the narrower)
   const int64_t wide = (int64_t)cdiv(H, 128) * cdiv(B, 128), cus = device_cus();

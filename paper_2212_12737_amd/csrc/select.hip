@@ -150,8 +150,8 @@ void select_weighted(int64_t n, const double* w, int64_t k, uint64_t seed, int s
 // ends when it is, or when the rank test stops the factorization.  What a
 // pivot costs is then a share of a few passes over n x kPool and of a K = m
 // product instead of a pass over the factor: at n = 126000, k = 2000
-// 415 ms became 45, of which half is the products that form new candidates.
-constexpr int kPool = 128;       // candidates (two per lane of the greedy wave)
+// 415 ms became 39, of which 14 are the products that form new candidates.
+constexpr int kPool = 128;       // candidates (two per lane of the greedy waves)
 constexpr int kBins = 2048;      // histogram of the diagonals, 2^-10 of an octave each
 constexpr int kBinShift = 10;    // of the high word
 
@@ -534,7 +534,7 @@ __global__ __launch_bounds__(256) void k_piv_list(const double* __restrict__ d, 
 // atomics) with the pool; the others get free slots, then those of rows no
 // longer listed.
 __global__ __launch_bounds__(kPool) void k_piv_match(PivState* st, int slots, PivHost* host) {
-  __shared__ int key[kPool], row[kPool], used[kPool], slot_of[kPool], avail[kPool];
+  __shared__ int key[kPool], row[kPool], used[kPool], avail[kPool];
   const int t = threadIdx.x;
   const int count = st->stop ? 0 : min(st->count, slots);
   key[t] = t < count ? st->list[t] : 0x7FFFFFFF;
@@ -559,7 +559,6 @@ __global__ __launch_bounds__(kPool) void k_piv_match(PivState* st, int slots, Pi
   for (int q = 0; q < kPool; ++q)
     if (row[q] == key[t]) mine = q;
   if (t >= count) mine = -1;
-  slot_of[t] = mine;
   __syncthreads();
   if (mine >= 0) used[mine] = 1;
   __syncthreads();
@@ -830,13 +829,13 @@ int64_t select_pivchol(ffk_system* s, int64_t k, int64_t* idx_out, hipStream_t s
     }
   };
   // Blocks start short (an early pivot lowers a whole class of rows, those of
-  // one coordinate of one atom) and grow past twenty pivots.  A pivot by
-  // itself takes 24 us and a pass over L, a block 300 us and more, and more
-  // with n (M = 22, N = 1005, k = 130: 3.9 ms with three kernels a pivot, 4.1
-  // with blocks from 64 pivots on; M = 12, N = 200, k = 180: 3.7 and 2.1).  So
-  // the first pivots go one at a time, more of them at large n, all where few
-  // would be left for blocks, and kFew after a block of fewer than kShort while
-  // the pass is short (4e8 bytes).
+  // one coordinate of one atom) and grow past twenty pivots.  A pivot by itself
+  // takes 19 us (24 when these lines were drawn) and a pass over L, a block 300
+  // us and more, and more with n (M = 22, N = 1005, k = 130: 3.9 ms with three
+  // kernels a pivot, 4.1 with blocks from 64 pivots on; M = 12, N = 200, k = 180:
+  // 3.7 and 2.1).  So the first pivots go one at a time, more of them at large n,
+  // all where few would be left for blocks, and kFew after a block of fewer than
+  // kShort while the pass is short (4e8 bytes).
   constexpr int kFew = 16, kShort = 10;
   const int64_t first = n >= 32768 ? 112 : 64;
   bool tables = pair_table(s, st);   // which the single pivots' kernel reads
