@@ -774,23 +774,34 @@ static GemmOut mvm_gemms_row(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t
 // leaves the least padding past D (and stays inside the padded rows Dr).  112
 // columns take four waves in FP64 (at M = 21, N = 2000 74 us against 89 by
 // eight, whose fragments spill) and eight in FP32 (N = 10000: 1032 against 1066).
-static int gemm2_width(int64_t D, int64_t Dr) {
+// rows: row tiles times K splits where these are given (FP32, whose splits do not
+// go by the width).  The two workgroups of a CU share one matrix rate, so another width
+// with fewer tiles on the busiest CU is taken if these make up for its padding (us a
+// product: M = 42, N = 4095, 64 x 9 tiles of 96 on 256 CUs 1251, 64 x 8 of 112 966; M = 50,
+// N = 1500, 48 x 11 of 112 304, 48 x 10 of 128 270; M = 42, N = 1000 134 and 115).
+static int gemm2_width(int64_t D, int64_t Dr, int64_t rows = 0) {
   int best = 128;
   for (int w : {112, 96})
     if (rup(D, w) < rup(D, best) && rup(D, w) <= Dr) best = w;
+  if (rows == 0) return best;
+  auto rounds = [&](int w) { return (int64_t)cdiv(cdiv(D, w) * rows, device_cus()); };
+  for (int w : {128, 112, 96})
+    if (rup(D, w) <= Dr && rounds(w) < rounds(best) && rounds(w) * w < rounds(best) * best) best = w;
   return best;
 }
 
 template <typename T, class TL1>
 static GemmOut mvm_gemms_wide(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t Dk, int64_t Dr, const DmaOps& o,
                               hipStream_t st, hipEvent_t* ev) {
-  const int w = gemm2_width(a.D, Dr);
-  int splits;
-  if (sizeof(T) == 4)
+  int w, splits;
+  if (sizeof(T) == 4) {
     splits = gemm2_splits(Dr / 128 * (Ntr / 128), 2 * Nsr / 16, a.Nt, a.D, 2, 2.0 * 128 * 128 * 2.0 * Nsr / (1.15e14 / 256));
-  else
+    w = gemm2_width(a.D, Dr, cdiv(a.Nt, 128) * (int64_t)splits);
+  } else {
+    w = gemm2_width(a.D, Dr);
     splits = gemm2_splits_fp64((int64_t)cdiv(a.D, w) * cdiv(a.Nt, 128), 2 * cdiv(a.Ns, 8), a.Nt, a.D,
                                2.0 * 128 * w * 2.0 * a.Ns);
+  }
   if (w == 112) return mvm_gemms_row<T, TL1, RowTile<128, 112, sizeof(T) == 4 ? 8 : 4, 1, 2>>(a, Ntr, Nsr, Dk, splits, o, st, ev);
   if (w == 96) return mvm_gemms_row<T, TL1, RowTile<128, 96, 4, 2, 2>>(a, Ntr, Nsr, Dk, splits, o, st, ev);
   return mvm_gemms_row<T, TL1, RowTile<128, 128, 2, 4, 2>>(a, Ntr, Nsr, Dk, splits, o, st, ev);
