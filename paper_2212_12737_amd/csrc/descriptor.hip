@@ -478,11 +478,17 @@ void ensure_coeffs_pair(const ffk_system* t, const ffk_system* src, CoeffSet* se
     const bool square = t == src && diag_off == 0;
     EpiCoeffPair e{t->sqn.as<double>(), src->sqn.as<double>(), c64.dA_hi.as<double>(), c64.B.as<double>(), (int)Nt,
                    (int)Ns, Nsr, diag_off, sqrt(5.0) / t->sigma, t->a0, t->bcoef, square};
-    // Up to 1024^2 pairs the small tiles, which fill the GPU at once and need
+    // Up to some 2000^2 pairs the small tiles, which fill the GPU at once and need
     // no padded operands; beyond, where they would read every row from L2 N /
     // 16 times, the pipelined engine, on and below the diagonal if the matrix
-    // is symmetric.
-    if (Ntr * Nsr <= 1024 * 1024) {
+    // is symmetric.  The line is lower for longer rows.  Of a system's memory the
+    // runtime keeps 64 MB for the next; with the padded copy, which a system that never
+    // multiplies does not need, it may have to give back and map anew.  Build and
+    // release, small tiles and engine, us: M = 16, N = 1500 135, 154, N = 2000 156, 492;
+    // M = 30, N = 1500 210, 258, N = 1700 247, 531, N = 2000 554, 547; M = 33, N = 2000 647,
+    // 546; M = 36, N = 1500 258, 283, N = 1700 589, 551; M = 48, N = 1500 318, 622.
+    const int64_t most = t->D <= 448 ? 2048 * 2048 : 1536 * 1536;
+    if (Ntr * Nsr <= most) {
       k_coeff_small<<<dim3((unsigned)(Nsr / 16), (unsigned)(Ntr / 16)), 256, 0, st>>>(
           t->Xc.as<double>(), src->Xc.as<double>(), (int)t->D, e);
       LAUNCHCHK();
