@@ -325,19 +325,6 @@ void permute_stack(const ffk_system* s, const double* v, double* out, hipStream_
 size_t product_rows_bytes(int64_t N, int64_t D, int64_t most);
 void product_rows(const ffk_system* src, const double* mean, const double* v, const double* R, const double* X,
                   int64_t T, int64_t most, bool first, double* y, void* work, hipStream_t st);
-// The FP64 product on the GEMMs against T rows of another system (geometries R,
-// descriptors X), whose T x N coefficients are made for the call: y = K(rows, src) v,
-// `mean` centring both.  work: product_rows_bytes(src->N, src->D, most) for up to
-// `most` rows; with first, J v is formed there, without it is the last call's.
-size_t product_rows_bytes(int64_t N, int64_t D, int64_t most);
-void product_rows(const ffk_system* src, const double* mean, const double* v, const double* R, const double* X,
-                  int64_t T, int64_t most, bool first, double* y, void* work, hipStream_t st);
-// descriptor.hip -- coefficients dA, B (ld columns) of T padded rows Xt (|x|^2: sqt)
-// against the padded copy of src; zeros past T and past the sources.
-void rect_coeffs(const ffk_system* src, const double* Xt, const double* sqt, int64_t T, int64_t Ttr, int64_t ld,
-                 double* dA, double* B, hipStream_t st);
-// X_c rows (N x D) into a zero-padded Nr x ld array.
-void pad_rows_copy(const double* Xc, int64_t N, int64_t D, int64_t Nr, int64_t ld, double* out, hipStream_t st);
 
 // predict.hip -- both dense steps of the FP64 product against few sources in one
 // kernel: chunks x Nt x D parts of G and the Nt x chunks row sums of W.

@@ -669,8 +669,9 @@ struct GemmOut {
 };
 
 // K splits of the BF16 GEMM 2, counted on tiles of BM x BN of which a CU holds
-// per_cu.  Below 4096 geometries these are 64 x 256 whatever tile the product
-// takes, so that the choice of a tile changes no bit of the result.
+// per_cu.  Below 4096 geometries these are 64 x 256 whatever tile GEMM 2
+// takes, so that the choice of its tile changes no bit of the result (that of
+// GEMM 1's does: the row sums of W are grouped by its tiles).
 template <int BM, int BN>
 static int gemm2_splits_bf16(const MvmArgs& a, int64_t Ntr, int64_t Nsr, int64_t Dr, int per_cu, bool x3) {
   const double t_tile = 2.0 * BM * BN * 2.0 * Nsr * (x3 ? 3 : 1) / (1.2e15 / 256.0);

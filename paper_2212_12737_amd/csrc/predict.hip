@@ -8,8 +8,10 @@
 // all of it: the Gram products that give dA and B and those that give P share
 // the rows of X_t; dA and W stay in LDS and are the left operand of its part of
 // G.  Nothing of size T x N reaches memory, only the parts of G, which a second
-// kernel sums in a fixed order.  Bound by latency for a few test geometries
-// and by reading the training rows from L2 for hundreds.  A prediction (with the
+// kernel sums in a fixed order (they are more bytes: at M = 42, N = 5000, T = 200
+// 134 MB beside the 16 MB of dA and W).  Bound by latency for a few test geometries
+// and by reading the training rows from L2 for hundreds; large predictions take the
+// product's GEMMs instead (predict_by_gemms).  A prediction (with the
 // test system's setup) against the same products as separate scalar GEMMs on
 // 128-row tiles with T x N results in memory: 442 -> 95 us at M = 21, N = 2000,
 // T = 1; 1894 -> 438 us at M = 42, N = 5000, T = 200, and 360 since two
