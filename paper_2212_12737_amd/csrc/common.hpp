@@ -211,7 +211,9 @@ struct ffk_system {
   ffk::DBuf Xc;             // N x D double (centred)
   ffk::DBuf sqn;            // N double (|x_c|^2)
   mutable ffk::DBuf Xp64;   // X_c as FP64, padded: Nr x Dk
-  ffk::DBuf XpT64;          // and transposed: Dr x Nr
+  mutable ffk::DBuf XpT64;  // and transposed: Dr x Nr
+  mutable std::mutex form_lock;           // held while PT or these are formed
+  mutable bool padded_complete = false;   // no stream is still filling these (complete_padded)
   ffk::DBuf Xp32, XpT32;    // the same in FP32
   ffk::DBuf Xch, Xcl;       // N x D bf16 hi/lo
   ffk::DBuf XcTh, XcTl;     // D x N bf16 hi/lo
@@ -299,6 +301,8 @@ void ensure_coeffs(ffk_system* sys, int prec, hipStream_t st);
 void ensure_coeffs_pair(const ffk_system* t, const ffk_system* src, CoeffSet* sets, int prec, int64_t diag_off,
                         hipStream_t st);
 void ensure_lowp_descriptor(ffk_system* sys, int prec, hipStream_t st);
+// Xp64 and XpT64, complete on return: for readers on any stream.
+void complete_padded(const ffk_system* sys, hipStream_t st);
 // Coefficients of T rows Xc (T x D, |x|^2: sq) against src, whose padded copies exist:
 // padded copy of the rows in Xp (Tr x Dk), dA and B (Tr x ld), and zeros in the
 // padding of these and of W (Tr x ld).

@@ -68,6 +68,7 @@ __global__ void k_pair_table(const double* __restrict__ R, const int* __restrict
 // do not need: so it is formed here, and where it would be a large part of what
 // is left, the columns do without (kernel_columns_src).
 bool pair_table(const ffk_system* s, hipStream_t st) {
+  std::lock_guard<std::mutex> lock(s->form_lock);
   if (s->PT) return true;
   const size_t bytes = (size_t)(4 * s->N * s->D) * sizeof(double);
   size_t free_bytes = 0, total = 0;
@@ -321,23 +322,41 @@ template <typename T>
 static void padded_rows(const ffk_system* s, DBuf& P, hipStream_t st) {
   if (P) return;
   const int64_t Nr = pad_rows(s->N), Dk = rup(s->D, 64);
-  P.alloc(Nr * Dk * sizeof(T));
-  k_pad_copy<T><<<cdiv(Nr * Dk, 256), 256, 0, st>>>(s->Xc.as<double>(), s->N, s->D, s->D, Nr, Dk, P.as<T>());
+  DBuf t(Nr * Dk * sizeof(T));
+  k_pad_copy<T><<<cdiv(Nr * Dk, 256), 256, 0, st>>>(s->Xc.as<double>(), s->N, s->D, s->D, Nr, Dk, t.as<T>());
   LAUNCHCHK();
+  P = std::move(t);
 }
 template <typename T>
 static void padded_columns(const ffk_system* s, DBuf& PT, hipStream_t st) {
   if (PT) return;
   const int64_t Nr = pad_rows(s->N), Dr = pad_rows(s->D);
-  PT.alloc(Dr * Nr * sizeof(T));
+  DBuf t(Dr * Nr * sizeof(T));
   dim3 grid(cdiv(Nr, 64), cdiv(Dr, 64));
-  k_pad_transpose<T><<<grid, 256, 0, st>>>(s->Xc.as<double>(), s->N, s->D, s->D, Dr, Nr, PT.as<T>());
+  k_pad_transpose<T><<<grid, 256, 0, st>>>(s->Xc.as<double>(), s->N, s->D, s->D, Dr, Nr, t.as<T>());
   LAUNCHCHK();
+  PT = std::move(t);
+}
+
+// The FP64 copies for a reader that is not a product of the system (a large
+// prediction): a product may have formed them on another stream, whose work is still
+// queued, and the next one may come on another stream than this call's.  So they
+// are complete on return; the wait is once for each system.
+void complete_padded(const ffk_system* s, hipStream_t st) {
+  std::lock_guard<std::mutex> lock(s->form_lock);
+  if (s->padded_complete) return;
+  const bool formed = (bool)s->Xp64 || (bool)s->XpT64;
+  padded_rows<double>(s, s->Xp64, st);
+  padded_columns<double>(s, s->XpT64, st);
+  if (formed) HIPCHK(hipDeviceSynchronize());
+  else HIPCHK(hipStreamSynchronize(st));
+  s->padded_complete = true;
 }
 
 void ensure_lowp_descriptor(ffk_system* s, int prec, hipStream_t st) {
   const int64_t N = s->N, D = s->D;
   if (prec == FFK_FP64) {
+    std::lock_guard<std::mutex> lock(s->form_lock);
     padded_rows<double>(s, s->Xp64, st);
     padded_columns<double>(s, s->XpT64, st);
   }
@@ -493,8 +512,10 @@ void ensure_coeffs_pair(const ffk_system* t, const ffk_system* src, CoeffSet* se
           t->Xc.as<double>(), src->Xc.as<double>(), (int)t->D, e);
       LAUNCHCHK();
     } else {
-      padded_rows<double>(t, t->Xp64, st);
-      padded_rows<double>(src, src->Xp64, st);
+      for (const ffk_system* x : {t, src}) {
+        std::lock_guard<std::mutex> lock(x->form_lock);
+        padded_rows<double>(x, x->Xp64, st);
+      }
       coeff_gemm(t->Xp64.as<double>(), src->Xp64.as<double>(), t->D, Ntr, square, e, st);
     }
     c64.ready = true;

@@ -1357,16 +1357,15 @@ static size_t carve_rows(int64_t N, int64_t D, int64_t most, double* base, RowsB
 
 size_t product_rows_bytes(int64_t N, int64_t D, int64_t most) { return carve_rows(N, D, most, nullptr, nullptr); }
 
-void product_rows(const ffk_system* src_, const double* mean, const double* v, const double* R, const double* X,
+void product_rows(const ffk_system* src, const double* mean, const double* v, const double* R, const double* X,
                   int64_t T, int64_t most, bool first, double* y, void* work, hipStream_t st) {
-  ffk_system* src = const_cast<ffk_system*>(src_);   // its padded copies are formed as for a product
   const int64_t N = src->N, D = src->D;
   const int M = src->M;
   const int64_t Nsr = pad_rows(N), Tr = pad_rows(T), Dk = rup(D, 64), Dr = pad_rows(D);
   RowsBufs b;
   carve_rows(N, D, most, static_cast<double*>(work), &b);
   if (first) {
-    ensure_lowp_descriptor(src, FFK_FP64, st);
+    complete_padded(src, st);
     zero_fill(b.U, Nsr * Dk * 8, st);
     zero_fill(b.UT, Dr * Nsr * 8, st);
     launch_jv<0>(N, M, st, src->R.as<double>(), src->pairs.as<int>(), v, src->Xc.as<double>(), N, M, D, (void*)b.U,
